@@ -76,11 +76,13 @@ typedef enum {
 typedef enum {
     FF_VARIANT_AUTO = 0,
     FF_VARIANT_TILED_FUSED = 1,   /* MFMA tiles; row statistics merged across
-                                     tiles inside the launch, G stays in registers */
+                                     tiles inside the launch, G stays in registers
+                                     (few tiles: K cut over several workgroups) */
     FF_VARIANT_TILED_TWOPASS = 2, /* MFMA tiles write fp32 G + statistics; a second
                                      kernel normalises (used when a row spans more
                                      tiles than can be co-resident) */
-    FF_VARIANT_SMALL_M = 3        /* M <= 32, bf16: streams W once at HBM rate */
+    FF_VARIANT_SMALL_M = 3        /* M <= 32, bf16: streams W once at HBM rate
+                                     (strips of columns, or tiles with K cut) */
 } ff_variant;
 
 /*
@@ -101,10 +103,11 @@ int ff_fused_linear_gelu_ln(const void *X, const void *W, const void *b,
  * layout, dtypes, errors and result (bit for bit) as ff_fused_linear_gelu_ln, but no workspace is
  * used, bound or allocated: the row statistics and arrival counters of the call live in a static
  * device array inside the library (ff_noalloc_max_bytes() bytes, 8 MiB, one copy on every device
- * that loads the library, held until the process ends).  The call makes no hipMalloc, hipFree,
+ * that loads the library, held until the process ends; the partial products of shapes whose K is cut
+ * over several workgroups have a second one, 16 MiB).  The call makes no hipMalloc, hipFree,
  * memset or synchronising call; it launches one small kernel that clears the counters it is about
  * to use, then the operator's kernel, both on `stream`.  Shapes whose scratch need exceeds the array
- * return FF_ERR_WORKSPACE: that is every shape ff_workspace_bytes() reports above the limit, in
+ * return FF_ERR_WORKSPACE: that is every shape whose ff_workspace_bytes(), partial products apart, is above the limit, in
  * particular rows spanning more tiles than fit the device at once (the two-pass variant needs an fp32
  * copy of G).  All calls on one device share the one array: calls that overlap in time on a device
  * (two streams, two host threads) race on it and give wrong results; serialise them.
@@ -187,7 +190,9 @@ size_t ff_rowmean_workspace_bytes(int64_t M, int64_t K, int64_t N, int dtype);
 
 /*
  * Bytes of workspace a call with this shape needs under the current variant
- * selection (0 on invalid arguments).  Pure host arithmetic.
+ * selection (0 on invalid arguments).  Pure host arithmetic.  Shapes whose K is cut over several
+ * workgroups count their partial products (up to 16 MiB); with a bound workspace too small for those
+ * the call takes a kernel that needs none, and is slower.
  */
 size_t ff_workspace_bytes(int64_t M, int64_t K, int64_t N, int dtype);
 

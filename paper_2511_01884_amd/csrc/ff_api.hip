@@ -20,6 +20,9 @@ constexpr int kMaxDevices = 64;
 // comes from hipGetSymbolAddress (no_alloc_scratch below).
 constexpr size_t kNoAllocBytes = 8u << 20;
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
+// The split kernel's partial products of such a call: at most one 64 KiB tile for each of 256 units.
+constexpr size_t kNoAllocSumBytes = 16u << 20;
+static __device__ __align__(256) unsigned char scratch_sums[kNoAllocSumBytes];
 
 // Sets `words` 32-bit words at `dst` to `value` (a fill kernel, not a memset node, so that a caller
 // may record it into a graph).
@@ -46,10 +49,12 @@ struct DeviceState {
     size_t ws_bytes = 0;
     bool ws_owned = false;
     void *no_alloc_ptr = nullptr;            // this device's copy of `scratch`, once asked for
+    void *no_alloc_sums = nullptr;           // the same for `scratch_sums`
     bool no_alloc_used = false;
     unsigned long long *timeline = nullptr;  // test hook: phase timestamps of the tiled kernels
     size_t timeline_bytes = 0;
     signed char blocks_per_cu[2][kNumTileShapes][3] = {};  // cached occupancy answers [bf16][shape][mode], 0 = not asked
+    signed char split_blocks[2][kNumSplitShapes] = {};     // the same for the split kernel
 };
 
 std::mutex g_mutex;
@@ -74,6 +79,9 @@ struct Plan {
     size_t partial_off = 0, partial_bytes = 0;
     size_t g_off = 0, g_bytes = 0;
     size_t total_bytes = 0;
+    int split_s = 0;             // split kernel: workgroups per tile, 0 = another kernel
+    int split_shape = 0;         // a SplitShape
+    size_t sums_off = 0;
 };
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -109,10 +117,98 @@ int resident_blocks_per_cu(DeviceState *st, bool bf16, int shape, int mode)
     return slot < 0 ? 0 : slot;
 }
 
-int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceState *st, int forced,
-              bool linear_only, Plan &pl)
+int resident_split_blocks(DeviceState *st, bool bf16, int shape)
 {
-    (void)K;
+    if (st == nullptr)
+        return 0;
+    signed char &slot = st->split_blocks[bf16 ? 1 : 0][shape];
+    if (slot == 0) {
+        const int n = split_kernel_blocks_per_cu(bf16, shape);
+        slot = (signed char)(n <= 0 ? -1 : (n > 100 ? 100 : n));
+    }
+    return slot < 0 ? 0 : slot;
+}
+
+// Split kernel: the (shape, S) with the smallest estimated time among those whose workgroups all fit the
+// chip at once, or false if there is none.  The estimate (microseconds, one launch after another, inputs
+// from HBM) adds up what the kernel does one after the other:
+//     start + max(slabs of a workgroup * time of one, W read at the rate its bytes in flight allow)
+//     + epilogue of a tile's share + exchange with the NT tiles of the rows
+//     + S > 1: meeting of the tile's S workgroups and one write and read of the partial products
+// Its constants were fitted to 2 800 runs (340 shapes drawn over M 1..8192, K 128..16384, N 128..16384, every
+// shape and S of each): they reproduce the times of the configurations within 1.6 times of the best to 9 %
+// (bf16) and 4 % (fp32) rms, and the configuration picked is 1.4 and 0.9 % slower than the best on average.
+bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceState *st, Plan &pl)
+{
+    // workgroups per compute unit that the LDS allows (what the runtime reports is asked as well)
+    constexpr int kPerCu[kNumSplitShapes] = {3, 2, 2, 1, 1};
+    struct Cost { double start, slab, mfma, hbm, fabric, flight, exch, exch_s, sums, epi, epi128, tiles; };
+    constexpr Cost kBf16 = {4.6, 0.024, 0.128, 5.4e6, 57e3, 0.44, 3.0, 0.26, 3.0e6, 2.1, 1.6, 0.05};
+    constexpr Cost kF32 = {5.4, 0.093, 0.50, 5.4e6, 1e9, 1.06, 3.3, 0.16, 2.5e6, 2.3, 0.8, 0.04};
+    const Cost &c = bf16 ? kBf16 : kF32;
+    const int size = bf16 ? 2 : 4;
+    const int64_t slabs = (K * size + 127) / 128;
+    double best = 0.0;
+    for (int shape = 0; shape < kNumSplitShapes; ++shape) {
+        const int bm = split_shape_rows(shape), bn = split_shape_cols(shape);
+        // tiles of few rows pay only where they spare the padding of larger ones
+        if (bm == 32 && M > 64)
+            continue;
+        const int64_t RB = (M + bm - 1) / bm, NT = (N + bn - 1) / bn;
+        if (RB * NT > (int64_t)num_cus * kPerCu[shape])
+            continue;
+        int per_cu = resident_split_blocks(st, bf16, shape);
+        per_cu = per_cu > 0 && per_cu < kPerCu[shape] ? per_cu : kPerCu[shape];
+        for (int S = 1; S <= kSplitMaxS; S *= 2) {
+            const int64_t groups = RB * NT * S;
+            if (groups > (int64_t)num_cus * per_cu ||
+                (RB * NT + RB * S * kSplitWays) * kSplitCounterStride * 4 > (int64_t)(kCtrlBytes - 2 * kCounterOffset))
+                break;
+            // A share of fewer than two slabs, or a bf16 product of under ten (fp32: four), is not worth
+            // the meeting: 256 x 512 x 512 bf16 takes 9.8 us whole and 9.6 to 9.9 split.
+            if (S > 1 && (slabs < 2 * S || slabs < (bf16 ? 10 : 4)))
+                break;
+            // One 128 x 128 tile per unit with the whole of K is the tile kernel's ground where the
+            // product is short (3584 x 512 x 768 bf16: 18.2 us there, 18.8 here; from nine slabs on the
+            // deeper ring wins, 2048 x 8192 x 2048: 114 against 96) and in fp32, which is bound by the
+            // matrix units (7400 x 1792 x 384: 126 against 135).
+            if (shape == kSplit128 && S == 1 && (!bf16 || slabs <= 8))
+                continue;
+            const double per = (double)((slabs + S - 1) / S), wpc = (double)((groups + num_cus - 1) / num_cus);
+            const double unit = bm * bn / 4096.0;
+            const double in_flight = (double)groups / (double)RB * 3 * bn * 128;
+            const double slab = c.slab + std::max(c.mfma * unit * wpc, (bn + bm) * 128 * wpc / c.fabric);
+            const double stream = (double)N * K * size / std::min(c.hbm, in_flight / c.flight);
+            double t = c.start + std::max(per * slab, stream) + c.epi * unit / S * wpc + c.tiles * (double)NT +
+                       (shape == kSplit128 ? c.epi128 : 0.0);
+            if (S > 1)
+                t += c.exch + c.exch_s * S + (double)groups * bm * bn * 4 / c.sums;
+            if (best != 0.0 && t >= best)
+                continue;
+            best = t;
+            pl.split_s = S;
+            pl.split_shape = shape;
+            pl.tile_m = bm;
+            pl.tile_n = bn;
+            pl.RB = (int)RB;
+            pl.NT = (int)NT;
+            pl.grid = (int)groups;
+        }
+    }
+    if (pl.split_s == 0)
+        return false;
+    pl.rounds = 1;
+    const size_t rows = (size_t)pl.tile_m / pl.split_s, tiles = (size_t)pl.RB * pl.NT;
+    pl.partial_off = kCtrlBytes;
+    pl.partial_bytes = round_up(tiles * pl.split_s * (rows < 16 ? 16 : rows) * sizeof(floatx2), 256);
+    pl.sums_off = pl.partial_off + pl.partial_bytes;
+    pl.total_bytes = pl.sums_off + (pl.split_s > 1 ? tiles * pl.split_s * pl.tile_m * pl.tile_n * sizeof(float) : 0);
+    return true;
+}
+
+int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceState *st, int forced,
+              bool linear_only, Plan &pl, bool may_split = true)
+{
     const bool bf16 = dtype == FF_BF16;
     const int64_t strips = (N + kSmallMStripCols - 1) / kSmallMStripCols;
     const bool smallm_ok = bf16 && M <= 32 && strips <= (int64_t)num_cus * kSmallMMaxStripsPerGroup;
@@ -123,9 +219,21 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     else if (variant == FF_VARIANT_AUTO)
         variant = smallm_ok ? FF_VARIANT_SMALL_M : 0;
 
+    if (variant == FF_VARIANT_SMALL_M && !smallm_ok)
+        return FF_ERR_UNSUPPORTED;
+    // The streamer keeps M <= 16 with one 32-column strip on more than half the units but at most one on
+    // each (16 x 8192 x 8192: 37.2 us, split 37.9; 4 x 4608 x 8024: 23.0, 25.0).  With fewer strips the
+    // split kernel spreads K over the idle units (2 x 16128 x 1904: 41.7 us, split 26), with several strips
+    // a unit reads one after the other (14 x 4608 x 12888: 40, 34), and over 16 rows the streamer's
+    // registers no longer cover its loads (22 x 5888 x 6008: 34.6, 22).
+    may_split = may_split && !linear_only && g_forced_tile == 0 && g_forced_waves == 0;
+    const bool stream = M <= 16 && strips <= num_cus && strips * 2 > num_cus;
+    if (may_split && (variant == FF_VARIANT_SMALL_M ? !stream : variant == 0 || variant == FF_VARIANT_TILED_FUSED) &&
+        plan_split(M, K, N, bf16, num_cus, st, pl)) {
+        pl.variant = variant == FF_VARIANT_SMALL_M ? FF_VARIANT_SMALL_M : FF_VARIANT_TILED_FUSED;
+        return FF_OK;
+    }
     if (variant == FF_VARIANT_SMALL_M) {
-        if (!smallm_ok)
-            return FF_ERR_UNSUPPORTED;
         pl.variant = FF_VARIANT_SMALL_M;
         pl.mt = M <= 16 ? 1 : 2;
         pl.strips = (int)strips;
@@ -151,7 +259,8 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     //     overlap of one workgroup's epilogue with the other's K loop does not pay for the 1.5 times
     //     larger L2 -> LDS traffic per flop (4096^3: 148 us);
     //   else 128 x 128 tiles, up to two per unit, which finish in one round; and for at most a
-    //     quarter of the units' worth of those, 64 x 64 tiles, which spread them further.
+    //     quarter of the units' worth of those, 64 x 64 tiles, which spread them further.  (Most of these
+    //     smaller problems go to the split kernel above; what is left is what does not fit it.)
     const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
     const int64_t tiles256x128 = ((M + 127) / 128) * ((N + 255) / 256);
     const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
@@ -297,19 +406,36 @@ int prepare_workspace(DeviceState &st, size_t bytes, hipStream_t stream)
     return FF_OK;
 }
 
+// The largest workspace a call on this stream can have: what a caller bound, or during a capture what the
+// library already owns (growing it would be illegal), is fixed.
+size_t workspace_limit(DeviceState &st, hipStream_t stream)
+{
+    if (st.ws != nullptr && !st.ws_owned)
+        return st.ws_bytes;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return st.ws_bytes;
+    }
+    return capture != hipStreamCaptureStatusNone ? st.ws_bytes : SIZE_MAX;
+}
+
 bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
-// This device's copy of the static scratch array (asked of the runtime once per device, with that
+// This device's copies of the static scratch arrays (asked of the runtime once per device, with that
 // device current), or null if the runtime refuses.
 void *no_alloc_scratch(DeviceState &st)
 {
     if (st.no_alloc_ptr == nullptr) {
         void *ptr = nullptr;
-        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || ptr == nullptr) {
+        void *sums = nullptr;
+        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || ptr == nullptr ||
+            hipGetSymbolAddress(&sums, HIP_SYMBOL(scratch_sums)) != hipSuccess || sums == nullptr) {
             (void)hipGetLastError();
             return nullptr;
         }
         st.no_alloc_ptr = ptr;
+        st.no_alloc_sums = sums;
     }
     return st.no_alloc_ptr;
 }
@@ -336,10 +462,19 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
     if (rc != FF_OK)
         return rc;
     char *ws = nullptr;
+    if (pl.split_s > 0 &&
+        (no_alloc ? pl.sums_off > kNoAllocBytes || pl.total_bytes - pl.sums_off > kNoAllocSumBytes
+                  : pl.total_bytes > st->ws_bytes && pl.total_bytes > workspace_limit(*st, stream))) {
+        // not enough scratch memory for the partial products: the kernels that need less
+        pl = Plan();
+        rc = make_plan(M, K, N, dtype, st->num_cus, st, g_forced_variant, linear_only, pl, false);
+        if (rc != FF_OK)
+            return rc;
+    }
     if (no_alloc) {
         // the static array is the workspace; what the kernels expect to find zero (error word, the
         // arrival counters this plan uses) is cleared by a kernel on the caller's stream first
-        if (pl.total_bytes > kNoAllocBytes)
+        if ((pl.split_s > 0 ? pl.sums_off : pl.total_bytes) > kNoAllocBytes)
             return FF_ERR_WORKSPACE;
         ws = static_cast<char *>(no_alloc_scratch(*st));
         if (ws == nullptr)
@@ -347,9 +482,11 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
         // the error word (offset 0) is cleared by the first call on a device only: later calls leave a
         // failure flagged by an earlier one for ff_check_device to report
         const size_t first = st->no_alloc_used ? kCounterOffset : 0;
-        const size_t ctrl = pl.variant == FF_VARIANT_SMALL_M
-                                ? kCounterOffset + (size_t)kSyncWays * kSyncStride * sizeof(unsigned)
-                                : kCounterOffset + (size_t)pl.RB * 2 * sizeof(unsigned);
+        const size_t ctrl =
+            kCounterOffset +
+            sizeof(unsigned) * (pl.split_s > 0 ? ((size_t)pl.RB * pl.NT + (size_t)pl.RB * pl.split_s * kSplitWays) * kSplitCounterStride
+                                : pl.variant == FF_VARIANT_SMALL_M ? (size_t)kSyncWays * kSyncStride
+                                                                   : (size_t)pl.RB * 2);
         const size_t words = (ctrl - first + 3) / 4;
         hipLaunchKernelGGL(fill_words_kernel, dim3((unsigned)((words + 255) / 256 < 64 ? (words + 255) / 256 : 64)),
                            dim3(256), 0, stream, reinterpret_cast<unsigned *>(ws + first), words, 0u);
@@ -367,7 +504,7 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
     const long long wait_ticks = g_wait_limit_us * st->ticks_per_us;
     const bool bf16 = dtype == FF_BF16;
 
-    if (pl.variant == FF_VARIANT_SMALL_M) {
+    if (pl.variant == FF_VARIANT_SMALL_M && pl.split_s == 0) {
         SmallMParams p{};
         p.X = X; p.W = W; p.b = b; p.gamma = gamma; p.beta = beta; p.Y = Y;
         p.partials = reinterpret_cast<floatx2 *>(ws + pl.partial_off);
@@ -383,6 +520,28 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
                          ? st->timeline
                          : nullptr;
         if (launch_smallm_kernel(pl.mt, p, pl.grid, stream) != hipSuccess)
+            return FF_ERR_LAUNCH;
+        t_last_variant = pl.variant;
+        return FF_OK;
+    }
+
+    if (pl.split_s > 0) {
+        SplitParams p{};
+        p.X = X; p.W = W; p.b = b; p.gamma = gamma; p.beta = beta; p.Y = Y;
+        p.sums = static_cast<float *>(no_alloc ? st->no_alloc_sums : ws + pl.sums_off);
+        p.partials = reinterpret_cast<floatx2 *>(ws + pl.partial_off);
+        p.counters = counters;
+        p.err = err;
+        p.eps = eps;
+        p.M = (int)M; p.K = (int)K; p.N = (int)N;
+        p.NT = pl.NT; p.RB = pl.RB; p.S = pl.split_s;
+        p.extra_arrivals = g_extra_arrivals;
+        p.wait_ticks = wait_ticks;
+        p.timeline = (st->timeline != nullptr &&
+                      st->timeline_bytes >= (size_t)pl.grid * kTimelineSlots * sizeof(unsigned long long))
+                         ? st->timeline
+                         : nullptr;
+        if (launch_split_kernel(bf16, pl.split_shape, p, pl.grid, stream) != hipSuccess)
             return FF_ERR_LAUNCH;
         t_last_variant = pl.variant;
         return FF_OK;
@@ -719,15 +878,15 @@ int ff_plan_query(int64_t M, int64_t K, int64_t N, int dtype, int out[8])
     const int prc = make_plan(M, K, N, dtype, num_cus, st, g_forced_variant, false, pl);
     if (prc != FF_OK)
         return prc;
-    const bool small = pl.variant == FF_VARIANT_SMALL_M;
+    const bool small = pl.variant == FF_VARIANT_SMALL_M && pl.split_s == 0;
     out[0] = pl.variant;
     out[1] = small ? (int)M : pl.tile_m;
     out[2] = small ? kSmallMStripCols : pl.tile_n;
-    out[3] = small ? 8 : tile_shape_waves(pl.shape);
+    out[3] = small ? 8 : (pl.split_s > 0 ? 4 : tile_shape_waves(pl.shape));
     out[4] = pl.grid;
     out[5] = small ? 1 : pl.rounds;
     out[6] = (pl.grid + num_cus - 1) / num_cus;
-    out[7] = (!small && pl.swz_sc_log2 >= 0) ? 1 : 0;
+    out[7] = (pl.split_s > 0 || (!small && pl.swz_sc_log2 >= 0)) ? 1 : 0;
     return FF_OK;
 }
 

@@ -160,14 +160,10 @@ __device__ __forceinline__ bool wait_counter(const unsigned *counter, unsigned t
 constexpr int kSyncWays = 32;
 constexpr int kSyncStride = 1024;  // uint32 words between ways
 
-// Called by every lane of one wavefront; lane l < kSyncWays polls way l until it has seen
-// `target` arrivals there (sticky: a way counts once seen).  False if the bound expired.
-__device__ __forceinline__ bool wait_counters_wave(const unsigned *counters, unsigned target,
-                                                   long long limit_ticks)
+// Called by every lane of one wavefront: the lanes with `polls` set wait for their own word `mine` to
+// reach their `target` (sticky: a word counts once seen).  False if the bound expired.
+__device__ __forceinline__ bool wait_ways(const unsigned *mine, bool polls, unsigned target, long long limit_ticks)
 {
-    const int lane = threadIdx.x & 63;
-    const bool polls = lane < kSyncWays;
-    const unsigned *mine = counters + (size_t)(polls ? lane : 0) * kSyncStride;
     bool seen = !polls || atomic_load_device(mine) >= target;
     if (__all(seen))
         return true;
@@ -183,6 +179,15 @@ __device__ __forceinline__ bool wait_counters_wave(const unsigned *counters, uns
         if (wall_clock64() - t0 > limit_ticks)
             return false;
     }
+}
+
+// Lane l < kSyncWays polls way l.
+__device__ __forceinline__ bool wait_counters_wave(const unsigned *counters, unsigned target,
+                                                   long long limit_ticks)
+{
+    const int lane = threadIdx.x & 63;
+    const bool polls = lane < kSyncWays;
+    return wait_ways(counters + (size_t)(polls ? lane : 0) * kSyncStride, polls, target, limit_ticks);
 }
 
 }  // namespace ff

@@ -1,0 +1,548 @@
+// Fused linear + erf-GELU + LayerNorm for problems with too few tiles to fill the chip (gfx950):
+// output tiles of 64 x 32, 64 x 64 or 128 x 128 (columns x rows) whose K range is cut over S workgroups.
+//
+// One round: grid = tiles * S workgroups, all resident.  Workgroup (tile, s) walks its share of the
+// 128-byte K slabs through a ring of kRing LDS stages filled by direct-to-LDS loads, so kRing - 1
+// slabs are in flight while one is multiplied: such a problem is bound by the latency and rate of
+// reading W and X (the two-stage loop of the persistent tile kernel keeps one slab, 16 KB, in flight
+// per workgroup and waits 0.8 us for each).  Then
+//   1  S > 1: the fp32 tile goes to global memory in row slices, the tile's S workgroups meet, and each
+//      adds the S partial products of its slice of BM / S rows in s order;
+//   2  bias, GELU and the slice's row statistics (mean, M2) over the tile's columns; the workgroups
+//      with the same rows exchange those and merge them in fixed order;
+//   3  normalise, convert, store.
+// Measured against the two-stage loop of the tile kernel (cold inputs, whole call): 96 x 8192 x 8192
+// bf16 104.7 -> 46.5 us (W at 2.9 TB/s), 512 x 8192 x 8192 bf16 125 -> 103, 64 x 4096 x 4096 fp32 98 -> 31,
+// 256 x 512 x 512 fp32 17.3 -> 11.5 (on the device); over 336 drawn shapes 1.36 (bf16) and 1.50 (fp32) times
+// as fast, none slower.  What is left at 96 x 8192 x 8192: 27 us of reading W at the rate of a large copy, and
+// launch, two meetings and the ramp of the stream.
+// A thread owns four consecutive columns of one row per pass, so everything after the product stays in
+// its registers and a row's statistics are sums over 16 or 32 neighbouring lanes.
+// All sums run in fixed order: results are bitwise reproducible.
+#include "ff_tile.hpp"
+
+namespace ff {
+
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kRowBytes = 128;   // bytes of one tile row per K slab (8 chunks of 16 B)
+constexpr int kRing = 4;         // LDS stages
+
+__device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 &c, const __bf16 *)
+{
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 &c, const float *)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(b[e]), c, 0, 0, 0);
+}
+
+// LDS placement of 16-byte chunk c of tile row `row`: slot c ^ swizzle, conflict-free for the fragment reads
+__device__ __forceinline__ int swizzle_of_row(int row) { return (row & 7) ^ ((row >> 3) & 1); }
+
+// s_waitcnt vmcnt(n), n < 64, nothing else
+template <int n> __device__ __forceinline__ void wait_vm()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (n & 15) | ((n >> 4) << 14));
+}
+
+template <int ror> __device__ __forceinline__ float rotate16(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ror, 0xf, 0xf, true));
+}
+// Sum over the 16 or 32 neighbouring lanes of a row; the same bits in each of them (every step adds
+// the two same numbers in both lanes of a pair).
+template <int LANES> __device__ __forceinline__ float row_sum(float v)
+{
+    v += rotate16<8>(v);
+    v += rotate16<4>(v);
+    v += rotate16<2>(v);
+    v += rotate16<1>(v);
+    if (LANES == 32)
+        v += __shfl_xor(v, 16);
+    return v;
+}
+
+// Four neighbouring elements of a column vector as they lie in memory
+template <typename T> struct RawCols;
+template <> struct RawCols<float> {
+    floatx4 v;
+    static __device__ __forceinline__ RawCols load(const void *p, int n)
+    {
+        return RawCols{*reinterpret_cast<const floatx4 *>(reinterpret_cast<const float *>(p) + n)};
+    }
+    __device__ __forceinline__ floatx4 get() const { return v; }
+};
+template <> struct RawCols<__bf16> {
+    uintx2 v;
+    static __device__ __forceinline__ RawCols load(const void *p, int n)
+    {
+        return RawCols{*reinterpret_cast<const uintx2 *>(reinterpret_cast<const __bf16 *>(p) + n)};
+    }
+    __device__ __forceinline__ floatx4 get() const
+    {
+        return floatx4{__uint_as_float(v[0] << 16), __uint_as_float(v[0] & 0xffff0000u), __uint_as_float(v[1] << 16),
+                       __uint_as_float(v[1] & 0xffff0000u)};
+    }
+};
+
+// kWN x kWM x kWK wavefronts: kWN x kWM blocks of WTN x WTM MFMA tiles, the k-steps of a slab dealt to kWK.
+template <typename T, int kWN, int kWM, int kWK, int WTN, int WTM>
+__global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const SplitParams p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)  // the body uses device-only types (buffer descriptors)
+    static_assert(kWN * kWM * kWK == 4, "four wavefronts");
+    constexpr int BN = kWN * WTN * 32, BM = kWM * WTM * 32;
+    constexpr int kChunkElems = 16 / (int)sizeof(T);
+    constexpr int kSlabElems = kRowBytes / (int)sizeof(T);
+    constexpr int kStageBytes = (BN + BM) * kRowBytes;
+    constexpr int kDmaA = BN / 32, kDmaB = BM / 32;  // direct-to-LDS instructions (8 rows each) per wave and slab
+    constexpr int kDma = kDmaA + kDmaB;
+    constexpr int kPitch = BN + 4;                   // floats of a row of the product in LDS
+    constexpr int kProdBytes = kWK * BM * kPitch * 4;
+    constexpr int kSmemBytes = kRing * kStageBytes > kProdBytes ? kRing * kStageBytes : kProdBytes;
+    constexpr int kLanes = BN / 4;                   // lanes that share a row after the product
+    constexpr int kRowsPerPass = kThreads / kLanes;
+    constexpr int kMaxPass = BM / kRowsPerPass;
+    __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % kWN, wm = (wave / kWN) % kWM, wk = wave / (kWN * kWM);
+    const int h = lane >> 5, l32 = lane & 31;
+    const int M = p.M, N = p.N, K = p.K, S = p.S;
+
+    // Workgroup -> (s, column tile, row block), row block fastest: the workgroups of one XCD (blockIdx
+    // modulo 8) get consecutive numbers, so that those which read the same rows of W share an L2.
+    int rb, cb, s;
+    {
+        const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+        const int each = (int)gridDim.x >> 3, more = (int)gridDim.x & 7;
+        const int t = xcd * each + (xcd < more ? xcd : more) + slot;
+        const int u = t / p.RB;
+        rb = t - u * p.RB;
+        s = u / p.NT;
+        cb = u - s * p.NT;
+    }
+    const int m0 = rb * BM, n0 = cb * BN;
+
+    // Phase timestamps (test hook), as in the tile kernel
+    auto stamp = [&](int k) {
+        if (p.timeline != nullptr && tid == 0)
+            p.timeline[(size_t)blockIdx.x * kTimelineSlots + k] = k < kTimelineCycleSlot ? wall_clock64() : clock64();
+    };
+    stamp(0);
+
+    // this thread's column vectors: the oldest loads in flight, waited for together with the first slab
+    const int c4 = (tid % kLanes) * 4;
+    const bool col_ok = n0 + c4 < N;  // N is a multiple of 4: four columns are in or out together
+    const int n4 = col_ok ? n0 + c4 : 0;
+    // (loads never branch and nothing uses them before the product is there: a use, a conversion
+    // included, would wait for the load first)
+    const RawCols<T> raw_b = RawCols<T>::load(p.b ? p.b : p.W, p.b ? n4 : 0);
+    const RawCols<T> raw_g = RawCols<T>::load(p.gamma ? p.gamma : p.W, p.gamma ? n4 : 0);
+    const RawCols<T> raw_be = RawCols<T>::load(p.beta ? p.beta : p.W, p.beta ? n4 : 0);
+
+    // ---- this workgroup's slabs ----
+    const int slabs = (K + kSlabElems - 1) / kSlabElems;
+    const int per = (slabs + S - 1) / S;
+    const int sl0 = s * per < slabs ? s * per : slabs;
+    const int sl1 = sl0 + per < slabs ? sl0 + per : slabs;
+    const bool cut = sl1 > sl0 && sl1 * kSlabElems > K;  // the last one is cut by K: through registers
+    const int full = sl1 - sl0 - (cut ? 1 : 0);
+
+    const size_t row_stride = (size_t)K * sizeof(T);
+    const char *w_tile = (const char *)p.W + (size_t)n0 * row_stride + (size_t)sl0 * kRowBytes;
+    const char *x_tile = (const char *)p.X + (size_t)m0 * row_stride + (size_t)sl0 * kRowBytes;
+    unsigned offa[kDmaA], offb[kDmaB];
+    // lane -> (row of an instruction's eight, stored chunk slot); rows beyond the matrix read its last row
+#pragma unroll
+    for (int j = 0; j < kDmaA; ++j) {
+        const int row = wave * (BN / 4) + j * 8 + (lane >> 3);
+        const int rr = n0 + row < N ? row : N - 1 - n0;
+        offa[j] = (unsigned)rr * (unsigned)row_stride + (((lane & 7) ^ swizzle_of_row(row)) << 4);
+    }
+#pragma unroll
+    for (int j = 0; j < kDmaB; ++j) {
+        const int row = wave * (BM / 4) + j * 8 + (lane >> 3);
+        const int rr = m0 + row < M ? row : M - 1 - m0;
+        offb[j] = (unsigned)rr * (unsigned)row_stride + (((lane & 7) ^ swizzle_of_row(row)) << 4);
+    }
+    // all addresses are in bounds by construction; the descriptors do not rely on range checking
+    const __amdgpu_buffer_rsrc_t w_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(w_tile), 0, 0xffffffffu, 0x00020000);
+    const __amdgpu_buffer_rsrc_t x_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(x_tile), 0, 0xffffffffu, 0x00020000);
+    auto request = [&](int i) {  // slab i of this workgroup into stage i % kRing
+        char *st = smem + (i % kRing) * kStageBytes;
+#pragma unroll
+        for (int j = 0; j < kDmaA; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                w_rsrc, (__attribute__((address_space(3))) void *)(st + (wave * (BN / 4) + j * 8) * kRowBytes), 16,
+                offa[j], i * kRowBytes, 0, 0);
+#pragma unroll
+        for (int j = 0; j < kDmaB; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                x_rsrc, (__attribute__((address_space(3))) void *)(st + (BN + wave * (BM / 4) + j * 8) * kRowBytes), 16,
+                offb[j], i * kRowBytes, 0, 0);
+    };
+
+    floatx16 acc[WTN][WTM];
+#pragma unroll
+    for (int i = 0; i < WTN; ++i)
+#pragma unroll
+        for (int j = 0; j < WTM; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                acc[i][j][r] = 0.0f;
+    const int swz = swizzle_of_row(l32);
+    const int a_base = (wn * WTN * 32 + l32) * kRowBytes;
+    const int b_base = (BN + wm * WTM * 32 + l32) * kRowBytes;
+    auto multiply = [&](int stage) {
+        const char *st = smem + stage * kStageBytes;
+        constexpr int kSteps = 4 / kWK;
+        uintx4 a[kSteps][WTN], b[kSteps][WTM];
+#pragma unroll
+        for (int ks = 0; ks < kSteps; ++ks) {
+            const int coff = ((2 * (wk * kSteps + ks) + h) ^ swz) << 4;
+#pragma unroll
+            for (int i = 0; i < WTN; ++i)
+                a[ks][i] = *reinterpret_cast<const uintx4 *>(st + a_base + i * 32 * kRowBytes + coff);
+#pragma unroll
+            for (int j = 0; j < WTM; ++j)
+                b[ks][j] = *reinterpret_cast<const uintx4 *>(st + b_base + j * 32 * kRowBytes + coff);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // all reads are under way before the first product waits for its own
+#pragma unroll
+        for (int ks = 0; ks < kSteps; ++ks)
+#pragma unroll
+            for (int i = 0; i < WTN; ++i)
+#pragma unroll
+                for (int j = 0; j < WTM; ++j)
+                    mma(a[ks][i], b[ks][j], acc[i][j], (const T *)nullptr);
+    };
+
+    // the slab cut by K, requested first: chunks at or beyond K are zeros in both operands
+    uintx4 cutv[kDma];
+    if (cut) {
+#pragma unroll
+        for (int j = 0; j < kDma; ++j) {
+            const bool is_w = j < kDmaA;
+            const int jj = is_w ? j : j - kDmaA;
+            const int row = wave * ((is_w ? BN : BM) / 4) + jj * 8 + (lane >> 3);
+            const int chunk = (lane & 7) ^ swizzle_of_row(row);
+            const bool in = (sl1 - 1) * kSlabElems + chunk * kChunkElems < K;
+            const char *src = (is_w ? w_tile + offa[is_w ? jj : 0] : x_tile + offb[is_w ? 0 : jj]) + (size_t)full * kRowBytes;
+            cutv[j] = *reinterpret_cast<const uintx4 *>(in ? src : (const char *)(is_w ? p.W : p.X));
+        }
+    }
+
+    // ---- main loop ----
+#pragma unroll
+    for (int t = 0; t < kRing - 1; ++t)
+        if (t < full)
+            request(t);
+    int i = 0;
+    for (; i + kRing - 1 < full; ++i) {
+        wait_vm<(kRing - 2) * kDma>();  // this wave's rows of slab i have landed
+        lds_barrier();                  // everyone's have, and everyone has read slab i - 1
+        request(i + kRing - 1);         // into the stage slab i - 1 occupied
+        multiply(i % kRing);
+    }
+#pragma unroll
+    for (int left = kRing - 2; left >= 0; --left)
+        if (full - i > left) {
+            if (left == 2)
+                wait_vm<2 * kDma>();
+            else if (left == 1)
+                wait_vm<kDma>();
+            else
+                wait_vm<0>();
+            lds_barrier();
+            multiply(i % kRing);
+            ++i;
+        }
+    static_assert(kRing == 4, "the waits above are written for four stages");
+    if (cut) {
+        lds_barrier();
+#pragma unroll
+        for (int j = 0; j < kDma; ++j) {
+            const int row = j < kDmaA ? wave * (BN / 4) + j * 8 : wave * (BM / 4) + (j - kDmaA) * 8;
+            const int chunk = (lane & 7) ^ swizzle_of_row(row + (lane >> 3));
+            const bool in = (sl1 - 1) * kSlabElems + chunk * kChunkElems < K;
+            *reinterpret_cast<uintx4 *>(smem + (j < kDmaA ? row : BN + row) * kRowBytes + lane * 16) =
+                cutv[j] & (in ? 0xffffffffu : 0u);
+        }
+        lds_barrier();
+        multiply(0);
+    }
+    stamp(2);
+    lds_barrier();  // all fragment reads done: the stages become the product's place
+
+    // ---- product to LDS, [kWK][row][column] ----
+    float *prod = reinterpret_cast<float *>(smem);
+    {
+        // a lane's registers of a 32 x 32 block: row (of the output) l32, columns 8 q + 4 h + (0..3)
+        float *mine = prod + wk * BM * kPitch;
+#pragma unroll
+        for (int i = 0; i < WTN; ++i)
+#pragma unroll
+            for (int j = 0; j < WTM; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<floatx4 *>(mine + ((wm * WTM + j) * 32 + l32) * kPitch + (wn * WTN + i) * 32 + q * 8 + h * 4) =
+                        floatx4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    }
+    lds_barrier();
+    const int r_in_pass = tid / kLanes;
+    auto product = [&](int row) {
+        floatx4 v = *reinterpret_cast<const floatx4 *>(prod + row * kPitch + c4);
+#pragma unroll
+        for (int w = 1; w < kWK; ++w)
+            v += *reinterpret_cast<const floatx4 *>(prod + (w * BM + row) * kPitch + c4);
+        return v;
+    };
+    const int rows = BM / S;            // rows of this workgroup's slice
+    const int row0 = s * rows;          // first of them in the tile
+    const int passes = (rows + kRowsPerPass - 1) / kRowsPerPass;
+    const bool mine = r_in_pass < rows; // fewer rows than a pass takes: the rest of the threads idle
+
+    // ---- 1: sum over the tile's workgroups ----
+    floatx4 v[kMaxPass];
+    const int tile = rb * p.NT + cb;
+    if (S > 1) {
+        // partial products [tile][s][BM][BN]; the writer keeps its own slice.  Written through (sc1) to
+        // the level all XCDs share; each 128-byte line has one writer and is read by one other workgroup.
+        float *part = p.sums + ((size_t)tile * S + s) * (BM * BN);
+        const __amdgpu_buffer_rsrc_t st_rsrc = __builtin_amdgcn_make_buffer_rsrc(part, 0, BM * BN * 4, 0x00020000);
+#pragma unroll
+        for (int q = 0; q < kMaxPass; ++q) {
+            const int row = q * kRowsPerPass + r_in_pass;
+            if (row < row0 || row >= row0 + rows)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, product(row)), st_rsrc,
+                                                       (row * BN + c4) * 4, 0, 16 /* sc1 */);
+        }
+        wait_published();
+        __syncthreads();
+        unsigned *c = p.counters + (size_t)tile * kSplitCounterStride;
+        if (tid == 0) {
+            atomic_add_device(c, 1u);
+            if (!wait_counter(c, (unsigned)S, p.wait_ticks))
+                atomic_store_device(p.err, 1u);
+        }
+        __syncthreads();
+        const float *all = p.sums + (size_t)tile * S * (BM * BN);
+#pragma unroll
+        for (int q = 0; q < kMaxPass; ++q)
+            if (q < passes) {
+                const int row = row0 + q * kRowsPerPass + r_in_pass;
+                const int rr = mine ? row : row0;
+                const floatx4 own = product(rr);
+                floatx4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+                for (int t0 = 0; t0 < S; t0 += 4) {
+                    floatx4 u[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const int o = t0 + t < S ? t0 + t : S - 1;
+                        u[t] = *reinterpret_cast<const floatx4 *>(all + ((size_t)o * BM + rr) * BN + c4);
+                    }
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        if (t0 + t < S)
+                            sum += t0 + t == s ? own : u[t];
+                }
+                v[q] = sum;
+            }
+    } else {
+#pragma unroll
+        for (int q = 0; q < kMaxPass; ++q)
+            v[q] = product(q * kRowsPerPass + r_in_pass);
+    }
+    stamp(1);
+
+    // ---- 2: bias, GELU, row statistics over the tile's columns, exchange ----
+    floatx4 bias = {0.0f, 0.0f, 0.0f, 0.0f}, gamma = {1.0f, 1.0f, 1.0f, 1.0f}, beta = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (p.b)
+        bias = raw_b.get();
+    if (p.gamma)
+        gamma = raw_g.get();
+    if (p.beta)
+        beta = raw_be.get();
+    const int nvalid = N - n0 < BN ? N - n0 : BN;
+    const float inv_valid = 1.0f / (float)nvalid;
+    const int rows_pad = rows < 16 ? 16 : rows;  // a workgroup's partials fill whole 128-byte lines
+    floatx2 *stats = p.partials + (size_t)(rb * S + s) * p.NT * rows_pad;
+#pragma unroll
+    for (int q = 0; q < kMaxPass; ++q)
+        if (q < passes) {
+            float sum = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[q][e] = gelu_erf(v[q][e] + bias[e]);
+                sum += v[q][e];
+            }
+            const float mean = row_sum<kLanes>(col_ok ? sum : 0.0f) * inv_valid;
+            float m2 = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float d = v[q][e] - mean;
+                m2 = fmaf(d, d, m2);
+            }
+            m2 = row_sum<kLanes>(col_ok ? m2 : 0.0f);
+            if (mine && c4 == 0)
+                publish_pair(stats + (size_t)cb * rows_pad + q * kRowsPerPass + r_in_pass, floatx2{mean, m2});
+        }
+    stamp(3);
+    wait_published();
+    __syncthreads();
+    // the row slice's NT workgroups meet: arrivals spread over kSplitWays words in lines of their own
+    unsigned *group = p.counters + ((size_t)p.RB * p.NT + (size_t)(rb * S + s) * kSplitWays) * kSplitCounterStride;
+    if (tid == 0)
+        atomic_add_device(group + (cb % kSplitWays) * kSplitCounterStride, 1u);
+    if (wave == 0) {
+        const int w = lane < kSplitWays ? lane : 0;
+        const unsigned target = (unsigned)((p.NT + kSplitWays - 1 - w) / kSplitWays + (w == 0 ? p.extra_arrivals : 0));
+        if (!wait_ways(group + (size_t)w * kSplitCounterStride, lane < kSplitWays, target, p.wait_ticks) && lane == 0)
+            atomic_store_device(p.err, 1u);
+    }
+    __syncthreads();
+    stamp(4);
+
+    // ---- 3: merge, normalise, store ----
+    // Thread -> (row of the slice, every chunks-th tile), so that a load instruction reads neighbouring
+    // rows of one tile and up to eight are in flight; the chunks of a row meet in LDS in chunk order.
+    // (A row's own lanes reading its tiles touch a line each: 40 x 512 x 15360, 240 tiles, 34 us a call.)
+    float *s_n = reinterpret_cast<float *>(smem);             // [kMaxChunks][rows]: columns seen
+    floatx2 *s_mm = reinterpret_cast<floatx2 *>(smem + 1024); // [kMaxChunks][rows]: mean, M2
+    floatx2 *s_row = reinterpret_cast<floatx2 *>(smem + 4096);  // [rows]: mean, 1 / standard deviation
+    constexpr int kMaxChunks = 16, kBatch = 8;
+    const int rows_log2 = 31 - __builtin_clz(rows);
+    const int chunks = (kThreads >> rows_log2) < kMaxChunks ? (kThreads >> rows_log2) : kMaxChunks;
+    {
+        const int r = tid & (rows - 1), chunk = tid >> rows_log2;
+        if (chunk < chunks) {
+            float na = 0.0f, mean_a = 0.0f, m2a = 0.0f;
+            for (int c0 = chunk; c0 < p.NT; c0 += chunks * kBatch) {
+                floatx2 u[kBatch];
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    const int c = c0 + j * chunks < p.NT ? c0 + j * chunks : p.NT - 1;
+                    u[j] = stats[(size_t)c * rows_pad + r];
+                }
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    const int c = c0 + j * chunks;
+                    if (c < p.NT)
+                        merge_stats(na, mean_a, m2a, (float)(N - c * BN < BN ? N - c * BN : BN), u[j][0], u[j][1]);
+                }
+            }
+            s_n[tid] = na;
+            s_mm[tid] = floatx2{mean_a, m2a};
+        }
+        __syncthreads();
+        if (tid < rows) {
+            float na = s_n[tid];
+            floatx2 u = s_mm[tid];
+            float mean_a = u[0], m2a = u[1];
+            for (int c = 1; c < chunks; ++c) {
+                u = s_mm[c * rows + tid];
+                merge_stats(na, mean_a, m2a, s_n[c * rows + tid], u[0], u[1]);
+            }
+            s_row[tid] = floatx2{mean_a, 1.0f / sqrtf(m2a / (float)N + p.eps)};
+        }
+        __syncthreads();
+    }
+    stamp(5);
+    T *Y = reinterpret_cast<T *>(p.Y);
+#pragma unroll
+    for (int q = 0; q < kMaxPass; ++q)
+        if (q < passes) {
+            const int r = q * kRowsPerPass + r_in_pass;
+            const int gm = m0 + row0 + r;
+            if (mine && col_ok && gm < M) {
+                const floatx2 ms = s_row[r];
+                float y[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    y[e] = fmaf((v[q][e] - ms[0]) * ms[1], gamma[e], beta[e]);
+                T *dst = Y + (size_t)gm * N + n0 + c4;
+                if (sizeof(T) == 2)
+                    *reinterpret_cast<uintx2 *>(dst) = uintx2{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+                else
+                    *reinterpret_cast<floatx4 *>(dst) = floatx4{y[0], y[1], y[2], y[3]};
+            }
+        }
+    // ---- departure: the last to leave a counter re-arms it ----
+    if (tid == 0) {
+        if (S > 1) {
+            unsigned *c = p.counters + (size_t)tile * kSplitCounterStride;
+            if (atomic_add_device(c + 1, 1u) == (unsigned)S - 1u) {
+                atomic_store_device(c, 0u);
+                atomic_store_device(c + 1, 0u);
+            }
+        }
+        if (atomic_add_device(group + 1, 1u) == (unsigned)p.NT - 1u) {
+            for (int w = 0; w < kSplitWays; ++w)
+                atomic_store_device(group + (size_t)w * kSplitCounterStride, 0u);
+            atomic_store_device(group + 1, 0u);
+        }
+    }
+    stamp(6);
+#else
+    (void)p;
+#endif
+}
+
+}  // namespace
+
+#define FF_SPLIT_TYPES(WN, WM, WK, WTN, WTM, CALL) \
+    return bf16 ? CALL(__bf16, WN, WM, WK, WTN, WTM) : CALL(float, WN, WM, WK, WTN, WTM);
+#define FF_SPLIT_DISPATCH(CALL)                              \
+    switch (shape) {                                         \
+    case kSplit64x32: FF_SPLIT_TYPES(2, 1, 2, 1, 1, CALL)    \
+    case kSplit128x32: FF_SPLIT_TYPES(2, 1, 2, 2, 1, CALL)   \
+    case kSplit64: FF_SPLIT_TYPES(2, 2, 1, 1, 1, CALL)       \
+    case kSplit128x64: FF_SPLIT_TYPES(2, 2, 1, 2, 1, CALL)   \
+    default: FF_SPLIT_TYPES(2, 2, 1, 2, 2, CALL)             \
+    }
+
+template <typename T, int WN, int WM, int WK, int WTN, int WTM>
+static hipError_t launch_split(const SplitParams &p, int grid, hipStream_t stream)
+{
+    hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM>), dim3(grid), dim3(kThreads), 0, stream, p);
+    return hipGetLastError();
+}
+
+template <typename T, int WN, int WM, int WK, int WTN, int WTM>
+static int split_blocks()
+{
+    int a = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, split_kernel<T, WN, WM, WK, WTN, WTM>, kThreads, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return a;
+}
+
+hipError_t launch_split_kernel(bool bf16, int shape, const SplitParams &p, int grid, hipStream_t stream)
+{
+#define FF_CALL(T, WN, WM, WK, WTN, WTM) launch_split<T, WN, WM, WK, WTN, WTM>(p, grid, stream)
+    FF_SPLIT_DISPATCH(FF_CALL)
+#undef FF_CALL
+}
+
+// Workgroups of this kernel that fit one compute unit at once, as the runtime reports it; 0 if it does not.
+int split_kernel_blocks_per_cu(bool bf16, int shape)
+{
+#define FF_CALL(T, WN, WM, WK, WTN, WTM) split_blocks<T, WN, WM, WK, WTN, WTM>()
+    FF_SPLIT_DISPATCH(FF_CALL)
+#undef FF_CALL
+}
+#undef FF_SPLIT_DISPATCH
+#undef FF_SPLIT_TYPES
+
+}  // namespace ff

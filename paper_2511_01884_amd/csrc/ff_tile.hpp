@@ -51,6 +51,36 @@ struct FinalizeParams {
     int M, N, NT, BM, BN;
 };
 
+// Split kernel: counters in 128-byte lines of their own, one per tile (the S workgroups that share its
+// K range), then kSplitWays per row slice (the workgroups that share its rows); word 0 of a line counts
+// arrivals, word 1 (of a slice's first line) departures.
+constexpr int kSplitCounterStride = 32;  // uint32 words
+constexpr int kSplitWays = 8;
+constexpr int kSplitMaxS = 16;
+
+struct SplitParams {
+    const void *X, *W, *b, *gamma, *beta;
+    void *Y;
+    float *sums;         // [tile][S][BM][BN] partial products (S > 1)
+    floatx2 *partials;   // [RB][S][NT][max(BM / S, 16)] (mean, M2) per row of a slice and column tile
+    unsigned *counters;
+    unsigned *err;
+    float eps;
+    int M, K, N;
+    int NT, RB;          // tiles along N, row blocks
+    int S;               // workgroups that share a tile's K range
+    int extra_arrivals;  // test hook: added to the arrival target (non-zero makes waits expire)
+    long long wait_ticks;
+    unsigned long long *timeline;  // test hook: phase timestamps, or null
+};
+
+// Shapes of the split kernel (columns x rows of a tile)
+enum SplitShape { kSplit64x32 = 0, kSplit128x32 = 1, kSplit64 = 2, kSplit128x64 = 3, kSplit128 = 4, kNumSplitShapes = 5 };
+inline int split_shape_cols(int shape) { return shape == kSplit64x32 || shape == kSplit64 ? 64 : 128; }
+inline int split_shape_rows(int shape) { return shape == kSplit128 ? 128 : (shape >= kSplit64 ? 64 : 32); }
+hipError_t launch_split_kernel(bool bf16, int shape, const SplitParams &p, int grid, hipStream_t stream);
+int split_kernel_blocks_per_cu(bool bf16, int shape);
+
 struct SmallMParams {
     const void *X, *W, *b, *gamma, *beta;
     void *Y;
