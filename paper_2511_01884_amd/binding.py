@@ -348,8 +348,8 @@ def _selection_outputs(n: int, J: int, k: int):
 
 
 def _selection_result(r, score, top, selected, threshold):
-    return {"r": r, "score": score, "top": [[int(m) for m in row if m >= 0] for row in top],
-            "selected": [int(m) for m in selected.nonzero()[0]], "threshold": float(threshold[0])}
+    return {"r": r, "score": score, "top": [[m for m in row if m >= 0] for row in top.tolist()],
+            "selected": selected.nonzero()[0].tolist(), "threshold": float(threshold[0])}
 
 
 def ff_metric_selection(values: torch.Tensor, runtime: torch.Tensor, top_k: int = 20, percentile: float = 75.0,

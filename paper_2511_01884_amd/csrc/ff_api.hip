@@ -803,48 +803,67 @@ int ff_metric_selection(const double *values, const double *runtime, int64_t n_t
     const int n = (int)n_tasks, V = (int)n_kernels, J = (int)n_metrics;
     hipStream_t st_stream = static_cast<hipStream_t>(stream);
     try {
-    std::vector<double> r((size_t)n * J);
-    std::vector<uint8_t> keep;
+    // one host buffer, r then the filter's verdicts: one copy brings both
+    const size_t count = (size_t)n * J;
+    std::vector<double> results(count + (filter ? (count + 7) / 8 : 0));
+    double *const r = results.data();
+    uint8_t *const keep = filter ? reinterpret_cast<uint8_t *>(r + count) : nullptr;
     {
         std::lock_guard<std::mutex> lock(g_mutex);
         DeviceState *st = current_device_state();
         if (!st)
             return FF_ERR_LAUNCH;
-        const size_t r_bytes = round_up((size_t)n * J * sizeof(double), 256);
-        const size_t z_bytes = filter ? round_up((size_t)V * J * sizeof(double), 256) : 0;
-        const size_t c_bytes = filter ? round_up((size_t)J * J * sizeof(double), 256) : 0;
-        const int rc = prepare_workspace(*st, kCtrlBytes + r_bytes + z_bytes + c_bytes, st_stream);
+        // Workspace: r and the verdicts of all tasks; for a batch of tasks, the columns' means and scales and
+        // the pair bits.  A batch is what 64 MiB hold, or a bound workspace.  Where that has no room for all
+        // verdicts (very many tasks of very few metrics), a batch's are copied out before the next.
+        const size_t words = ((size_t)J + 63) / 64;
+        const size_t per_task = filter ? (size_t)J * (2 * sizeof(double) + words * sizeof(unsigned long long) + 1) : 0;
+        const bool bound = st->ws != nullptr && !st->ws_owned;
+        const size_t have = bound ? (st->ws_bytes > kCtrlBytes ? st->ws_bytes - kCtrlBytes : 0) : SIZE_MAX;
+        size_t out_bytes = round_up(count * (sizeof(double) + (filter ? 1 : 0)), 256);
+        const bool together = have >= out_bytes + per_task;
+        if (!together)
+            out_bytes = round_up(count * sizeof(double), 256);
+        int batch = n;
+        if (filter) {
+            const size_t fit = (bound ? (have > out_bytes ? have - out_bytes : 0) : (size_t)64 << 20) / per_task;
+            batch = (int)std::min<size_t>({(size_t)n, fit < 1 ? 1 : fit, 32768});
+        }
+        const int rc = prepare_workspace(*st, kCtrlBytes + out_bytes + (size_t)batch * per_task, st_stream);
         if (rc != FF_OK)
             return rc;
         char *ws = static_cast<char *>(st->ws);
         double *r_dev = reinterpret_cast<double *>(ws + kCtrlBytes);
-        double *z_dev = reinterpret_cast<double *>(ws + kCtrlBytes + r_bytes);
-        double *c_dev = reinterpret_cast<double *>(ws + kCtrlBytes + r_bytes + z_bytes);
-        if (launch_pearson(values, runtime, r_dev, n, V, J, st_stream) != hipSuccess)
-            return FF_ERR_LAUNCH;
-        if (hipMemcpyAsync(r.data(), r_dev, (size_t)n * J * sizeof(double), hipMemcpyDeviceToHost, st_stream) !=
-            hipSuccess)
-            return FF_ERR_LAUNCH;
-        if (filter) {
-            keep.resize((size_t)n * J);
-            std::vector<double> C((size_t)J * J);
-            for (int i = 0; i < n; ++i) {
-                if (launch_corr_matrix(values + (size_t)i * V * J, z_dev, c_dev, V, J, st_stream) != hipSuccess)
+        double *mean_dev = filter ? reinterpret_cast<double *>(ws + kCtrlBytes + out_bytes) : nullptr;
+        double *inv_dev = filter ? mean_dev + (size_t)batch * J : nullptr;
+        unsigned long long *mask_dev = filter ? reinterpret_cast<unsigned long long *>(inv_dev + (size_t)batch * J) : nullptr;
+        unsigned char *batch_keep = reinterpret_cast<unsigned char *>(mask_dev + (filter ? (size_t)batch * J * words : 0));
+        for (int i = 0; i < n; i += batch) {
+            const int m = n - i < batch ? n - i : batch;
+            const double *vals = values + (size_t)i * V * J;
+            if (launch_pearson(vals, runtime + (size_t)i * V, r_dev + (size_t)i * J, mean_dev, inv_dev, m, V, J, st_stream) !=
+                hipSuccess)
+                return FF_ERR_LAUNCH;
+            if (filter) {
+                const size_t done = (size_t)i * J;
+                unsigned char *keep_dev = together ? reinterpret_cast<unsigned char *>(r_dev + count) + done : batch_keep;
+                if (launch_duplicate_filter(vals, mean_dev, inv_dev, collinear_tau, mask_dev, keep_dev, m, V, J,
+                                            st_stream) != hipSuccess)
                     return FF_ERR_LAUNCH;
-                if (hipMemcpyAsync(C.data(), c_dev, (size_t)J * J * sizeof(double), hipMemcpyDeviceToHost,
-                                   st_stream) != hipSuccess ||
-                    hipStreamSynchronize(st_stream) != hipSuccess)
+                if (!together && hipMemcpyAsync(keep + done, keep_dev, (size_t)m * J, hipMemcpyDeviceToHost, st_stream) !=
+                                     hipSuccess)
                     return FF_ERR_LAUNCH;
-                metric_greedy_keep(C.data(), J, collinear_tau, keep.data() + (size_t)i * J);
             }
         }
-        if (hipStreamSynchronize(st_stream) != hipSuccess)
+        if (hipMemcpyAsync(r, r_dev, count * (sizeof(double) + (filter && together ? 1 : 0)), hipMemcpyDeviceToHost,
+                           st_stream) != hipSuccess ||
+            hipStreamSynchronize(st_stream) != hipSuccess)
             return FF_ERR_LAUNCH;
     }
-    metric_select_host(r.data(), filter ? keep.data() : nullptr, n, J, top_k, percentile, min_tasks, top_host,
+    metric_select_host(r, keep, n, J, top_k, percentile, min_tasks, top_host,
                        score_host, selected_host, threshold_host);
     if (r_host)
-        std::copy(r.begin(), r.end(), r_host);
+        std::copy(r, r + count, r_host);
     } catch (...) {  // host allocation failed: nothing may leave through the C boundary
         return FF_ERR_WORKSPACE;
     }

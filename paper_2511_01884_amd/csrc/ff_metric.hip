@@ -7,11 +7,11 @@
 //   Step 3: candidates = union of the Top-k lists; score S[m] = mean over all tasks of |r[i][m]|;
 //   selected = candidates that are in the Top-k of at least `min_tasks` tasks, whose r has one sign
 //   over those tasks, and whose score exceeds the given percentile of the candidates' scores.
-// The correlations (one thread per task and metric, and one per pair of metrics for the duplicate
-// filter) are computed on the GPU in fp64; the selection itself is a few hundred numbers and runs
-// on the host.  An undefined correlation (constant column or constant runtime) is NaN: it never
-// enters a Top-k and counts as 0 in the score.  Ties in |r| go to the lower metric index.  The
-// percentile interpolates linearly between order statistics.
+// The correlations (one thread per task and metric, and one pair of metrics at a time for the duplicate
+// filter) are computed on the GPU in fp64, all tasks in one launch, and so is the filter's greedy pass; the
+// selection itself is a few hundred numbers and runs on the host.  An undefined correlation (constant
+// column or constant runtime) is NaN: it never enters a Top-k and counts as 0 in the score.  Ties in |r|
+// go to the lower metric index.  The percentile interpolates linearly between order statistics.
 #include "ff_tile.hpp"
 
 #include <algorithm>
@@ -22,11 +22,15 @@ namespace ff {
 
 namespace {
 
-// r[i][m]: two passes over the V values of the column (mean, then centred sums), all in fp64.
-__global__ __launch_bounds__(256) void pearson_kernel(const double *values, const double *runtime, double *r,
-                                                      int V, int J)
+// One thread per task and metric, two passes over the V values of the column (mean, then centred sums),
+// all in fp64: r, and for the duplicate filter (STATS) the column's mean and 1 / sqrt(sum of squares about
+// it), NaN for a constant column.  Workgroups of one wavefront: a few thousand columns are all there is.
+constexpr int kColumnThreads = 64;
+template <bool STATS>
+__global__ __launch_bounds__(kColumnThreads) void pearson_kernel(const double *values, const double *runtime, double *r,
+                                                                 double *mean, double *inv, int V, int J)
 {
-    const int m = blockIdx.x * 256 + threadIdx.x;
+    const int m = blockIdx.x * kColumnThreads + threadIdx.x;
     const int i = blockIdx.y;
     if (m >= J)
         return;
@@ -36,20 +40,19 @@ __global__ __launch_bounds__(256) void pearson_kernel(const double *values, cons
     // values need not round back to that value, so the variance is no test)
     double mx = 0.0, my = 0.0;
     bool x_const = true, y_const = true;
+    const double x0 = col[0], y0 = rt[0];
+#pragma unroll 8
     for (int v = 0; v < V; ++v) {
-        const double x = col[(size_t)v * J];
+        const double x = col[(size_t)v * J], y = rt[v];
         mx += x;
-        my += rt[v];
-        x_const = x_const && x == col[0];
-        y_const = y_const && rt[v] == rt[0];
-    }
-    if (x_const || y_const) {
-        r[(size_t)i * J + m] = __builtin_nan("");
-        return;
+        my += y;
+        x_const = x_const && x == x0;
+        y_const = y_const && y == y0;
     }
     mx /= (double)V;
     my /= (double)V;
     double sxy = 0.0, sxx = 0.0, syy = 0.0;
+#pragma unroll 8
     for (int v = 0; v < V; ++v) {
         const double dx = col[(size_t)v * J] - mx;
         const double dy = rt[v] - my;
@@ -57,80 +60,199 @@ __global__ __launch_bounds__(256) void pearson_kernel(const double *values, cons
         sxx += dx * dx;
         syy += dy * dy;
     }
-    r[(size_t)i * J + m] = (sxx > 0.0 && syy > 0.0) ? sxy / sqrt(sxx * syy) : __builtin_nan("");
+    const size_t at = (size_t)i * J + m;
+    r[at] = (!x_const && !y_const && sxx > 0.0 && syy > 0.0) ? sxy / sqrt(sxx * syy) : __builtin_nan("");
+    if (STATS) {
+        mean[at] = mx;
+        inv[at] = (!x_const && sxx > 0.0) ? 1.0 / sqrt(sxx) : __builtin_nan("");
+    }
 }
 
-// Z[v][m] = (x - mean) / sqrt(sum (x - mean)^2) for one task; a constant column becomes NaN.
-__global__ __launch_bounds__(256) void standardise_kernel(const double *task_values, double *Z, int V, int J)
+// Bit b of mask[task][a][b / 64], b > a: the columns a and b, standardised, correlate at |c| >= tau (never for a
+// constant column: its c is NaN).  A workgroup takes 64 x 64 pairs on or above the diagonal, a thread 4 x 4 of
+// them; the sum of a pair runs over v in order, the next 16 rows are requested before these are used.  (8 x 8
+// pairs per lane of a lone wavefront read the LDS half as often and took 65 instead of 45 us on twelve tasks of
+// 64 x 1024: nothing covered the loads.)  Bits, not the matrix of correlations: the greedy pass needs no
+// more, and they are a 64th of its bytes (eight tasks of 300 metrics: 92 KB against 5.8 MB that went to the host).
+constexpr int kPairTile = 64, kPairRows = 16;
+__global__ __launch_bounds__(256) void duplicate_kernel(const double *values, const double *mean, const double *inv,
+                                                        unsigned long long *mask, double tau, int V, int J)
 {
-    const int m = blockIdx.x * 256 + threadIdx.x;
-    if (m >= J)
+    if (blockIdx.x < blockIdx.y)
         return;
-    double mx = 0.0;
-    bool x_const = true;
-    for (int v = 0; v < V; ++v) {
-        mx += task_values[(size_t)v * J + m];
-        x_const = x_const && task_values[(size_t)v * J + m] == task_values[m];
+    __shared__ __align__(16) double za[kPairRows][kPairTile], zb[kPairRows][kPairTile];
+    __shared__ unsigned long long bits[kPairTile];
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const int a0 = blockIdx.y * kPairTile, b0 = blockIdx.x * kPairTile;
+    const size_t task = blockIdx.z;
+    values += task * V * J;
+    mean += task * J;
+    inv += task * J;
+    // a thread standardises one column of each side, every fourth row
+    const int col = tid & 63, vrow = tid >> 6;
+    const int ca = a0 + col < J ? a0 + col : J - 1, cb = b0 + col < J ? b0 + col : J - 1;
+    const double ma = mean[ca], ia = inv[ca], mb = mean[cb], ib = inv[cb];
+    double acc[4][4], ra[kPairRows / 4], rb[kPairRows / 4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            acc[i][j] = 0.0;
+    if (tid < kPairTile)
+        bits[tid] = 0;
+    auto request = [&](int v0) {  // rows past the end read the last one; they are not summed
+#pragma unroll
+        for (int u = 0; u < kPairRows / 4; ++u) {
+            const int v = v0 + vrow + u * 4 < V ? v0 + vrow + u * 4 : V - 1;
+            ra[u] = values[(size_t)v * J + ca];
+            rb[u] = values[(size_t)v * J + cb];
+        }
+    };
+    request(0);
+    for (int v0 = 0; v0 < V; v0 += kPairRows) {
+        const int left = V - v0 < kPairRows ? V - v0 : kPairRows;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kPairRows / 4; ++u) {
+            za[vrow + u * 4][col] = (ra[u] - ma) * ia;
+            zb[vrow + u * 4][col] = (rb[u] - mb) * ib;
+        }
+        __syncthreads();
+        if (v0 + kPairRows < V)
+            request(v0 + kPairRows);
+        for (int v = 0; v < left; ++v) {
+            typedef double double2_t __attribute__((ext_vector_type(2)));
+            double x[4], y[4];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const double2_t xv = *reinterpret_cast<const double2_t *>(&za[v][ty * 4 + 2 * i]);
+                const double2_t yv = *reinterpret_cast<const double2_t *>(&zb[v][tx * 2 + 32 * i]);
+                x[2 * i] = xv[0];
+                x[2 * i + 1] = xv[1];
+                y[2 * i] = yv[0];
+                y[2 * i + 1] = yv[1];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[i][j] += x[i] * y[j];
+        }
     }
-    mx /= (double)V;
-    double sxx = 0.0;
-    for (int v = 0; v < V; ++v) {
-        const double d = task_values[(size_t)v * J + m] - mx;
-        sxx += d * d;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned long long w = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int at = tx * 2 + (j & 1) + 32 * (j >> 1);  // column inside the tile
+            const int a = a0 + ty * 4 + i, b = b0 + at;
+            if (b < J && b > a && fabs(acc[i][j]) >= tau)
+                w |= 1ull << at;
+        }
+        if (w != 0)
+            atomicOr(&bits[ty * 4 + i], w);
     }
-    const double inv = (!x_const && sxx > 0.0) ? 1.0 / sqrt(sxx) : __builtin_nan("");
-    for (int v = 0; v < V; ++v)
-        Z[(size_t)v * J + m] = (task_values[(size_t)v * J + m] - mx) * inv;
+    __syncthreads();
+    const int words = (J + 63) / 64;
+    if (tid < kPairTile && a0 + tid < J)
+        mask[(task * J + a0 + tid) * words + blockIdx.x] = bits[tid];
 }
 
-// C[a][b] = sum_v Z[v][a] Z[v][b]: the correlation of metrics a and b (NaN if either is constant)
-__global__ __launch_bounds__(256) void corr_matrix_kernel(const double *Z, double *C, int V, int J)
+// keep[task][m]: metrics in index order, a metric goes when it duplicates (bit in the mask) one already kept.
+// One workgroup per task walks the metrics 64 at a time: the wavefronts have the 64 rows of the mask in
+// registers (requested a block ahead: they do not depend on what is kept), the first one decides the block's 64
+// metrics one after the other from the rows' diagonal word, then every kept row strikes out later metrics.
+constexpr int kGreedyWaves = 16, kGreedyRows = 64 / kGreedyWaves;
+constexpr int kGreedyMaxWords = 128;  // 8192 metrics
+__global__ __launch_bounds__(64 * kGreedyWaves) void greedy_kernel(const unsigned long long *mask, unsigned char *keep, int J)
 {
-    const int b = blockIdx.x * 16 + (threadIdx.x & 15);
-    const int a = blockIdx.y * 16 + (threadIdx.x >> 4);
-    if (a >= J || b >= J)
-        return;
-    double acc = 0.0;
-    for (int v = 0; v < V; ++v)
-        acc += Z[(size_t)v * J + a] * Z[(size_t)v * J + b];
-    C[(size_t)a * J + b] = acc;
+    __shared__ unsigned long long gone[kGreedyMaxWords];
+    __shared__ unsigned long long kept_block;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int words = (J + 63) / 64;
+    mask += (size_t)blockIdx.x * J * words;
+    keep += (size_t)blockIdx.x * J;
+    if (tid < kGreedyMaxWords)
+        gone[tid] = 0;
+    unsigned long long row[kGreedyRows][2], diag = 0;
+    auto request = [&](int block) {  // in bounds for every lane; what is not wanted is dropped below
+#pragma unroll
+        for (int u = 0; u < kGreedyRows; ++u) {
+            const int m = block * 64 + wave * kGreedyRows + u < J ? block * 64 + wave * kGreedyRows + u : J - 1;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                row[u][h] = mask[(size_t)m * words + (lane + 64 * h < words ? lane + 64 * h : words - 1)];
+        }
+        if (wave == 0)
+            diag = mask[(size_t)(block * 64 + lane < J ? block * 64 + lane : J - 1) * words + block];
+    };
+    request(0);
+    __syncthreads();
+    for (int block = 0; block < words; ++block) {
+        if (wave == 0) {
+            // only rows with a duplicate inside the block can decide anything in it
+            const unsigned long long here = gone[block];
+            unsigned long long g = (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(here >> 32)) << 32 |
+                                   (unsigned)__builtin_amdgcn_readfirstlane((unsigned)here);
+            const int count = J - block * 64 < 64 ? J - block * 64 : 64;
+            unsigned long long deciders = __ballot(lane < count && diag != 0);
+            while (deciders != 0) {
+                const int j = __builtin_ctzll(deciders);
+                deciders &= deciders - 1;
+                if (!((g >> j) & 1))
+                    g |= (unsigned long long)(unsigned)__builtin_amdgcn_readlane((unsigned)(diag >> 32), j) << 32 |
+                         (unsigned)__builtin_amdgcn_readlane((unsigned)diag, j);
+            }
+            if (lane < count)
+                keep[block * 64 + lane] = ((g >> lane) & 1) ? 0 : 1;
+            if (lane == 0)
+                kept_block = ~g & (count == 64 ? ~0ull : (1ull << count) - 1);
+        }
+        __syncthreads();
+        const unsigned long long kept = kept_block;
+        unsigned long long strike[2] = {0, 0};
+#pragma unroll
+        for (int u = 0; u < kGreedyRows; ++u)
+            if ((kept >> (wave * kGreedyRows + u)) & 1) {
+                strike[0] |= row[u][0];
+                strike[1] |= row[u][1];
+            }
+        if (block + 1 < words)
+            request(block + 1);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int w = lane + 64 * h;
+            if (w > block && w < words && strike[h] != 0)  // words at or below the diagonal are not written
+                atomicOr(&gone[w], strike[h]);
+        }
+        __syncthreads();
+    }
 }
 
 }  // namespace
 
-hipError_t launch_pearson(const double *values, const double *runtime, double *r, int n, int V, int J,
-                          hipStream_t stream)
+hipError_t launch_pearson(const double *values, const double *runtime, double *r, double *mean, double *inv, int n,
+                          int V, int J, hipStream_t stream)
 {
-    hipLaunchKernelGGL(pearson_kernel, dim3((J + 255) / 256, n), dim3(256), 0, stream, values, runtime, r, V, J);
+    const dim3 grid((J + kColumnThreads - 1) / kColumnThreads, n);
+    if (mean != nullptr)
+        hipLaunchKernelGGL(pearson_kernel<true>, grid, dim3(kColumnThreads), 0, stream, values, runtime, r, mean, inv, V, J);
+    else
+        hipLaunchKernelGGL(pearson_kernel<false>, grid, dim3(kColumnThreads), 0, stream, values, runtime, r, mean, inv, V, J);
     return hipGetLastError();
 }
 
-hipError_t launch_corr_matrix(const double *task_values, double *Z, double *C, int V, int J, hipStream_t stream)
+// keep[n][J] of n tasks; mask has room for n * J * ((J + 63) / 64) words
+hipError_t launch_duplicate_filter(const double *values, const double *mean, const double *inv, double tau,
+                                   unsigned long long *mask, unsigned char *keep, int n, int V, int J, hipStream_t stream)
 {
-    hipLaunchKernelGGL(standardise_kernel, dim3((J + 255) / 256), dim3(256), 0, stream, task_values, Z, V, J);
-    hipLaunchKernelGGL(corr_matrix_kernel, dim3((J + 15) / 16, (J + 15) / 16), dim3(256), 0, stream, Z, C, V, J);
+    const int words = (J + 63) / 64;
+    hipLaunchKernelGGL(duplicate_kernel, dim3(words, words, n), dim3(256), 0, stream, values, mean, inv, mask, tau, V, J);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(greedy_kernel, dim3(n), dim3(64 * kGreedyWaves), 0, stream, mask, keep, J);
     return hipGetLastError();
-}
-
-// keep[m] for one task from its J x J correlation matrix: metrics in index order, a metric goes when
-// it correlates at |c| >= tau with one already kept.
-void metric_greedy_keep(const double *C, int J, double tau, unsigned char *keep)
-{
-    std::vector<int> kept;
-    kept.reserve(J);
-    for (int m = 0; m < J; ++m) {
-        bool ok = true;
-        for (int m2 : kept) {
-            const double c = C[(size_t)m * J + m2];
-            if (!std::isnan(c) && std::fabs(c) >= tau) {
-                ok = false;
-                break;
-            }
-        }
-        keep[m] = ok ? 1 : 0;
-        if (ok)
-            kept.push_back(m);
-    }
 }
 
 // Steps after the correlations, on the host.  r [n][J]; keep [n][J] or null (all kept).
@@ -147,7 +269,8 @@ void metric_select_host(const double *r, const unsigned char *keep, int n, int J
         for (int m = 0; m < J; ++m)
             if ((!keep || keep[(size_t)i * J + m]) && !std::isnan(ri[m]))
                 cand.push_back(m);
-        std::sort(cand.begin(), cand.end(), [ri](int a, int b) {
+        const size_t top_n = cand.size() < (size_t)k ? cand.size() : (size_t)k;
+        std::partial_sort(cand.begin(), cand.begin() + top_n, cand.end(), [ri](int a, int b) {
             const double fa = std::fabs(ri[a]), fb = std::fabs(ri[b]);
             return fa > fb || (fa == fb && a < b);
         });

@@ -132,10 +132,10 @@ hipError_t launch_mfma_loop(long long iters, float *sink, int num_cus, hipStream
 hipError_t launch_stream_read(const void *src, size_t bytes, unsigned *sink, int num_cus, hipStream_t stream);
 
 // profiling-metric selection: device correlations, host selection
-hipError_t launch_pearson(const double *values, const double *runtime, double *r, int n, int V, int J,
-                          hipStream_t stream);
-hipError_t launch_corr_matrix(const double *task_values, double *Z, double *C, int V, int J, hipStream_t stream);
-void metric_greedy_keep(const double *C, int J, double tau, unsigned char *keep);
+hipError_t launch_pearson(const double *values, const double *runtime, double *r, double *mean, double *inv, int n,
+                          int V, int J, hipStream_t stream);
+hipError_t launch_duplicate_filter(const double *values, const double *mean, const double *inv, double tau,
+                                   unsigned long long *mask, unsigned char *keep, int n, int V, int J, hipStream_t stream);
 void metric_select_host(const double *r, const unsigned char *keep, int n, int J, int k, double q,
                         int min_tasks, int *top, double *score, unsigned char *selected, double *threshold);
 
