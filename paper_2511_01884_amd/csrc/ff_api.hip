@@ -724,22 +724,53 @@ int ff_cross_entropy_mean(const void *logits, const int64_t *targets, int64_t B,
     if (!st)
         return FF_ERR_LAUNCH;
     XentParams p{};
-    const int64_t row_bytes = C * (dtype == FF_BF16 ? 2 : 4);
-    // a wavefront per row while there are rows enough to fill the chip and a row is short;
-    // otherwise the whole workgroup shares a row
-    p.wg_per_row = (row_bytes >= 64 * 1024 || B < (int64_t)st->num_cus * 16) ? 1 : 0;
-    const int64_t groups = p.wg_per_row ? B : (B + 3) / 4;
-    // Workgroups per compute unit (measured): fp32 rows stream fastest from few (2: 6.4 against
-    // 5.7 TB/s with 8); bf16 rows carry twice the exponentials per byte and need more wavefronts to
-    // keep the vector ALUs fed (8), unless that leaves a wavefront fewer than four rows, whose
-    // load / reduce phases then stop overlapping across the chip.
-    int64_t per_cu = dtype == FF_BF16 ? 8 : 2;
-    const int64_t fill = groups / ((int64_t)st->num_cus * 4);
-    if (per_cu > fill)
-        per_cu = fill < 2 ? 2 : fill;
-    const int64_t cap = (int64_t)st->num_cus * per_cu;
-    p.grid = (int)(groups < cap ? groups : cap);
-    const int rc = prepare_workspace(*st, kCtrlBytes + round_up((size_t)p.grid * sizeof(floatx2), 256),
+    p.B = (int)B;
+    p.C = (int)C;
+    const int full = dtype == FF_BF16 ? 8 : 4;  // elements of a 16-byte load
+    p.vec = C >= 4 * full ? full : 1;
+    const int64_t chunks = C / p.vec;
+    // Scratch memory: one pair per workgroup, or per segment and row.  A workspace of
+    // ff_cross_entropy_workspace_bytes() holds either; a smaller one that a caller bound (or that the
+    // library owns while the stream is captured) bounds the grid and rules segments out.
+    const size_t limit = st->ws_bytes >= ff_cross_entropy_workspace_bytes(B, C, dtype)
+                             ? st->ws_bytes
+                             : workspace_limit(*st, static_cast<hipStream_t>(stream));
+    const int64_t pairs = limit <= kCtrlBytes ? 1 : (int64_t)std::min<size_t>((limit - kCtrlBytes) / sizeof(floatx2), 8192);
+    int64_t groups, per_cu = 8;  // workgroups of four wavefronts: with 4 (2) per unit 65536 x 1000 fp32 takes 4 % (49 %) more
+    if (chunks <= 512) {
+        // A row in the registers of 4, 16 or 64 lanes, at most eight loads each.  (A wavefront per row whatever
+        // its length, with the remainder of a batch loaded one after the other: 65536 x 16 fp32 41.4 us, now
+        // 6.0; 65536 x 1000 106 -> 46.7; 56832 x 373 106 -> 24.)
+        p.lanes = chunks <= 16 ? 4 : (chunks <= 64 ? 16 : 64);
+        const int q = (int)((chunks + p.lanes - 1) / p.lanes);
+        p.per_lane = q <= 1 && p.lanes == 4 ? 1 : (q <= 2 ? 2 : (q <= 4 ? 4 : 8));
+        groups = (B * p.lanes + 255) / 256;
+    } else {
+        // A wavefront per row; fewer than six rows per unit are cut into segments, up to as many as make
+        // about two wavefronts per SIMD (256 x 50257 fp32: 28.0 us whole, 14.1 in 8 segments, 14.8 in 12;
+        // 512 x 32000 bf16: 16.0, 11.3 in 4, 12.3 in 8; 1792 x 9216 fp32: 15.3, 15.4 in 4).
+        p.segs = 1;
+        while (B * p.segs < (int64_t)st->num_cus * 6 && p.segs < 16 && chunks / (2 * p.segs) >= 64 &&
+               B * (2 * p.segs + 1) <= pairs)
+            p.segs *= 2;
+        const int64_t batch = 64 * 8;  // whole batches of loads per segment where there are enough
+        p.seg_chunks = (int)((chunks + p.segs - 1) / p.segs);
+        if (p.segs > 1 && p.seg_chunks > 4 * batch)
+            p.seg_chunks = (int)((p.seg_chunks + batch - 1) / batch * batch);
+        groups = (B * p.segs + 3) / 4;
+        // Rows of two batches or more keep enough loads in flight with two workgroups per unit, and DRAM reads
+        // few streams faster than many (32768 x 4096 fp32 84.7 against 86.9 us with eight, 4096 x 50257 bf16
+        // 69.5 against 71.5), provided their rounds come out even (5120 x 13018 bf16, 2.5 rounds: 29.0, 26.8).
+        const int64_t few = (int64_t)st->num_cus * 2, even = (groups + few - 1) / few * few;
+        if (chunks >= 2 * batch && groups * 10 >= even * 9)
+            per_cu = 2;
+    }
+    // as many rounds as the resident workgroups need, then as few workgroups as finish in that many
+    const int64_t cap = std::min<int64_t>((int64_t)st->num_cus * per_cu, pairs);
+    const int64_t rounds = (groups + cap - 1) / cap;
+    p.grid = (int)((groups + rounds - 1) / rounds);
+    const int64_t need = p.segs > 1 ? B * p.segs + B : p.grid;
+    const int rc = prepare_workspace(*st, kCtrlBytes + round_up((size_t)need * sizeof(floatx2), 256),
                                      static_cast<hipStream_t>(stream));
     if (rc != FF_OK)
         return rc;
@@ -749,10 +780,10 @@ int ff_cross_entropy_mean(const void *logits, const int64_t *targets, int64_t B,
     p.row_loss = row_loss;
     p.mean_loss = mean_loss;
     p.partials = reinterpret_cast<floatx2 *>(ws + kCtrlBytes);
+    p.picked = p.partials + B * p.segs;
+    p.ways = reinterpret_cast<unsigned *>(ws + kCounterOffset);
     // the last counter pair of the control region; the tiled kernels never reach it
     p.counter = reinterpret_cast<unsigned *>(ws + kCounterOffset) + 2 * (kMaxRowBlocks - 1);
-    p.B = (int)B;
-    p.C = (int)C;
     if (launch_xent_kernel(dtype == FF_BF16, p, static_cast<hipStream_t>(stream)) != hipSuccess)
         return FF_ERR_LAUNCH;
     return FF_OK;

@@ -120,11 +120,14 @@ struct XentParams {
     const long long *targets;  // [B]
     float *row_loss;           // [B] or null
     float *mean_loss;          // [1]
-    floatx2 *partials;         // [grid]: one number per workgroup (second component unused)
-    unsigned *counter;         // arrivals of this launch; zero before and after
+    floatx2 *partials;         // [grid]: one number per workgroup; with segments [B][segs]: (maximum, sum)
+    floatx2 *picked;           // [B] with segments: the target's logit
+    unsigned *counter, *ways;  // arrivals of this launch, final and in kSyncWays words; zero before and after
     int B, C;
     int grid;
-    int wg_per_row;            // 1: a workgroup per row (long rows, few rows); 0: a wavefront per row
+    int vec;                   // elements per load: 16 bytes' worth, or 1 for rows of fewer than four such loads
+    int lanes, per_lane;       // short rows: lanes per row and loads per lane; lanes = 0: a wavefront per row or segment
+    int segs, seg_chunks;      // long rows: segments per row, 16-byte loads of a segment
 };
 
 hipError_t launch_copy_kernel(const void *src, void *dst, size_t bytes, int num_cus, hipStream_t stream);
