@@ -74,7 +74,7 @@ struct Plan {
     int tile_m = 0, tile_n = 0;  // rows and columns of a tile
     int stagger_us = 0;
     int NT = 0, RB = 0;
-    int grid = 0, rounds = 0, swz_sc_log2 = -1, nt_log2 = 0, grid_log2 = 0;
+    int grid = 0, rounds = 0, swz_sc_log2 = -1, nt_log2 = 0, grid_log2 = 0, round_rows = 0;
     int mt = 0, strips = 0;  // small-M
     size_t partial_off = 0, partial_bytes = 0;
     size_t g_off = 0, g_bytes = 0;
@@ -329,6 +329,18 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
         while ((1 << pl.swz_sc_log2) < sc)
             ++pl.swz_sc_log2;
     }
+    // Every other fused launch: rounds of whole row-blocks, as many in each.  A row-block whose tiles lie in
+    // two rounds makes those of the first wait, accumulators and all, for the second (23040 x 408 x 9584, 37
+    // tiles a row: 651 us, with whole row-blocks 492 in one round more); spreading the row-blocks evenly
+    // costs nothing, as the chip's power sets the rate (24064 x 7056 x 768, 47 row-blocks in each of two
+    // rounds instead of 85 and 9: 460 -> 436 us).  Rows of more than half the grid's tiles stay in plain order:
+    // whole ones would leave up to half the chip idle.
+    if (pl.swz_sc_log2 < 0 && NT * 2 <= pl.grid && variant == FF_VARIANT_TILED_FUSED && !linear_only) {
+        const int64_t most = pl.grid / NT < RB ? pl.grid / NT : RB;
+        pl.rounds = (int)((RB + most - 1) / most);
+        pl.round_rows = (int)((RB + pl.rounds - 1) / pl.rounds);
+        pl.grid = (int)(pl.round_rows * NT);
+    }
     // start delay of the second workgroup of every compute unit (256 x 128 tiles, full grid only)
     pl.stagger_us = (pl.shape == kTile256x128 && per_cu == 2 && pl.grid == 2 * num_cus) ? g_stagger_us : 0;
     pl.partial_off = kCtrlBytes;
@@ -555,7 +567,7 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
     p.err = err;
     p.eps = eps;
     p.M = (int)M; p.K = (int)K; p.N = (int)N;
-    p.NT = pl.NT; p.RB = pl.RB; p.rounds = pl.rounds; p.swz_sc_log2 = pl.swz_sc_log2; p.nt_log2 = pl.nt_log2;
+    p.NT = pl.NT; p.RB = pl.RB; p.rounds = pl.rounds; p.round_rows = pl.round_rows; p.swz_sc_log2 = pl.swz_sc_log2; p.nt_log2 = pl.nt_log2;
     p.grid_log2 = pl.grid_log2;
     p.stagger_ticks = (long long)pl.stagger_us * st->ticks_per_us;
     p.extra_arrivals = g_extra_arrivals;

@@ -211,6 +211,15 @@ void tile_kernel(const TileParams p)
             const int sbr = xcd >> across_log2, sbc = xcd & ((1 << across_log2) - 1);
             rb = (round << (p.grid_log2 - p.nt_log2)) + (sbr << (p.grid_log2 - 3 - scl)) + (slot >> scl);
             cb = (sbc << scl) + (slot & ((1 << scl) - 1));
+        } else if (p.round_rows > 0) {
+            // A round takes round_rows whole row-blocks (grid = round_rows * NT).  The workgroups of one XCD
+            // get consecutive numbers, row-block fastest: a block of round_rows x a few tiles, which share
+            // their X and W panels in its L2.
+            const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+            const int each = (int)gridDim.x >> 3, more = (int)gridDim.x & 7;
+            const int t = xcd * each + (xcd < more ? xcd : more) + slot;
+            cb = t / p.round_rows;
+            rb = round * p.round_rows + t - cb * p.round_rows;
         } else {
             const int t = round * (int)gridDim.x + (int)blockIdx.x;
             rb = t / p.NT;
@@ -283,38 +292,25 @@ void tile_kernel(const TileParams p)
                     offb[y >= 0 && y < kDmaB ? y : 0], slab * kRowBytes, 0, 0);
             }
         };
-        // K-cut (last) slab: through registers, chunks at or beyond K are zero-filled
-        auto issue_cut = [&](int slab, int half) {
+        // The last slab when K cuts it: a lane whose chunk lies at or beyond K reads the first chunk of its row's
+        // slab instead; what that leaves in LDS is not multiplied (cut_frags).  (Through registers, with zeros
+        // written for the missing chunks, it was a load latency in the open: 3001 x 2056 x 5000 spent 54.5 us up
+        // to the end of the product, against 46.2 for K = 2048.)
+        auto dma_cut = [&](int slab, int half) {
             // lane geometry re-derived through an opaque move: this rarely taken path
-            // must not have its masks precomputed (and spilled) at kernel entry
+            // must not have its offsets precomputed (and spilled) at kernel entry
             const int lane_c = opaque_lane();
-            const int dma_r = lane_c / kChunksPerRow;
-            const int dma_cs = lane_c % kChunksPerRow;
             const int stage = slab % kStages;
-            if (half == 0) {
-                char *sa = smem + stage * kWStride + wave * (BN / kWaves) * kRowBytes;
-                const char *wk = w_tile + (size_t)slab * kRowBytes;
 #pragma unroll
-                for (int j = 0; j < kDmaA; ++j) {
-                    const int row = wave * (BN / kWaves) + j * kRowsPerDma + dma_r;
-                    const int c = dma_cs ^ swizzle_of_row(row);
-                    const bool in = slab * kSlabElems + c * kChunkElems < K;
-                    uintx4 v = *reinterpret_cast<const uintx4 *>(in ? wk + offa[j] : w_tile);
-                    v &= in ? 0xffffffffu : 0u;
-                    *reinterpret_cast<uintx4 *>(sa + j * 1024 + lane_c * 16) = v;
-                }
-            } else {
-                char *sb = smem + kXBase + stage * kXStride + wave * (BM / kWaves) * kRowBytes;
-                const char *xk = x_tile + (size_t)slab * kRowBytes;
-#pragma unroll
-                for (int j = 0; j < kDmaB; ++j) {
-                    const int row = wave * (BM / kWaves) + j * kRowsPerDma + dma_r;
-                    const int c = dma_cs ^ swizzle_of_row(row);
-                    const bool in = slab * kSlabElems + c * kChunkElems < K;
-                    uintx4 v = *reinterpret_cast<const uintx4 *>(in ? xk + offb[j] : x_tile);
-                    v &= in ? 0xffffffffu : 0u;
-                    *reinterpret_cast<uintx4 *>(sb + j * 1024 + lane_c * 16) = v;
-                }
+            for (int x = 0; x < (half == 0 ? kDmaA : kDmaB); ++x) {
+                const int row = wave * ((half == 0 ? BN : BM) / kWaves) + x * kRowsPerDma + lane_c / kChunksPerRow;
+                const int c = (lane_c % kChunksPerRow) ^ swizzle_of_row(row);
+                const unsigned back = slab * kSlabElems + c * kChunkElems < K ? 0u : (unsigned)c * 16u;
+                char *dst = smem + (half == 0 ? stage * kWStride : kXBase + stage * kXStride) +
+                            wave * ((half == 0 ? BN : BM) / kWaves) * kRowBytes + x * 1024;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    half == 0 ? w_rsrc : x_rsrc, (__attribute__((address_space(3))) void *)dst, 16,
+                    (half == 0 ? offa[x < kDmaA ? x : 0] : offb[x < kDmaB ? x : 0]) - back, slab * kRowBytes, 0, 0);
             }
         };
 
@@ -372,6 +368,19 @@ void tile_kernel(const TileParams p)
                 mma_group(g, a, b);
         };
 
+        // fragments of k-step s of the slab that K cuts: chunks at or beyond K become zeros, in both operands
+        auto cut_frags = [&](int slab, int s, uintx4 (&a)[WTN], uintx4 (&b)[WTM]) {
+            if (k_ragged && slab + 1 == slabs) {
+                const unsigned keep = slab * kSlabElems + (2 * s + h) * kChunkElems < K ? 0xffffffffu : 0u;
+#pragma unroll
+                for (int x = 0; x < WTN; ++x)
+                    a[x] &= keep;
+#pragma unroll
+                for (int x = 0; x < WTM; ++x)
+                    b[x] &= keep;
+            }
+        };
+
         // ---- main loop over K slabs ----
         // Per slab: four k-steps, each one group-interleaved stream of MFMAs with one
         // LDS fragment read (for the next k-step) and at most one DMA instruction in
@@ -383,13 +392,13 @@ void tile_kernel(const TileParams p)
         static_assert(kStepsPerSlab == 4 && kStages == 2, "loop body written for 4 k-steps, 2 stages");
         static_assert(kXReg || (kDmaA <= kGroups && kDmaB <= kGroups), "one DMA instruction per MFMA group at most");
         auto dma_half_any = [&](int slab, int half) {
-            // half 0: W rows (x in [0, kDmaA)), half 1: X rows; K-cut slabs go through registers
+            // half 0: W rows (x in [0, kDmaA)), half 1: X rows
             if (!k_ragged || slab + 1 < slabs) {
 #pragma unroll
                 for (int x = 0; x < (half == 0 ? kDmaA : kDmaB); ++x)
                     dma_one(slab, half == 0 ? x : kDmaA + x);
             } else {
-                issue_cut(slab, half);
+                dma_cut(slab, half);
             }
         };
         if constexpr (kXReg) {
@@ -412,7 +421,7 @@ void tile_kernel(const TileParams p)
             if (!k_ragged || slab + 1 < slabs) {
                 x_load_full(slab);
             } else {
-                const int lane_c = opaque_lane();  // as in issue_cut
+                const int lane_c = opaque_lane();  // as in dma_cut
 #pragma unroll
                 for (int j = 0; j < kDmaB; ++j) {
                     const int row = wave * (BM / kWaves) + j * kRowsPerDma + lane_c / kChunksPerRow;
@@ -496,19 +505,22 @@ void tile_kernel(const TileParams p)
             const bool more = i + 1 < slabs;
             if (more)
                 x_load(i + 1);
+            cut_frags(i, 0, fa[0], fb[0]);
             load_frags(i, 1, fa[1], fb[1]);
             mma_all(fa[0], fb[0]);
+            cut_frags(i, 1, fa[1], fb[1]);
             load_frags(i, 2, fa[0], fb[0]);
             mma_all(fa[1], fb[1]);
+            cut_frags(i, 2, fa[0], fb[0]);
             load_frags(i, 3, fa[1], fb[1]);
             mma_all(fa[0], fb[0]);
+            cut_frags(i, 3, fa[1], fb[1]);
             if (more) {
                 lds_barrier();                       // A
                 __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
                 x_store();
                 if (i + 2 < slabs)
                     dma_half_any(i + 2, 0);
-                __builtin_amdgcn_s_waitcnt(0x0f70);  // a K-cut W slab went through registers
                 lds_barrier();                       // B
                 load_frags(i + 1, 0, fa[0], fb[0]);
             }
@@ -537,7 +549,7 @@ void tile_kernel(const TileParams p)
         dma_half_any(0, 1);
         if (slabs > 1)
             dma_half_any(1, 0);
-        if (first_tile && p.timeline == nullptr && slabs > 1 && !(k_ragged && slabs == 2))
+        if (first_tile && p.timeline == nullptr && slabs > 1)
             __builtin_amdgcn_s_waitcnt(0x0f70 | (kDmaA & 15) | ((kDmaA >> 4) << 14));  // slab 0 landed
         else
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): also the previous tile's stores, whose
@@ -598,12 +610,16 @@ void tile_kernel(const TileParams p)
         for (; i < slabs; ++i) {
             if (i + 1 < slabs)
                 dma_half_any(i + 1, 1);
+            cut_frags(i, 0, fa[0], fb[0]);
             load_frags(i, 1, fa[1], fb[1]);
             mma_all(fa[0], fb[0]);
+            cut_frags(i, 1, fa[1], fb[1]);
             load_frags(i, 2, fa[0], fb[0]);
             mma_all(fa[1], fb[1]);
+            cut_frags(i, 2, fa[0], fb[0]);
             load_frags(i, 3, fa[1], fb[1]);
             mma_all(fa[0], fb[0]);
+            cut_frags(i, 3, fa[1], fb[1]);
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
             lds_barrier();
             if (i + 2 < slabs)
@@ -652,23 +668,14 @@ void tile_kernel(const TileParams p)
         // taken about the lane's first value (a shift that keeps sum-of-squares
         // cancellation harmless), merged with the other lane half, then across waves.
         {
-            constexpr bool kRagged = RAGGED_N;
-            int cnt_own = WTN * 16, cnt_other = WTN * 16;
-            if (kRagged) {
-                cnt_own = cnt_other = 0;
-#pragma unroll
-                for (int i = 0; i < WTN; ++i)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int c0 = ncol_wave + i * 32 + q * 8 + e;
-                            cnt_own += (c0 + h * 4 < nvalid_tile) ? 1 : 0;
-                            cnt_other += (c0 + (h ^ 1) * 4 < nvalid_tile) ? 1 : 0;
-                        }
-            }
-            int cntw_i = nvalid_tile - ncol_wave;
-            cntw_i = cntw_i < 0 ? 0 : (cntw_i > WTN * 32 ? WTN * 32 : cntw_i);
+            const bool cut = RAGGED_N && nvalid_tile < BN;  // only the last tile of a row is cut by N
+            // a half-wave's columns of the wave's strip are 8 k + 4 half + (0..3); those below the tile's end
+            auto columns_of = [&](int half) {
+                const int t = nvalid_tile - ncol_wave - half * 4;
+                const int c = t < 0 ? 0 : (t > WTN * 32 ? WTN * 32 : t);
+                return (c >> 3) * 4 + ((c & 7) < 4 ? (c & 7) : 4);
+            };
+            const int cnt_own = cut ? columns_of(h) : WTN * 16, cnt_other = cut ? columns_of(h ^ 1) : WTN * 16;
             float shift[WTM], s1[WTM], s2[WTM];
 #pragma unroll
             for (int j = 0; j < WTM; ++j)
@@ -679,6 +686,12 @@ void tile_kernel(const TileParams p)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     bb[q] = *reinterpret_cast<const floatx4 *>(s_b + ncol_wave + i * 32 + q * 8 + h * 4);
+                float s1_before[WTM], s2_before[WTM];
+#pragma unroll
+                for (int j = 0; j < WTM; ++j) {
+                    s1_before[j] = s1[j];
+                    s2_before[j] = s2[j];
+                }
 #pragma unroll
                 for (int j = 0; j < WTM; ++j) {
                     // one 32x32 block at a time: read its 16 registers, write back 16 G values
@@ -690,14 +703,10 @@ void tile_kernel(const TileParams p)
                             v[r] = z;
                             continue;
                         }
-                        float g = gelu_erf(z);
+                        const float g = gelu_erf(z);
                         if (i == 0 && r == 0)
                             shift[j] = g;  // column ncol_wave + 4h: valid whenever the lane has any
-                        float d = g - shift[j];
-                        if (kRagged && ncol_wave + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3) >= nvalid_tile) {
-                            g = 0.0f;
-                            d = 0.0f;
-                        }
+                        const float d = g - shift[j];
                         v[r] = g;
                         s1[j] += d;
                         s2[j] = fmaf(d, d, s2[j]);
@@ -705,6 +714,28 @@ void tile_kernel(const TileParams p)
                     acc[i][j] = v;
                     pin_order(acc[i][j]);  // G goes back to the accumulator registers
                     __builtin_amdgcn_sched_barrier(0);
+                }
+                // A block row that N cuts is summed again, with what lies beyond N left out.  (Masks in
+                // the pass itself made it 10.0 instead of 6.8 us for every tile of such a problem; two passes
+                // behind a branch spilled 60 registers; the columns beyond N repeat the last one, are
+                // never stored, and only the sums must not see them.)
+                const int limit = nvalid_tile - ncol_wave - i * 32;
+                if (RAGGED_N && MODE != kLinearOnly && limit < 32) {
+#pragma unroll
+                    for (int j = 0; j < WTM; ++j) {
+                        s1[j] = s1_before[j];
+                        s2[j] = s2_before[j];
+                        if (limit > 0) {
+                            int lane_limit = limit - h * 4;
+                            asm volatile("" : "+v"(lane_limit));  // the masks are made anew for every block
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) {
+                                const float d = (r >> 2) * 8 + (r & 3) < lane_limit ? acc[i][j][r] - shift[j] : 0.0f;
+                                s1[j] += d;
+                                s2[j] = fmaf(d, d, s2[j]);
+                            }
+                        }
+                    }
                 }
             }
             if (MODE != kLinearOnly) {
@@ -720,7 +751,7 @@ void tile_kernel(const TileParams p)
                     const float inv_own = cnt_own > 0 ? 1.0f / n_own : 0.0f;
                     float mean_own = fmaf(s1[j], inv_own, shift[j]);
                     float m2_own = fmaxf(s2[j] - s1[j] * s1[j] * inv_own, 0.0f);
-                    if (kRagged && cnt_own == 0)
+                    if (RAGGED_N && cnt_own == 0)
                         mean_own = 0.0f;
                     const float mean_oth = swap_halves(mean_own, lane);
                     const float m2_oth = swap_halves(m2_own, lane);
@@ -735,7 +766,6 @@ void tile_kernel(const TileParams p)
                     }
                 }
             }
-            (void)cntw_i;
         }
 
         const int tid = wave * 64 + opaque_lane();  // taken afresh: not carried across the pass above

@@ -25,6 +25,7 @@ struct TileParams {
     int NT;              // tiles along N
     int RB;              // row-blocks
     int rounds;          // ceil(RB * NT / grid)
+    int round_rows;      // row-blocks of a round when the grid is made of whole ones, else 0
     int swz_sc_log2;     // XCD-aware order: log2 of the super-block width in tiles, -1 = plain order
     int nt_log2;         // log2(NT) when the XCD-aware order is on
     int grid_log2;       // log2(grid) when the XCD-aware order is on
