@@ -629,26 +629,33 @@ int ff_debug_linear(const void *X, const void *W, const void *b, int64_t M, int6
 
 namespace {
 
-// Column strips and row chunks of the second chain's first phase: 128-byte strips, and as many row
-// chunks as give about one (strip, chunk) item per compute unit of the part this was tuned on (the
-// kernel loops when there are more items than workgroups).  Few chunks keep the second phase's sum short.
+// Column strips and row chunks of the second chain's first phase: 128-byte strips, and the number of row
+// chunks with the least estimated time, in rows of a workgroup: its rounds of (strip, chunk) items, each worth
+// its rows and 48 more for the reductions, and 4 per chunk for the second phase's sum.  (One item per unit at
+// most, 256 / strips chunks, left units idle: 160 strips of 256 x 5120 x 2072 fp32 ran whole on 160 of 256.)
+// `most` bounds the scratch memory for the partial sums.
 struct RowMeanPlan {
     int strips, k_pad, chunks, rows_per_chunk;
     size_t partial_bytes, cpart_bytes;
 };
 
-RowMeanPlan rowmean_plan(int64_t K, int64_t N, int dtype, int num_cus)
+RowMeanPlan rowmean_plan(int64_t K, int64_t N, int dtype, int num_cus, size_t most = SIZE_MAX)
 {
     RowMeanPlan r{};
     const int64_t strip_elems = 128 / (dtype == FF_BF16 ? 2 : 4);
     r.strips = (int)((K + strip_elems - 1) / strip_elems);
     r.k_pad = (int)(r.strips * strip_elems);
-    int64_t want = 256 / r.strips;
-    if (want < 1)
-        want = 1;
     const int64_t q = kRowMeanRowsPerStep;
-    r.rows_per_chunk = (int)(((N + want - 1) / want + q - 1) / q * q);
-    r.chunks = (int)((N + r.rows_per_chunk - 1) / r.rows_per_chunk);
+    int64_t best = 0;
+    for (int64_t want = 1; want <= 64; ++want) {
+        const int64_t rows = ((N + want - 1) / want + q - 1) / q * q, chunks = (N + rows - 1) / rows;
+        const int64_t cost = (r.strips * chunks + 255) / 256 * (rows + 48) + 4 * chunks;
+        if (want > 1 && (cost >= best || (size_t)(chunks * r.k_pad) * sizeof(float) > most))
+            continue;
+        best = cost;
+        r.rows_per_chunk = (int)rows;
+        r.chunks = (int)chunks;
+    }
     r.partial_bytes = round_up((size_t)r.chunks * (size_t)r.k_pad * sizeof(float), 256);
     r.cpart_bytes = round_up((size_t)num_cus * sizeof(float), 256);
     return r;
@@ -677,7 +684,10 @@ int ff_fused_linear_sub_rowmean_gelu_residual(const void *X, const void *W, cons
     if (!st)
         return FF_ERR_LAUNCH;
     RowMeanParams p{};
-    const RowMeanPlan pl = rowmean_plan(K, N, dtype, st->num_cus);
+    // a bound workspace, or the library's own during a capture, bounds the chunks; one chunk needs no more than before
+    const size_t head = kCtrlBytes + round_up((size_t)st->num_cus * sizeof(float), 256);
+    const size_t limit = workspace_limit(*st, static_cast<hipStream_t>(stream));
+    const RowMeanPlan pl = rowmean_plan(K, N, dtype, st->num_cus, limit > head ? (limit - head) / 256 * 256 : 0);
     rc = prepare_workspace(*st, kCtrlBytes + pl.partial_bytes + pl.cpart_bytes, static_cast<hipStream_t>(stream));
     if (rc != FF_OK)
         return rc;

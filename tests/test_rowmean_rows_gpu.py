@@ -1,0 +1,60 @@
+"""The second chain where its two phases split their work differently: rows shared by 1, 2, 4 and 8 wavefronts, sets
+of rows with a short last one, every remainder of a chunk of W's rows, few columns under many chunks."""
+import pytest
+import torch
+
+import oracle
+from paper_2511_01884_amd import binding as B
+from paper_2511_01884_amd.inputs import make_inputs, sample_rows
+from parity_util import to_np32
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(M, K, N, dtype, seed):
+    print("[case] rowmean", M, K, N, dtype, flush=True)
+    d = make_inputs(M, K, N, dtype, seed=seed)
+    s = (torch.rand(N, generator=torch.Generator().manual_seed(seed)) * 0.2 - 0.1).to(d["b"].dtype)
+    args = [t.cuda() for t in (d["X"], d["W"], d["b"], s)]
+    out = B.ff_fused_linear_sub_rowmean_gelu_residual(*args)
+    B.ff_check_device()
+    rows = sample_rows(M, 40, seed=seed)
+    pick = torch.tensor(rows)
+    ref = torch.from_numpy(oracle.linear_sub_rowmean_gelu_residual(to_np32(d["X"][pick]), to_np32(d["W"]), to_np32(d["b"]),
+                                                                   to_np32(s)))
+    got = out.cpu()[pick].double()
+    # fp32 sums of N * K products' magnitude, then one rounding of the result to its type (bf16: half of 2**-7)
+    bound = 2e-5 + ref.abs() * (2.0 ** -8 if dtype == "bf16" else 2.0 ** -22)
+    assert ((got - ref).abs() <= bound).all(), float(((got - ref).abs() - bound).max())
+    assert torch.equal(out, B.ff_fused_linear_sub_rowmean_gelu_residual(*args))
+
+
+@pytest.mark.parametrize("M,K,N,dtype", [
+    (5000, 8, 40, "bf16"), (4097, 256, 24, "bf16"), (6200, 520, 8, "bf16"), (4100, 1032, 8, "bf16"), (4500, 2056, 8, "bf16"),
+    (300, 4104, 16, "bf16"), (1030, 8192, 8, "bf16"), (600, 8200, 8, "bf16"), (300, 16392, 8, "bf16"), (70, 32768, 8, "bf16"),
+    (600, 2052, 4, "f32"), (300, 4100, 4, "f32"), (150, 8196, 4, "f32"), (70, 16388, 4, "f32"), (9000, 4, 12, "f32")])
+def test_rows(M, K, N, dtype):
+    _check(M, K, N, dtype, 95)
+
+
+@pytest.mark.parametrize("M,K,N,dtype", [
+    (20, 8, 64, "bf16"), (20, 64, 128, "bf16"), (20, 4096, 72, "bf16"), (20, 8192, 264, "bf16"), (20, 8192, 520, "bf16"),
+    (20, 8192, 1032, "bf16"), (20, 256, 16384, "bf16"), (20, 264, 5000, "bf16"), (20, 4096, 1288, "f32"), (20, 5120, 2072, "f32")])
+def test_chunks(M, K, N, dtype):
+    _check(M, K, N, dtype, 96)
+
+
+def test_small_bound_workspace():
+    """Room for one chunk's sums only, where the plan would take several."""
+    M, K, N = 40, 512, 4096
+    d = make_inputs(M, K, N, "bf16", seed=97)
+    args = [t.cuda() for t in (d["X"], d["W"], d["b"])]
+    want = B.ff_fused_linear_sub_rowmean_gelu_residual(*args, None)
+    ws = torch.empty((1 << 20) + 512 * 4 + 1024, dtype=torch.uint8, device="cuda")
+    B.ff_set_workspace(ws)
+    try:
+        got = B.ff_fused_linear_sub_rowmean_gelu_residual(*args, None)
+        B.ff_check_device()
+    finally:
+        B.ff_set_workspace(None)
+    assert (got.float() - want.float()).abs().max() <= 2.0 ** -7 * 8    # one bf16 step of |x| < 8
