@@ -247,13 +247,16 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // Tiled variants, by how many tiles of a shape there are per compute unit (measured on one device,
     // 1024 x 4096 x 8192, whole call: 256 x 256 tiles 108 us with half the units idle, 256 x 128 tiles
     // 82 us, 128 x 128 tiles two per unit 92 us, the same in two passes 84 us):
-    //   more 256 x 256 tiles than half the compute units: 256 x 256 tiles, one workgroup of eight
+    //   more 256 x 256 tiles than half the compute units (in fp32, which is bound by the matrix units, only
+    //     when 128 x 128 tiles two per unit would not do in one round: 2927 x 2952 x 2692 takes 395 us with
+    //     those, 688 with 132 tiles of 256): 256 x 256 tiles, one workgroup of eight
     //     wavefronts per unit.  Eight wavefronts run the epilogue faster than four (two wavefronts per
     //     SIMD hide each other's latencies) and the K loop up to 4 % slower (half again as many LDS
     //     fragment reads per MFMA); the sum favours eight (4096^3 115.7 against 116.7 us; 65536 x 1024
     //     x 1024 159.5 against 170.7; 8192 x 4096 x 16384 950 against 966);
-    //   else, in bf16, if the 128 x 128 tiles outnumber the units but the 256-column x 128-row tiles do
-    //     not: 256 x 128 tiles, one per unit, in one round (14 to 20 % faster than 128 x 128 tiles two
+    //   else, in bf16, if the 128 x 128 tiles outnumber the units by more than a quarter (up to there two per
+    //     unit are faster: 2304 x 4352 x 1848, 270 tiles, 74.7 against 82.8 us; 7085 x 768 x 560, 280: 24.7, 28.4;
+    //     3328 x 1576 x 1536, 312: 48.4, 48.7) but the 256-column x 128-row tiles do not: 256 x 128 tiles, one per unit, in one round (14 to 20 % faster than 128 x 128 tiles two
     //     per unit on five such shapes; in fp32, where the K loop is eight times longer per slab and
     //     that kernel spills, 128 x 128 tiles win by a third).  Two of those per unit are never chosen: the
     //     overlap of one workgroup's epilogue with the other's K loop does not pay for the 1.5 times
@@ -264,9 +267,9 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
     const int64_t tiles256x128 = ((M + 127) / 128) * ((N + 255) / 256);
     const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
-    if (tiles256 * 2 > num_cus)
+    if (tiles256 * 2 > num_cus && (bf16 || tiles128 > 2 * num_cus))
         pl.shape = kTile256W8;
-    else if (bf16 && tiles128 > num_cus && tiles256x128 <= num_cus)
+    else if (bf16 && tiles128 * 4 > 5 * num_cus && tiles256x128 <= num_cus)
         pl.shape = kTile256x128;
     else
         pl.shape = tiles128 * 4 > num_cus ? kTile128 : kTile64;
