@@ -132,19 +132,20 @@ int resident_split_blocks(DeviceState *st, bool bf16, int shape)
 // Split kernel: the (shape, S) with the smallest estimated time among those whose workgroups all fit the
 // chip at once, or false if there is none.  The estimate (microseconds, one launch after another, inputs
 // from HBM) adds up what the kernel does one after the other:
-//     start + max(slabs of a workgroup * time of one, W read at the rate its bytes in flight allow)
+//     start + max(slabs of a workgroup * time of one, W from HBM at the chip's rate or the active units')
 //     + epilogue of a tile's share + exchange with the NT tiles of the rows
 //     + S > 1: meeting of the tile's S workgroups and one write and read of the partial products
-// Its constants were fitted to 2 800 runs (340 shapes drawn over M 1..8192, K 128..16384, N 128..16384, every
-// shape and S of each): they reproduce the times of the configurations within 1.6 times of the best to 9 %
-// (bf16) and 4 % (fp32) rms, and the configuration picked is 1.4 and 0.9 % slower than the best on average.
+// Its constants were fitted to 3 600 runs (420 shapes drawn over M 1..8192, K 128..16384, N 128..16384, every
+// shape and S of each): the configuration picked is 1.4 (bf16) and 1.2 % (fp32) slower than the best on average.
+// A unit draws at most 32 (26) bytes a nanosecond of W from HBM, so a few workgroups cannot stream at the chip's
+// rate: 4 x 9272 x 15096 bf16 takes 102 us in 118 workgroups of 128-column tiles, 66 in 236 of 64.
 bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceState *st, Plan &pl)
 {
     // workgroups per compute unit that the LDS allows (what the runtime reports is asked as well)
     constexpr int kPerCu[kNumSplitShapes] = {3, 2, 2, 1, 1};
-    struct Cost { double start, slab, mfma, hbm, fabric, flight, exch, exch_s, sums, epi, epi128, tiles; };
-    constexpr Cost kBf16 = {4.6, 0.024, 0.128, 5.4e6, 57e3, 0.44, 3.0, 0.26, 3.0e6, 2.1, 1.6, 0.05};
-    constexpr Cost kF32 = {5.4, 0.093, 0.50, 5.4e6, 1e9, 1.06, 3.3, 0.16, 2.5e6, 2.3, 0.8, 0.04};
+    struct Cost { double start, slab, mfma, hbm, fabric, unit_hbm, exch, exch_s, sums, epi, epi128, tiles; };
+    constexpr Cost kBf16 = {4.2, 0.0, 0.128, 5.1e6, 51.6e3, 32e3, 2.4, 0.25, 2.8e6, 2.3, 1.9, 0.052};
+    constexpr Cost kF32 = {4.5, 0.134, 0.48, 5.1e6, 1e9, 26e3, 2.5, 0.2, 2.5e6, 3.0, 0.78, 0.056};
     const Cost &c = bf16 ? kBf16 : kF32;
     const int size = bf16 ? 2 : 4;
     const int64_t slabs = (K * size + 127) / 128;
@@ -176,9 +177,8 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
                 continue;
             const double per = (double)((slabs + S - 1) / S), wpc = (double)((groups + num_cus - 1) / num_cus);
             const double unit = bm * bn / 4096.0;
-            const double in_flight = (double)groups / (double)RB * 3 * bn * 128;
             const double slab = c.slab + std::max(c.mfma * unit * wpc, (bn + bm) * 128 * wpc / c.fabric);
-            const double stream = (double)N * K * size / std::min(c.hbm, in_flight / c.flight);
+            const double stream = (double)N * K * size / std::min(c.hbm, std::min<double>((double)groups, num_cus) * c.unit_hbm);
             double t = c.start + std::max(per * slab, stream) + c.epi * unit / S * wpc + c.tiles * (double)NT +
                        (shape == kSplit128 ? c.epi128 : 0.0);
             if (S > 1)
@@ -221,13 +221,14 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
 
     if (variant == FF_VARIANT_SMALL_M && !smallm_ok)
         return FF_ERR_UNSUPPORTED;
-    // The streamer keeps M <= 16 with one 32-column strip on more than half the units but at most one on
-    // each (16 x 8192 x 8192: 37.2 us, split 37.9; 4 x 4608 x 8024: 23.0, 25.0).  With fewer strips the
-    // split kernel spreads K over the idle units (2 x 16128 x 1904: 41.7 us, split 26), with several strips
-    // a unit reads one after the other (14 x 4608 x 12888: 40, 34), and over 16 rows the streamer's
-    // registers no longer cover its loads (22 x 5888 x 6008: 34.6, 22).
+    // The streamer keeps M <= 16 with one 32-column strip on more than half the units but at most one on each,
+    // where rows of W are short or nearly every unit has a strip (9 x 840 x 7248: 13.7 us, split 15.6; 4 x 4608 x
+    // 8024: 23.0, 25.0; 16 x 8192 x 8192: 37.2, 37.0 to 42).  With fewer strips, or long rows on part of the
+    // units, the split kernel spreads K over the idle ones (2 x 16128 x 1904: 41.7 us, split 26; 10 x 8712 x 5536:
+    // 42.1, 34.6), with several strips a unit reads one after the other (14 x 4608 x 12888: 40, 34), and over
+    // 16 rows the streamer's registers no longer cover its loads (22 x 5888 x 6008: 34.6, 22).
     may_split = may_split && !linear_only && g_forced_tile == 0 && g_forced_waves == 0;
-    const bool stream = M <= 16 && strips <= num_cus && strips * 2 > num_cus;
+    const bool stream = M <= 16 && strips <= num_cus && strips * 2 > num_cus && (K < 3584 || strips > num_cus - 6);
     if (may_split && (variant == FF_VARIANT_SMALL_M ? !stream : variant == 0 || variant == FF_VARIANT_TILED_FUSED) &&
         plan_split(M, K, N, bf16, num_cus, st, pl)) {
         pl.variant = variant == FF_VARIANT_SMALL_M ? FF_VARIANT_SMALL_M : FF_VARIANT_TILED_FUSED;

@@ -15,10 +15,10 @@ CASES = [
     (17, 2056, 520, "bf16", 64, 32, 4),
     (33, 2056, 8, "bf16", 64, 32, 8),         # second row block of one row
     (40, 528, 1032, "f32", 64, 32, 4),
-    (3, 2060, 12, "f32", 64, 32, 16),         # slices of two rows, shares without slabs
+    (3, 4108, 12, "f32", 64, 32, 16),         # slices of two rows, a share without slabs
     (17, 72, 4104, "bf16", 128, 32, 1),
     (32, 2056, 4104, "bf16", 128, 32, 4),
-    (17, 4104, 2056, "bf16", 128, 32, 8),
+    (17, 8200, 4104, "bf16", 128, 32, 8),
     (64, 1032, 2056, "f32", 128, 32, 4),
     (65, 264, 200, "bf16", 64, 64, 1),
     (500, 2056, 520, "bf16", 64, 64, 2),
