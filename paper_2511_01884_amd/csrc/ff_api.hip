@@ -207,7 +207,7 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
 }
 
 int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceState *st, int forced,
-              bool linear_only, Plan &pl, bool may_split = true)
+              bool linear_only, Plan &pl, bool roomy = true)
 {
     const bool bf16 = dtype == FF_BF16;
     const int64_t strips = (N + kSmallMStripCols - 1) / kSmallMStripCols;
@@ -227,7 +227,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // units, the split kernel spreads K over the idle ones (2 x 16128 x 1904: 41.7 us, split 26; 10 x 8712 x 5536:
     // 42.1, 34.6), with several strips a unit reads one after the other (14 x 4608 x 12888: 40, 34), and over
     // 16 rows the streamer's registers no longer cover its loads (22 x 5888 x 6008: 34.6, 22).
-    may_split = may_split && !linear_only && g_forced_tile == 0 && g_forced_waves == 0;
+    const bool may_split = roomy && !linear_only && g_forced_tile == 0 && g_forced_waves == 0;
     const bool stream = M <= 16 && strips <= num_cus && strips * 2 > num_cus && (K < 3584 || strips > num_cus - 6);
     if (may_split && (variant == FF_VARIANT_SMALL_M ? !stream : variant == 0 || variant == FF_VARIANT_TILED_FUSED) &&
         plan_split(M, K, N, bf16, num_cus, st, pl)) {
@@ -268,9 +268,11 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
     const int64_t tiles256x128 = ((M + 127) / 128) * ((N + 255) / 256);
     const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
-    if (tiles256 * 2 > num_cus && (bf16 || tiles128 > 2 * num_cus))
+    // (A plan for little scratch memory, roomy = false, splits nothing and keeps the larger tiles, which have
+    // half the row statistics.)
+    if (tiles256 * 2 > num_cus && (bf16 || !roomy || tiles128 > 2 * num_cus))
         pl.shape = kTile256W8;
-    else if (bf16 && tiles128 * 4 > 5 * num_cus && tiles256x128 <= num_cus)
+    else if (bf16 && tiles128 * 4 > (roomy ? 5 : 4) * num_cus && tiles256x128 <= num_cus)
         pl.shape = kTile256x128;
     else
         pl.shape = tiles128 * 4 > num_cus ? kTile128 : kTile64;
@@ -478,10 +480,10 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
     if (rc != FF_OK)
         return rc;
     char *ws = nullptr;
-    if (pl.split_s > 0 &&
-        (no_alloc ? pl.sums_off > kNoAllocBytes || pl.total_bytes - pl.sums_off > kNoAllocSumBytes
-                  : pl.total_bytes > st->ws_bytes && pl.total_bytes > workspace_limit(*st, stream))) {
-        // not enough scratch memory for the partial products: the kernels that need less
+    const size_t held = pl.split_s > 0 ? pl.sums_off : pl.total_bytes;  // without the partial products
+    if (no_alloc ? held > kNoAllocBytes || pl.total_bytes - held > kNoAllocSumBytes
+                 : pl.total_bytes > st->ws_bytes && pl.total_bytes > workspace_limit(*st, stream)) {
+        // not enough scratch memory for this plan: the one that needs least
         pl = Plan();
         rc = make_plan(M, K, N, dtype, st->num_cus, st, g_forced_variant, linear_only, pl, false);
         if (rc != FF_OK)

@@ -51,3 +51,19 @@ def test_cut_slabs_through_registers(K):
     plan = B.ff_plan_query(1000, K, 8136, B.FF_BF16)
     assert (plan["tile_m"], plan["tile_n"]) == (128, 256)
     _check(1000, K, 8136, "bf16", 94)
+
+
+@pytest.mark.parametrize("M,K,N,dtype,cols", [(2900, 64, 2692, "f32", 256), (2304, 128, 1848, "bf16", 256)])
+def test_small_bound_workspace_keeps_the_larger_tiles(M, K, N, dtype, cols):
+    """Room for the row statistics of 256-column tiles only, where the plan takes 128 x 128 tiles."""
+    plan = B.ff_plan_query(M, K, N, B.FF_BF16 if dtype == "bf16" else B.FF_F32)
+    assert (plan["tile_m"], plan["tile_n"], plan["workgroups_per_cu"]) == (128, 128, 2)
+    rows = 256 if dtype == "f32" else 128
+    need = (1 << 20) + -(-M // rows) * rows * -(-N // cols) * 8
+    assert need < B.ff_workspace_bytes(M, K, N, B.FF_BF16 if dtype == "bf16" else B.FF_F32)
+    ws = torch.empty(-(-need // 256) * 256, dtype=torch.uint8, device="cuda")
+    B.ff_set_workspace(ws)
+    try:
+        _check(M, K, N, dtype, 98)
+    finally:
+        B.ff_set_workspace(None)
