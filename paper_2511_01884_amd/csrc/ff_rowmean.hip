@@ -58,7 +58,7 @@ __device__ __forceinline__ void unpack(const uintx4 &v, float (&f)[8], const __b
         f[2 * i + 1] = __uint_as_float(v[i] & 0xffff0000u);
     }
 }
-__device__ __forceinline__ void unpack(const uintx4 &v, float (&f)[8], const float *)
+__device__ __forceinline__ void unpack(const uintx4 &v, float (&f)[4], const float *)
 {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
                     }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        float f[8];
+                        float f[E];
                         unpack(kMask ? v[u] & (n + u * kRowsPerStep < n_end ? 0xffffffffu : 0u) : v[u], f, (const T *)nullptr);
 #pragma unroll
                         for (int e = 0; e < E; ++e)
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
                 const int ch_raw = u * 64 * WPR + first;
                 const bool live = ch_raw < nchunks;
                 const int ch = live ? ch_raw : nchunks - 1;
-                float f[8];
+                float f[E];
                 unpack(rows[r][u], f, (const T *)nullptr);
                 float part = 0.0f;
 #pragma unroll
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
             for (int u = PL; u < per_lane; ++u) {
                 const int ch = u * 64 * WPR + first;
                 if (ch < nchunks) {
-                    float f[8];
+                    float f[E];
                     unpack(*reinterpret_cast<const uintx4 *>(x + (size_t)ch * E), f, (const T *)nullptr);
                     float part = 0.0f;
 #pragma unroll
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
             T *o = Out + (size_t)(m0 + r * row_step) * K;
             const float g = gelu_erf(dot[r] + c);
             auto emit = [&](const uintx4 &v, int ch) {
-                float f[8];
+                float f[E];
                 unpack(v, f, (const T *)nullptr);
                 uintx4 q;
                 if (sizeof(T) == 2) {
@@ -419,7 +419,9 @@ hipError_t launch_plr(const RowMeanParams &p, hipStream_t stream)
 }
 
 // rows of a set: two sets fill up to 128 registers of chunks, unless a wavefront has no more than two rows
-// (14848 x 1792 x 256 bf16: 23.3 us, with 64 registers 29.9)
+// (14848 x 1792 x 256 bf16: 23.3 us, with 64 registers 29.9).  Registers they are only while every array around
+// them is used whole: with an eight-wide array for four floats the compiler put the sets on the stack (528
+// bytes a lane), and 10692 x 992 x 1792 fp32 took 39.7 us for 21.8, 16384 x 1024 x 1024 52.9 for 29.0.
 template <typename T, int PL>
 hipError_t launch_pl(const RowMeanParams &p, hipStream_t stream)
 {

@@ -44,6 +44,12 @@ def test_chunks(M, K, N, dtype):
     _check(M, K, N, dtype, 96)
 
 
+@pytest.mark.parametrize("M,K,N", [(4200, 260, 8), (4300, 516, 72), (4097, 1024, 132), (6300, 1028, 8), (4500, 2048, 68)])
+def test_two_sets_of_fp32_rows(M, K, N):
+    """fp32 rows of several loads a lane, more than two rows a wavefront."""
+    _check(M, K, N, "f32", 99)
+
+
 def test_small_bound_workspace():
     """Room for one chunk's sums only, where the plan would take several."""
     M, K, N = 40, 512, 4096
