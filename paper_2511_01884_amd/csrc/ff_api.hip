@@ -682,8 +682,7 @@ int ff_fused_linear_sub_rowmean_gelu_residual(const void *X, const void *W, cons
         return FF_ERR_NULL;
     if (misaligned(X) || misaligned(W) || misaligned(b) || misaligned(s) || misaligned(Out))
         return FF_ERR_ALIGN;
-    // rowdot keeps K floats of the column means in LDS
-    if (K > 32768)
+    if (K > kRowMeanMaxK)
         return FF_ERR_UNSUPPORTED;
     std::lock_guard<std::mutex> lock(g_mutex);
     DeviceState *st = current_device_state();

@@ -72,8 +72,8 @@ __device__ __forceinline__ floatx4 masked(const floatx4 &v, bool ok)
 }
 
 // A row is shared by WPR wavefronts; PL = 16-byte chunks of it a lane keeps in registers; R = rows of a set: in
-// phase 2 one set is finished while another travels.
-template <typename T, int PL, int R, int WPR>
+// phase 2 one of SETS = 2 is finished while the other travels, or (SETS = 1) a wavefront has no row after its first.
+template <typename T, int PL, int R, int WPR, int SETS>
 __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p)
 {
     constexpr int E = Vec16<T>::n;
@@ -137,8 +137,10 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
                     batch(std::integral_constant<int, kInFlight>(), std::true_type(), n + r);
                 else if (left > kInFlight / 4)
                     batch(std::integral_constant<int, kInFlight / 2>(), std::true_type(), n + r);
-                else if (left > 0)
+                else if (left > 1)
                     batch(std::integral_constant<int, kInFlight / 4>(), std::true_type(), n + r);
+                else if (n + r < n_end)
+                    batch(std::integral_constant<int, 1>(), std::false_type(), n + r);
             }
             // the 8 rows of a wavefront (lane / 8), fixed butterfly; lanes 0..7 end with the piece sums
 #pragma unroll
@@ -186,13 +188,14 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
     if (tid == 0)
         atomic_add_device(p.counters + (size_t)way * kSyncStride, 1u);
 
-    // ---- the first 2 R rows of every wavefront: requested now, they travel while the grid meets ----
+    // ---- the first sets of every wavefront: requested now, they travel while the grid meets ----
     const int nchunks = K / E;                       // 16-byte chunks per row
     const int per_lane = (nchunks + 64 * WPR - 1) / (64 * WPR);  // chunks per lane, interleaved by lane
+    constexpr bool kRest = WPR == kWaves && E * PL * 64 * WPR < kRowMeanMaxK;  // a row may outgrow the registers
     constexpr int kRowsAtOnce = kWaves / WPR;
     const int row_step = G * kRowsAtOnce;
     const int first = (wave % WPR) * 64 + lane;      // this lane's chunks: first, first + 64 WPR, ...
-    uintx4 keep[2][R][PL];
+    uintx4 keep[SETS][R][PL];
     // a lane past the row's end re-reads the last chunk and masks it out later
     auto load_rows = [&](int m, uintx4 (&dst)[R][PL]) {
 #pragma unroll
@@ -209,7 +212,8 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
     };
     const int m_first = blockIdx.x * kRowsAtOnce + wave / WPR;
     load_rows(m_first, keep[0]);
-    load_rows(m_first + R * row_step, keep[1]);
+    if constexpr (SETS == 2)
+        load_rows(m_first + R * row_step, keep[1]);
 
     if (wave == 0) {
         const int l = lane < kSyncWays ? lane : 0;
@@ -258,11 +262,25 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
             const float *src1 = p.partial + (two ? k2 : k);
             floatx4 t0 = {0.0f, 0.0f, 0.0f, 0.0f};
             floatx4 t1 = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int ch = 0; ch < p.chunks; ch += 4) {
+            int ch = 0;
+            for (; ch + 4 <= p.chunks; ch += 4) {
+                floatx4 u0[4], u1[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j, src0 += p.k_pad, src1 += p.k_pad) {
+                    u0[j] = *reinterpret_cast<const floatx4 *>(src0);
+                    u1[j] = *reinterpret_cast<const floatx4 *>(src1);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    t0 += u0[j];
+                    t1 += u1[j];
+                }
+            }
+            if (ch < p.chunks) {
                 floatx4 u0[4], u1[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {  // past the end the last chunk is read again and not added
-                    const size_t at = (size_t)(ch + j < p.chunks ? ch + j : p.chunks - 1) * p.k_pad;
+                    const size_t at = (size_t)(ch + j < p.chunks ? j : p.chunks - 1 - ch) * p.k_pad;
                     u0[j] = *reinterpret_cast<const floatx4 *>(src0 + at);
                     u1[j] = *reinterpret_cast<const floatx4 *>(src1 + at);
                 }
@@ -286,12 +304,24 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
     c /= (float)N;
     __syncthreads();
     int turn = 0;
+    // One branch for a set: were its rows tested again before the stores, the compiler would count them as still
+    // travelling there and each store would wait for the one before it (1792 x 524 x 768 fp32: 0.2 us; 10692 x
+    // 992 x 1792 fp32: 21.2 us, 20.2).  Two bf16 rows of eight loads a lane spill with it and test each row twice.
+    constexpr bool kOneTest = R == 1 || PL < 8 || sizeof(T) == 4;
     auto finish_rows = [&](int m0, const uintx4 (&rows)[R][PL]) {
+        if (kOneTest && m0 >= M) {
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // nothing travels any more; known here, nothing later waits for stores instead
+            if (WPR > 1) {
+                lds_barrier();
+                turn ^= 1;
+            }
+            return;
+        }
         float dot[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             dot[r] = 0.0f;
-            if (m0 + r * row_step >= M)
+            if ((r > 0 || !kOneTest) && m0 + r * row_step >= M)
                 continue;
             const T *x = X + (size_t)(m0 + r * row_step) * K;
 #pragma unroll
@@ -308,7 +338,7 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
                 dot[r] += live ? part : 0.0f;
             }
             // rows longer than the register budget: the rest is read here and again below
-            for (int u = PL; u < per_lane; ++u) {
+            for (int u = PL; kRest && u < per_lane; ++u) {
                 const int ch = u * 64 * WPR + first;
                 if (ch < nchunks) {
                     float f[E];
@@ -345,7 +375,7 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if (m0 + r * row_step >= M)
+            if ((r > 0 || !kOneTest) && m0 + r * row_step >= M)
                 continue;
             const T *x = X + (size_t)(m0 + r * row_step) * K;
             T *o = Out + (size_t)(m0 + r * row_step) * K;
@@ -371,20 +401,24 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
                 if (ch < nchunks)
                     emit(rows[r][u], ch);
             }
-            for (int u = PL; u < per_lane; ++u) {
+            for (int u = PL; kRest && u < per_lane; ++u) {
                 const int ch = u * 64 * WPR + first;
                 if (ch < nchunks)
                     emit(*reinterpret_cast<const uintx4 *>(x + (size_t)ch * E), ch);
             }
         }
     };
-    // (the bound is the workgroup's first row: with a shared row its wavefronts meet at barriers)
-    for (int base = blockIdx.x * kRowsAtOnce, m = m_first; base < M; base += 2 * R * row_step, m += 2 * R * row_step) {
-        finish_rows(m, keep[0]);
-        load_rows(m + 2 * R * row_step, keep[0]);
-        if (base + R * row_step < M)
-            finish_rows(m + R * row_step, keep[1]);
-        load_rows(m + 3 * R * row_step, keep[1]);
+    if constexpr (SETS == 1) {
+        finish_rows(m_first, keep[0]);
+    } else {
+        // (the bound is the workgroup's first row: with a shared row its wavefronts meet at barriers)
+        for (int base = blockIdx.x * kRowsAtOnce, m = m_first; base < M; base += 2 * R * row_step, m += 2 * R * row_step) {
+            finish_rows(m, keep[0]);
+            load_rows(m + 2 * R * row_step, keep[0]);
+            if (base + R * row_step < M)
+                finish_rows(m + R * row_step, keep[1]);
+            load_rows(m + 3 * R * row_step, keep[1]);
+        }
     }
 
     // ---- departure: the last workgroup of the last way re-arms every counter ----
@@ -404,17 +438,17 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
     }
 }
 
-template <typename T, int PL, int R, int WPR>
+template <typename T, int PL, int R, int WPR, int SETS = 2>
 hipError_t launch_plr(const RowMeanParams &p, hipStream_t stream)
 {
     const size_t lds_bytes = (size_t)p.K * sizeof(float);
     if (lds_bytes > 32 * 1024) {  // static + dynamic beyond the default limit
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&rowmean_kernel<T, PL, R, WPR>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&rowmean_kernel<T, PL, R, WPR, SETS>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess)
             return e;
     }
-    hipLaunchKernelGGL((rowmean_kernel<T, PL, R, WPR>), dim3(p.grid), dim3(kThreads), lds_bytes, stream, p);
+    hipLaunchKernelGGL((rowmean_kernel<T, PL, R, WPR, SETS>), dim3(p.grid), dim3(kThreads), lds_bytes, stream, p);
     return hipGetLastError();
 }
 
@@ -426,6 +460,10 @@ template <typename T, int PL>
 hipError_t launch_pl(const RowMeanParams &p, hipStream_t stream)
 {
     constexpr int kMost = 16 / PL < 8 ? 16 / PL : 8;
+    // One row a wavefront at the most: no second set, whose code every launch would run past (a launch that
+    // short reads its instructions from memory: 92 x 1048 x 544 bf16 11.4 us, 10.9 without; 1000^3 fp32 11.7, 11.4).
+    if (p.M <= p.grid * kWaves)
+        return launch_plr<T, PL, 1, 1, 1>(p, stream);
     return p.M > p.grid * kWaves * 2 ? launch_plr<T, PL, kMost, 1>(p, stream) : launch_plr<T, PL, 1, 1>(p, stream);
 }
 

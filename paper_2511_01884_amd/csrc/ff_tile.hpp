@@ -99,6 +99,7 @@ struct SmallMParams {
 // second chain: 512 threads; phase 1 covers 64 rows x 128 bytes of W per load instruction
 constexpr int kRowMeanThreads = 512;
 constexpr int kRowMeanRowsPerStep = 64;
+constexpr int kRowMeanMaxK = 32768;  // the column means lie in LDS, four bytes each
 
 struct RowMeanParams {
     const void *X, *W, *b, *s;

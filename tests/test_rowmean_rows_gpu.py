@@ -50,6 +50,13 @@ def test_two_sets_of_fp32_rows(M, K, N):
     _check(M, K, N, "f32", 99)
 
 
+@pytest.mark.parametrize("M,K,N,dtype", [(2048, 640, 84, "f32"), (2049, 640, 84, "f32"), (2048, 72, 200, "bf16"), (2049, 72, 200, "bf16"),
+                                         (1, 3328, 64, "bf16"), (9, 520, 8, "bf16"), (2047, 1028, 324, "f32"), (4096, 264, 320, "bf16")])
+def test_one_row_a_wavefront_and_one_more(M, K, N, dtype):
+    """At most one row a wavefront (one set), and the first shapes beyond; chunks of W with 1 to 5 rows a thread."""
+    _check(M, K, N, dtype, 100)
+
+
 def test_small_bound_workspace():
     """Room for one chunk's sums only, where the plan would take several."""
     M, K, N = 40, 512, 4096
