@@ -636,9 +636,13 @@ int ff_debug_linear(const void *X, const void *W, const void *b, int64_t M, int6
 namespace {
 
 // Column strips and row chunks of the second chain's first phase: 128-byte strips, and the number of row
-// chunks with the least estimated time, in rows of a workgroup: its rounds of (strip, chunk) items, each worth
-// its rows and 48 more for the reductions, and 4 per chunk for the second phase's sum.  (One item per unit at
-// most, 256 / strips chunks, left units idle: 160 strips of 256 x 5120 x 2072 fp32 ran whole on 160 of 256.)
+// chunks with the least estimated time, in rows of a workgroup (4 ns): its rounds of (strip, chunk) items, each
+// worth its rows and 75 more for the reductions; 60 for a batch of four chunks in the second phase's sum (16 chunks
+// or more share the work of adding); and the reading of the partial sums, which every unit does for itself.
+// Fitted to 301 shapes (K 8..32768, N 64..2^20, up to 18 chunk counts of each): 0.6 % slower than the best count on
+// average.  (256 / strips chunks at most: 2.7 %, with 160 strips of 256 x 5120 x 2072 fp32 whole on 160 of 256
+// units; without the last two terms: 2.9 %, with 120 x 960 x 16036 fp32 20.6 us in 17 chunks, 19.0 in 8, and
+// 64 x 6560 x 1816 23.1 in 6, 18.7 in one.)
 // `most` bounds the scratch memory for the partial sums.
 struct RowMeanPlan {
     int strips, k_pad, chunks, rows_per_chunk;
@@ -653,9 +657,13 @@ RowMeanPlan rowmean_plan(int64_t K, int64_t N, int dtype, int num_cus, size_t mo
     r.k_pad = (int)(r.strips * strip_elems);
     const int64_t q = kRowMeanRowsPerStep;
     int64_t best = 0;
-    for (int64_t want = 1; want <= 64; ++want) {
+    // Up to 64 chunks; of very many rows, an item for every unit where there are fewer than four strips (2669 x 120 x
+    // 961536 bf16, two strips, 99.7 us in 64, 84.8 in 128; 20 x 64 x 20000, one strip, 10.5 in 63, 11.1 in 105).
+    const int64_t limit = r.strips < 4 && N >= (int64_t)1 << 17 ? 256 / r.strips : 64;
+    for (int64_t want = 1; want <= limit; ++want) {
         const int64_t rows = ((N + want - 1) / want + q - 1) / q * q, chunks = (N + rows - 1) / rows;
-        const int64_t cost = (r.strips * chunks + 255) / 256 * (rows + 48) + 4 * chunks;
+        const int64_t cost = (r.strips * chunks + 255) / 256 * (rows + 75) + ((chunks < 16 ? chunks : 16) + 3) / 4 * 60 +
+                             chunks * r.k_pad / 28;
         if (want > 1 && (cost >= best || (size_t)(chunks * r.k_pad) * sizeof(float) > most))
             continue;
         best = cost;

@@ -115,3 +115,13 @@ def test_plan_query_is_host_arithmetic():
         q(8, 12, 8)
     lib = B.load()
     assert lib.ff_plan_query(8, 8, 8, B.FF_BF16, None) == 1
+
+
+@pytest.mark.parametrize("K,N,dtype,chunks", [(960, 16036, "f32", 8), (6560, 1816, "f32", 1), (4096, 4096, "bf16", 4), (8, 1392, "bf16", 8),
+                                              (24, 52696, "bf16", 64), (5120, 2072, "f32", 3)])
+def test_row_chunks_of_the_second_chain(K, N, dtype, chunks):
+    """Host arithmetic: the workspace is the control region, the chunks' column sums and a slice for each unit."""
+    width = 64 if dtype == "bf16" else 32
+    sums = chunks * (-(-K // width) * width) * 4
+    want = (1 << 20) + -(-sums // 256) * 256 + 4096
+    assert B.load().ff_rowmean_workspace_bytes(64, K, N, B.FF_BF16 if dtype == "bf16" else B.FF_F32) == want
