@@ -76,14 +76,16 @@ typedef enum {
 typedef enum {
     FF_VARIANT_AUTO = 0,
     FF_VARIANT_TILED_FUSED = 1,   /* MFMA tiles; row statistics merged across
-                                     tiles inside the launch, G stays in registers
-                                     (few tiles: K cut over several workgroups) */
+                                     tiles inside the launch, G stays in registers */
     FF_VARIANT_TILED_TWOPASS = 2, /* MFMA tiles write fp32 G + statistics; a second
                                      kernel normalises (used when a row spans more
                                      tiles than can be co-resident) */
-    FF_VARIANT_SMALL_M = 3        /* M <= 32, bf16: streams W once at HBM rate
-                                     (strips of columns, or tiles with K cut) */
+    FF_VARIANT_SMALL_M = 3        /* M <= 32, bf16: streams W once at HBM rate */
 } ff_variant;
+/* Under automatic selection a problem of few tiles may run a third single-launch kernel, whose smaller
+ * tiles have K cut over several workgroups.  It is reported as FF_VARIANT_SMALL_M for bf16 with M <= 32
+ * (and N <= 65536 on 256 compute units), else as FF_VARIANT_TILED_FUSED; a forced variant never runs it.
+ * ff_plan_query tells the kernels apart. */
 
 /*
  * The fused operator.  Implements the chain above;

@@ -227,10 +227,10 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // units, the split kernel spreads K over the idle ones (2 x 16128 x 1904: 41.7 us, split 26; 10 x 8712 x 5536:
     // 42.1, 34.6), with several strips a unit reads one after the other (14 x 4608 x 12888: 40, 34), and over
     // 16 rows the streamer's registers no longer cover its loads (22 x 5888 x 6008: 34.6, 22).
-    const bool may_split = roomy && !linear_only && g_forced_tile == 0 && g_forced_waves == 0;
+    // (A forced variant, tile or wavefront count names the kernel it named before there was a split one.)
+    const bool may_split = roomy && !linear_only && forced == FF_VARIANT_AUTO && g_forced_tile == 0 && g_forced_waves == 0;
     const bool stream = M <= 16 && strips <= num_cus && strips * 2 > num_cus && (K < 3584 || strips > num_cus - 6);
-    if (may_split && (variant == FF_VARIANT_SMALL_M ? !stream : variant == 0 || variant == FF_VARIANT_TILED_FUSED) &&
-        plan_split(M, K, N, bf16, num_cus, st, pl)) {
+    if (may_split && !(variant == FF_VARIANT_SMALL_M && stream) && plan_split(M, K, N, bf16, num_cus, st, pl)) {
         pl.variant = variant == FF_VARIANT_SMALL_M ? FF_VARIANT_SMALL_M : FF_VARIANT_TILED_FUSED;
         return FF_OK;
     }
