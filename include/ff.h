@@ -44,7 +44,9 @@
  *     included, can be recorded into a HIP graph; a call that would have to
  *     allocate or grow the library's own workspace while its stream is being
  *     captured returns FF_ERR_WORKSPACE instead (bind a workspace, or make one
- *     call of that shape, before capturing).  Calls that share a workspace must
+ *     call of that shape, before capturing).  The library's own workspace stays
+ *     allocated once a captured call has used it, also when later calls outgrow
+ *     it or a caller binds another: graphs recorded with it stay valid.  Calls that share a workspace must
  *     not overlap in time: use one stream, or bind distinct workspaces serially.
  */
 #ifndef FF_H

@@ -48,6 +48,9 @@ struct DeviceState {
     void *ws = nullptr;       // bound or owned workspace; its control region is zeroed when it is bound or allocated
     size_t ws_bytes = 0;
     bool ws_owned = false;
+    bool ws_recorded = false;                // owned, and a captured call holds its address
+    struct Kept { void *ptr; size_t bytes; } kept[64] = {};  // recorded ones that were outgrown or unbound
+    int n_kept = 0;
     void *no_alloc_ptr = nullptr;            // this device's copy of `scratch`, once asked for
     void *no_alloc_sums = nullptr;           // the same for `scratch_sums`
     bool no_alloc_used = false;
@@ -381,15 +384,46 @@ DeviceState *current_device_state(int *dev_out = nullptr)
     return &st;
 }
 
+void note_recording(DeviceState &st, hipStream_t stream)
+{
+    if (!st.ws_owned || st.ws_recorded)
+        return;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess)
+        (void)hipGetLastError();
+    else
+        st.ws_recorded = capture != hipStreamCaptureStatusNone;
+}
+
+// Gives up the library's own workspace: kept if a graph may use it, else freed.
+bool release_own(DeviceState &st)
+{
+    if (st.ws_recorded && st.n_kept < (int)(sizeof(st.kept) / sizeof(st.kept[0])))
+        st.kept[st.n_kept++] = {st.ws, st.ws_bytes};
+    else if (hipDeviceSynchronize() != hipSuccess || hipFree(st.ws) != hipSuccess)
+        return false;
+    st.ws = nullptr;
+    st.ws_bytes = 0;
+    st.ws_owned = st.ws_recorded = false;
+    return true;
+}
+
 // Makes sure a workspace of at least `bytes` exists.  The control region of a workspace is zeroed,
 // synchronously, when it is allocated here or bound by ff_set_workspace, never on a caller's stream;
 // the kernels leave it zero behind them.  Allocating, freeing and synchronising are illegal while a
 // stream is being captured, so a call that would have to grow the library's own workspace during a
 // capture is refused instead.
+//
+// A graph holds the address of the workspace it was recorded with.  One of the library's own that a captured
+// call has used is therefore never freed: outgrown, or replaced by a caller's, it is kept for the replays (and
+// taken again where it is large enough).  Each is at least a quarter larger than the need that outgrew the one
+// before, so they are few (64 reach from 1 MiB to beyond any device) and no more than five times the largest.
 int prepare_workspace(DeviceState &st, size_t bytes, hipStream_t stream)
 {
-    if (st.ws != nullptr && st.ws_bytes >= bytes)
+    if (st.ws != nullptr && st.ws_bytes >= bytes) {
+        note_recording(st, stream);
         return FF_OK;
+    }
     if (st.ws != nullptr && !st.ws_owned)
         return FF_ERR_WORKSPACE;  // the caller's workspace is too small
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -399,13 +433,20 @@ int prepare_workspace(DeviceState &st, size_t bytes, hipStream_t stream)
     }
     if (capture != hipStreamCaptureStatusNone)
         return FF_ERR_WORKSPACE;
-    if (st.ws != nullptr) {
-        if (hipDeviceSynchronize() != hipSuccess || hipFree(st.ws) != hipSuccess) {
-            (void)hipGetLastError();
-            return FF_ERR_LAUNCH;
-        }
-        st.ws = nullptr;
-        st.ws_bytes = 0;
+    if (st.ws != nullptr && !release_own(st)) {
+        (void)hipGetLastError();
+        return FF_ERR_LAUNCH;
+    }
+    int fits = -1;  // the smallest kept one that is large enough
+    for (int i = 0; i < st.n_kept; ++i)
+        if (st.kept[i].bytes >= bytes && (fits < 0 || st.kept[i].bytes < st.kept[fits].bytes))
+            fits = i;
+    if (fits >= 0) {
+        st.ws = st.kept[fits].ptr;
+        st.ws_bytes = st.kept[fits].bytes;
+        st.ws_owned = st.ws_recorded = true;
+        st.kept[fits] = st.kept[--st.n_kept];
+        return FF_OK;
     }
     const size_t want = round_up(bytes + bytes / 4, 1 << 20);
     void *mem = nullptr;
@@ -421,6 +462,7 @@ int prepare_workspace(DeviceState &st, size_t bytes, hipStream_t stream)
     st.ws = mem;
     st.ws_bytes = want;
     st.ws_owned = true;
+    st.ws_recorded = false;
     return FF_OK;
 }
 
@@ -989,11 +1031,9 @@ int ff_set_workspace(void *dev_ptr, size_t bytes)
         (void)hipGetLastError();
         return FF_ERR_LAUNCH;  // the old binding stays
     }
-    if (st->ws != nullptr && st->ws_owned) {
-        if (hipDeviceSynchronize() != hipSuccess || hipFree(st->ws) != hipSuccess) {
-            (void)hipGetLastError();
-            return FF_ERR_LAUNCH;
-        }
+    if (st->ws != nullptr && st->ws_owned && !release_own(*st)) {
+        (void)hipGetLastError();
+        return FF_ERR_LAUNCH;
     }
     st->ws = dev_ptr;
     st->ws_bytes = dev_ptr ? bytes : 0;
@@ -1012,8 +1052,8 @@ int ff_check_device(void *stream)
         return FF_ERR_LAUNCH;
     }
     bool failed = false;
-    void *regions[2] = {st->ws, st->no_alloc_used ? st->no_alloc_ptr : nullptr};
-    for (void *region : regions) {
+    for (int i = -2; i < st->n_kept; ++i) {
+        void *region = i == -2 ? st->ws : (i == -1 ? (st->no_alloc_used ? st->no_alloc_ptr : nullptr) : st->kept[i].ptr);
         if (region == nullptr)
             continue;
         unsigned flag = 0;
