@@ -84,6 +84,7 @@ struct Plan {
     size_t total_bytes = 0;
     int split_s = 0;             // split kernel: workgroups per tile, 0 = another kernel
     int split_shape = 0;         // a SplitShape
+    double split_us = 0.0;       // its estimated time
     size_t sums_off = 0;
 };
 
@@ -142,6 +143,9 @@ int resident_split_blocks(DeviceState *st, bool bf16, int shape)
 // shape and S of each): the configuration picked is 1.4 (bf16) and 1.2 % (fp32) slower than the best on average.
 // A unit draws at most 32 (26) bytes a nanosecond of W from HBM, so a few workgroups cannot stream at the chip's
 // rate: 4 x 9272 x 15096 bf16 takes 102 us in 118 workgroups of 128-column tiles, 66 in 236 of 64.
+// The busiest unit's share counts up to 16 rows, where the streamer is the other choice: of a grid of a few more
+// workgroups than units some units read twice what the others do (3 x 10232 x 17024: 127 us in 266 workgroups, 110
+// in 532 smaller ones).
 bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceState *st, Plan &pl)
 {
     // workgroups per compute unit that the LDS allows (what the runtime reports is asked as well)
@@ -181,7 +185,8 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
             const double per = (double)((slabs + S - 1) / S), wpc = (double)((groups + num_cus - 1) / num_cus);
             const double unit = bm * bn / 4096.0;
             const double slab = c.slab + std::max(c.mfma * unit * wpc, (bn + bm) * 128 * wpc / c.fabric);
-            const double stream = (double)N * K * size / std::min(c.hbm, std::min<double>((double)groups, num_cus) * c.unit_hbm);
+            const double busiest = M <= 16 && wpc > 1 ? wpc * per * bn * 128 / c.unit_hbm : 0.0;
+            const double stream = std::max((double)N * K * size / std::min(c.hbm, std::min<double>((double)groups, num_cus) * c.unit_hbm), busiest);
             double t = c.start + std::max(per * slab, stream) + c.epi * unit / S * wpc + c.tiles * (double)NT +
                        (shape == kSplit128 ? c.epi128 : 0.0);
             if (S > 1)
@@ -201,6 +206,7 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
     if (pl.split_s == 0)
         return false;
     pl.rounds = 1;
+    pl.split_us = best;
     const size_t rows = (size_t)pl.tile_m / pl.split_s, tiles = (size_t)pl.RB * pl.NT;
     pl.partial_off = kCtrlBytes;
     pl.partial_bytes = round_up(tiles * pl.split_s * (rows < 16 ? 16 : rows) * sizeof(floatx2), 256);
@@ -224,18 +230,25 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
 
     if (variant == FF_VARIANT_SMALL_M && !smallm_ok)
         return FF_ERR_UNSUPPORTED;
-    // The streamer keeps M <= 16 with one 32-column strip on more than half the units but at most one on each,
-    // where rows of W are short or nearly every unit has a strip (9 x 840 x 7248: 13.7 us, split 15.6; 4 x 4608 x
-    // 8024: 23.0, 25.0; 16 x 8192 x 8192: 37.2, 37.0 to 42).  With fewer strips, or long rows on part of the
-    // units, the split kernel spreads K over the idle ones (2 x 16128 x 1904: 41.7 us, split 26; 10 x 8712 x 5536:
-    // 42.1, 34.6), with several strips a unit reads one after the other (14 x 4608 x 12888: 40, 34), and over
-    // 16 rows the streamer's registers no longer cover its loads (22 x 5888 x 6008: 34.6, 22).
+    // The streamer keeps M <= 16 where its estimated time is at most 2 % above the split kernel's: launch and merge,
+    // W at the rate of the chip, the rounds of strips of a unit at the unit's rate, a round's epilogue, the meeting
+    // of the strips (fitted to 440 shapes, K 64..16384, N 64..40000; it is off by 3 % on average).  Both sides were
+    // timed on all of them: with this choice a call takes 0.891 of the streamer's time on average, 6 of them more
+    // than 1.03 (at most 1.06).  The streamer wins mostly with nearly whole rounds of strips (16 x 8192 x 8192: 37.2
+    // us, 39 split; 2 x 800 x 16280, 509 strips: 18.6, 20.6) and with few slabs to cut (9 x 840 x 7248: 13.7, 15.6), the
+    // split kernel elsewhere (14 x 4608 x 12888, 403 strips: 40, 34; 2 x 16128 x 1904, 60: 41.7, 26).
+    // Over 16 rows the streamer's registers no longer cover its loads (22 x 5888 x 6008: 34.6, 22; never faster).
     // (A forced variant, tile or wavefront count names the kernel it named before there was a split one.)
     const bool may_split = roomy && !linear_only && forced == FF_VARIANT_AUTO && g_forced_tile == 0 && g_forced_waves == 0;
-    const bool stream = M <= 16 && strips <= num_cus && strips * 2 > num_cus && (K < 3584 || strips > num_cus - 6);
-    if (may_split && !(variant == FF_VARIANT_SMALL_M && stream) && plan_split(M, K, N, bf16, num_cus, st, pl)) {
-        pl.variant = variant == FF_VARIANT_SMALL_M ? FF_VARIANT_SMALL_M : FF_VARIANT_TILED_FUSED;
-        return FF_OK;
+    if (may_split && plan_split(M, K, N, bf16, num_cus, st, pl)) {
+        const double split_us = pl.split_us + (K % 64 != 0 ? 0.7 : 0.0);  // a slab cut by K goes through registers
+        const double rounds = (double)((strips + num_cus - 1) / num_cus);
+        const double streamer_us = 7.3 + (double)N * K * 2 / 20e6 + rounds * ((double)K * 64 / 31.6e3 + 1.36) + 0.0102 * (double)strips;
+        if (!(variant == FF_VARIANT_SMALL_M && M <= 16 && streamer_us < 1.02 * split_us)) {
+            pl.variant = variant == FF_VARIANT_SMALL_M ? FF_VARIANT_SMALL_M : FF_VARIANT_TILED_FUSED;
+            return FF_OK;
+        }
+        pl = Plan();
     }
     if (variant == FF_VARIANT_SMALL_M) {
         pl.variant = FF_VARIANT_SMALL_M;
