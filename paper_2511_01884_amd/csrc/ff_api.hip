@@ -271,11 +271,16 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     //     SIMD hide each other's latencies) and the K loop up to 4 % slower (half again as many LDS
     //     fragment reads per MFMA); the sum favours eight (4096^3 115.7 against 116.7 us; 65536 x 1024
     //     x 1024 159.5 against 170.7; 8192 x 4096 x 16384 950 against 966);
-    //   else, in bf16, if the 128 x 128 tiles outnumber the units by more than a quarter (up to there two per
-    //     unit are faster: 2304 x 4352 x 1848, 270 tiles, 74.7 against 82.8 us; 7085 x 768 x 560, 280: 24.7, 28.4;
-    //     3328 x 1576 x 1536, 312: 48.4, 48.7) but the 256-column x 128-row tiles do not: 256 x 128 tiles, one per unit, in one round (14 to 20 % faster than 128 x 128 tiles two
-    //     per unit on five such shapes; in fp32, where the K loop is eight times longer per slab and
-    //     that kernel spills, 128 x 128 tiles win by a third).  Two of those per unit are never chosen: the
+    //   else, in bf16, if the 128 x 128 tiles outnumber the units but the 256-column x 128-row tiles do not:
+    //     256 x 128 tiles, one per unit, in one round (14 to 20 % faster than 128 x 128 tiles two per unit on five
+    //     such shapes; in fp32, where the K loop is eight times longer per slab and that kernel spills, 128 x 128
+    //     tiles win by a third), except up to a quarter more 128 x 128 tiles than units, where two per unit are
+    //     faster (2304 x 4352 x 1848, 270 tiles: 74.7 against 82.8 us; 7085 x 768 x 560, 280: 24.7, 28.4) unless
+    //     twice the tiles of a row to merge outweigh the product (rows of more than 12 tiles of 256 columns with
+    //     K < 32 times their number: 426 x 104 x 10240, 320: 27.7, 23.9; 523 x 256 x 7872, 310: 27.0, 22.8) or W is
+    //     narrow and K long (up to 2 such tiles, K >= 4500: 9354 x 5680 x 512, 296: 147, 121).  260 shapes of 257
+    //     to 330 tiles: 0.4 % above the better of the two on average, and 5 % below 256 x 128 throughout (without
+    //     the two exceptions 2.8 and 3 %).  Two 256 x 128 tiles per unit are never chosen: the
     //     overlap of one workgroup's epilogue with the other's K loop does not pay for the 1.5 times
     //     larger L2 -> LDS traffic per flop (4096^3: 148 us);
     //   else 128 x 128 tiles, up to two per unit, which finish in one round; and for at most a
@@ -284,11 +289,13 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
     const int64_t tiles256x128 = ((M + 127) / 128) * ((N + 255) / 256);
     const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
+    const int64_t across = (N + 255) / 256;
+    const bool pays = across > 12 ? K >= 32 * across : (across > 2 || K < 4500);
     // (A plan for little scratch memory, roomy = false, splits nothing and keeps the larger tiles, which have
     // half the row statistics.)
     if (tiles256 * 2 > num_cus && (bf16 || !roomy || tiles128 > 2 * num_cus))
         pl.shape = kTile256W8;
-    else if (bf16 && tiles128 * 4 > (roomy ? 5 : 4) * num_cus && tiles256x128 <= num_cus)
+    else if (bf16 && tiles128 > num_cus && tiles256x128 <= num_cus && !(roomy && tiles128 * 4 <= 5 * num_cus && pays))
         pl.shape = kTile256x128;
     else
         pl.shape = tiles128 * 4 > num_cus ? kTile128 : kTile64;

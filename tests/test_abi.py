@@ -125,3 +125,11 @@ def test_row_chunks_of_the_second_chain(K, N, dtype, chunks):
     sums = chunks * (-(-K // width) * width) * 4
     want = (1 << 20) + -(-sums // 256) * 256 + 4096
     assert B.load().ff_rowmean_workspace_bytes(64, K, N, B.FF_BF16 if dtype == "bf16" else B.FF_F32) == want
+
+
+@pytest.mark.parametrize("M,K,N,cols", [(2304, 4352, 1848, 128), (7085, 768, 560, 128), (426, 104, 10240, 256), (523, 256, 7872, 256),
+                                        (9354, 5680, 512, 256), (591, 936, 6560, 128), (12310, 4352, 336, 128), (1000, 320, 8136, 256)])
+def test_tile_shape_just_above_one_128_tile_a_unit(M, K, N, cols):
+    """bf16, 257 to 320 tiles of 128 x 128: two a unit, or one of 256 columns where a row has many tiles for its K."""
+    plan = B.ff_plan_query(M, K, N, B.FF_BF16)
+    assert (plan["variant"], plan["tile_m"], plan["tile_n"]) == (B.FF_VARIANT_TILED_FUSED, 128, cols)
