@@ -363,12 +363,18 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // tiles a row: 651 us, with whole row-blocks 492 in one round more); spreading the row-blocks evenly
     // costs nothing, as the chip's power sets the rate (24064 x 7056 x 768, 47 row-blocks in each of two
     // rounds instead of 85 and 9: 460 -> 436 us).  Rows of more than half the grid's tiles stay in plain order:
-    // whole ones would leave up to half the chip idle.
+    // whole ones would leave up to half the chip idle.  So does a long bf16 product of one row-block more than a
+    // round holds: a full round and a few tiles on a cool chip beat two half rounds (10823 x 4608 x 1536, 43 row-blocks
+    // of which 42 fit: 240 us in halves, 223; 3614 x 2904 x 4584, 15 and 14: 204, 180; 20 such shapes with K >= 2048 take
+    // 0.95 of the time on average, none more than 1.02.  With K below that, two row-blocks more, or three rounds
+    // halves are as fast or faster: 3736 x 1656 x 8632, three rounds: 178, 211).
     if (pl.swz_sc_log2 < 0 && NT * 2 <= pl.grid && variant == FF_VARIANT_TILED_FUSED && !linear_only) {
-        const int64_t most = pl.grid / NT < RB ? pl.grid / NT : RB;
-        pl.rounds = (int)((RB + most - 1) / most);
-        pl.round_rows = (int)((RB + pl.rounds - 1) / pl.rounds);
-        pl.grid = (int)(pl.round_rows * NT);
+        const int64_t most = pl.grid / NT < RB ? pl.grid / NT : RB, rounds = (RB + most - 1) / most;
+        if (!(bf16 && RB == most + 1 && K >= 2048)) {
+            pl.rounds = (int)rounds;
+            pl.round_rows = (int)((RB + rounds - 1) / rounds);
+            pl.grid = (int)(pl.round_rows * NT);
+        }
     }
     // start delay of the second workgroup of every compute unit (256 x 128 tiles, full grid only)
     pl.stagger_us = (pl.shape == kTile256x128 && per_cu == 2 && pl.grid == 2 * num_cus) ? g_stagger_us : 0;

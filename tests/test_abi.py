@@ -133,3 +133,11 @@ def test_tile_shape_just_above_one_128_tile_a_unit(M, K, N, cols):
     """bf16, 257 to 320 tiles of 128 x 128: two a unit, or one of 256 columns where a row has many tiles for its K."""
     plan = B.ff_plan_query(M, K, N, B.FF_BF16)
     assert (plan["variant"], plan["tile_m"], plan["tile_n"]) == (B.FF_VARIANT_TILED_FUSED, 128, cols)
+
+
+@pytest.mark.parametrize("M,K,N,grid,rounds", [(10823, 4608, 1536, 256, 2), (3614, 2904, 4584, 256, 2), (3736, 1656, 8632, 170, 3),
+                                               (3614, 1288, 4584, 144, 2), (24064, 7056, 768, 141, 2)])
+def test_rounds_of_one_row_block_more_than_fits(M, K, N, grid, rounds):
+    """A long bf16 product keeps its full round; the others share their row-blocks evenly."""
+    plan = B.ff_plan_query(M, K, N, B.FF_BF16)
+    assert (plan["tile_m"], plan["tile_n"], plan["grid"], plan["rounds"]) == (256, 256, grid, rounds)

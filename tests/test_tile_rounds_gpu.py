@@ -30,6 +30,14 @@ def test_rounds_of_whole_row_blocks(M, K, N, dtype, rounds):
     _check(M, K, N, dtype, 91)
 
 
+@pytest.mark.parametrize("M,K,N", [(10800, 2056, 1480), (3600, 2048, 4584)])
+def test_one_row_block_more_than_a_round_holds(M, K, N):
+    print("[case] plain order", M, K, N, flush=True)
+    plan = B.ff_plan_query(M, K, N, B.FF_BF16)
+    assert (plan["tile_m"], plan["tile_n"], plan["grid"], plan["rounds"]) == (256, 256, 256, 2)
+    _check(M, K, N, "bf16", 92)
+
+
 @pytest.mark.parametrize("K", [8, 56, 64, 72, 80, 88, 120, 128, 136, 184, 192, 200, 248])
 @pytest.mark.parametrize("N", [4616, 4720])
 def test_cut_slabs_and_columns(K, N):
