@@ -312,6 +312,7 @@ void tile_kernel(const TileParams p)
                     half == 0 ? w_rsrc : x_rsrc, (__attribute__((address_space(3))) void *)dst, 16,
                     (half == 0 ? offa[x < kDmaA ? x : 0] : offb[x < kDmaB ? x : 0]) - back, slab * kRowBytes, 0, 0);
             }
+            asm volatile("");  // keeps the last instruction apart from the uncut slab's: merged, every fragment read waits for both
         };
 
         // The accumulators start from a zero the optimiser cannot see through: given a constant it
@@ -368,17 +369,30 @@ void tile_kernel(const TileParams p)
                 mma_group(g, a, b);
         };
 
-        // fragments of k-step s of the slab that K cuts: chunks at or beyond K become zeros, in both operands
+        // The slab that K cuts (the last): chunks at or beyond K become zeros, in both operands.  A body of its own:
+        // tests for it in the ordinary one broke up its schedule (4785 x 128 x 59136, of which no slab is cut: 838 us,
+        // with the tests 884, so 870; 3179 x 576 x 2032 fp32 88, 93, 87).
         auto cut_frags = [&](int slab, int s, uintx4 (&a)[WTN], uintx4 (&b)[WTM]) {
-            if (k_ragged && slab + 1 == slabs) {
-                const unsigned keep = slab * kSlabElems + (2 * s + h) * kChunkElems < K ? 0xffffffffu : 0u;
+            const unsigned keep = slab * kSlabElems + (2 * s + h) * kChunkElems < K ? 0xffffffffu : 0u;
 #pragma unroll
-                for (int x = 0; x < WTN; ++x)
-                    a[x] &= keep;
+            for (int x = 0; x < WTN; ++x)
+                a[x] &= keep;
 #pragma unroll
-                for (int x = 0; x < WTM; ++x)
-                    b[x] &= keep;
-            }
+            for (int x = 0; x < WTM; ++x)
+                b[x] &= keep;
+        };
+        auto multiply_cut = [&](int slab) {
+            cut_frags(slab, 0, fa[0], fb[0]);
+            load_frags(slab, 1, fa[1], fb[1]);
+            mma_all(fa[0], fb[0]);
+            cut_frags(slab, 1, fa[1], fb[1]);
+            load_frags(slab, 2, fa[0], fb[0]);
+            mma_all(fa[1], fb[1]);
+            cut_frags(slab, 2, fa[0], fb[0]);
+            load_frags(slab, 3, fa[1], fb[1]);
+            mma_all(fa[0], fb[0]);
+            cut_frags(slab, 3, fa[1], fb[1]);
+            mma_all(fa[1], fb[1]);
         };
 
         // ---- main loop over K slabs ----
@@ -500,21 +514,17 @@ void tile_kernel(const TileParams p)
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        // last iterations: slab i+1 or i+2 is missing or cut by K
-        for (; i < slabs; ++i) {
+        // last uncut iterations: slab i+1 or i+2 is missing or cut by K
+        for (; i < slabs - (k_ragged ? 1 : 0); ++i) {
             const bool more = i + 1 < slabs;
             if (more)
                 x_load(i + 1);
-            cut_frags(i, 0, fa[0], fb[0]);
             load_frags(i, 1, fa[1], fb[1]);
             mma_all(fa[0], fb[0]);
-            cut_frags(i, 1, fa[1], fb[1]);
             load_frags(i, 2, fa[0], fb[0]);
             mma_all(fa[1], fb[1]);
-            cut_frags(i, 2, fa[0], fb[0]);
             load_frags(i, 3, fa[1], fb[1]);
             mma_all(fa[0], fb[0]);
-            cut_frags(i, 3, fa[1], fb[1]);
             if (more) {
                 lds_barrier();                       // A
                 __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
@@ -526,6 +536,8 @@ void tile_kernel(const TileParams p)
             }
             mma_all(fa[1], fb[1]);
         }
+        if (k_ragged)
+            multiply_cut(i);
         } else {
         // The previous tile's epilogue is done with the LDS once every wave is here (its LDS reads
         // completed before its stores could issue).  No wait for those stores: they drain while the
@@ -606,20 +618,16 @@ void tile_kernel(const TileParams p)
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        // last iterations: slab i+1 or i+2 is missing or cut by K
-        for (; i < slabs; ++i) {
+        // last uncut iterations: slab i+1 or i+2 is missing or cut by K
+        for (; i < slabs - (k_ragged ? 1 : 0); ++i) {
             if (i + 1 < slabs)
                 dma_half_any(i + 1, 1);
-            cut_frags(i, 0, fa[0], fb[0]);
             load_frags(i, 1, fa[1], fb[1]);
             mma_all(fa[0], fb[0]);
-            cut_frags(i, 1, fa[1], fb[1]);
             load_frags(i, 2, fa[0], fb[0]);
             mma_all(fa[1], fb[1]);
-            cut_frags(i, 2, fa[0], fb[0]);
             load_frags(i, 3, fa[1], fb[1]);
             mma_all(fa[0], fb[0]);
-            cut_frags(i, 3, fa[1], fb[1]);
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
             lds_barrier();
             if (i + 2 < slabs)
@@ -628,6 +636,8 @@ void tile_kernel(const TileParams p)
                 load_frags(i + 1, 0, fa[0], fb[0]);
             mma_all(fa[1], fb[1]);
         }
+        if (k_ragged)
+            multiply_cut(i);
         }  // kPipeDma
         __syncthreads();  // all fragment reads done: LDS becomes epilogue scratch
         stamp(2);
