@@ -368,7 +368,12 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // of which 42 fit: 240 us in halves, 223; 3614 x 2904 x 4584, 15 and 14: 204, 180; 20 such shapes with K >= 2048 take
     // 0.95 of the time on average, none more than 1.02.  With K below that, two row-blocks more, or three rounds
     // halves are as fast or faster: 3736 x 1656 x 8632, three rounds: 178, 211).
-    if (pl.swz_sc_log2 < 0 && NT * 2 <= pl.grid && variant == FF_VARIANT_TILED_FUSED && !linear_only) {
+    // And so does a short fp32 product on more than one workgroup per unit but not two, where plain order already
+    // gives an XCD whole columns (NT a multiple of 8): its row-blocks end one after the other, and their stores
+    // run beside the products of the rest (652 x 172 x 8084, 384 tiles: 52.1 us in rounds, 44.0; 1227 x 204 x 4032:
+    // 47.0, 42.7; 34 such shapes with K < 600 take 0.98 of the time on average, 36 longer ones 1.01).
+    const bool staggered = !bf16 && total > num_cus && total == pl.grid && NT % 8 == 0 && K < 600;
+    if (pl.swz_sc_log2 < 0 && NT * 2 <= pl.grid && variant == FF_VARIANT_TILED_FUSED && !linear_only && !staggered) {
         const int64_t most = pl.grid / NT < RB ? pl.grid / NT : RB, rounds = (RB + most - 1) / most;
         if (!(bf16 && RB == most + 1 && K >= 2048)) {
             pl.rounds = (int)rounds;
