@@ -858,7 +858,7 @@ int ff_cross_entropy_mean(const void *logits, const int64_t *targets, int64_t B,
         // about two wavefronts per SIMD (256 x 50257 fp32: 28.0 us whole, 14.1 in 8 segments, 14.8 in 12;
         // 512 x 32000 bf16: 16.0, 11.3 in 4, 12.3 in 8; 1792 x 9216 fp32: 15.3, 15.4 in 4).
         p.segs = 1;
-        while (B * p.segs < (int64_t)st->num_cus * 6 && p.segs < 16 && chunks / (2 * p.segs) >= 64 &&
+        while (B * p.segs < (int64_t)st->num_cus * 6 && p.segs < kXentMaxSegs && chunks / (2 * p.segs) >= 64 &&
                B * (2 * p.segs + 1) <= pairs)
             p.segs *= 2;
         const int64_t batch = 64 * 8;  // whole batches of loads per segment where there are enough

@@ -117,6 +117,8 @@ struct RowMeanParams {
     long long wait_ticks;
 };
 
+constexpr int kXentMaxSegs = 16;  // segments of a long row
+
 struct XentParams {
     const void *logits;        // [B][C]
     const long long *targets;  // [B]

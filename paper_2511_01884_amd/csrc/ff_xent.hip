@@ -24,6 +24,8 @@
 // bitwise reproducible.
 #include "ff_tile.hpp"
 
+#include <type_traits>
+
 namespace ff {
 
 namespace {
@@ -394,29 +396,35 @@ __global__ __launch_bounds__(kThreads) void xent_long_kernel(XentParams p)
     __shared__ unsigned s_last;
     if (!last_to_arrive(p, &s_last))
         return;
-    // a thread combines the segments of every 256th row, in order
+    // a thread combines the segments of every 256th row, in order; all of a row's travel together (four at a
+    // time, one batch after the other, they were 0.7 of 5.9 us at 1 x 4517 fp32, 16 segments)
     float acc = 0.0f;
-    for (int r = threadIdx.x; r < p.B; r += kThreads) {
+    auto combine = [&](auto count, int r) {
+        constexpr int U = decltype(count)::value;
         const float xt = read_pair(p.picked + r)[0];
+        floatx2 u[U];
+#pragma unroll
+        for (int g = 0; g < U; ++g)
+            u[g] = read_pair(p.partials + (size_t)r * segs + (g < segs ? g : segs - 1));
         float m = -INFINITY, s = 0.0f;
-        for (int g0 = 0; g0 < segs; g0 += 4) {
-            floatx2 u[4];
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                u[g] = read_pair(p.partials + (size_t)r * segs + (g0 + g < segs ? g0 + g : segs - 1));
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                if (g0 + g < segs) {
-                    const float mn = fmaxf(m, u[g][0]);
-                    const float ref = ref_of(mn);
-                    s = s * exp2_hw((m - ref) * kLog2e) + u[g][1] * exp2_hw((u[g][0] - ref) * kLog2e);
-                    m = mn;
-                }
-        }
+        for (int g = 0; g < U; ++g)
+            if (g < segs) {
+                const float mn = fmaxf(m, u[g][0]);
+                const float ref = ref_of(mn);
+                s = s * exp2_hw((m - ref) * kLog2e) + u[g][1] * exp2_hw((u[g][0] - ref) * kLog2e);
+                m = mn;
+            }
         const float loss = (m - xt) + __builtin_amdgcn_logf(s) * kLn2;
         if (p.row_loss)
             p.row_loss[r] = loss;
         acc += loss;
+    };
+    for (int r = threadIdx.x; r < p.B; r += kThreads) {
+        if (segs <= 4)
+            combine(std::integral_constant<int, 4>(), r);
+        else
+            combine(std::integral_constant<int, kXentMaxSegs>(), r);
     }
     finish_mean(p, acc, s_red);
 }
