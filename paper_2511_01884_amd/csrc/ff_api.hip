@@ -856,10 +856,14 @@ int ff_cross_entropy_mean(const void *logits, const int64_t *targets, int64_t B,
     } else {
         // A wavefront per row; fewer than six rows per unit are cut into segments, up to as many as make
         // about two wavefronts per SIMD (256 x 50257 fp32: 28.0 us whole, 14.1 in 8 segments, 14.8 in 12;
-        // 512 x 32000 bf16: 16.0, 11.3 in 4, 12.3 in 8; 1792 x 9216 fp32: 15.3, 15.4 in 4).
+        // 512 x 32000 bf16: 16.0, 11.3 in 4, 12.3 in 8; 143 x 154624 fp32 28.7 in 8, 22.8 in 16) and down to 100 loads
+        // each (26 x 5074 fp32 5.8 us in 4, 5.3 in 8, 6.1 in 16).  More rows than 2.5 per unit nearly fill the chip
+        // themselves: two segments pay only for long ones in bf16 whose wavefronts still fit one round (963 x 50944
+        // 26.4 whole, 23.9; but 1080 x 4899 fp32 9.6, 11.9; 1019 x 65536 fp32 48.8, 53.9; 1380 x 17976 bf16 14.9, 18.0).
         p.segs = 1;
-        while (B * p.segs < (int64_t)st->num_cus * 6 && p.segs < kXentMaxSegs && chunks / (2 * p.segs) >= 64 &&
-               B * (2 * p.segs + 1) <= pairs)
+        const int64_t cus = st->num_cus;
+        const bool cut = B * 2 <= cus * 5 || (dtype == FF_BF16 && chunks >= 1024 && B <= cus * 4);
+        while (cut && B * p.segs < cus * 6 && p.segs < kXentMaxSegs && chunks / (2 * p.segs) >= 100 && B * (2 * p.segs + 1) <= pairs)
             p.segs *= 2;
         const int64_t batch = 64 * 8;  // whole batches of loads per segment where there are enough
         p.seg_chunks = (int)((chunks + p.segs - 1) / p.segs);

@@ -423,6 +423,8 @@ __global__ __launch_bounds__(kThreads) void xent_long_kernel(XentParams p)
     for (int r = threadIdx.x; r < p.B; r += kThreads) {
         if (segs <= 4)
             combine(std::integral_constant<int, 4>(), r);
+        else if (segs <= 8)
+            combine(std::integral_constant<int, 8>(), r);
         else
             combine(std::integral_constant<int, kXentMaxSegs>(), r);
     }

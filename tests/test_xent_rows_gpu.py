@@ -39,6 +39,13 @@ def test_rows_against_the_oracle(Bn, C, dtype):
     assert torch.equal(rows, rows2) and torch.equal(mean, mean2)
 
 
+@pytest.mark.parametrize("Bn,C,dtype", [(1, 4517, "f32"), (26, 5074, "f32"), (9, 10285, "bf16"), (700, 8199, "bf16"), (1025, 8200, "bf16"),
+                                        (641, 2049, "f32"), (640, 3203, "f32"), (143, 40001, "f32"), (300, 802, "f32")])
+def test_segment_counts(Bn, C, dtype):
+    """One to sixteen segments a row: two, four, eight or sixteen pairs read together when they meet."""
+    test_rows_against_the_oracle(Bn, C, dtype)
+
+
 @pytest.mark.parametrize("Bn,C,dtype", [(64, 37, "f32"), (64, 515, "bf16"), (48, 9001, "f32"), (3000, 4104, "bf16")])
 def test_special_values_stay_in_their_rows(Bn, C, dtype):
     logits, targets = make_xent_inputs(Bn, C, dtype, seed=82)
