@@ -843,7 +843,8 @@ int ff_cross_entropy_mean(const void *logits, const int64_t *targets, int64_t B,
     const size_t limit = st->ws_bytes >= ff_cross_entropy_workspace_bytes(B, C, dtype)
                              ? st->ws_bytes
                              : workspace_limit(*st, static_cast<hipStream_t>(stream));
-    const int64_t pairs = limit <= kCtrlBytes ? 1 : (int64_t)std::min<size_t>((limit - kCtrlBytes) / sizeof(floatx2), 8192);
+    // (in whole 256 bytes, as the need is rounded up to)
+    const int64_t pairs = limit < kCtrlBytes + 256 ? 1 : (int64_t)std::min<size_t>((limit - kCtrlBytes) / 256 * 256 / sizeof(floatx2), 8192);
     int64_t groups, per_cu = 8;  // workgroups of four wavefronts: with 4 (2) per unit 65536 x 1000 fp32 takes 4 % (49 %) more
     if (chunks <= 512) {
         // A row in the registers of 4, 16 or 64 lanes, at most eight loads each.  (A wavefront per row whatever

@@ -83,3 +83,24 @@ def test_a_small_workspace_rules_segments_out():
     finally:
         B.ff_set_workspace(None)
     assert np.abs(rows.cpu().double().numpy() - ref_rows).max() <= REL * np.abs(ref_rows).max()
+
+
+@pytest.mark.parametrize("extra", [256, 4224, 4351, 4352])
+def test_a_workspace_of_any_size_bounds_the_grid(extra):
+    """Sizes between two multiples of 256 bytes count as the lower one; less than 256 beyond the control region is refused."""
+    logits, targets = make_xent_inputs(4160, 1000, "f32", seed=84)
+    ref_rows, ref_mean = oracle.cross_entropy(logits.numpy(), targets.numpy())
+    Ld, td = logits.cuda(), targets.cuda()
+    ws = torch.empty((1 << 20) + extra, dtype=torch.uint8, device="cuda")
+    try:
+        B.ff_set_workspace(ws)
+        mean, rows = B.ff_cross_entropy_mean(Ld, td, with_rows=True)
+        torch.cuda.synchronize()
+        B.ff_set_workspace(ws[:(1 << 20) + 255])
+        with pytest.raises(B.FFError) as e:
+            B.ff_cross_entropy_mean(Ld, td)
+        assert e.value.status == 6
+    finally:
+        B.ff_set_workspace(None)
+    assert np.abs(rows.cpu().double().numpy() - ref_rows).max() <= REL * np.abs(ref_rows).max()
+    assert abs(float(mean.cpu()[0]) - ref_mean) <= REL * abs(ref_mean)
