@@ -275,8 +275,9 @@ def main() -> int:
     # kernels further down leave the chip at a lower clock for a while
     timeline = None
     if args.timeline:
-        grid = B.ff_plan_query(M, K, N, B.FF_F32 if wl.dtype == "f32" else B.FF_BF16)["grid"]
-        timeline = phase_timeline(torch, B, step, small_m=(variant == B.FF_VARIANT_SMALL_M), grid=grid)
+        plan = B.ff_plan_query(M, K, N, B.FF_F32 if wl.dtype == "f32" else B.FF_BF16)
+        streamer = variant == B.FF_VARIANT_SMALL_M and plan["waves"] == 8   # the split kernel stamps like the tiles
+        timeline = phase_timeline(torch, B, step, small_m=streamer, grid=plan["grid"])
 
     hbm_bound = args.workload == "cfg3"
     if hbm_bound:

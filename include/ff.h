@@ -295,7 +295,8 @@ int ff_debug_set_stagger_us(int microseconds);
  * writes, for each of its tiles that fits, 16 uint64 words at
  * [(round * grid + workgroup) * 16]: words 0..6 the 100 MHz wall clock at tile start, first K slab
  * in LDS, end of the K loop, row statistics published, other tiles of the rows arrived, statistics
- * merged, stores issued; words 8, 9 the shader clock at the start and end of the K loop.  The
+ * merged, stores issued; word 7, where K is cut over several workgroups, the tile's partial
+ * products summed; words 8, 9 the shader clock at the start and end of the K loop.  The
  * timings a launch reports this way differ from an untimed launch by the stores themselves. */
 int ff_debug_set_timeline(void *dev_ptr, size_t bytes);
 

@@ -1,5 +1,5 @@
 // Fused linear + erf-GELU + LayerNorm for problems with too few tiles to fill the chip (gfx950):
-// output tiles of 64 x 32, 64 x 64 or 128 x 128 (columns x rows) whose K range is cut over S workgroups.
+// output tiles of 64 x 32 to 128 x 128 (columns x rows, five shapes) whose K range is cut over S workgroups.
 //
 // One round: grid = tiles * S workgroups, all resident.  Workgroup (tile, s) walks its share of the
 // 128-byte K slabs through a ring of kRing LDS stages filled by direct-to-LDS loads, so kRing - 1
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const
     }
     const int m0 = rb * BM, n0 = cb * BN;
 
-    // Phase timestamps (test hook), as in the tile kernel
+    // Phase timestamps (test hook), as in the tile kernel; slot 7 where the tile's S workgroups have met
     auto stamp = [&](int k) {
         if (p.timeline != nullptr && tid == 0)
             p.timeline[(size_t)blockIdx.x * kTimelineSlots + k] = k < kTimelineCycleSlot ? wall_clock64() : clock64();
@@ -246,6 +246,15 @@ __global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const
     for (int t = 0; t < kRing - 1; ++t)
         if (t < full)
             request(t);
+    if (p.timeline != nullptr) {  // the first slab has landed
+        if (full >= kRing - 1)
+            wait_vm<(kRing - 2) * kDma>();
+        else
+            wait_vm<0>();
+        lds_barrier();
+    }
+    stamp(1);
+    stamp(kTimelineCycleSlot);
     int i = 0;
     for (; i + kRing - 1 < full; ++i) {
         wait_vm<(kRing - 2) * kDma>();  // this wave's rows of slab i have landed
@@ -281,6 +290,7 @@ __global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const
         multiply(0);
     }
     stamp(2);
+    stamp(kTimelineCycleSlot + 1);
     lds_barrier();  // all fragment reads done: the stages become the product's place
 
     // ---- product to LDS, [kWK][row][column] ----
@@ -362,7 +372,7 @@ __global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const
         for (int q = 0; q < kMaxPass; ++q)
             v[q] = product(q * kRowsPerPass + r_in_pass);
     }
-    stamp(1);
+    stamp(7);
 
     // ---- 2: bias, GELU, row statistics over the tile's columns, exchange ----
     floatx4 bias = {0.0f, 0.0f, 0.0f, 0.0f}, gamma = {1.0f, 1.0f, 1.0f, 1.0f}, beta = {0.0f, 0.0f, 0.0f, 0.0f};

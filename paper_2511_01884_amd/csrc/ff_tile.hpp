@@ -24,7 +24,7 @@ struct TileParams {
     int M, K, N;
     int NT;              // tiles along N
     int RB;              // row-blocks
-    int rounds;          // ceil(RB * NT / grid)
+    int rounds;          // ceil(RB * NT / grid), or ceil(RB / round_rows)
     int round_rows;      // row-blocks of a round when the grid is made of whole ones, else 0
     int swz_sc_log2;     // XCD-aware order: log2 of the super-block width in tiles, -1 = plain order
     int nt_log2;         // log2(NT) when the XCD-aware order is on
@@ -38,7 +38,8 @@ struct TileParams {
 
 // Timeline record of one tile: slots 0..6 wall-clock stamps (tile start, first slab landed, main
 // loop done, statistics published, other tiles arrived, statistics merged, stores issued); slots
-// kTimelineCycleSlot, +1 the shader clock at the start and end of the main loop.
+// kTimelineCycleSlot, +1 the shader clock at the start and end of the main loop.  Slot 7, split kernel only:
+// the tile's partial products are summed.
 constexpr int kTimelineSlots = 16;
 constexpr int kTimelineCycleSlot = 8;
 

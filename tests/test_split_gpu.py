@@ -90,3 +90,23 @@ def test_expired_waits_of_a_split_call_are_reported():
         B.ff_debug_expect_extra_arrivals(0)
         B.ff_debug_set_wait_limit_us(2000000)
     check_against_oracle(gpu_run(d)[0], oracle_on(d), "bf16")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", [(96, 4096, 2048), (65, 264, 200), (1, 8, 8), (17, 72, 4104)])
+def test_timeline_of_a_split_call(M, K, N):
+    """Every workgroup's stamps in their order, the meeting in word 7, the shader clock around the K loop."""
+    plan = B.ff_plan_query(M, K, N, B.FF_BF16)
+    buf = torch.zeros(plan["grid"] * 16, dtype=torch.int64, device="cuda")
+    d = make_inputs(M, K, N, "bf16", seed=68)
+    want, _ = gpu_run(d)
+    B.ff_debug_set_timeline(buf)
+    try:
+        got, _ = gpu_run(d)
+    finally:
+        B.ff_debug_set_timeline(None)
+    assert torch.equal(got, want)
+    rec = buf.cpu().view(-1, 16)
+    order = rec[:, [0, 1, 2, 7, 3, 4, 5, 6]]
+    assert bool((order > 0).all()) and bool((order[:, 1:] >= order[:, :-1]).all())
+    assert bool((rec[:, 9] > rec[:, 8]).all())
