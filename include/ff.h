@@ -46,7 +46,13 @@
  *     captured returns FF_ERR_WORKSPACE instead (bind a workspace, or make one
  *     call of that shape, before capturing).  The library's own workspace stays
  *     allocated once a captured call has used it, also when later calls outgrow
- *     it or a caller binds another: graphs recorded with it stay valid.  Calls that share a workspace must
+ *     it or a caller binds another: graphs recorded with it stay valid.
+ *     A call whose automatic plan needs more than a bound workspace, or during a
+ *     capture than the library's own, takes a plan that needs less where there is
+ *     one (another kernel, or a smaller grid) before it returns FF_ERR_WORKSPACE:
+ *     slower, and not bit for bit the result with a workspace of the size that the
+ *     *_workspace_bytes functions report.  With that size results are bitwise
+ *     reproducible on a device.  Calls that share a workspace must
  *     not overlap in time: use one stream, or bind distinct workspaces serially.
  */
 #ifndef FF_H
@@ -104,15 +110,15 @@ int ff_fused_linear_gelu_ln(const void *X, const void *W, const void *b,
 /*
  * The same operator for callers that cannot allocate device memory: code under HIP graph capture
  * before any workspace exists, tight serving loops, harnesses that forbid hipMalloc.  Arguments,
- * layout, dtypes, errors and result (bit for bit) as ff_fused_linear_gelu_ln, but no workspace is
- * used, bound or allocated: the row statistics and arrival counters of the call live in a static
+ * layout, dtypes, errors and result (bit for bit) as ff_fused_linear_gelu_ln with a workspace of
+ * ff_workspace_bytes(), but no workspace is used, bound or allocated: the row statistics and arrival counters of the call live in a static
  * device array inside the library (ff_noalloc_max_bytes() bytes, 8 MiB, one copy on every device
  * that loads the library, held until the process ends; the partial products of shapes whose K is cut
  * over several workgroups have a second one, 16 MiB).  The call makes no hipMalloc, hipFree,
  * memset or synchronising call; it launches one small kernel that clears the counters it is about
  * to use, then the operator's kernel, both on `stream`.  Shapes whose scratch need exceeds the array
- * return FF_ERR_WORKSPACE: that is every shape whose ff_workspace_bytes(), partial products apart, is above the limit, in
- * particular rows spanning more tiles than fit the device at once (the two-pass variant needs an fp32
+ * return FF_ERR_WORKSPACE: that is every shape whose ff_workspace_bytes(), partial products apart, is
+ * above the limit, in particular rows spanning more tiles than fit the device at once (the two-pass variant needs an fp32
  * copy of G).  All calls on one device share the one array: calls that overlap in time on a device
  * (two streams, two host threads) race on it and give wrong results; serialise them.
  * ff_check_device() covers these calls too.
@@ -130,13 +136,14 @@ size_t ff_noalloc_max_bytes(void);
  * study (Sec. 4: row maximum, sum of exponentials, pick of the target's logit):
  *     loss[r] = log( sum_c exp(L[r][c]) ) - L[r][t[r]],   *mean_loss = (1/B) sum_r loss[r]
  *   logits   device, [B,C] row-major, dtype FF_F32 or FF_BF16, 16-byte aligned, read once.
- *            Any C >= 1 (rows whose byte length is a multiple of 16 use 16-byte loads).
+ *            Any C >= 1 (16-byte loads wherever a row begins, for rows of four such loads or more).
  *   targets  device, [B] int64 class indices.  A target outside [0, C) makes that row's
  *            loss, and the mean, NaN; nothing is read out of bounds.
  *   row_loss device, [B] fp32, optional (NULL): the per-row losses.
  *   mean_loss device, one fp32, required.
  * Arithmetic is fp32 whatever the input dtype.  Asynchronous on `stream`; uses the
- * workspace (one number per workgroup and an arrival counter).  Results are bitwise
+ * workspace (a pair of numbers per workgroup, or per segment of a long row, and arrival
+ * counters).  Results are bitwise
  * reproducible on a given device.  Returns an ff_status.
  */
 int ff_cross_entropy_mean(const void *logits, const int64_t *targets, int64_t B, int64_t C,
@@ -195,18 +202,19 @@ size_t ff_rowmean_workspace_bytes(int64_t M, int64_t K, int64_t N, int dtype);
 /*
  * Bytes of workspace a call with this shape needs under the current variant
  * selection (0 on invalid arguments).  Pure host arithmetic.  Shapes whose K is cut over several
- * workgroups count their partial products (up to 16 MiB); with a bound workspace too small for those
- * the call takes a kernel that needs none, and is slower.
+ * workgroups count their partial products (up to 16 MiB); with a workspace too small for those that
+ * cannot grow the call takes a kernel that needs none, and is slower.
  */
 size_t ff_workspace_bytes(int64_t M, int64_t K, int64_t N, int dtype);
 
 /*
  * The launch plan a call with this shape would take under the current variant selection, without
  * launching anything: out[0] the ff_variant, out[1] rows and out[2] columns of the output tile a
- * workgroup owns (small-M: all M rows x one 32-column strip at a time), out[3] wavefronts per
- * workgroup, out[4] workgroups in the launch, out[5] tiles per workgroup (rounds), out[6] workgroups
- * per compute unit, out[7] 1 if the tile order is the XCD-aware one.  `out` is host memory of eight
- * ints.  Returns the status the call itself would return for a shape that cannot run.  With no GPU
+ * workgroup owns (small-M streamer: all M rows x one 32-column strip at a time), out[3] wavefronts
+ * per workgroup (8 for the small-M streamer, 4 where K is cut over several workgroups), out[4]
+ * workgroups in the launch (several per tile where K is cut), out[5] tiles per workgroup (rounds),
+ * out[6] workgroups per compute unit, out[7] 1 if the tile order is the XCD-aware one by powers of
+ * two or the launch cuts K.  `out` is host memory of eight ints.  Returns the status the call itself would return for a shape that cannot run.  With no GPU
  * visible it plans for 256 compute units.
  */
 int ff_plan_query(int64_t M, int64_t K, int64_t N, int dtype, int out[8]);

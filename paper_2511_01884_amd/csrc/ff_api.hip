@@ -941,7 +941,7 @@ int ff_metric_selection(const double *values, const double *runtime, int64_t n_t
         return FF_ERR_SHAPE;
     const bool filter = collinear_tau > 0.0 && collinear_tau <= 1.0;
     if (filter && n_metrics > 8192)
-        return FF_ERR_UNSUPPORTED;  // the J x J correlation matrix of a task is held in the workspace
+        return FF_ERR_UNSUPPORTED;  // the greedy pass keeps a bit for each metric in LDS and a row of bits in registers
     if ((reinterpret_cast<uintptr_t>(values) & 7u) || (reinterpret_cast<uintptr_t>(runtime) & 7u))
         return FF_ERR_ALIGN;
     const int n = (int)n_tasks, V = (int)n_kernels, J = (int)n_metrics;

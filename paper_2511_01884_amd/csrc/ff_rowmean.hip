@@ -22,9 +22,9 @@
 //      one wavefront per row (several, for rows of more than 512 loads): the row is read once and kept in
 //      registers (the case study's "cache the original row in registers"), dotted with wbar,
 //      butterfly-reduced, GELU, broadcast add, store, while the next set of rows travels.
-// Bound by HBM: 16384 x 8192 x 256 bf16 moves 541 MB in 102 us, 5.3 TB/s (one row after the other, whole in the
-// registers of one wavefront: 190 us); 4096 x 4096 x 4096 bf16 100.7 MB in 22.3 us (23.4), which is the three
-// streams at the rate of a large copy and 4 us of launch, ramp and meeting; 4096 x 4096 x 2048 fp32 36.5 us (51).
+// Bound by HBM: 16384 x 8192 x 256 bf16 moves 541 MB in 105 us, 5.2 TB/s (one row after the other, whole in the
+// registers of one wavefront: 195 us); 4096 x 4096 x 4096 bf16 100.7 MB in 22.7 us (24.3), which is the three
+// streams at the rate of a large copy and 4 us of launch, ramp and meeting; 4096 x 4096 x 2048 fp32 38.0 us (52).
 // All sums run in fixed order: results are bitwise reproducible on a device.
 #include "ff_tile.hpp"
 

@@ -1,5 +1,7 @@
-// Small-M path (M <= 32, bf16) of the fused linear + erf-GELU + LayerNorm
-// operator: a streamer, not a tiled GEMM.  The cost is reading W once, so each
+// Small-M path (bf16) of the fused linear + erf-GELU + LayerNorm operator: a
+// streamer, not a tiled GEMM.  The plan takes it for M <= 16 where its estimated
+// time is the better one; 17 to 32 rows run here when the variant is forced or the
+// scratch memory too small for the kernel that cuts K.  The cost is reading W once, so each
 // workgroup owns a strip of 32 output columns (32 rows of W, one contiguous
 // block), its 8 wavefronts split K, and every wave streams its share with 16-byte
 // loads arranged so that eight lanes cover one whole 128-byte line of a row — the

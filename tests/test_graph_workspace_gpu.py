@@ -56,3 +56,26 @@ def test_recorded_workspace_outlives_growth_and_binding():
             assert torch.equal(Y, want) and torch.equal(big_Y, big_want) and torch.equal(again, want), step
         B.ff_check_device()
     check_against_oracle(Y, oracle_on(d), "bf16")
+
+
+def test_capture_with_a_workspace_too_small_for_the_plan():
+    """The library's own memory cannot grow during a capture: a shape whose partial products do not fit takes a
+    kernel without them.  Whatever earlier calls left allocated, the replays are right and repeat their bits."""
+    B.ff_set_workspace(torch.zeros(1 << 18, dtype=torch.float32, device="cuda"))
+    B.ff_set_workspace(None)
+    _, small = _args(16, 256, 512, 53)
+    B.ff_fused_linear_gelu_ln(*small)
+    d, args = _args(96, 4096, 2048, 54)
+    Y = torch.zeros((96, 2048), dtype=torch.bfloat16, device="cuda")
+    g = _record(args, Y)
+    B.ff_fused_linear_gelu_ln(*args)              # eager: the plan's own kernel, in a workspace that may have grown
+    ref, first = oracle_on(d), None
+    for _ in range(3):
+        Y.zero_()
+        g.replay()
+        B.ff_fused_linear_gelu_ln(*small)
+        torch.cuda.synchronize()
+        check_against_oracle(Y, ref, "bf16", "captured with a small workspace")
+        first = Y.clone() if first is None else first
+        assert torch.equal(Y, first)
+    B.ff_check_device()
