@@ -577,7 +577,7 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
             kCounterOffset +
             sizeof(unsigned) * (pl.split_s > 0 ? ((size_t)pl.RB * pl.NT + (size_t)pl.RB * pl.split_s * kSplitWays) * kSplitCounterStride
                                 : pl.variant == FF_VARIANT_SMALL_M ? (size_t)kSyncWays * kSyncStride
-                                                                   : (size_t)pl.RB * 2);
+                                                                   : (size_t)row_counter_pairs(pl.RB) * 2);
         const size_t words = (ctrl - first + 3) / 4;
         hipLaunchKernelGGL(fill_words_kernel, dim3((unsigned)((words + 255) / 256 < 64 ? (words + 255) / 256 : 64)),
                            dim3(256), 0, stream, reinterpret_cast<unsigned *>(ws + first), words, 0u);

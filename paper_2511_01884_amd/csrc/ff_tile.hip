@@ -807,7 +807,7 @@ void tile_kernel(const TileParams p)
             wait_published();
             __syncthreads();
             if (tid == 0) {
-                unsigned *arrive = p.counters + 2 * (size_t)rb;
+                unsigned *arrive = p.counters + 2 * row_counter(rb);
                 atomic_add_device(arrive, 1u);
                 if (!wait_counter(arrive, (unsigned)(p.NT + p.extra_arrivals), p.wait_ticks))
                     atomic_store_device(p.err, 1u);
@@ -940,7 +940,7 @@ void tile_kernel(const TileParams p)
             // Departure, after the stores have been issued so that the wait for the counter's old value
             // delays nothing: the last tile of the row-block to get here re-arms its counters (every
             // tile of the row-block has read the partials by then).
-            unsigned *cnt = p.counters + 2 * (size_t)rb;
+            unsigned *cnt = p.counters + 2 * row_counter(rb);
             if (atomic_add_device(cnt + 1, 1u) == (unsigned)p.NT - 1u) {
                 atomic_store_device(cnt, 0u);
                 atomic_store_device(cnt + 1, 0u);

@@ -18,7 +18,7 @@ struct TileParams {
     void *Y;             // kFused: [M,N] in the tensor dtype
     float *F;            // kTwoPass: fp32 G scratch [M,N]; kLinearOnly: fp32 Z out
     floatx2 *partials;   // [RB][NT][BM] (mean, M2) per tile row
-    unsigned *counters;  // [RB][2] arrival, departure
+    unsigned *counters;  // pairs (arrival, departure), a row-block's at row_counter()
     unsigned *err;       // error word
     float eps;
     int M, K, N;
