@@ -68,11 +68,25 @@ __device__ __forceinline__ void wave_lds_sync()
 }
 
 // Ordering point for the instruction scheduler: the listed accumulators must have
-// been produced before it, and no memory operation moves across it.
-__device__ __forceinline__ void pin_order(floatx16 &c0) { asm volatile("" : "+a"(c0) : : "memory"); }
-__device__ __forceinline__ void pin_order(floatx16 &c0, floatx16 &c1)
+// been produced before it, and no memory operation moves across it.  The constraint also says where
+// they live.  Where a wavefront's 256 registers hold everything, the accumulators are ordinary vector
+// registers, which the epilogue reads and writes as they are: as accumulation registers they cost two
+// copies an element in the GELU pass and one before the stores (v_accvgpr_read, _write: 640 of 2900 vector instructions
+// of an epilogue) and 46 registers more (1018 x 256 x 10944 bf16 25.9 -> 25.1 us, 6912 x 256 x 15208 196 -> 186).  Only
+// the four-wavefront 256 x 256 tile, whose accumulators alone are 256 registers, needs the other half of the register file.
+template <bool kAcc> __device__ __forceinline__ void pin_order(floatx16 &c0)
 {
-    asm volatile("" : "+a"(c0), "+a"(c1) : : "memory");
+    if (kAcc)
+        asm volatile("" : "+a"(c0) : : "memory");
+    else
+        asm volatile("" : "+v"(c0) : : "memory");
+}
+template <bool kAcc> __device__ __forceinline__ void pin_order(floatx16 &c0, floatx16 &c1)
+{
+    if (kAcc)
+        asm volatile("" : "+a"(c0), "+a"(c1) : : "memory");
+    else
+        asm volatile("" : "+v"(c0), "+v"(c1) : : "memory");
 }
 
 // The lane index, computed where it is asked for: the compiler can neither move the computation out
@@ -133,6 +147,7 @@ void tile_kernel(const TileParams p)
     constexpr int kThreads = 64 * kWaves;
     constexpr int BN = kWavesN * WTN * 32;
     constexpr int BM = kWavesM * WTM * 32;
+    constexpr bool kAccRegs = WTN * WTM >= 16;
     constexpr int kChunkElems = 16 / (int)sizeof(T);
     constexpr int kSlabElems = kRowBytes / (int)sizeof(T);
     constexpr int kABytes = BN * kRowBytes;
@@ -359,9 +374,9 @@ void tile_kernel(const TileParams p)
             const int p0 = g * kPairs / kGroups;
             const int n = (g + 1) * kPairs / kGroups - p0;
             if (n == 2)
-                pin_order(acc[p0 / WTM][p0 % WTM], acc[(p0 + 1) / WTM][(p0 + 1) % WTM]);
+                pin_order<kAccRegs>(acc[p0 / WTM][p0 % WTM], acc[(p0 + 1) / WTM][(p0 + 1) % WTM]);
             else if (n == 1)
-                pin_order(acc[p0 / WTM][p0 % WTM]);
+                pin_order<kAccRegs>(acc[p0 / WTM][p0 % WTM]);
         };
         auto mma_all = [&](const uintx4 (&a)[WTN], const uintx4 (&b)[WTM]) {
 #pragma unroll
@@ -722,7 +737,7 @@ void tile_kernel(const TileParams p)
                         s2[j] = fmaf(d, d, s2[j]);
                     }
                     acc[i][j] = v;
-                    pin_order(acc[i][j]);  // G goes back to the accumulator registers
+                    pin_order<kAccRegs>(acc[i][j]);  // G goes back to the accumulator registers
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 // A block row that N cuts is summed again, with what lies beyond N left out.  (Masks in
