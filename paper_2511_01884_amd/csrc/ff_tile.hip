@@ -3,12 +3,12 @@
 // One workgroup (4 or 8 wavefronts) owns a BM x BN tile of the output and walks K in
 // 128-byte slabs (whole cache lines: one L2 request per line).  X and W slabs go
 // HBM -> LDS with 16-byte direct-to-LDS loads into two stages; the loads of the
-// next slab are issued in the shadow of the MFMAs, the single barrier per slab
-// sits before the last k-step, and MFMA fragments are read one k-step ahead of
+// slab after the next are issued in the shadow of the MFMAs, the single barrier per slab
+// sits in its last k-step, and MFMA fragments are read one k-step ahead of
 // their use, so the matrix pipe does not wait on LDS latency after the barrier.  The MFMA is issued
-// "transposed" (A operand = W rows, B operand = X rows), so that a lane's 16
-// accumulator registers of a 32x32 block run along N — the LayerNorm reduction
-// axis — and the row statistics need only one cross-lane step.
+// "transposed" (A operand = W rows, B operand = X rows), so that a lane's
+// accumulator registers run along N — the LayerNorm reduction
+// axis — and the row statistics need only one or two cross-lane steps.
 //
 // The epilogue never leaves the registers (the fused-epilogue pattern of the
 // paper's App. B.1 case, with the "cross-tile aggregation" it names as the hard
@@ -29,27 +29,36 @@ namespace {
 
 constexpr int kRowBytes = 128;  // bytes of one tile row per K slab (8 chunks of 16 B)
 constexpr int kChunksPerRow = kRowBytes / 16;
-constexpr int kStepsPerSlab = kChunksPerRow / 2;  // a k-step consumes two chunks (one per lane half)
 constexpr int kStages = 2;
 constexpr int kRowsPerDma = 1024 / kRowBytes;     // one direct-to-LDS instruction fills 1 KiB
 
+// The matrix instruction of a type: blocks of kBlock x kBlock outputs, whose kLaneGroups lane groups hold one
+// 16-byte chunk along K each, so that a k-step takes kLaneGroups chunks of a row.  A lane's results are those of
+// row lane % kBlock (of X), columns 4 (kLaneGroups q + group) + (0..3), q = 0 .. kQuads - 1.
+//
+// bf16 multiplies in blocks of 16: the chip's power sets the rate of a long product, and a 16 x 16 x 32 instruction
+// moves half the accumulators of a 32 x 32 x 16 one for each product.  Nothing but either in a loop, random operands:
+// 2002 against 1774 TFLOP/s.  fp32 is bound by the issue of its matrix instructions, whatever their shape.
 template <typename T>
 struct Mma;
 
 template <>
 struct Mma<__bf16> {
-    // One 16-byte fragment per lane holds 8 bf16 along K: one 32x32x16 MFMA.
-    static __device__ __forceinline__ void step(const uintx4 &a, const uintx4 &b, floatx16 &c)
+    using Acc = floatx4;
+    static constexpr int kBlock = 16, kLaneGroups = 4, kQuads = 1;
+    static __device__ __forceinline__ void step(const uintx4 &a, const uintx4 &b, Acc &c)
     {
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                     __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     }
 };
 
 template <>
 struct Mma<float> {
+    using Acc = floatx16;
+    static constexpr int kBlock = 32, kLaneGroups = 2, kQuads = 4;
     // One 16-byte fragment per lane holds 4 floats along K: four 32x32x2 MFMAs.
-    static __device__ __forceinline__ void step(const uintx4 &a, const uintx4 &b, floatx16 &c)
+    static __device__ __forceinline__ void step(const uintx4 &a, const uintx4 &b, Acc &c)
     {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -74,19 +83,12 @@ __device__ __forceinline__ void wave_lds_sync()
 // copies an element in the GELU pass and one before the stores (v_accvgpr_read, _write: 640 of 2900 vector instructions
 // of an epilogue) and 46 registers more (1018 x 256 x 10944 bf16 25.9 -> 25.1 us, 6912 x 256 x 15208 196 -> 186).  Only
 // the four-wavefront 256 x 256 tile, whose accumulators alone are 256 registers, needs the other half of the register file.
-template <bool kAcc> __device__ __forceinline__ void pin_order(floatx16 &c0)
+template <bool kAcc, typename Acc> __device__ __forceinline__ void pin_order(Acc &c)
 {
     if (kAcc)
-        asm volatile("" : "+a"(c0) : : "memory");
+        asm volatile("" : "+a"(c) : : "memory");
     else
-        asm volatile("" : "+v"(c0) : : "memory");
-}
-template <bool kAcc> __device__ __forceinline__ void pin_order(floatx16 &c0, floatx16 &c1)
-{
-    if (kAcc)
-        asm volatile("" : "+a"(c0), "+a"(c1) : : "memory");
-    else
-        asm volatile("" : "+v"(c0), "+v"(c1) : : "memory");
+        asm volatile("" : "+v"(c) : : "memory");
 }
 
 // The lane index, computed where it is asked for: the compiler can neither move the computation out
@@ -105,10 +107,10 @@ __device__ __forceinline__ int opaque_uniform(int v)
     asm volatile("s_mov_b32 %0, %1" : "=s"(r) : "s"(v));
     return r;
 }
-// The other half-wave's value (lane ^ 32), through the LDS crossbar.
-__device__ __forceinline__ float swap_halves(float v, int lane)
+// Another lane's value, through the LDS crossbar.
+__device__ __forceinline__ float from_lane(float v, int lane)
 {
-    return __int_as_float(__builtin_amdgcn_ds_bpermute((lane ^ 32) << 2, __float_as_int(v)));
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(lane << 2, __float_as_int(v)));
 }
 
 // LDS placement of 16-byte chunk `c` (0..7) of tile row `row`: chunks are XORed
@@ -116,14 +118,10 @@ __device__ __forceinline__ float swap_halves(float v, int lane)
 // (stride 128 B) spread over all banks, for 8-lane and for 16-lane passes.
 __device__ __forceinline__ int swizzle_of_row(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
-// MFMA instructions one fragment pair costs per k-step (scheduling hints only).
-template <typename T> struct MmaCount { static constexpr int value = 1; };
-template <> struct MmaCount<float> { static constexpr int value = 4; };
-
 // RAGGED_N: N is not a multiple of the tile width, so the last tile of each row
 // masks the columns at or beyond N in the statistics (chosen on the host).
 //
-// Wave layout: kWavesN x kWavesM wavefronts, each owning WTN x WTM MFMA blocks of 32 x 32.  The
+// Wave layout: kWavesN x kWavesM wavefronts, each owning WTN x WTM times 32 x 32 outputs.  The
 // 256-tile runs as 2 x 4 wavefronts of 4 x 2 blocks (two wavefronts per SIMD: 128 accumulator
 // registers each, and eight wavefronts keep twice as many loads in flight on the L2 -> LDS path
 // as four) or as 2 x 2 wavefronts of 4 x 4 blocks; the 128- and 64-tiles as 2 x 2 wavefronts, two
@@ -148,6 +146,10 @@ void tile_kernel(const TileParams p)
     constexpr int BN = kWavesN * WTN * 32;
     constexpr int BM = kWavesM * WTM * 32;
     constexpr bool kAccRegs = WTN * WTM >= 16;
+    using Acc = typename Mma<T>::Acc;
+    constexpr int kBlock = Mma<T>::kBlock, kLaneGroups = Mma<T>::kLaneGroups;
+    constexpr int kBlocksN = WTN * 32 / kBlock, kBlocksM = WTM * 32 / kBlock;  // matrix blocks of a wavefront
+    constexpr int kSteps = kChunksPerRow / kLaneGroups;                        // k-steps of a slab
     constexpr int kChunkElems = 16 / (int)sizeof(T);
     constexpr int kSlabElems = kRowBytes / (int)sizeof(T);
     constexpr int kABytes = BN * kRowBytes;
@@ -253,12 +255,12 @@ void tile_kernel(const TileParams p)
         stamp(0);
         const int m0 = rb * BM;
         const int n0 = cb * BN;
-        const int h = lane >> 5;
-        const int l32 = lane & 31;
-        // fragment read offsets (bytes inside a stage); k-step s reads chunk (2s + h) ^ swizzle
-        const int frag_swz = swizzle_of_row(l32);
-        const int a_frag_base = (wn * WTN * 32 + l32) * kRowBytes;
-        const int b_frag_base = kXBase + (wm * WTM * 32 + l32) * kRowBytes;
+        const int group = lane / kBlock;
+        const int block_row = lane % kBlock;
+        // fragment read offsets (bytes inside a stage); k-step s reads chunk (s * kLaneGroups + group) ^ swizzle
+        const int frag_swz = swizzle_of_row(block_row);
+        const int a_frag_base = (wn * WTN * 32 + block_row) * kRowBytes;
+        const int b_frag_base = kXBase + (wm * WTM * 32 + block_row) * kRowBytes;
         // DMA lane geometry: lane -> (row within a 16-row group, stored chunk slot)
         const int dma_r = lane / kChunksPerRow;
         const int dma_cs = lane % kChunksPerRow;
@@ -287,11 +289,13 @@ void tile_kernel(const TileParams p)
         // Buffer descriptors over the tile's rows: the per-lane 32-bit byte offset is
         // the loop-invariant part of a load's address, the slab offset rides in a scalar
         // register, so a DMA instruction costs no vector ALU work.  All addresses are
-        // clamped in-bounds above; the descriptors do not rely on range checking.
+        // clamped in-bounds above; K is bounded so that a tile's rows span at most kRangeBytes, and an
+        // offset of kRangeBytes is outside: such a lane reads zeros (dma_cut).
+        constexpr unsigned kRangeBytes = 0x80000000u;
         const __amdgpu_buffer_rsrc_t w_rsrc =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(w_tile), 0, 0xffffffffu, 0x00020000);
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(w_tile), 0, kRangeBytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t x_rsrc =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(x_tile), 0, 0xffffffffu, 0x00020000);
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(x_tile), 0, kRangeBytes, 0x00020000);
         auto dma_one = [&](int slab, int x) {
             const int stage = slab % kStages;
             if (x < kDmaA) {
@@ -307,8 +311,8 @@ void tile_kernel(const TileParams p)
                     offb[y >= 0 && y < kDmaB ? y : 0], slab * kRowBytes, 0, 0);
             }
         };
-        // The last slab when K cuts it: a lane whose chunk lies at or beyond K reads the first chunk of its row's
-        // slab instead; what that leaves in LDS is not multiplied (cut_frags).  (Through registers, with zeros
+        // The last slab when K cuts it: a lane whose chunk lies at or beyond K reads outside the descriptor's range,
+        // which puts zeros into its place in LDS.  (Through registers, with zeros
         // written for the missing chunks, it was a load latency in the open: 3001 x 2056 x 5000 spent 54.5 us up
         // to the end of the product, against 46.2 for K = 2048.)
         auto dma_cut = [&](int slab, int half) {
@@ -320,12 +324,12 @@ void tile_kernel(const TileParams p)
             for (int x = 0; x < (half == 0 ? kDmaA : kDmaB); ++x) {
                 const int row = wave * ((half == 0 ? BN : BM) / kWaves) + x * kRowsPerDma + lane_c / kChunksPerRow;
                 const int c = (lane_c % kChunksPerRow) ^ swizzle_of_row(row);
-                const unsigned back = slab * kSlabElems + c * kChunkElems < K ? 0u : (unsigned)c * 16u;
+                const bool in = slab * kSlabElems + c * kChunkElems < K;
                 char *dst = smem + (half == 0 ? stage * kWStride : kXBase + stage * kXStride) +
                             wave * ((half == 0 ? BN : BM) / kWaves) * kRowBytes + x * 1024;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     half == 0 ? w_rsrc : x_rsrc, (__attribute__((address_space(3))) void *)dst, 16,
-                    (half == 0 ? offa[x < kDmaA ? x : 0] : offb[x < kDmaB ? x : 0]) - back, slab * kRowBytes, 0, 0);
+                    in ? (half == 0 ? offa[x < kDmaA ? x : 0] : offb[x < kDmaB ? x : 0]) : kRangeBytes, slab * kRowBytes, 0, 0);
             }
             asm volatile("");  // keeps the last instruction apart from the uncut slab's: merged, every fragment read waits for both
         };
@@ -334,92 +338,74 @@ void tile_kernel(const TileParams p)
         // parks a block of sixteen zeros in scratch memory for the path that skips the steady iterations.
         float zero;
         asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
-        floatx16 acc[WTN][WTM];
+        Acc acc[kBlocksN][kBlocksM];
 #pragma unroll
-        for (int i = 0; i < WTN; ++i)
+        for (int i = 0; i < kBlocksN; ++i)
 #pragma unroll
-            for (int j = 0; j < WTM; ++j)
+            for (int j = 0; j < kBlocksM; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
+                for (int r = 0; r < 4 * Mma<T>::kQuads; ++r)
                     acc[i][j][r] = zero;
 
-        uintx4 fa[2][WTN], fb[2][WTM];  // fragment registers, double-buffered by k-step
-        // x-th fragment read of (slab, k-step s): W fragments first, then X fragments
-        auto read_one = [&](int slab, int s, int x, uintx4 (&a)[WTN], uintx4 (&b)[WTM]) {
-            const int coff = ((2 * s + h) ^ frag_swz) << 4;
-            if (x < WTN)
-                a[x < WTN ? x : 0] = *reinterpret_cast<const uintx4 *>(
-                    smem + (slab % kStages) * kWStride + a_frag_base + x * 32 * kRowBytes + coff);
-            else
-                b[x >= WTN ? x - WTN : 0] = *reinterpret_cast<const uintx4 *>(
-                    smem + (slab % kStages) * kXStride + b_frag_base + (x - WTN) * 32 * kRowBytes + coff);
+        // Fragments: W's in one buffer, each read again for the next k-step as soon as its products are issued; X's,
+        // which every group of products reads, in two, by k-step.
+        uintx4 fa[kBlocksN], fb[2][kBlocksM];
+        auto read_a = [&](int slab, int s, int x) {
+            const int coff = ((s * kLaneGroups + group) ^ frag_swz) << 4;
+            fa[x] = *reinterpret_cast<const uintx4 *>(smem + (slab % kStages) * kWStride + a_frag_base +
+                                                      x * kBlock * kRowBytes + coff);
         };
-        auto load_frags = [&](int slab, int s, uintx4 (&a)[WTN], uintx4 (&b)[WTM]) {
+        auto read_b = [&](int slab, int s, int x) {
+            const int coff = ((s * kLaneGroups + group) ^ frag_swz) << 4;
+            fb[s & 1][x] = *reinterpret_cast<const uintx4 *>(smem + (slab % kStages) * kXStride + b_frag_base +
+                                                             x * kBlock * kRowBytes + coff);
+        };
+        auto load_frags = [&](int slab, int s) {
 #pragma unroll
-            for (int x = 0; x < WTN + WTM; ++x)
-                read_one(slab, s, x, a, b);
-        };
-        // the MFMAs of a k-step are issued in kGroups groups (one per fragment read); group g takes the
-        // fragment pairs [g * kPairs / kGroups, (g + 1) * kPairs / kGroups): two each for 4 x 4 blocks per
-        // wave, one each for 2 x 2, and for a single block the second group takes the only pair
-        constexpr int kGroups = WTN + WTM;
-        constexpr int kPairs = WTN * WTM;
-        static_assert(kPairs <= 2 * kGroups, "pin_order takes at most two accumulators");
-        auto mma_group = [&](int g, const uintx4 (&a)[WTN], const uintx4 (&b)[WTM]) {
+            for (int x = 0; x < kBlocksM; ++x)
+                read_b(slab, s, x);
 #pragma unroll
-            for (int pair = g * kPairs / kGroups; pair < (g + 1) * kPairs / kGroups; ++pair)
-                Mma<T>::step(a[pair / WTM], b[pair % WTM], acc[pair / WTM][pair % WTM]);
+            for (int x = 0; x < kBlocksN; ++x)
+                read_a(slab, s, x);
         };
-        auto pin_group = [&](int g) {
-            const int p0 = g * kPairs / kGroups;
-            const int n = (g + 1) * kPairs / kGroups - p0;
-            if (n == 2)
-                pin_order<kAccRegs>(acc[p0 / WTM][p0 % WTM], acc[(p0 + 1) / WTM][(p0 + 1) % WTM]);
-            else if (n == 1)
-                pin_order<kAccRegs>(acc[p0 / WTM][p0 % WTM]);
-        };
-        auto mma_all = [&](const uintx4 (&a)[WTN], const uintx4 (&b)[WTM]) {
+        // The products of a k-step are issued in groups, one per fragment of W.
+        auto products = [&](int g, int s) {
 #pragma unroll
-            for (int g = 0; g < kGroups; ++g)
-                mma_group(g, a, b);
+            for (int j = 0; j < kBlocksM; ++j)
+                Mma<T>::step(fa[g], fb[s & 1][j], acc[g][j]);
         };
-
-        // The slab that K cuts (the last): chunks at or beyond K become zeros, in both operands.  A body of its own:
-        // tests for it in the ordinary one broke up its schedule (4785 x 128 x 59136, of which no slab is cut: 838 us,
-        // with the tests 884, so 870; 3179 x 576 x 2032 fp32 88, 93, 87).
-        auto cut_frags = [&](int slab, int s, uintx4 (&a)[WTN], uintx4 (&b)[WTM]) {
-            const unsigned keep = slab * kSlabElems + (2 * s + h) * kChunkElems < K ? 0xffffffffu : 0u;
+        auto end_group = [&](int g) {
 #pragma unroll
-            for (int x = 0; x < WTN; ++x)
-                a[x] &= keep;
-#pragma unroll
-            for (int x = 0; x < WTM; ++x)
-                b[x] &= keep;
+            for (int j = 0; j < kBlocksM; ++j)
+                pin_order<kAccRegs>(acc[g][j]);
+            __builtin_amdgcn_sched_barrier(0);
         };
-        auto multiply_cut = [&](int slab) {
-            cut_frags(slab, 0, fa[0], fb[0]);
-            load_frags(slab, 1, fa[1], fb[1]);
-            mma_all(fa[0], fb[0]);
-            cut_frags(slab, 1, fa[1], fb[1]);
-            load_frags(slab, 2, fa[0], fb[0]);
-            mma_all(fa[1], fb[1]);
-            cut_frags(slab, 2, fa[0], fb[0]);
-            load_frags(slab, 3, fa[1], fb[1]);
-            mma_all(fa[0], fb[0]);
-            cut_frags(slab, 3, fa[1], fb[1]);
-            mma_all(fa[1], fb[1]);
+        static_assert(kBlocksM <= kBlocksN && kSteps % 2 == 0, "the X fragments of the next k-step, one per group");
+        // k-step s of a slab, not its last: the next one's fragments are read behind its products.
+        auto step_inside = [&](int slab, int s) {
+#pragma unroll
+            for (int g = 0; g < kBlocksN; ++g) {
+                if (g < kBlocksM)
+                    read_b(slab, s + 1, g);
+                products(g, s);
+                read_a(slab, s + 1, g);
+                end_group(g);
+            }
+        };
+        auto steps_inside = [&](int slab) {
+#pragma unroll
+            for (int s = 0; s + 1 < kSteps; ++s)
+                step_inside(slab, s);
         };
 
         // ---- main loop over K slabs ----
-        // Per slab: four k-steps, each one group-interleaved stream of MFMAs with one
-        // LDS fragment read (for the next k-step) and at most one DMA instruction in
-        // the shadow of each MFMA group.  The W half of slab i+1 is issued during
-        // k-step 3 of slab i-1... concretely, iteration i issues the X half of slab
-        // i+1 in k-step 0 and the W half of slab i+2 in k-step 3; the barrier before
-        // k-step 3 is the point where slab i+1 has landed for everyone and everyone
-        // has finished reading slab i (its stage is then refilled).
-        static_assert(kStepsPerSlab == 4 && kStages == 2, "loop body written for 4 k-steps, 2 stages");
-        static_assert(kXReg || (kDmaA <= kGroups && kDmaB <= kGroups), "one DMA instruction per MFMA group at most");
+        // Every group of products has the fragment reads of the next k-step, and in a slab's last k-step the direct-to-LDS
+        // loads of the slab after the next, in its shadow.  The slab's one barrier stands in its last k-step, behind the
+        // first kSync groups, which cover the last fragment reads: there slab i + 1 has landed for everyone and
+        // everyone has read slab i, whose stage takes slab i + 2.  So a load has a whole slab's time to arrive.
+        constexpr int kSync = kBlocksN >= 8 ? 2 : (kBlocksN > 1 ? 1 : 0);
+        static_assert(kStages == 2 && kSync < kBlocksN, "loop body written for 2 stages, the reads behind the barrier");
+        enum { kNoDma = 0, kDmaFull = 1, kDmaCut = 2 };
         auto dma_half_any = [&](int slab, int half) {
             // half 0: W rows (x in [0, kDmaA)), half 1: X rows
             if (!k_ragged || slab + 1 < slabs) {
@@ -456,10 +442,8 @@ void tile_kernel(const TileParams p)
                     const int row = wave * (BM / kWaves) + j * kRowsPerDma + lane_c / kChunksPerRow;
                     const int c = (lane_c % kChunksPerRow) ^ swizzle_of_row(row);
                     const bool in = slab * kSlabElems + c * kChunkElems < K;
-                    uintx4 v = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                              x_rsrc, in ? offb[j] : 0u, in ? slab * kRowBytes : 0, 0));
-                    v &= in ? 0xffffffffu : 0u;
-                    xr[j] = v;
+                    xr[j] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                           x_rsrc, in ? offb[j] : kRangeBytes, slab * kRowBytes, 0));
                 }
             }
         };
@@ -479,80 +463,42 @@ void tile_kernel(const TileParams p)
         lds_barrier();
         stamp(1);
         stamp(kTimelineCycleSlot);
-        load_frags(0, 0, fa[0], fb[0]);
-        // steady iterations: slab i+1 and slab i+2 exist and are full ones
-        const int n_steady = slabs - 2 - (k_ragged ? 1 : 0);
+        load_frags(0, 0);
         int i = 0;
-        for (; i < n_steady; ++i) {
-            x_load_full(i + 1);
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {  // k-step 0
-                read_one(i, 1, g, fa[1], fb[1]);
-                mma_group(g, fa[0], fb[0]);
-                pin_group(g);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {  // k-step 1
-                mma_group(g, fa[1], fb[1]);
-                read_one(i, 2, g, fa[0], fb[0]);
-                pin_group(g);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {  // k-step 2
-                mma_group(g, fa[0], fb[0]);
-                read_one(i, 3, g, fa[1], fb[1]);
-                pin_group(g);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            lds_barrier();                       // A: everyone has read slab i
-            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): X registers and this wave's W rows of slab i+1
-            x_store();
-#pragma unroll
-            for (int x = 0; x < kDmaA; ++x)
-                dma_one(i + 2, x);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int g = 0; g < kGroups / 2; ++g) {  // k-step 3, first half
-                mma_group(g, fa[1], fb[1]);
-                pin_group(g);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            lds_barrier();                       // B: slab i+1 is complete in the LDS
-            load_frags(i + 1, 0, fa[0], fb[0]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int g = kGroups / 2; g < kGroups; ++g) {  // k-step 3, second half
-                mma_group(g, fa[1], fb[1]);
-                pin_group(g);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // last uncut iterations: slab i+1 or i+2 is missing or cut by K
-        for (; i < slabs - (k_ragged ? 1 : 0); ++i) {
+        for (; i < slabs; ++i) {
             const bool more = i + 1 < slabs;
             if (more)
                 x_load(i + 1);
-            load_frags(i, 1, fa[1], fb[1]);
-            mma_all(fa[0], fb[0]);
-            load_frags(i, 2, fa[0], fb[0]);
-            mma_all(fa[1], fb[1]);
-            load_frags(i, 3, fa[1], fb[1]);
-            mma_all(fa[0], fb[0]);
+            steps_inside(i);
             if (more) {
-                lds_barrier();                       // A
-                __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+                lds_barrier();                       // A: everyone has read slab i
+                __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): X registers and this wave's W rows of slab i+1
                 x_store();
                 if (i + 2 < slabs)
                     dma_half_any(i + 2, 0);
-                lds_barrier();                       // B
-                load_frags(i + 1, 0, fa[0], fb[0]);
             }
-            mma_all(fa[1], fb[1]);
+#pragma unroll
+            for (int g = 0; g < kBlocksN / 2; ++g) {
+                products(g, kSteps - 1);
+                end_group(g);
+            }
+            if (more) {
+                lds_barrier();                       // B: slab i+1 is complete in the LDS
+#pragma unroll
+                for (int x = 0; x < kBlocksM; ++x)
+                    read_b(i + 1, 0, x);
+#pragma unroll
+                for (int x = 0; x < kBlocksN / 2; ++x)
+                    read_a(i + 1, 0, x);
+            }
+#pragma unroll
+            for (int g = kBlocksN / 2; g < kBlocksN; ++g) {
+                products(g, kSteps - 1);
+                if (more)
+                    read_a(i + 1, 0, g);
+                end_group(g);
+            }
         }
-        if (k_ragged)
-            multiply_cut(i);
         } else {
         // The previous tile's epilogue is done with the LDS once every wave is here (its LDS reads
         // completed before its stores could issue).  No wait for those stores: they drain while the
@@ -574,13 +520,20 @@ void tile_kernel(const TileParams p)
         lds_barrier();
         dma_half_any(0, 0);
         dma_half_any(0, 1);
-        if (slabs > 1)
+        // (Slab 1 is requested behind the first fragment reads: its sixty-four instructions ahead of the wait
+        // delayed the start of every tile by 1 us.  A workgroup's first tile has nothing to wait for but slab 0.)
+        const bool ahead = first_tile && p.timeline == nullptr && slabs > 1;
+        auto request_slab_1 = [&]() {
             dma_half_any(1, 0);
-        if (first_tile && p.timeline == nullptr && slabs > 1)
-            __builtin_amdgcn_s_waitcnt(0x0f70 | (kDmaA & 15) | ((kDmaA >> 4) << 14));  // slab 0 landed
-        else
+            dma_half_any(1, 1);
+        };
+        if (ahead) {
+            request_slab_1();
+            __builtin_amdgcn_s_waitcnt(0x0f70 | (kDmaPerSlab & 15) | ((kDmaPerSlab >> 4) << 14));  // slab 0 landed
+        } else {
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): also the previous tile's stores, whose
                                                  // completion order relative to loads is not relied on
+        }
         first_tile = false;
         // the previous tile's last readers of the parameter region passed the barrier above
 #pragma unroll
@@ -592,67 +545,66 @@ void tile_kernel(const TileParams p)
         lds_barrier();
         stamp(1);
         stamp(kTimelineCycleSlot);
-        load_frags(0, 0, fa[0], fb[0]);
-
-        // steady iterations: slab i+1 and slab i+2 exist and are full ones
-        const int n_steady = slabs - 2 - (k_ragged ? 1 : 0);
+        load_frags(0, 0);
+        if (!ahead && slabs > 1)
+            request_slab_1();
+        // The last k-step of a slab; `dma`: what to do about slab i + 2, `more`: there is a slab i + 1.
+        auto step_last = [&](int i, auto more_c, auto dma_c) {
+            constexpr bool more = decltype(more_c)::value;
+            constexpr int dma = decltype(dma_c)::value;
+            constexpr int kRest = kBlocksN - kSync;  // groups behind the barrier
+#pragma unroll
+            for (int g = 0; g < kBlocksN; ++g) {
+                if (more && g >= kSync) {
+                    const int q = g - kSync;
+                    if (q == 0) {
+                        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's rows of slab i + 1 have landed
+                        lds_barrier();
+                        if (dma == kDmaCut) {
+                            dma_half_any(i + 2, 0);
+                            dma_half_any(i + 2, 1);
+                        }
+                    }
+                    if (dma == kDmaFull) {
+#pragma unroll
+                        for (int x = q * kDmaPerSlab / kRest; x < (q + 1) * kDmaPerSlab / kRest; ++x)
+                            dma_one(i + 2, x);
+                    }
+#pragma unroll
+                    for (int x = q * kBlocksM / kRest; x < (q + 1) * kBlocksM / kRest; ++x)
+                        read_b(i + 1, 0, x);
+                    if (q == 0) {
+#pragma unroll
+                        for (int x = 0; x < kSync; ++x)
+                            read_a(i + 1, 0, x);
+                    }
+                }
+                products(g, kSteps - 1);
+                if (more && g >= kSync)
+                    read_a(i + 1, 0, g);
+                end_group(g);
+            }
+        };
+        using std::integral_constant;
+        const integral_constant<bool, true> yes;
+        const integral_constant<bool, false> no;
         int i = 0;
-        for (; i < n_steady; ++i) {
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {  // k-step 0
-                if (g < kDmaB)
-                    dma_one(i + 1, kDmaA + g);
-                read_one(i, 1, g, fa[1], fb[1]);
-                mma_group(g, fa[0], fb[0]);
-                pin_group(g);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {  // k-step 1
-                mma_group(g, fa[1], fb[1]);
-                read_one(i, 2, g, fa[0], fb[0]);
-                pin_group(g);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {  // k-step 2
-                mma_group(g, fa[0], fb[0]);
-                read_one(i, 3, g, fa[1], fb[1]);
-                pin_group(g);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): slab i+1 has landed
-            lds_barrier();
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {  // k-step 3
-                if (g < kDmaA)
-                    dma_one(i + 2, g);
-                mma_group(g, fa[1], fb[1]);
-                read_one(i + 1, 0, g, fa[0], fb[0]);
-                pin_group(g);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+        for (; i < slabs - 2 - (k_ragged ? 1 : 0); ++i) {
+            steps_inside(i);
+            step_last(i, yes, integral_constant<int, kDmaFull>());
         }
-        // last uncut iterations: slab i+1 or i+2 is missing or cut by K
-        for (; i < slabs - (k_ragged ? 1 : 0); ++i) {
-            if (i + 1 < slabs)
-                dma_half_any(i + 1, 1);
-            load_frags(i, 1, fa[1], fb[1]);
-            mma_all(fa[0], fb[0]);
-            load_frags(i, 2, fa[0], fb[0]);
-            mma_all(fa[1], fb[1]);
-            load_frags(i, 3, fa[1], fb[1]);
-            mma_all(fa[0], fb[0]);
-            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-            lds_barrier();
-            if (i + 2 < slabs)
-                dma_half_any(i + 2, 0);
-            if (i + 1 < slabs)
-                load_frags(i + 1, 0, fa[0], fb[0]);
-            mma_all(fa[1], fb[1]);
+        if (k_ragged && slabs > 2) {
+            steps_inside(i);
+            step_last(i, yes, integral_constant<int, kDmaCut>());
+            ++i;
         }
-        if (k_ragged)
-            multiply_cut(i);
+        if (slabs > 1) {
+            steps_inside(i);
+            step_last(i, yes, integral_constant<int, kNoDma>());
+            ++i;
+        }
+        steps_inside(i);
+        step_last(i, no, integral_constant<int, kNoDma>());
         }  // kPipeDma
         __syncthreads();  // all fragment reads done: LDS becomes epilogue scratch
         stamp(2);
@@ -665,8 +617,8 @@ void tile_kernel(const TileParams p)
         {
         const int lane = opaque_lane();
         const int M = opaque_uniform(p.M), N = opaque_uniform(p.N);
-        const int h = lane >> 5;
-        const int l32 = lane & 31;
+        const int group = lane / kBlock;
+        const int block_row = lane % kBlock;
         float *s_b = kPrmEarly ? s_prm_early : reinterpret_cast<float *>(smem + kOffPrm);
         float *s_g = s_b + BN;
         float *s_be = s_g + BN;
@@ -688,76 +640,85 @@ void tile_kernel(const TileParams p)
         const int ncol_wave = wn * WTN * 32;            // wave's first column inside the tile
         const int nvalid_tile = (N - n0 < BN) ? (N - n0) : BN;
 
+        // A lane's values of one of its rows, in quads of neighbouring columns: quad t of the wavefront's strip starts at
+        // column t * kQuadStep + 4 * group.
+        constexpr int kQpb = Mma<T>::kQuads, kQuadStep = 4 * kLaneGroups;
+        constexpr int kQuadsRow = kBlocksN * kQpb;
+        constexpr int kPass = kQuadsRow < 4 ? kQuadsRow : 4;  // quads of a row worked on at a time
+
         // bias + GELU in place in the accumulators, and per-row (count, mean, M2) of
-        // the tile.  A lane holds 16 WTN values of each of its WTM rows; their sums are
-        // taken about the lane's first value (a shift that keeps sum-of-squares
-        // cancellation harmless), merged with the other lane half, then across waves.
+        // the tile.  Sums are taken about the row's first value in the strip (a shift that keeps sum-of-squares
+        // cancellation harmless), added up over the lane groups, merged across waves.
         {
             const bool cut = RAGGED_N && nvalid_tile < BN;  // only the last tile of a row is cut by N
-            // a half-wave's columns of the wave's strip are 8 k + 4 half + (0..3); those below the tile's end
-            auto columns_of = [&](int half) {
-                const int t = nvalid_tile - ncol_wave - half * 4;
-                const int c = t < 0 ? 0 : (t > WTN * 32 ? WTN * 32 : t);
-                return (c >> 3) * 4 + ((c & 7) < 4 ? (c & 7) : 4);
-            };
-            const int cnt_own = cut ? columns_of(h) : WTN * 16, cnt_other = cut ? columns_of(h ^ 1) : WTN * 16;
-            float shift[WTM], s1[WTM], s2[WTM];
+            float shift[kBlocksM], s1[kBlocksM], s2[kBlocksM];
+            {
+                const floatx4 bb = *reinterpret_cast<const floatx4 *>(s_b + ncol_wave + group * 4);
 #pragma unroll
-            for (int j = 0; j < WTM; ++j)
-                shift[j] = s1[j] = s2[j] = 0.0f;
+                for (int j = 0; j < kBlocksM; ++j) {
+                    shift[j] = from_lane(gelu_erf(acc[0][j][0] + bb[0]), block_row);
+                    s1[j] = s2[j] = 0.0f;
+                }
+            }
 #pragma unroll
-            for (int i = 0; i < WTN; ++i) {
-                floatx4 bb[4];  // bias of this lane's 16 columns of block row i
+            for (int t0 = 0; t0 < kQuadsRow; t0 += kPass) {
+                floatx4 bb[kPass];  // bias of this lane's columns
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    bb[q] = *reinterpret_cast<const floatx4 *>(s_b + ncol_wave + i * 32 + q * 8 + h * 4);
-                float s1_before[WTM], s2_before[WTM];
+                for (int q = 0; q < kPass; ++q)
+                    bb[q] = *reinterpret_cast<const floatx4 *>(s_b + ncol_wave + (t0 + q) * kQuadStep + group * 4);
+                float s1_before[kBlocksM], s2_before[kBlocksM];
 #pragma unroll
-                for (int j = 0; j < WTM; ++j) {
+                for (int j = 0; j < kBlocksM; ++j) {
                     s1_before[j] = s1[j];
                     s2_before[j] = s2[j];
                 }
 #pragma unroll
-                for (int j = 0; j < WTM; ++j) {
-                    // one 32x32 block at a time: read its 16 registers, write back 16 G values
-                    floatx16 v = acc[i][j];
+                for (int j = 0; j < kBlocksM; ++j) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float z = v[r] + bb[r >> 2][r & 3];
-                        if (MODE == kLinearOnly) {
-                            v[r] = z;
-                            continue;
+                    for (int q = 0; q < kPass; ++q) {
+                        Acc &c = acc[(t0 + q) / kQpb][j];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int r = (t0 + q) % kQpb * 4 + e;
+                            const float z = c[r] + bb[q][e];
+                            if (MODE == kLinearOnly) {
+                                c[r] = z;
+                                continue;
+                            }
+                            const float g = gelu_erf(z);
+                            const float d = g - shift[j];
+                            c[r] = g;
+                            s1[j] += d;
+                            s2[j] = fmaf(d, d, s2[j]);
                         }
-                        const float g = gelu_erf(z);
-                        if (i == 0 && r == 0)
-                            shift[j] = g;  // column ncol_wave + 4h: valid whenever the lane has any
-                        const float d = g - shift[j];
-                        v[r] = g;
-                        s1[j] += d;
-                        s2[j] = fmaf(d, d, s2[j]);
                     }
-                    acc[i][j] = v;
-                    pin_order<kAccRegs>(acc[i][j]);  // G goes back to the accumulator registers
+#pragma unroll
+                    for (int i = t0 / kQpb; i < (t0 + kPass) / kQpb; ++i)
+                        pin_order<kAccRegs>(acc[i][j]);  // G goes back to the accumulator registers
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                // A block row that N cuts is summed again, with what lies beyond N left out.  (Masks in
+                // What N cuts is summed again, with what lies beyond N left out.  (Masks in
                 // the pass itself made it 10.0 instead of 6.8 us for every tile of such a problem; two passes
                 // behind a branch spilled 60 registers; the columns beyond N repeat the last one, are
                 // never stored, and only the sums must not see them.)
-                const int limit = nvalid_tile - ncol_wave - i * 32;
-                if (RAGGED_N && MODE != kLinearOnly && limit < 32) {
+                const int limit = nvalid_tile - ncol_wave - t0 * kQuadStep;
+                if (RAGGED_N && MODE != kLinearOnly && limit < kPass * kQuadStep) {
 #pragma unroll
-                    for (int j = 0; j < WTM; ++j) {
+                    for (int j = 0; j < kBlocksM; ++j) {
                         s1[j] = s1_before[j];
                         s2[j] = s2_before[j];
                         if (limit > 0) {
-                            int lane_limit = limit - h * 4;
-                            asm volatile("" : "+v"(lane_limit));  // the masks are made anew for every block
+                            int lane_limit = limit - group * 4;
+                            asm volatile("" : "+v"(lane_limit));  // the masks are made anew for every row
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                const float d = (r >> 2) * 8 + (r & 3) < lane_limit ? acc[i][j][r] - shift[j] : 0.0f;
-                                s1[j] += d;
-                                s2[j] = fmaf(d, d, s2[j]);
+                            for (int q = 0; q < kPass; ++q) {  // a quad lies inside or beyond N as a whole
+                                const bool in = q * kQuadStep < lane_limit;
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) {
+                                    const float d = in ? acc[(t0 + q) / kQpb][j][(t0 + q) % kQpb * 4 + e] - shift[j] : 0.0f;
+                                    s1[j] += d;
+                                    s2[j] = fmaf(d, d, s2[j]);
+                                }
                             }
                         }
                     }
@@ -767,27 +728,21 @@ void tile_kernel(const TileParams p)
                 // (the lane index is taken afresh after the pass over the accumulators and again
                 // before the stores: values derived from it are not carried across those passes)
                 const int lane = opaque_lane();
-                const int h = lane >> 5;
-                const int l32 = lane & 31;
+                const int cols = cut ? nvalid_tile - ncol_wave : WTN * 32;  // of the strip, inside N
+                const float inv = cols > 0 ? 1.0f / (float)(cols < WTN * 32 ? cols : WTN * 32) : 0.0f;
 #pragma unroll
-                for (int j = 0; j < WTM; ++j) {
-                    // lane statistics -> merged with the other half-wave (lower half first)
-                    const float n_own = (float)cnt_own, n_oth = (float)cnt_other;
-                    const float inv_own = cnt_own > 0 ? 1.0f / n_own : 0.0f;
-                    float mean_own = fmaf(s1[j], inv_own, shift[j]);
-                    float m2_own = fmaxf(s2[j] - s1[j] * s1[j] * inv_own, 0.0f);
-                    if (RAGGED_N && cnt_own == 0)
-                        mean_own = 0.0f;
-                    const float mean_oth = swap_halves(mean_own, lane);
-                    const float m2_oth = swap_halves(m2_own, lane);
-                    float na = h == 0 ? n_own : n_oth;
-                    float mean_a = h == 0 ? mean_own : mean_oth;
-                    float m2a = h == 0 ? m2_own : m2_oth;
-                    merge_stats(na, mean_a, m2a, h == 0 ? n_oth : n_own,
-                                h == 0 ? mean_oth : mean_own, h == 0 ? m2_oth : m2_own);
-                    if (h == 0) {
-                        floatx2 v = {mean_a, m2a};
-                        s_wst[wn * BM + wm * WTM * 32 + j * 32 + l32] = v;
+                for (int j = 0; j < kBlocksM; ++j) {
+                    // sums of the lane groups: the same bits in each of them
+#pragma unroll
+                    for (int across = kBlock; across < 64; across *= 2) {
+                        s1[j] += from_lane(s1[j], lane ^ across);
+                        s2[j] += from_lane(s2[j], lane ^ across);
+                    }
+                    if (lane < kBlock) {
+                        floatx2 v = {fmaf(s1[j], inv, shift[j]), fmaxf(s2[j] - s1[j] * s1[j] * inv, 0.0f)};
+                        if (RAGGED_N && cols <= 0)
+                            v[0] = 0.0f;
+                        s_wst[wn * BM + wm * WTM * 32 + j * kBlock + lane] = v;
                     }
                 }
             }
@@ -921,34 +876,40 @@ void tile_kernel(const TileParams p)
         const int lane_o = opaque_lane();
         {
         const int lane = lane_o;
-        const int h = lane >> 5;
-        const int l32 = lane & 31;
+        const int group = lane / kBlock;
+        const int block_row = lane % kBlock;
+        constexpr int kRowBlocks = 32 / kBlock;  // blocks of a pass of 32 rows
 #pragma unroll
         for (int j = 0; j < WTM; ++j) {
-            float rstd = 1.0f, shift = 0.0f;  // y = (g * rstd + shift) * gamma + beta
-            if (MODE == kFused) {
-                const floatx2 ms = s_rst[wm * WTM * 32 + j * 32 + l32];
-                rstd = ms[1];
-                shift = -ms[0] * ms[1];
+            float rstd[kRowBlocks], shift[kRowBlocks];  // y = (g * rstd + shift) * gamma + beta
+#pragma unroll
+            for (int u = 0; u < kRowBlocks; ++u) {
+                rstd[u] = 1.0f;
+                shift[u] = 0.0f;
+                if (MODE == kFused) {
+                    const floatx2 ms = s_rst[wm * WTM * 32 + j * 32 + u * kBlock + block_row];
+                    rstd[u] = ms[1];
+                    shift[u] = -ms[0] * ms[1];
+                }
             }
 #pragma unroll
-            for (int i = 0; i < WTN; ++i)
+            for (int t = 0; t < kQuadsRow; ++t) {
+                const int cw = t * kQuadStep + group * 4;  // column inside the wave's strip
+                floatx4 ga4, be4;
+                if (MODE == kFused) {
+                    ga4 = *reinterpret_cast<const floatx4 *>(s_g + ncol_wave + cw);
+                    be4 = *reinterpret_cast<const floatx4 *>(s_be + ncol_wave + cw);
+                }
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int cw = i * 32 + q * 8 + h * 4;  // column inside the wave's strip
+                for (int u = 0; u < kRowBlocks; ++u) {
                     float y[4];
-                    if (MODE == kFused) {
-                        const floatx4 ga4 = *reinterpret_cast<const floatx4 *>(s_g + ncol_wave + cw);
-                        const floatx4 be4 = *reinterpret_cast<const floatx4 *>(s_be + ncol_wave + cw);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            y[e] = fmaf(fmaf(acc[i][j][q * 4 + e], rstd, shift), ga4[e], be4[e]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            y[e] = acc[i][j][q * 4 + e];
+                    for (int e = 0; e < 4; ++e) {
+                        y[e] = acc[t / kQpb][j * kRowBlocks + u][t % kQpb * 4 + e];
+                        if (MODE == kFused)
+                            y[e] = fmaf(fmaf(y[e], rstd[u], shift[u]), ga4[e], be4[e]);
                     }
-                    char *dst = s_out + l32 * kOutPitch + cw * (int)sizeof(OutT);
+                    char *dst = s_out + (u * kBlock + block_row) * kOutPitch + cw * (int)sizeof(OutT);
                     if (sizeof(OutT) == 2) {
                         uintx2 v = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
                         *reinterpret_cast<uintx2 *>(dst) = v;
@@ -957,6 +918,7 @@ void tile_kernel(const TileParams p)
                         *reinterpret_cast<floatx4 *>(dst) = v;
                     }
                 }
+            }
             wave_lds_sync();
             constexpr int kCpr = kOutRowBytes / 16;  // 16-byte chunks per row
             constexpr int kIters = 32 * kCpr / 64;
