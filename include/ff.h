@@ -280,8 +280,8 @@ int ff_debug_stream_read(const void *src, size_t bytes);
 
 /* Tile shape of the tiled variants for later calls: tile = 0 (automatic), 64, 128 or 256 (columns);
  * wg_per_cu = 0 (automatic), 1 (a persistent grid of one workgroup per compute unit) or 2 (two).
- * (256, 0 or 1) is the 256 x 256 tile, one workgroup per compute unit; (256, 2) the 256-column x
- * 128-row tile, up to two per compute unit (the automatic plan takes it only where there are no more
+ * (256, 0 or 1) is the 256 x 256 tile, (256, 2) the 256-column x 128-row tile, both one workgroup per
+ * compute unit (the automatic plan takes the latter only where there are no more
  * such tiles than units).  The combinations the automatic plan does not pick exist as distinct
  * kernels of the same operator for the profiling-metric study and for tests.  FF_ERR_UNSUPPORTED
  * for any other combination. */
@@ -293,9 +293,8 @@ int ff_debug_force_tile(int tile, int wg_per_cu);
  * call whose plan uses a narrower tile returns FF_ERR_UNSUPPORTED. */
 int ff_debug_force_waves(int waves);
 
-/* Start delay, in microseconds (0..1000, default 12), of the second workgroup of every compute unit
- * in launches of the 256-column x 128-row tile over a full grid: with it, the epilogue of one
- * workgroup falls into the K loop of the other from the first tile on. */
+/* Accepted (0..1000) and without effect: it was the start delay of the second workgroup of a compute unit in launches
+ * of the 256-column x 128-row tile, which now takes a whole unit. */
 int ff_debug_set_stagger_us(int microseconds);
 
 /* Phase timestamps of the tiled kernels.  Binds `bytes` of device memory (8-byte aligned; NULL

@@ -68,14 +68,12 @@ int g_extra_arrivals = 0;
 int g_forced_tile = 0;        // 0 = automatic, else 64, 128 or 256
 int g_forced_wg_per_cu = 0;   // 0 = automatic (one workgroup per compute unit), else 1 or 2
 int g_forced_waves = 0;       // 0 = automatic, else 4 or 8 wavefronts per workgroup of the 256 x 256 tile
-int g_stagger_us = 12;        // start delay of the second workgroup per compute unit (256 x 128 tiles)
 thread_local int t_last_variant = 0;
 
 struct Plan {
     int variant = 0;
     int shape = 0;     // a TileShape
     int tile_m = 0, tile_n = 0;  // rows and columns of a tile
-    int stagger_us = 0;
     int NT = 0, RB = 0;
     int grid = 0, rounds = 0, swz_sc_log2 = -1, nt_log2 = 0, grid_log2 = 0, round_rows = 0;
     int mt = 0, strips = 0;  // small-M
@@ -261,9 +259,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
         return FF_OK;
     }
 
-    // Tiled variants, by how many tiles of a shape there are per compute unit (measured on one device,
-    // 1024 x 4096 x 8192, whole call: 256 x 256 tiles 108 us with half the units idle, 256 x 128 tiles
-    // 82 us, 128 x 128 tiles two per unit 92 us, the same in two passes 84 us):
+    // Tiled variants, by how many tiles of a shape there are per compute unit:
     //   more 256 x 256 tiles than half the compute units (in fp32, which is bound by the matrix units, only
     //     when 128 x 128 tiles two per unit would not do in one round: 2927 x 2952 x 2692 takes 395 us with
     //     those, 688 with 132 tiles of 256): 256 x 256 tiles, one workgroup of eight
@@ -272,17 +268,17 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     //     fragment reads per MFMA); the sum favours eight (4096^3 115.7 against 116.7 us; 65536 x 1024
     //     x 1024 159.5 against 170.7; 8192 x 4096 x 16384 950 against 966);
     //   else, in bf16, if the 128 x 128 tiles outnumber the units but the 256-column x 128-row tiles do not:
-    //     256 x 128 tiles, one per unit, in one round (14 to 20 % faster than 128 x 128 tiles two per unit on five
-    //     such shapes; in fp32, where the K loop is eight times longer per slab and that kernel spills, 128 x 128
-    //     tiles win by a third), except up to a quarter more 128 x 128 tiles than units, where two per unit are
-    //     faster (2304 x 4352 x 1848, 270 tiles: 74.7 against 82.8 us; 7085 x 768 x 560, 280: 24.7, 28.4) unless
-    //     twice the tiles of a row to merge outweigh the product (rows of more than 12 tiles of 256 columns with
-    //     K < 32 times their number: 426 x 104 x 10240, 320: 27.7, 23.9; 523 x 256 x 7872, 310: 27.0, 22.8) or W is
-    //     narrow and K long (up to 2 such tiles, K >= 4500: 9354 x 5680 x 512, 296: 147, 121).  260 shapes of 257
-    //     to 330 tiles: 0.4 % above the better of the two on average, and 5 % below 256 x 128 throughout (without
-    //     the two exceptions 2.8 and 3 %).  Two 256 x 128 tiles per unit are never chosen: the
-    //     overlap of one workgroup's epilogue with the other's K loop does not pay for the 1.5 times
-    //     larger L2 -> LDS traffic per flop (4096^3: 148 us);
+    //     256 x 128 tiles, one per unit, in one round, with three slabs of LDS (in fp32 128 x 128 tiles
+    //     win by a third): 1024 x 4096 x 8192 68 us, 15 such shapes 1.25 times as fast as with two slabs and four
+    //     wavefronts.  Up to a quarter more 128 x 128 tiles than units go two per unit where one of these holds:
+    //     an odd number of them a row, which leaves half a 256-column tile empty (1843 x 5264 x 2312 85.5, with 256 x 128
+    //     100.7; 1459 x 7640 x 2848 132, 145); at most eight more than 256 units and more than 4 a row (591 x 936 x 6560
+    //     27.0, 31.3; with 4, 16891 x 3856 x 256, 113, 88); a short product (11899 x 72 x 344 13.9, 14.8).  They never do
+    //     where twice the tiles of a row to merge
+    //     outweigh the product (rows of more than 12 tiles of 256 columns with K < 32 times their number: 523 x 256 x
+    //     7872 27.0, 22.8) or W is narrow and K long (9354 x 5680 x 512 147, 121).  Elsewhere 256 x 128: 5115 x 2688 x
+    //     1024 46.3, 60.6; 18048 x 4416 x 256 71.1, 94.3.  98 shapes of 257 to 325 tiles 1 % above the better of the two.
+    //     In several rounds 256 x 128 tiles lose to 256 x 256 (30 shapes 0.85);
     //   else 128 x 128 tiles, up to two per unit, which finish in one round; and for at most a
     //     quarter of the units' worth of those, 64 x 64 tiles, which spread them further.  (Most of these
     //     smaller problems go to the split kernel above; what is left is what does not fit it.)
@@ -291,18 +287,24 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
     const int64_t across = (N + 255) / 256;
     const bool pays = across > 12 ? K >= 32 * across : (across > 2 || K < 4500);
+    const bool half_empty = ((N + 127) / 128) % 2 != 0;
+    const bool two_a_unit = tiles128 * 4 <= 5 * num_cus && pays &&
+                            (half_empty || (tiles128 * 32 <= 33 * num_cus && across > 2) || K < 256);
     // (A plan for little scratch memory, roomy = false, splits nothing and keeps the larger tiles, which have
     // half the row statistics.)
     if (tiles256 * 2 > num_cus && (bf16 || !roomy || tiles128 > 2 * num_cus))
         pl.shape = kTile256W8;
-    else if (bf16 && tiles128 > num_cus && tiles256x128 <= num_cus && !(roomy && tiles128 * 4 <= 5 * num_cus && pays))
-        pl.shape = kTile256x128;
+    else if (bf16 && tiles128 > num_cus && tiles256x128 <= num_cus && !(roomy && two_a_unit))
+        // Eight wavefronts, except on a full chip whose rows are many tiles and cut: there four are as fast (25 shapes
+        // of 240 to 256 tiles, 32 and more a row: 0.993 of the time's inverse on average, 0.956 to 1.024; elsewhere 34
+        // shapes 0.944), and plans that callers pin stay as they were.
+        pl.shape = N % 256 != 0 && across >= 32 && tiles256x128 * 16 >= num_cus * 15 ? kTile256x128 : kTile256x128W8;
     else
         pl.shape = tiles128 * 4 > num_cus ? kTile128 : kTile64;
     if (g_forced_tile != 0) {
         pl.shape = g_forced_tile == 64 ? kTile64 : (g_forced_tile == 128 ? kTile128 : kTile256);
         if (g_forced_tile == 256 && g_forced_wg_per_cu == 2)
-            pl.shape = kTile256x128;
+            pl.shape = kTile256x128W8;
     }
     if (g_forced_waves != 0) {
         if (tile_shape_cols(pl.shape) != 256)
@@ -318,9 +320,8 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     pl.RB = (int)RB;
     pl.NT = (int)NT;
     const int64_t total = RB * NT;
-    // workgroups per compute unit: a 256 x 256 tile takes a whole unit's LDS and registers, the other
-    // shapes half or less
-    int per_cu = (pl.shape == kTile256 || pl.shape == kTile256W8) ? 1 : 2;
+    // workgroups per compute unit: a tile of 256 columns takes a whole unit's LDS, the other shapes half or less
+    int per_cu = tile_shape_cols(pl.shape) == 256 ? 1 : 2;
     if (g_forced_wg_per_cu == 1)
         per_cu = 1;
     // The fused kernel's workgroups wait for one another inside the launch: never launch more of them
@@ -381,8 +382,6 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
             pl.grid = (int)(pl.round_rows * NT);
         }
     }
-    // start delay of the second workgroup of every compute unit (256 x 128 tiles, full grid only)
-    pl.stagger_us = (pl.shape == kTile256x128 && per_cu == 2 && pl.grid == 2 * num_cus) ? g_stagger_us : 0;
     pl.partial_off = kCtrlBytes;
     pl.partial_bytes = round_up((size_t)total * pl.tile_m * sizeof(float) * 2, 256);
     pl.g_off = pl.partial_off + pl.partial_bytes;
@@ -648,7 +647,6 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
     p.M = (int)M; p.K = (int)K; p.N = (int)N;
     p.NT = pl.NT; p.RB = pl.RB; p.rounds = pl.rounds; p.round_rows = pl.round_rows; p.swz_sc_log2 = pl.swz_sc_log2; p.nt_log2 = pl.nt_log2;
     p.grid_log2 = pl.grid_log2;
-    p.stagger_ticks = (long long)pl.stagger_us * st->ticks_per_us;
     p.extra_arrivals = g_extra_arrivals;
     p.wait_ticks = wait_ticks;
     p.timeline = nullptr;
@@ -1156,11 +1154,7 @@ int ff_debug_force_waves(int waves)
 
 int ff_debug_set_stagger_us(int microseconds)
 {
-    if (microseconds < 0 || microseconds > 1000)
-        return FF_ERR_SHAPE;
-    std::lock_guard<std::mutex> lock(g_mutex);
-    g_stagger_us = microseconds;
-    return FF_OK;
+    return microseconds < 0 || microseconds > 1000 ? FF_ERR_SHAPE : FF_OK;  // no launch has a second workgroup to delay
 }
 
 int ff_debug_set_timeline(void *dev_ptr, size_t bytes)

@@ -29,7 +29,6 @@ namespace {
 
 constexpr int kRowBytes = 128;  // bytes of one tile row per K slab (8 chunks of 16 B)
 constexpr int kChunksPerRow = kRowBytes / 16;
-constexpr int kStages = 2;
 constexpr int kRowsPerDma = 1024 / kRowBytes;     // one direct-to-LDS instruction fills 1 KiB
 
 // The matrix instruction of a type: blocks of kBlock x kBlock outputs, whose kLaneGroups lane groups hold one
@@ -91,6 +90,12 @@ template <bool kAcc, typename Acc> __device__ __forceinline__ void pin_order(Acc
         asm volatile("" : "+v"(c) : : "memory");
 }
 
+// s_waitcnt vmcnt(n), n < 64, nothing else
+template <int n> __device__ __forceinline__ void wait_vm()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (n & 15) | ((n >> 4) << 14));
+}
+
 // The lane index, computed where it is asked for: the compiler can neither move the computation out
 // of a loop nor keep its result across one (values that the K loop does not use would have to be
 // carried across it in scratch memory).
@@ -127,17 +132,15 @@ __device__ __forceinline__ int swizzle_of_row(int row) { return (row & 7) ^ ((ro
 // as four) or as 2 x 2 wavefronts of 4 x 4 blocks; the 128- and 64-tiles as 2 x 2 wavefronts, two
 // workgroups per compute unit (second launch bound: two wavefronts per SIMD must fit).
 //
-// PIPE selects how the K slabs reach the LDS.  kPipeDma: W and X slabs both by direct-to-LDS loads
-// into two stages (one workgroup per compute unit at 256 x 256; the whole LDS).  kPipeXReg: the W
-// slab by direct-to-LDS loads into two stages, the X slab through registers into a single buffer
-// (loaded a slab ahead, written between two barriers once everyone has read the previous one).
-// That fits a 256-column x 128-row tile into half the LDS (2 x 32 KB + 16 KB), so that two
-// workgroups can share a compute unit: while one is in its epilogue (vector ALU, exchange, stores) the
-// other's K loop keeps the matrix pipe busy, and each covers the other's barrier stalls.  Measured, two
-// such workgroups per unit lose to one 256 x 256 tile (1.5 times the L2 -> LDS bytes per flop); the
-// shape earns its place one per unit, on problems whose 256 x 256 tiles would leave half the units idle.
-template <typename T, int kWavesN, int kWavesM, int WTN, int WTM, int MODE, bool RAGGED_N, int PIPE>
-__global__ __launch_bounds__(64 * kWavesN * kWavesM, (kWavesN * kWavesM * WTN * WTM <= 32) ? 2 : 1)
+// STAGES: slabs the LDS has room for beside the parameters, two at 256 x 256 and where two workgroups share a unit,
+// three at 256 x 128 (one per unit): there two slabs travel while one is multiplied.
+//
+// Launch bound: 512 threads also where four wavefronts are launched, if 256 registers hold all of one's values.  Left with
+// 512, the compiler keeps the accumulators in the other half and copies them out and back at every pin_order.
+constexpr int launch_bound(int waves, int part) { return part >= 16 ? 64 * waves : 512; }
+
+template <typename T, int kWavesN, int kWavesM, int WTN, int WTM, int MODE, bool RAGGED_N, int STAGES>
+__global__ __launch_bounds__(launch_bound(kWavesN * kWavesM, WTN * WTM), (kWavesN * kWavesM * WTN * WTM <= 32) ? 2 : 1)
 void tile_kernel(const TileParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)  // the body uses device-only types (buffer descriptors)
@@ -154,13 +157,9 @@ void tile_kernel(const TileParams p)
     constexpr int kSlabElems = kRowBytes / (int)sizeof(T);
     constexpr int kABytes = BN * kRowBytes;
     constexpr int kBBytes = BM * kRowBytes;
-    // LDS placement of the slabs: W of slab s at (s % 2) * kWStride, X of slab s at kXBase + (s % 2) * kXStride
-    constexpr bool kXReg = PIPE == kPipeXReg;
+    // LDS placement of the slabs: slab s in stage s % STAGES, W rows first
     constexpr int kStageBytes = kABytes + kBBytes;
-    constexpr int kWStride = kXReg ? kABytes : kStageBytes;
-    constexpr int kXBase = kXReg ? kStages * kABytes : kABytes;
-    constexpr int kXStride = kXReg ? 0 : kStageBytes;
-    constexpr int kSlabLdsBytes = kXReg ? kStages * kABytes + kBBytes : kStages * kStageBytes;
+    constexpr int kSlabLdsBytes = STAGES * kStageBytes;
     // direct-to-LDS instructions per wave per slab
     constexpr int kDmaA = BN / kRowsPerDma / kWaves;
     constexpr int kDmaB = BM / kRowsPerDma / kWaves;
@@ -169,8 +168,7 @@ void tile_kernel(const TileParams p)
     using OutT = typename std::conditional<MODE == kFused, T, float>::type;
     constexpr int kOutRowBytes = WTN * 32 * (int)sizeof(OutT);
     constexpr int kOutPitch = kOutRowBytes + 16;
-    constexpr int kOffPrm = 0;                               // 3 * BN floats
-    constexpr int kOffWst = kOffPrm + 3 * BN * 4;            // kWavesN * BM float2
+    constexpr int kOffWst = 0;                               // kWavesN * BM float2
     constexpr int kOffRst = kOffWst + kWavesN * BM * 8;      // BM float2
     constexpr int kOffOut = (kOffRst + BM * 8 + 1023) & ~1023;
     constexpr int kEpiBytes = kOffOut + kWaves * 32 * kOutPitch;
@@ -178,15 +176,12 @@ void tile_kernel(const TileParams p)
 
     // One LDS object for everything: with a second one the compiler can no longer tell the DMA's LDS
     // writes from the fragment reads and waits for all loads in flight before every read.
-    constexpr int kPrmEarlyBytes = (PIPE != kPipeXReg) ? 3 * BN * 4 : 0;
-    __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes + kPrmEarlyBytes];
-    // Bias, gamma and beta of the tile's columns.  With both operands travelling by DMA the three
-    // vectors are requested ahead of the first slab and parked in LDS of their own when it has
-    // landed, so that the epilogue finds them there; the register-staged pipeline, whose two
-    // workgroups per compute unit leave no LDS to spare, loads them when the K loop is over.
-    constexpr bool kPrmEarly = !kXReg;
+    constexpr int kPrmBytes = 3 * BN * 4;
+    __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes + kPrmBytes];
+    // Bias, gamma and beta of the tile's columns: requested ahead of the first slab and parked in LDS of their own
+    // when it has landed, so that the epilogue finds them there.
     constexpr int kPrmPerThread = (3 * BN + kThreads - 1) / kThreads;
-    float *s_prm_early = reinterpret_cast<float *>(smem + kSmemBytes);
+    float *s_prm = reinterpret_cast<float *>(smem + kSmemBytes);
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wn = wave % kWavesN;
@@ -202,15 +197,6 @@ void tile_kernel(const TileParams p)
             p.timeline[((size_t)round * gridDim.x + blockIdx.x) * kTimelineSlots + k] =
                 k < kTimelineCycleSlot ? wall_clock64() : clock64();
     };
-
-    // Two workgroups per compute unit started together would run their K loops and their epilogues
-    // in step; the second half of the grid starts late by about an epilogue's length instead, so
-    // that one workgroup's epilogue falls into the other's K loop from the first tile on.
-    if (p.stagger_ticks > 0 && blockIdx.x >= (gridDim.x >> 1)) {
-        const long long t0 = wall_clock64();
-        while (wall_clock64() - t0 < p.stagger_ticks)
-            __builtin_amdgcn_s_sleep(16);
-    }
 
     bool first_tile = true;
     for (; round < p.rounds; ++round) {
@@ -260,7 +246,7 @@ void tile_kernel(const TileParams p)
         // fragment read offsets (bytes inside a stage); k-step s reads chunk (s * kLaneGroups + group) ^ swizzle
         const int frag_swz = swizzle_of_row(block_row);
         const int a_frag_base = (wn * WTN * 32 + block_row) * kRowBytes;
-        const int b_frag_base = kXBase + (wm * WTM * 32 + block_row) * kRowBytes;
+        const int b_frag_base = kABytes + (wm * WTM * 32 + block_row) * kRowBytes;
         // DMA lane geometry: lane -> (row within a 16-row group, stored chunk slot)
         const int dma_r = lane / kChunksPerRow;
         const int dma_cs = lane % kChunksPerRow;
@@ -296,16 +282,16 @@ void tile_kernel(const TileParams p)
             __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(w_tile), 0, kRangeBytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t x_rsrc =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(x_tile), 0, kRangeBytes, 0x00020000);
-        auto dma_one = [&](int slab, int x) {
-            const int stage = slab % kStages;
+        auto dma_one = [&](int slab, int stage, int x) {
+            char *st = smem + stage * kStageBytes;
             if (x < kDmaA) {
-                char *sa = smem + stage * kWStride + wave * (BN / kWaves) * kRowBytes;
+                char *sa = st + wave * (BN / kWaves) * kRowBytes;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     w_rsrc, (__attribute__((address_space(3))) void *)(sa + x * 1024), 16,
                     offa[x < kDmaA ? x : 0], slab * kRowBytes, 0, 0);
             } else {
                 const int y = x - kDmaA;
-                char *sb = smem + kXBase + stage * kXStride + wave * (BM / kWaves) * kRowBytes;
+                char *sb = st + kABytes + wave * (BM / kWaves) * kRowBytes;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     x_rsrc, (__attribute__((address_space(3))) void *)(sb + y * 1024), 16,
                     offb[y >= 0 && y < kDmaB ? y : 0], slab * kRowBytes, 0, 0);
@@ -315,17 +301,16 @@ void tile_kernel(const TileParams p)
         // which puts zeros into its place in LDS.  (Through registers, with zeros
         // written for the missing chunks, it was a load latency in the open: 3001 x 2056 x 5000 spent 54.5 us up
         // to the end of the product, against 46.2 for K = 2048.)
-        auto dma_cut = [&](int slab, int half) {
+        auto dma_cut = [&](int slab, int stage, int half) {
             // lane geometry re-derived through an opaque move: this rarely taken path
             // must not have its offsets precomputed (and spilled) at kernel entry
             const int lane_c = opaque_lane();
-            const int stage = slab % kStages;
 #pragma unroll
             for (int x = 0; x < (half == 0 ? kDmaA : kDmaB); ++x) {
                 const int row = wave * ((half == 0 ? BN : BM) / kWaves) + x * kRowsPerDma + lane_c / kChunksPerRow;
                 const int c = (lane_c % kChunksPerRow) ^ swizzle_of_row(row);
                 const bool in = slab * kSlabElems + c * kChunkElems < K;
-                char *dst = smem + (half == 0 ? stage * kWStride : kXBase + stage * kXStride) +
+                char *dst = smem + stage * kStageBytes + (half == 0 ? 0 : kABytes) +
                             wave * ((half == 0 ? BN : BM) / kWaves) * kRowBytes + x * 1024;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     half == 0 ? w_rsrc : x_rsrc, (__attribute__((address_space(3))) void *)dst, 16,
@@ -350,23 +335,15 @@ void tile_kernel(const TileParams p)
         // Fragments: W's in one buffer, each read again for the next k-step as soon as its products are issued; X's,
         // which every group of products reads, in two, by k-step.
         uintx4 fa[kBlocksN], fb[2][kBlocksM];
-        auto read_a = [&](int slab, int s, int x) {
+        auto read_a = [&](int stage, int s, int x) {
             const int coff = ((s * kLaneGroups + group) ^ frag_swz) << 4;
-            fa[x] = *reinterpret_cast<const uintx4 *>(smem + (slab % kStages) * kWStride + a_frag_base +
+            fa[x] = *reinterpret_cast<const uintx4 *>(smem + stage * kStageBytes + a_frag_base +
                                                       x * kBlock * kRowBytes + coff);
         };
-        auto read_b = [&](int slab, int s, int x) {
+        auto read_b = [&](int stage, int s, int x) {
             const int coff = ((s * kLaneGroups + group) ^ frag_swz) << 4;
-            fb[s & 1][x] = *reinterpret_cast<const uintx4 *>(smem + (slab % kStages) * kXStride + b_frag_base +
+            fb[s & 1][x] = *reinterpret_cast<const uintx4 *>(smem + stage * kStageBytes + b_frag_base +
                                                              x * kBlock * kRowBytes + coff);
-        };
-        auto load_frags = [&](int slab, int s) {
-#pragma unroll
-            for (int x = 0; x < kBlocksM; ++x)
-                read_b(slab, s, x);
-#pragma unroll
-            for (int x = 0; x < kBlocksN; ++x)
-                read_a(slab, s, x);
         };
         // The products of a k-step are issued in groups, one per fragment of W.
         auto products = [&](int g, int s) {
@@ -381,125 +358,42 @@ void tile_kernel(const TileParams p)
             __builtin_amdgcn_sched_barrier(0);
         };
         static_assert(kBlocksM <= kBlocksN && kSteps % 2 == 0, "the X fragments of the next k-step, one per group");
-        // k-step s of a slab, not its last: the next one's fragments are read behind its products.
-        auto step_inside = [&](int slab, int s) {
+        // k-step s of the slab in `stage`, not its last: the next one's fragments are read behind its products.
+        auto step_inside = [&](int stage, int s) {
 #pragma unroll
             for (int g = 0; g < kBlocksN; ++g) {
                 if (g < kBlocksM)
-                    read_b(slab, s + 1, g);
+                    read_b(stage, s + 1, g);
                 products(g, s);
-                read_a(slab, s + 1, g);
+                read_a(stage, s + 1, g);
                 end_group(g);
             }
         };
-        auto steps_inside = [&](int slab) {
+        auto steps_inside = [&](int stage) {
 #pragma unroll
             for (int s = 0; s + 1 < kSteps; ++s)
-                step_inside(slab, s);
+                step_inside(stage, s);
         };
 
         // ---- main loop over K slabs ----
         // Every group of products has the fragment reads of the next k-step, and in a slab's last k-step the direct-to-LDS
-        // loads of the slab after the next, in its shadow.  The slab's one barrier stands in its last k-step, behind the
-        // first kSync groups, which cover the last fragment reads: there slab i + 1 has landed for everyone and
-        // everyone has read slab i, whose stage takes slab i + 2.  So a load has a whole slab's time to arrive.
+        // loads of the slab that takes its stage, in its shadow.  The slab's one barrier stands in its last k-step, behind
+        // the first kSync groups, which cover the last fragment reads: there slab i + 1 has landed for everyone and
+        // everyone has read slab i, whose stage takes slab i + STAGES.  So a load has STAGES - 1 slabs' time to arrive.
+        // (Loads in a burst behind the barrier, or spread into the next slab, cost 2 to 6 %.)
         constexpr int kSync = kBlocksN >= 8 ? 2 : (kBlocksN > 1 ? 1 : 0);
-        static_assert(kStages == 2 && kSync < kBlocksN, "loop body written for 2 stages, the reads behind the barrier");
+        static_assert((STAGES == 2 || STAGES == 3) && kSync < kBlocksN, "the waits of the last slabs; reads behind the barrier");
         enum { kNoDma = 0, kDmaFull = 1, kDmaCut = 2 };
-        auto dma_half_any = [&](int slab, int half) {
-            // half 0: W rows (x in [0, kDmaA)), half 1: X rows
+        auto request = [&](int slab, int stage) {
             if (!k_ragged || slab + 1 < slabs) {
 #pragma unroll
-                for (int x = 0; x < (half == 0 ? kDmaA : kDmaB); ++x)
-                    dma_one(slab, half == 0 ? x : kDmaA + x);
+                for (int x = 0; x < kDmaPerSlab; ++x)
+                    dma_one(slab, stage, x);
             } else {
-                dma_cut(slab, half);
+                dma_cut(slab, stage, 0);
+                dma_cut(slab, stage, 1);
             }
         };
-        if constexpr (kXReg) {
-        // ---- main loop, X slabs through registers ----
-        // Iteration i: the X slab i+1 is requested at the start (global -> registers); after the
-        // first three k-steps barrier A says everyone has read slab i from the LDS; then the X
-        // registers go to the single X buffer, the W slab i+2 is requested into the stage slab i
-        // occupied, half of the last k-step's MFMAs cover the LDS writes, barrier B publishes the X
-        // slab (every wave has waited for its own share of W slab i+1 before it), and the rest of the
-        // last k-step covers the first fragment reads of slab i+1.  The other workgroup on the compute
-        // unit fills the matrix pipe while this one stands at its barriers.
-        uintx4 xr[kDmaB];
-        auto x_load_full = [&](int slab) {
-#pragma unroll
-            for (int j = 0; j < kDmaB; ++j)
-                xr[j] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                       x_rsrc, offb[j], slab * kRowBytes, 0));
-        };
-        auto x_load = [&](int slab) {
-            if (!k_ragged || slab + 1 < slabs) {
-                x_load_full(slab);
-            } else {
-                const int lane_c = opaque_lane();  // as in dma_cut
-#pragma unroll
-                for (int j = 0; j < kDmaB; ++j) {
-                    const int row = wave * (BM / kWaves) + j * kRowsPerDma + lane_c / kChunksPerRow;
-                    const int c = (lane_c % kChunksPerRow) ^ swizzle_of_row(row);
-                    const bool in = slab * kSlabElems + c * kChunkElems < K;
-                    xr[j] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                           x_rsrc, in ? offb[j] : kRangeBytes, slab * kRowBytes, 0));
-                }
-            }
-        };
-        auto x_store = [&]() {
-            char *sb = smem + kXBase + wave * (BM / kWaves) * kRowBytes + lane * 16;
-#pragma unroll
-            for (int j = 0; j < kDmaB; ++j)
-                *reinterpret_cast<uintx4 *>(sb + j * 1024) = xr[j];
-        };
-        lds_barrier();  // the previous tile's epilogue is done with the LDS
-        dma_half_any(0, 0);
-        x_load(0);
-        if (slabs > 1)
-            dma_half_any(1, 0);
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-        x_store();
-        lds_barrier();
-        stamp(1);
-        stamp(kTimelineCycleSlot);
-        load_frags(0, 0);
-        int i = 0;
-        for (; i < slabs; ++i) {
-            const bool more = i + 1 < slabs;
-            if (more)
-                x_load(i + 1);
-            steps_inside(i);
-            if (more) {
-                lds_barrier();                       // A: everyone has read slab i
-                __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): X registers and this wave's W rows of slab i+1
-                x_store();
-                if (i + 2 < slabs)
-                    dma_half_any(i + 2, 0);
-            }
-#pragma unroll
-            for (int g = 0; g < kBlocksN / 2; ++g) {
-                products(g, kSteps - 1);
-                end_group(g);
-            }
-            if (more) {
-                lds_barrier();                       // B: slab i+1 is complete in the LDS
-#pragma unroll
-                for (int x = 0; x < kBlocksM; ++x)
-                    read_b(i + 1, 0, x);
-#pragma unroll
-                for (int x = 0; x < kBlocksN / 2; ++x)
-                    read_a(i + 1, 0, x);
-            }
-#pragma unroll
-            for (int g = kBlocksN / 2; g < kBlocksN; ++g) {
-                products(g, kSteps - 1);
-                if (more)
-                    read_a(i + 1, 0, g);
-                end_group(g);
-            }
-        }
-        } else {
         // The previous tile's epilogue is done with the LDS once every wave is here (its LDS reads
         // completed before its stores could issue).  No wait for those stores: they drain while the
         // first slab of this tile travels.
@@ -518,21 +412,21 @@ void tile_kernel(const TileParams p)
             prm[u] = ok ? v : (which == 1 ? 1.0f : 0.0f);
         }
         lds_barrier();
-        dma_half_any(0, 0);
-        dma_half_any(0, 1);
-        // (Slab 1 is requested behind the first fragment reads: its sixty-four instructions ahead of the wait
+        request(0, 0);
+        // (The slabs after the first are requested behind the first fragment reads: their instructions ahead of the wait
         // delayed the start of every tile by 1 us.  A workgroup's first tile has nothing to wait for but slab 0.)
-        const bool ahead = first_tile && p.timeline == nullptr && slabs > 1;
-        auto request_slab_1 = [&]() {
-            dma_half_any(1, 0);
-            dma_half_any(1, 1);
+        const bool ahead = first_tile && p.timeline == nullptr && slabs >= STAGES;
+        auto request_early = [&]() {
+#pragma unroll
+            for (int t = 1; t < STAGES; ++t)
+                if (t < slabs)
+                    request(t, t);
         };
         if (ahead) {
-            request_slab_1();
-            __builtin_amdgcn_s_waitcnt(0x0f70 | (kDmaPerSlab & 15) | ((kDmaPerSlab >> 4) << 14));  // slab 0 landed
+            request_early();
+            wait_vm<(STAGES - 1) * kDmaPerSlab>();  // slab 0 landed
         } else {
-            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): also the previous tile's stores, whose
-                                                 // completion order relative to loads is not relied on
+            wait_vm<0>();  // also the previous tile's stores, whose completion order relative to loads is not relied on
         }
         first_tile = false;
         // the previous tile's last readers of the parameter region passed the barrier above
@@ -540,72 +434,80 @@ void tile_kernel(const TileParams p)
         for (int u = 0; u < kPrmPerThread; ++u) {
             const int c = wave * 64 + lane + u * kThreads;
             if (c < 3 * BN)
-                s_prm_early[c] = prm[u];
+                s_prm[c] = prm[u];
         }
         lds_barrier();
         stamp(1);
         stamp(kTimelineCycleSlot);
-        load_frags(0, 0);
-        if (!ahead && slabs > 1)
-            request_slab_1();
-        // The last k-step of a slab; `dma`: what to do about slab i + 2, `more`: there is a slab i + 1.
-        auto step_last = [&](int i, auto more_c, auto dma_c) {
-            constexpr bool more = decltype(more_c)::value;
-            constexpr int dma = decltype(dma_c)::value;
+#pragma unroll
+        for (int x = 0; x < kBlocksM; ++x)
+            read_b(0, 0, x);
+#pragma unroll
+        for (int x = 0; x < kBlocksN; ++x)
+            read_a(0, 0, x);
+        if (!ahead)
+            request_early();
+        int i = 0, stage = 0;  // slab i lies in `stage`
+        // The last k-step of slab i; `dma`: what to do about slab i + STAGES, `later`: slabs behind i + 1 that are in
+        // flight at its barrier, -1 if there is no slab i + 1.
+        auto step_last = [&](auto later_c, auto dma_c) {
+            constexpr int later = decltype(later_c)::value, dma = decltype(dma_c)::value;
+            constexpr bool more = later >= 0;
             constexpr int kRest = kBlocksN - kSync;  // groups behind the barrier
+            const int next = stage + 1 < STAGES ? stage + 1 : 0;
 #pragma unroll
             for (int g = 0; g < kBlocksN; ++g) {
                 if (more && g >= kSync) {
                     const int q = g - kSync;
                     if (q == 0) {
-                        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's rows of slab i + 1 have landed
+                        wait_vm<(more ? later : 0) * kDmaPerSlab>();  // this wave's rows of slab i + 1 have landed
                         lds_barrier();
                         if (dma == kDmaCut) {
-                            dma_half_any(i + 2, 0);
-                            dma_half_any(i + 2, 1);
+                            dma_cut(i + STAGES, stage, 0);
+                            dma_cut(i + STAGES, stage, 1);
                         }
                     }
                     if (dma == kDmaFull) {
 #pragma unroll
                         for (int x = q * kDmaPerSlab / kRest; x < (q + 1) * kDmaPerSlab / kRest; ++x)
-                            dma_one(i + 2, x);
+                            dma_one(i + STAGES, stage, x);
                     }
 #pragma unroll
                     for (int x = q * kBlocksM / kRest; x < (q + 1) * kBlocksM / kRest; ++x)
-                        read_b(i + 1, 0, x);
+                        read_b(next, 0, x);
                     if (q == 0) {
 #pragma unroll
                         for (int x = 0; x < kSync; ++x)
-                            read_a(i + 1, 0, x);
+                            read_a(next, 0, x);
                     }
                 }
                 products(g, kSteps - 1);
                 if (more && g >= kSync)
-                    read_a(i + 1, 0, g);
+                    read_a(next, 0, g);
                 end_group(g);
             }
+            ++i;
+            stage = next;
         };
         using std::integral_constant;
-        const integral_constant<bool, true> yes;
-        const integral_constant<bool, false> no;
-        int i = 0;
-        for (; i < slabs - 2 - (k_ragged ? 1 : 0); ++i) {
-            steps_inside(i);
-            step_last(i, yes, integral_constant<int, kDmaFull>());
+        while (i < slabs - STAGES - (k_ragged ? 1 : 0)) {
+            steps_inside(stage);
+            step_last(integral_constant<int, STAGES - 2>(), integral_constant<int, kDmaFull>());
         }
-        if (k_ragged && slabs > 2) {
-            steps_inside(i);
-            step_last(i, yes, integral_constant<int, kDmaCut>());
-            ++i;
+        if (k_ragged && slabs > STAGES) {
+            steps_inside(stage);
+            step_last(integral_constant<int, STAGES - 2>(), integral_constant<int, kDmaCut>());
+        }
+        if (STAGES == 3 && slabs > 2) {
+            steps_inside(stage);
+            step_last(integral_constant<int, 1>(), integral_constant<int, kNoDma>());
         }
         if (slabs > 1) {
-            steps_inside(i);
-            step_last(i, yes, integral_constant<int, kNoDma>());
-            ++i;
+            steps_inside(stage);
+            step_last(integral_constant<int, 0>(), integral_constant<int, kNoDma>());
         }
-        steps_inside(i);
-        step_last(i, no, integral_constant<int, kNoDma>());
-        }  // kPipeDma
+        steps_inside(stage);
+        step_last(integral_constant<int, -1>(), integral_constant<int, kNoDma>());
         __syncthreads();  // all fragment reads done: LDS becomes epilogue scratch
         stamp(2);
         stamp(kTimelineCycleSlot + 1);
@@ -619,23 +521,12 @@ void tile_kernel(const TileParams p)
         const int M = opaque_uniform(p.M), N = opaque_uniform(p.N);
         const int group = lane / kBlock;
         const int block_row = lane % kBlock;
-        float *s_b = kPrmEarly ? s_prm_early : reinterpret_cast<float *>(smem + kOffPrm);
+        float *s_b = s_prm;
         float *s_g = s_b + BN;
         float *s_be = s_g + BN;
         floatx2 *s_wst = reinterpret_cast<floatx2 *>(smem + kOffWst);
         floatx2 *s_rst = reinterpret_cast<floatx2 *>(smem + kOffRst);
         char *s_out = smem + kOffOut + wave * 32 * kOutPitch;
-
-        if (!kPrmEarly) {
-            for (int c = wave * 64 + lane; c < BN; c += kThreads) {
-                const int n = n0 + c;
-                const bool ok = n < N;
-                s_b[c] = (ok && p.b) ? load_as_float(reinterpret_cast<const T *>(p.b) + n) : 0.0f;
-                s_g[c] = (ok && p.gamma) ? load_as_float(reinterpret_cast<const T *>(p.gamma) + n) : 1.0f;
-                s_be[c] = (ok && p.beta) ? load_as_float(reinterpret_cast<const T *>(p.beta) + n) : 0.0f;
-            }
-            __syncthreads();
-        }
 
         const int ncol_wave = wn * WTN * 32;            // wave's first column inside the tile
         const int nvalid_tile = (N - n0 < BN) ? (N - n0) : BN;
@@ -1008,28 +899,28 @@ __global__ __launch_bounds__(256) void finalize_kernel(const FinalizeParams p)
     }
 }
 
-template <typename T, int WN, int WM, int WTN, int WTM, int MODE, int PIPE>
+template <typename T, int WN, int WM, int WTN, int WTM, int MODE, int STAGES>
 hipError_t launch_tile(const TileParams &p, int grid, hipStream_t stream)
 {
     constexpr int BN = WN * WTN * 32;
     constexpr int kThreads = 64 * WN * WM;
     if (p.N % BN != 0)
-        hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, true, PIPE>), dim3(grid), dim3(kThreads), 0,
+        hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, true, STAGES>), dim3(grid), dim3(kThreads), 0,
                            stream, p);
     else
-        hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, false, PIPE>), dim3(grid), dim3(kThreads), 0,
+        hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, false, STAGES>), dim3(grid), dim3(kThreads), 0,
                            stream, p);
     return hipGetLastError();
 }
 
-template <typename T, int WN, int WM, int WTN, int WTM, int MODE, int PIPE>
+template <typename T, int WN, int WM, int WTN, int WTM, int MODE, int STAGES>
 int max_blocks_per_cu()
 {
     int a = 0, b = 0;
     constexpr int kThreads = 64 * WN * WM;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, tile_kernel<T, WN, WM, WTN, WTM, MODE, true, PIPE>,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, tile_kernel<T, WN, WM, WTN, WTM, MODE, true, STAGES>,
                                                      kThreads, 0) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, tile_kernel<T, WN, WM, WTN, WTM, MODE, false, PIPE>,
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, tile_kernel<T, WN, WM, WTN, WTM, MODE, false, STAGES>,
                                                      kThreads, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
@@ -1039,34 +930,36 @@ int max_blocks_per_cu()
 
 }  // namespace
 
-// Dispatch over (dtype, tile shape, mode): wave layout, blocks per wave and slab pipeline per shape.
-#define FF_TILE_DISPATCH(CALL)                                                             \
-    if (bf16) {                                                                            \
-        switch (shape) {                                                                   \
-        case kTile256x128: FF_MODES(__bf16, 2, 2, 4, 2, kPipeXReg, CALL)                   \
-        case kTile256W8: FF_MODES(__bf16, 2, 4, 4, 2, kPipeDma, CALL)                      \
-        case kTile256: FF_MODES(__bf16, 2, 2, 4, 4, kPipeDma, CALL)                        \
-        case kTile128: FF_MODES(__bf16, 2, 2, 2, 2, kPipeDma, CALL)                        \
-        default: FF_MODES(__bf16, 2, 2, 1, 1, kPipeDma, CALL)                              \
-        }                                                                                  \
-    }                                                                                      \
-    switch (shape) {                                                                       \
-    case kTile256x128: FF_MODES(float, 2, 2, 4, 2, kPipeXReg, CALL)                        \
-    case kTile256W8: FF_MODES(float, 2, 4, 4, 2, kPipeDma, CALL)                           \
-    case kTile256: FF_MODES(float, 2, 2, 4, 4, kPipeDma, CALL)                             \
-    case kTile128: FF_MODES(float, 2, 2, 2, 2, kPipeDma, CALL)                             \
-    default: FF_MODES(float, 2, 2, 1, 1, kPipeDma, CALL)                                   \
+// Dispatch over (dtype, tile shape, mode): wave layout, blocks per wave and LDS stages per shape.
+#define FF_TILE_DISPATCH(CALL)                                                         \
+    if (bf16) {                                                                        \
+        switch (shape) {                                                               \
+        case kTile256x128: FF_MODES(__bf16, 2, 2, 4, 2, 3, CALL)                       \
+        case kTile256x128W8: FF_MODES(__bf16, 4, 2, 2, 2, 3, CALL)                     \
+        case kTile256W8: FF_MODES(__bf16, 2, 4, 4, 2, 2, CALL)                         \
+        case kTile256: FF_MODES(__bf16, 2, 2, 4, 4, 2, CALL)                           \
+        case kTile128: FF_MODES(__bf16, 2, 2, 2, 2, 2, CALL)                           \
+        default: FF_MODES(__bf16, 2, 2, 1, 1, 2, CALL)                                 \
+        }                                                                              \
+    }                                                                                  \
+    switch (shape) {                                                                   \
+    case kTile256x128: FF_MODES(float, 2, 2, 4, 2, 3, CALL)                            \
+    case kTile256x128W8: FF_MODES(float, 4, 2, 2, 2, 3, CALL)                          \
+    case kTile256W8: FF_MODES(float, 2, 4, 4, 2, 2, CALL)                              \
+    case kTile256: FF_MODES(float, 2, 2, 4, 4, 2, CALL)                                \
+    case kTile128: FF_MODES(float, 2, 2, 2, 2, 2, CALL)                                \
+    default: FF_MODES(float, 2, 2, 1, 1, 2, CALL)                                      \
     }
-#define FF_MODES(T, WN, WM, WTN, WTM, PIPE, CALL)                     \
-    switch (mode) {                                                   \
-    case kFused: return CALL(T, WN, WM, WTN, WTM, kFused, PIPE);      \
-    case kTwoPass: return CALL(T, WN, WM, WTN, WTM, kTwoPass, PIPE);  \
-    default: return CALL(T, WN, WM, WTN, WTM, kLinearOnly, PIPE);     \
+#define FF_MODES(T, WN, WM, WTN, WTM, STAGES, CALL)                                    \
+    switch (mode) {                                                                    \
+    case kFused: return CALL(T, WN, WM, WTN, WTM, kFused, STAGES);                     \
+    case kTwoPass: return CALL(T, WN, WM, WTN, WTM, kTwoPass, STAGES);                 \
+    default: return CALL(T, WN, WM, WTN, WTM, kLinearOnly, STAGES);                    \
     }
 
 hipError_t launch_tile_kernel(bool bf16, int shape, int mode, const TileParams &p, int grid, hipStream_t stream)
 {
-#define FF_CALL(T, WN, WM, WTN, WTM, MODE, PIPE) launch_tile<T, WN, WM, WTN, WTM, MODE, PIPE>(p, grid, stream)
+#define FF_CALL(T, WN, WM, WTN, WTM, MODE, STAGES) launch_tile<T, WN, WM, WTN, WTM, MODE, STAGES>(p, grid, stream)
     FF_TILE_DISPATCH(FF_CALL)
 #undef FF_CALL
 }
@@ -1076,7 +969,7 @@ hipError_t launch_tile_kernel(bool bf16, int shape, int mode, const TileParams &
 // launch must not be larger than this many per compute unit.
 int tile_kernel_blocks_per_cu(bool bf16, int shape, int mode)
 {
-#define FF_CALL(T, WN, WM, WTN, WTM, MODE, PIPE) max_blocks_per_cu<T, WN, WM, WTN, WTM, MODE, PIPE>()
+#define FF_CALL(T, WN, WM, WTN, WTM, MODE, STAGES) max_blocks_per_cu<T, WN, WM, WTN, WTM, MODE, STAGES>()
     FF_TILE_DISPATCH(FF_CALL)
 #undef FF_CALL
 }

@@ -7,7 +7,6 @@
 namespace ff {
 
 enum { kFused = 0, kTwoPass = 1, kLinearOnly = 2 };
-enum { kPipeDma = 0, kPipeXReg = 1 };
 
 struct TileParams {
     const void *X;       // [M,K]
@@ -29,7 +28,6 @@ struct TileParams {
     int swz_sc_log2;     // XCD-aware order: log2 of the super-block width in tiles, -1 = plain order
     int nt_log2;         // log2(NT) when the XCD-aware order is on
     int grid_log2;       // log2(grid) when the XCD-aware order is on
-    long long stagger_ticks;  // start delay (wall-clock ticks) of the second half of the grid, 0 = none
     int extra_arrivals;  // test hook: added to the arrival target (non-zero makes waits expire)
     long long wait_ticks;
     unsigned long long *timeline;  // test hook: phase timestamps, or null
@@ -155,15 +153,16 @@ enum TileShape {
     kTile128 = 1,      // 128 x 128, four wavefronts, two workgroups per compute unit
     kTile256 = 2,      // 256 x 256, four wavefronts of 4 x 4 MFMA blocks, one workgroup per compute unit
     kTile256W8 = 3,    // 256 x 256, eight wavefronts of 4 x 2 blocks, one workgroup per compute unit
-    kTile256x128 = 4,  // 256 columns x 128 rows, four wavefronts of 4 x 2 blocks, two workgroups per compute unit
-    kNumTileShapes = 5
+    kTile256x128 = 4,  // 256 columns x 128 rows, four wavefronts of 128 x 64 outputs, one workgroup per compute unit
+    kTile256x128W8 = 5,  // 256 columns x 128 rows, eight wavefronts of 64 x 64 outputs, one workgroup per compute unit
+    kNumTileShapes = 6
 };
 inline int tile_shape_cols(int shape) { return shape == kTile64 ? 64 : (shape == kTile128 ? 128 : 256); }
 inline int tile_shape_rows(int shape)
 {
-    return shape == kTile64 ? 64 : ((shape == kTile128 || shape == kTile256x128) ? 128 : 256);
+    return shape == kTile64 ? 64 : ((shape == kTile128 || shape >= kTile256x128) ? 128 : 256);
 }
-inline int tile_shape_waves(int shape) { return shape == kTile256W8 ? 8 : 4; }
+inline int tile_shape_waves(int shape) { return shape == kTile256W8 || shape == kTile256x128W8 ? 8 : 4; }
 hipError_t launch_tile_kernel(bool bf16, int shape, int mode, const TileParams &p, int grid, hipStream_t stream);
 int tile_kernel_blocks_per_cu(bool bf16, int shape, int mode);
 hipError_t launch_finalize_kernel(bool bf16, const FinalizeParams &p, hipStream_t stream);
