@@ -138,7 +138,8 @@ int resident_split_blocks(DeviceState *st, bool bf16, int shape)
 //     + epilogue of a tile's share + exchange with the NT tiles of the rows
 //     + S > 1: meeting of the tile's S workgroups and one write and read of the partial products
 // Its constants were fitted to 3 600 runs (420 shapes drawn over M 1..8192, K 128..16384, N 128..16384, every
-// shape and S of each): the configuration picked is 1.4 (bf16) and 1.2 % (fp32) slower than the best on average.
+// shape and S of each); those of the epilogue of the larger tiles, which run eight wavefronts, in bf16 to 4 800 runs more
+// (400 shapes, M 33..2048): the configuration picked is 0.6 (bf16) and 0.8 % (fp32) slower than the best on average.
 // A unit draws at most 32 (26) bytes a nanosecond of W from HBM, so a few workgroups cannot stream at the chip's
 // rate: 4 x 9272 x 15096 bf16 takes 102 us in 118 workgroups of 128-column tiles, 66 in 236 of 64.
 // The busiest unit's share counts up to 16 rows, where the streamer is the other choice: of a grid of a few more
@@ -148,9 +149,9 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
 {
     // workgroups per compute unit that the LDS allows (what the runtime reports is asked as well)
     constexpr int kPerCu[kNumSplitShapes] = {3, 2, 2, 1, 1};
-    struct Cost { double start, slab, mfma, hbm, fabric, unit_hbm, exch, exch_s, sums, epi, epi128, tiles; };
-    constexpr Cost kBf16 = {4.2, 0.0, 0.128, 5.1e6, 51.6e3, 32e3, 2.4, 0.25, 2.8e6, 2.3, 1.9, 0.052};
-    constexpr Cost kF32 = {4.5, 0.134, 0.48, 5.1e6, 1e9, 26e3, 2.5, 0.2, 2.5e6, 3.0, 0.78, 0.056};
+    struct Cost { double start, slab, mfma, hbm, fabric, unit_hbm, exch, exch_s, sums, epi, epi_large, epi128, tiles; };
+    constexpr Cost kBf16 = {4.2, 0.0, 0.128, 5.1e6, 51.6e3, 32e3, 2.4, 0.25, 2.8e6, 2.3, 1.9, 0.9, 0.052};
+    constexpr Cost kF32 = {4.5, 0.134, 0.48, 5.1e6, 1e9, 26e3, 2.5, 0.2, 2.5e6, 3.0, 3.0, 0.78, 0.056};
     const Cost &c = bf16 ? kBf16 : kF32;
     const int size = bf16 ? 2 : 4;
     const int64_t slabs = (K * size + 127) / 128;
@@ -158,7 +159,9 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
     for (int shape = 0; shape < kNumSplitShapes; ++shape) {
         const int bm = split_shape_rows(shape), bn = split_shape_cols(shape);
         // tiles of few rows pay only where they spare the padding of larger ones
-        if (bm == 32 && M > 64)
+        // (128 x 32 in bf16 up to 32 rows: two row blocks take W through four wavefronts' loads twice.  51 x 5080 x 15984
+        // 65.1 us, 51.5 in tiles of 128 x 64; 63 x 14584 x 7936 88.3, 64.4)
+        if (bm == 32 && M > (bf16 && bn == 128 ? 32 : 64))
             continue;
         const int64_t RB = (M + bm - 1) / bm, NT = (N + bn - 1) / bn;
         if (RB * NT > (int64_t)num_cus * kPerCu[shape])
@@ -185,7 +188,7 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
             const double slab = c.slab + std::max(c.mfma * unit * wpc, (bn + bm) * 128 * wpc / c.fabric);
             const double busiest = M <= 16 && wpc > 1 ? wpc * per * bn * 128 / c.unit_hbm : 0.0;
             const double stream = std::max((double)N * K * size / std::min(c.hbm, std::min<double>((double)groups, num_cus) * c.unit_hbm), busiest);
-            double t = c.start + std::max(per * slab, stream) + c.epi * unit / S * wpc + c.tiles * (double)NT +
+            double t = c.start + std::max(per * slab, stream) + (shape >= kSplit128x64 ? c.epi_large : c.epi) * unit / S * wpc + c.tiles * (double)NT +
                        (shape == kSplit128 ? c.epi128 : 0.0);
             if (S > 1)
                 t += c.exch + c.exch_s * S + (double)groups * bm * bn * 4 / c.sums;
@@ -232,14 +235,16 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // W at the rate of the chip, the rounds of strips of a unit at the unit's rate, a round's epilogue, the meeting
     // of the strips (fitted to 440 shapes, K 64..16384, N 64..40000; it is off by 3 % on average).  Both sides were
     // timed on all of them: with this choice a call takes 0.891 of the streamer's time on average, 6 of them more
-    // than 1.03 (at most 1.06).  The streamer wins mostly with nearly whole rounds of strips (16 x 8192 x 8192: 37.2
+    // than 1.03 (at most 1.06).  (With cut slabs of the split kernel loaded like the others: 104 more shapes 1.2 % above the
+    // better of the two.)  The streamer wins mostly with nearly whole rounds of strips (16 x 8192 x 8192: 37.2
     // us, 39 split; 2 x 800 x 16280, 509 strips: 18.6, 20.6) and with few slabs to cut (9 x 840 x 7248: 13.7, 15.6), the
     // split kernel elsewhere (14 x 4608 x 12888, 403 strips: 40, 34; 2 x 16128 x 1904, 60: 41.7, 26).
     // Over 16 rows the streamer's registers no longer cover its loads (22 x 5888 x 6008: 34.6, 22; never faster).
     // (A forced variant, tile or wavefront count names the kernel it named before there was a split one.)
     const bool may_split = roomy && !linear_only && forced == FF_VARIANT_AUTO && g_forced_tile == 0 && g_forced_waves == 0;
     if (may_split && plan_split(M, K, N, bf16, num_cus, st, pl)) {
-        const double split_us = pl.split_us + (K % 64 != 0 ? 0.7 : 0.0);  // a slab cut by K goes through registers
+        // (short rows of W that end inside a line: 3 x 136 x 7720 stays with the streamer; from 512 on no such shape gains)
+        const double split_us = pl.split_us + (K % 64 != 0 && K < 512 ? 0.7 : 0.0);
         const double rounds = (double)((strips + num_cus - 1) / num_cus);
         const double streamer_us = 7.3 + (double)N * K * 2 / 20e6 + rounds * ((double)K * 64 / 31.6e3 + 1.36) + 0.0102 * (double)strips;
         if (!(variant == FF_VARIANT_SMALL_M && M <= 16 && streamer_us < 1.02 * split_us)) {

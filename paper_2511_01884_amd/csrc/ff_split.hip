@@ -12,7 +12,7 @@
 //      with the same rows exchange those and merge them in fixed order;
 //   3  normalise, convert, store.
 // Measured against the two-stage loop of the tile kernel (cold inputs, whole call): 96 x 8192 x 8192
-// bf16 104.7 -> 46.5 us (W at 2.9 TB/s), 512 x 8192 x 8192 bf16 125 -> 103, 64 x 4096 x 4096 fp32 98 -> 31,
+// bf16 104.7 -> 46.3 us (W at 2.9 TB/s), 512 x 8192 x 8192 bf16 125 -> 86, 64 x 4096 x 4096 fp32 98 -> 31,
 // 256 x 512 x 512 fp32 17.3 -> 11.5 (on the device); over 336 drawn shapes 1.36 (bf16) and 1.50 (fp32) times
 // as fast, none slower.  What is left at 96 x 8192 x 8192: 27 us of reading W at the rate of a large copy, and
 // launch, two meetings and the ramp of the stream.
@@ -25,7 +25,6 @@ namespace ff {
 
 namespace {
 
-constexpr int kThreads = 256;
 constexpr int kRowBytes = 128;   // bytes of one tile row per K slab (8 chunks of 16 B)
 constexpr int kRing = 4;         // LDS stages
 
@@ -90,16 +89,25 @@ template <> struct RawCols<__bf16> {
 };
 
 // kWN x kWM x kWK wavefronts: kWN x kWM blocks of WTN x WTM MFMA tiles, the k-steps of a slab dealt to kWK.
+//
+// Tiles of 128 columns and 64 or more rows, one workgroup a unit, run eight wavefronts, two at each block with half the
+// k-steps each: the loads of a slab are issued by twice as many, one wavefront of a SIMD reads fragments while the other
+// multiplies, and the epilogue has twice the threads.  With four: 512 x 8192 x 8192 bf16 97.5 us, now 85.5;
+// 384 x 2048 x 6000 34.9, 31.4; 200 x 16384 x 3000 50.5, 47.2; 512 x 4096 x 4096 fp32 146, 139.  (A ring of five stages
+// is no faster, so it is not the time of a load; the fragments of the next slab read ahead of its barrier neither in
+// bf16, 4 % faster in long fp32 products and 0.3 us slower in short ones.  Both point at the rate at which a unit's
+// loads reach its LDS: 57 bytes a nanosecond.)
 template <typename T, int kWN, int kWM, int kWK, int WTN, int WTM>
-__global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const SplitParams p)
+__global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN == 1 ? 2 : 1) void split_kernel(const SplitParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)  // the body uses device-only types (buffer descriptors)
-    static_assert(kWN * kWM * kWK == 4, "four wavefronts");
+    constexpr int kWaves = kWN * kWM * kWK, kThreads = 64 * kWaves;
+    static_assert(kWaves == 4 || kWaves == 8, "four or eight wavefronts");
     constexpr int BN = kWN * WTN * 32, BM = kWM * WTM * 32;
     constexpr int kChunkElems = 16 / (int)sizeof(T);
     constexpr int kSlabElems = kRowBytes / (int)sizeof(T);
     constexpr int kStageBytes = (BN + BM) * kRowBytes;
-    constexpr int kDmaA = BN / 32, kDmaB = BM / 32;  // direct-to-LDS instructions (8 rows each) per wave and slab
+    constexpr int kDmaA = BN / 8 / kWaves, kDmaB = BM / 8 / kWaves;  // direct-to-LDS instructions (8 rows each) per wave and slab
     constexpr int kDma = kDmaA + kDmaB;
     constexpr int kPitch = BN + 4;                   // floats of a row of the product in LDS
     constexpr int kProdBytes = kWK * BM * kPitch * 4;
@@ -152,8 +160,8 @@ __global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const
     const int per = (slabs + S - 1) / S;
     const int sl0 = s * per < slabs ? s * per : slabs;
     const int sl1 = sl0 + per < slabs ? sl0 + per : slabs;
-    const bool cut = sl1 > sl0 && sl1 * kSlabElems > K;  // the last one is cut by K: through registers
-    const int full = sl1 - sl0 - (cut ? 1 : 0);
+    const int total = sl1 - sl0;
+    const int full = total - (total > 0 && sl1 * kSlabElems > K ? 1 : 0);  // the rest: the slab that K cuts
 
     const size_t row_stride = (size_t)K * sizeof(T);
     const char *w_tile = (const char *)p.W + (size_t)n0 * row_stride + (size_t)sl0 * kRowBytes;
@@ -162,33 +170,47 @@ __global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const
     // lane -> (row of an instruction's eight, stored chunk slot); rows beyond the matrix read its last row
 #pragma unroll
     for (int j = 0; j < kDmaA; ++j) {
-        const int row = wave * (BN / 4) + j * 8 + (lane >> 3);
+        const int row = wave * (BN / kWaves) + j * 8 + (lane >> 3);
         const int rr = n0 + row < N ? row : N - 1 - n0;
         offa[j] = (unsigned)rr * (unsigned)row_stride + (((lane & 7) ^ swizzle_of_row(row)) << 4);
     }
 #pragma unroll
     for (int j = 0; j < kDmaB; ++j) {
-        const int row = wave * (BM / 4) + j * 8 + (lane >> 3);
+        const int row = wave * (BM / kWaves) + j * 8 + (lane >> 3);
         const int rr = m0 + row < M ? row : M - 1 - m0;
         offb[j] = (unsigned)rr * (unsigned)row_stride + (((lane & 7) ^ swizzle_of_row(row)) << 4);
     }
-    // all addresses are in bounds by construction; the descriptors do not rely on range checking
+    // Addresses are in bounds by construction: a tile's rows span at most 2^30 bytes.  An offset of kRangeBytes is
+    // outside, and such a lane puts zeros into its place in LDS: the chunks of the last slab that lie beyond K.
+    constexpr unsigned kRangeBytes = 0x80000000u;
     const __amdgpu_buffer_rsrc_t w_rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(w_tile), 0, 0xffffffffu, 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(w_tile), 0, kRangeBytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t x_rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(x_tile), 0, 0xffffffffu, 0x00020000);
-    auto request = [&](int i) {  // slab i of this workgroup into stage i % kRing
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(x_tile), 0, kRangeBytes, 0x00020000);
+    // the x-th of the wave's loads of this workgroup's slab i, into stage i % kRing
+    auto dma_one = [&](int i, int x, bool in) {
         char *st = smem + (i % kRing) * kStageBytes;
-#pragma unroll
-        for (int j = 0; j < kDmaA; ++j)
+        if (x < kDmaA)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                w_rsrc, (__attribute__((address_space(3))) void *)(st + (wave * (BN / 4) + j * 8) * kRowBytes), 16,
-                offa[j], i * kRowBytes, 0, 0);
-#pragma unroll
-        for (int j = 0; j < kDmaB; ++j)
+                w_rsrc, (__attribute__((address_space(3))) void *)(st + (wave * (BN / kWaves) + x * 8) * kRowBytes), 16,
+                in ? offa[x < kDmaA ? x : 0] : kRangeBytes, i * kRowBytes, 0, 0);
+        else
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                x_rsrc, (__attribute__((address_space(3))) void *)(st + (BN + wave * (BM / 4) + j * 8) * kRowBytes), 16,
-                offb[j], i * kRowBytes, 0, 0);
+                x_rsrc, (__attribute__((address_space(3))) void *)(st + (BN + wave * (BM / kWaves) + (x - kDmaA) * 8) * kRowBytes), 16,
+                in ? offb[x < kDmaA ? 0 : x - kDmaA] : kRangeBytes, i * kRowBytes, 0, 0);
+    };
+    auto request = [&](int i) {
+#pragma unroll
+        for (int x = 0; x < kDma; ++x)
+            dma_one(i, x, true);
+    };
+    auto request_cut = [&](int i) {
+#pragma unroll
+        for (int x = 0; x < kDma; ++x) {
+            const int row = x < kDmaA ? wave * (BN / kWaves) + x * 8 : wave * (BM / kWaves) + (x - kDmaA) * 8;
+            const int chunk = (lane & 7) ^ swizzle_of_row(row + (lane >> 3));
+            dma_one(i, x, (sl0 + i) * kSlabElems + chunk * kChunkElems < K);
+        }
     };
 
     floatx16 acc[WTN][WTM];
@@ -226,28 +248,15 @@ __global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const
                     mma(a[ks][i], b[ks][j], acc[i][j], (const T *)nullptr);
     };
 
-    // the slab cut by K, requested first: chunks at or beyond K are zeros in both operands
-    uintx4 cutv[kDma];
-    if (cut) {
-#pragma unroll
-        for (int j = 0; j < kDma; ++j) {
-            const bool is_w = j < kDmaA;
-            const int jj = is_w ? j : j - kDmaA;
-            const int row = wave * ((is_w ? BN : BM) / 4) + jj * 8 + (lane >> 3);
-            const int chunk = (lane & 7) ^ swizzle_of_row(row);
-            const bool in = (sl1 - 1) * kSlabElems + chunk * kChunkElems < K;
-            const char *src = (is_w ? w_tile + offa[is_w ? jj : 0] : x_tile + offb[is_w ? 0 : jj]) + (size_t)full * kRowBytes;
-            cutv[j] = *reinterpret_cast<const uintx4 *>(in ? src : (const char *)(is_w ? p.W : p.X));
-        }
-    }
-
     // ---- main loop ----
 #pragma unroll
     for (int t = 0; t < kRing - 1; ++t)
         if (t < full)
             request(t);
+    if (__builtin_expect(total > full && total < kRing, 0))
+        request_cut(total - 1);
     if (p.timeline != nullptr) {  // the first slab has landed
-        if (full >= kRing - 1)
+        if (total >= kRing - 1)
             wait_vm<(kRing - 2) * kDma>();
         else
             wait_vm<0>();
@@ -259,36 +268,29 @@ __global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const
     for (; i + kRing - 1 < full; ++i) {
         wait_vm<(kRing - 2) * kDma>();  // this wave's rows of slab i have landed
         lds_barrier();                  // everyone's have, and everyone has read slab i - 1
-        request(i + kRing - 1);         // into the stage slab i - 1 occupied
+        request(i + kRing - 1);  // into the stage slab i - 1 occupied
         multiply(i % kRing);
     }
-#pragma unroll
-    for (int left = kRing - 2; left >= 0; --left)
-        if (full - i > left) {
-            if (left == 2)
-                wait_vm<2 * kDma>();
-            else if (left == 1)
-                wait_vm<kDma>();
-            else
-                wait_vm<0>();
+    if (__builtin_expect(i + kRing - 1 < total, 0)) {  // the last slab, cut by K
+        wait_vm<(kRing - 2) * kDma>();
+        lds_barrier();
+        request_cut(i + kRing - 1);
+        multiply(i % kRing);
+        ++i;
+    }
+    auto last = [&](auto left_c) {
+        constexpr int left = decltype(left_c)::value;
+        if (__builtin_expect(total - i > left, 1)) {  // in line: short calls pay for every jump to code of its own
+            wait_vm<left * kDma>();
             lds_barrier();
             multiply(i % kRing);
             ++i;
         }
-    static_assert(kRing == 4, "the waits above are written for four stages");
-    if (cut) {
-        lds_barrier();
-#pragma unroll
-        for (int j = 0; j < kDma; ++j) {
-            const int row = j < kDmaA ? wave * (BN / 4) + j * 8 : wave * (BM / 4) + (j - kDmaA) * 8;
-            const int chunk = (lane & 7) ^ swizzle_of_row(row + (lane >> 3));
-            const bool in = (sl1 - 1) * kSlabElems + chunk * kChunkElems < K;
-            *reinterpret_cast<uintx4 *>(smem + (j < kDmaA ? row : BN + row) * kRowBytes + lane * 16) =
-                cutv[j] & (in ? 0xffffffffu : 0u);
-        }
-        lds_barrier();
-        multiply(0);
-    }
+    };
+    static_assert(kRing == 4, "the last slabs");
+    last(std::integral_constant<int, 2>());
+    last(std::integral_constant<int, 1>());
+    last(std::integral_constant<int, 0>());
     stamp(2);
     stamp(kTimelineCycleSlot + 1);
     lds_barrier();  // all fragment reads done: the stages become the product's place
@@ -427,8 +429,8 @@ __global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const
     // rows of one tile and up to eight are in flight; the chunks of a row meet in LDS in chunk order.
     // (A row's own lanes reading its tiles touch a line each: 40 x 512 x 15360, 240 tiles, 34 us a call.)
     float *s_n = reinterpret_cast<float *>(smem);             // [kMaxChunks][rows]: columns seen
-    floatx2 *s_mm = reinterpret_cast<floatx2 *>(smem + 1024); // [kMaxChunks][rows]: mean, M2
-    floatx2 *s_row = reinterpret_cast<floatx2 *>(smem + 4096);  // [rows]: mean, 1 / standard deviation
+    floatx2 *s_mm = reinterpret_cast<floatx2 *>(smem + kThreads * 4);   // [kMaxChunks][rows]: mean, M2
+    floatx2 *s_row = reinterpret_cast<floatx2 *>(smem + kThreads * 12);  // [rows]: mean, 1 / standard deviation
     constexpr int kMaxChunks = 16, kBatch = 8;
     const int rows_log2 = 31 - __builtin_clz(rows);
     // (no more chunks than there are batches: 256 x 512 x 512 fp32, eight tiles a row, 13.4 us with 16 chunks
@@ -519,14 +521,14 @@ __global__ __launch_bounds__(kThreads, WTN == 1 ? 2 : 1) void split_kernel(const
     case kSplit64x32: FF_SPLIT_TYPES(2, 1, 2, 1, 1, CALL)    \
     case kSplit128x32: FF_SPLIT_TYPES(2, 1, 2, 2, 1, CALL)   \
     case kSplit64: FF_SPLIT_TYPES(2, 2, 1, 1, 1, CALL)       \
-    case kSplit128x64: FF_SPLIT_TYPES(2, 2, 1, 2, 1, CALL)   \
-    default: FF_SPLIT_TYPES(2, 2, 1, 2, 2, CALL)             \
+    case kSplit128x64: FF_SPLIT_TYPES(2, 2, 2, 2, 1, CALL)   \
+    default: FF_SPLIT_TYPES(2, 2, 2, 2, 2, CALL)             \
     }
 
 template <typename T, int WN, int WM, int WK, int WTN, int WTM>
 static hipError_t launch_split(const SplitParams &p, int grid, hipStream_t stream)
 {
-    hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM>), dim3(grid), dim3(kThreads), 0, stream, p);
+    hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM>), dim3(grid), dim3(64 * WN * WM * WK), 0, stream, p);
     return hipGetLastError();
 }
 
@@ -534,7 +536,7 @@ template <typename T, int WN, int WM, int WK, int WTN, int WTM>
 static int split_blocks()
 {
     int a = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, split_kernel<T, WN, WM, WK, WTN, WTM>, kThreads, 0) != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, split_kernel<T, WN, WM, WK, WTN, WTM>, 64 * WN * WM * WK, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
