@@ -38,11 +38,15 @@ constexpr int kRowsPerDma = 1024 / kRowBytes;     // one direct-to-LDS instructi
 // bf16 multiplies in blocks of 16: the chip's power sets the rate of a long product, and a 16 x 16 x 32 instruction
 // moves half the accumulators of a 32 x 32 x 16 one for each product.  Nothing but either in a loop, random operands:
 // 2002 against 1774 TFLOP/s.  fp32 is bound by the issue of its matrix instructions, whatever their shape.
-template <typename T>
+//
+// FULL: the accumulators take one half of the register file to the last register (256 x 256 by four wavefronts).  Blocks of
+// 32 there in bf16 too: with sixty-four blocks of 16 and no register to spare the compiler moved them about, 264
+// copies for the 128 instructions of a slab.
+template <typename T, bool FULL>
 struct Mma;
 
 template <>
-struct Mma<__bf16> {
+struct Mma<__bf16, false> {
     using Acc = floatx4;
     static constexpr int kBlock = 16, kLaneGroups = 4, kQuads = 1;
     static __device__ __forceinline__ void step(const uintx4 &a, const uintx4 &b, Acc &c)
@@ -53,7 +57,18 @@ struct Mma<__bf16> {
 };
 
 template <>
-struct Mma<float> {
+struct Mma<__bf16, true> {
+    using Acc = floatx16;
+    static constexpr int kBlock = 32, kLaneGroups = 2, kQuads = 4;
+    static __device__ __forceinline__ void step(const uintx4 &a, const uintx4 &b, Acc &c)
+    {
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    }
+};
+
+template <bool FULL>
+struct Mma<float, FULL> {
     using Acc = floatx16;
     static constexpr int kBlock = 32, kLaneGroups = 2, kQuads = 4;
     // One 16-byte fragment per lane holds 4 floats along K: four 32x32x2 MFMAs.
@@ -149,8 +164,9 @@ void tile_kernel(const TileParams p)
     constexpr int BN = kWavesN * WTN * 32;
     constexpr int BM = kWavesM * WTM * 32;
     constexpr bool kAccRegs = WTN * WTM >= 16;
-    using Acc = typename Mma<T>::Acc;
-    constexpr int kBlock = Mma<T>::kBlock, kLaneGroups = Mma<T>::kLaneGroups;
+    using Product = Mma<T, kAccRegs>;
+    using Acc = typename Product::Acc;
+    constexpr int kBlock = Product::kBlock, kLaneGroups = Product::kLaneGroups;
     constexpr int kBlocksN = WTN * 32 / kBlock, kBlocksM = WTM * 32 / kBlock;  // matrix blocks of a wavefront
     constexpr int kSteps = kChunksPerRow / kLaneGroups;                        // k-steps of a slab
     constexpr int kChunkElems = 16 / (int)sizeof(T);
@@ -329,7 +345,7 @@ void tile_kernel(const TileParams p)
 #pragma unroll
             for (int j = 0; j < kBlocksM; ++j)
 #pragma unroll
-                for (int r = 0; r < 4 * Mma<T>::kQuads; ++r)
+                for (int r = 0; r < 4 * Product::kQuads; ++r)
                     acc[i][j][r] = zero;
 
         // Fragments: W's in one buffer, each read again for the next k-step as soon as its products are issued; X's,
@@ -349,7 +365,7 @@ void tile_kernel(const TileParams p)
         auto products = [&](int g, int s) {
 #pragma unroll
             for (int j = 0; j < kBlocksM; ++j)
-                Mma<T>::step(fa[g], fb[s & 1][j], acc[g][j]);
+                Product::step(fa[g], fb[s & 1][j], acc[g][j]);
         };
         auto end_group = [&](int g) {
 #pragma unroll
@@ -359,7 +375,9 @@ void tile_kernel(const TileParams p)
         };
         static_assert(kBlocksM <= kBlocksN && kSteps % 2 == 0, "the X fragments of the next k-step, one per group");
         // k-step s of the slab in `stage`, not its last: the next one's fragments are read behind its products.
-        auto step_inside = [&](int stage, int s) {
+        // (Always in line: a call, which the compiler prefers for the 256 x 256 tile of four wavefronts in fp32, takes
+        // everything that the body names through scratch memory, accumulators and all.)
+        auto step_inside = [&](int stage, int s) __attribute__((always_inline)) {
 #pragma unroll
             for (int g = 0; g < kBlocksN; ++g) {
                 if (g < kBlocksM)
@@ -369,7 +387,7 @@ void tile_kernel(const TileParams p)
                 end_group(g);
             }
         };
-        auto steps_inside = [&](int stage) {
+        auto steps_inside = [&](int stage) __attribute__((always_inline)) {
 #pragma unroll
             for (int s = 0; s + 1 < kSteps; ++s)
                 step_inside(stage, s);
@@ -450,7 +468,7 @@ void tile_kernel(const TileParams p)
         int i = 0, stage = 0;  // slab i lies in `stage`
         // The last k-step of slab i; `dma`: what to do about slab i + STAGES, `later`: slabs behind i + 1 that are in
         // flight at its barrier, -1 if there is no slab i + 1.
-        auto step_last = [&](auto later_c, auto dma_c) {
+        auto step_last = [&](auto later_c, auto dma_c) __attribute__((always_inline)) {
             constexpr int later = decltype(later_c)::value, dma = decltype(dma_c)::value;
             constexpr bool more = later >= 0;
             constexpr int kRest = kBlocksN - kSync;  // groups behind the barrier
@@ -533,7 +551,7 @@ void tile_kernel(const TileParams p)
 
         // A lane's values of one of its rows, in quads of neighbouring columns: quad t of the wavefront's strip starts at
         // column t * kQuadStep + 4 * group.
-        constexpr int kQpb = Mma<T>::kQuads, kQuadStep = 4 * kLaneGroups;
+        constexpr int kQpb = Product::kQuads, kQuadStep = 4 * kLaneGroups;
         constexpr int kQuadsRow = kBlocksN * kQpb;
         constexpr int kPass = kQuadsRow < 4 ? kQuadsRow : 4;  // quads of a row worked on at a time
 
@@ -549,6 +567,8 @@ void tile_kernel(const TileParams p)
                 for (int j = 0; j < kBlocksM; ++j) {
                     shift[j] = from_lane(gelu_erf(acc[0][j][0] + bb[0]), block_row);
                     s1[j] = s2[j] = 0.0f;
+                    if (kAccRegs)
+                        pin_order<kAccRegs>(acc[0][j]);
                 }
             }
 #pragma unroll
@@ -586,6 +606,10 @@ void tile_kernel(const TileParams p)
 #pragma unroll
                     for (int i = t0 / kQpb; i < (t0 + kPass) / kQpb; ++i)
                         pin_order<kAccRegs>(acc[i][j]);  // G goes back to the accumulator registers
+                    // The sums are complete here.  The compiler put them off to where the statistics are stored, which
+                    // kept every G of a row in ordinary registers until then, and 24 to 76 bytes in scratch memory.
+                    if (kAccRegs)
+                        asm volatile("" : "+v"(s1[j]), "+v"(s2[j]));
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 // What N cuts is summed again, with what lies beyond N left out.  (Masks in
