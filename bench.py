@@ -276,7 +276,7 @@ def main() -> int:
     timeline = None
     if args.timeline:
         plan = B.ff_plan_query(M, K, N, B.FF_F32 if wl.dtype == "f32" else B.FF_BF16)
-        streamer = variant == B.FF_VARIANT_SMALL_M and plan["waves"] == 8   # the split kernel stamps like the tiles
+        streamer = variant == B.FF_VARIANT_SMALL_M and plan["tile_n"] == 32   # the split kernel stamps like the tiles
         timeline = phase_timeline(torch, B, step, small_m=streamer, grid=plan["grid"])
 
     hbm_bound = args.workload == "cfg3"

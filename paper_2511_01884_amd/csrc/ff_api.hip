@@ -1048,7 +1048,7 @@ int ff_plan_query(int64_t M, int64_t K, int64_t N, int dtype, int out[8])
     out[0] = pl.variant;
     out[1] = small ? (int)M : pl.tile_m;
     out[2] = small ? kSmallMStripCols : pl.tile_n;
-    out[3] = small ? 8 : (pl.split_s > 0 ? 4 : tile_shape_waves(pl.shape));
+    out[3] = small ? 8 : (pl.split_s > 0 ? split_shape_waves(pl.split_shape) : tile_shape_waves(pl.shape));
     out[4] = pl.grid;
     out[5] = small ? 1 : pl.rounds;
     out[6] = (pl.grid + num_cus - 1) / num_cus;

@@ -552,15 +552,17 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
 
 }  // namespace
 
-#define FF_SPLIT_TYPES(WN, WM, WK, WTN, WTM, CALL) \
+#define FF_SPLIT_TYPES(SHAPE, WN, WM, WK, WTN, WTM, CALL)                                                       \
+    static_assert(split_shape_cols(SHAPE) == WN * WTN * 32 && split_shape_rows(SHAPE) == WM * WTM * 32 &&       \
+                      split_shape_waves(SHAPE) == WN * WM * WK, "what the plan says of this shape");            \
     return bf16 ? CALL(__bf16, WN, WM, WK, WTN, WTM) : CALL(float, WN, WM, WK, WTN, WTM);
-#define FF_SPLIT_DISPATCH(CALL)                              \
-    switch (shape) {                                         \
-    case kSplit64x32: FF_SPLIT_TYPES(2, 1, 2, 1, 1, CALL)    \
-    case kSplit128x32: FF_SPLIT_TYPES(2, 1, 2, 2, 1, CALL)   \
-    case kSplit64: FF_SPLIT_TYPES(2, 2, 1, 1, 1, CALL)       \
-    case kSplit128x64: FF_SPLIT_TYPES(2, 2, 2, 2, 1, CALL)   \
-    default: FF_SPLIT_TYPES(2, 2, 2, 2, 2, CALL)             \
+#define FF_SPLIT_DISPATCH(CALL)                                            \
+    switch (shape) {                                                       \
+    case kSplit64x32: FF_SPLIT_TYPES(kSplit64x32, 2, 1, 2, 1, 1, CALL)     \
+    case kSplit128x32: FF_SPLIT_TYPES(kSplit128x32, 2, 1, 2, 2, 1, CALL)   \
+    case kSplit64: FF_SPLIT_TYPES(kSplit64, 2, 2, 1, 1, 1, CALL)           \
+    case kSplit128x64: FF_SPLIT_TYPES(kSplit128x64, 2, 2, 2, 2, 1, CALL)   \
+    default: FF_SPLIT_TYPES(kSplit128, 2, 2, 2, 2, 2, CALL)                \
     }
 
 template <typename T, int WN, int WM, int WK, int WTN, int WTM>

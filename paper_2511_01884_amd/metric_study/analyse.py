@@ -66,14 +66,15 @@ def read_task(task_dir):
 
 
 def _planned_variant(M, K, N):
-    """Label of the variant the automatic plan takes for a bf16 problem (ff_plan_query).  The 256 x 128
+    """Label of the variant the automatic plan takes for a bf16 problem (ff_plan_query), None if it is none
+    of them (the kernel that cuts K runs its 128 x 128 tiles with eight wavefronts).  The 256 x 128
     tile has one label whatever the number of workgroups per compute unit the grid comes to."""
     d = B.ff_plan_query(M, K, N, B.FF_BF16)
     for label, tile, per_cu, waves, variant in VARIANTS:
         half_height = (tile, per_cu) == (256, 2)
         if d["variant"] != variant or (d["tile_n"], d["tile_m"]) != ((256, 128) if half_height else (tile, tile)):
             continue
-        if half_height or (d["workgroups_per_cu"] == per_cu and (waves == 0 or d["waves"] == waves)):
+        if half_height or (d["workgroups_per_cu"] == per_cu and d["waves"] == (waves or 4)):
             return label
     return None
 
@@ -109,7 +110,7 @@ def main(argv) -> int:
         lines.append("| %s (%d x %d x %d) | " % ((t,) + TASKS[t]) + " | ".join("%.1f" % x for x in rt) + " |")
     lines += ["", "## Runtime of the whole call per variant: tile kernel plus, for the two-pass variants, the",
               "## normalisation kernel that follows it (microseconds; * marks the fastest of a task, P the",
-              "## automatic plan's choice)", "",
+              "## automatic plan's choice, nowhere if that is the kernel that cuts K)", "",
               "| task (M x K x N) | " + " | ".join(v[0] for v in VARIANTS) + " |",
               "|---|" + "---|" * len(VARIANTS)]
     for t, rt, sp in zip(tasks, runtimes, seconds):
