@@ -273,9 +273,10 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     //     fragment reads per MFMA); the sum favours eight (4096^3 115.7 against 116.7 us; 65536 x 1024
     //     x 1024 159.5 against 170.7; 8192 x 4096 x 16384 950 against 966);
     //   else, in bf16, if the 128 x 128 tiles outnumber the units but the 256-column x 128-row tiles do not:
-    //     256 x 128 tiles, one per unit, in one round, with three slabs of LDS (in fp32 128 x 128 tiles
-    //     win by a third): 1024 x 4096 x 8192 68 us, 15 such shapes 1.25 times as fast as with two slabs and four
-    //     wavefronts.  Up to a quarter more 128 x 128 tiles than units go two per unit where one of these holds:
+    //     256 x 128 tiles, one per unit, in one round, with three slabs of LDS and eight wavefronts (in fp32 128 x 128
+    //     tiles win by a third): 1024 x 4096 x 8192 68 us, 15 such shapes 1.25 times as fast as with two slabs and four
+    //     wavefronts.  (Four wavefronts and three slabs: 34 shapes 6 % slower, and 28 of nearly full chips with cut rows of
+    //     32 and more tiles 4 %; 256 x 4448 x 31976, 1 % faster, is the best of them.)  Up to a quarter more 128 x 128 tiles than units go two per unit where one of these holds:
     //     an odd number of them a row, which leaves half a 256-column tile empty (1843 x 5264 x 2312 85.5, with 256 x 128
     //     100.7; 1459 x 7640 x 2848 132, 145); at most eight more than 256 units and more than 4 a row (591 x 936 x 6560
     //     27.0, 31.3; with 4, 16891 x 3856 x 256, 113, 88); a short product (11899 x 72 x 344 13.9, 14.8).  They never do
@@ -300,16 +301,13 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     if (tiles256 * 2 > num_cus && (bf16 || !roomy || tiles128 > 2 * num_cus))
         pl.shape = kTile256W8;
     else if (bf16 && tiles128 > num_cus && tiles256x128 <= num_cus && !(roomy && two_a_unit))
-        // Eight wavefronts, except on a full chip whose rows are many tiles and cut: there four are as fast (25 shapes
-        // of 240 to 256 tiles, 32 and more a row: 0.993 of the time's inverse on average, 0.956 to 1.024; elsewhere 34
-        // shapes 0.944), and plans that callers pin stay as they were.
-        pl.shape = N % 256 != 0 && across >= 32 && tiles256x128 * 16 >= num_cus * 15 ? kTile256x128 : kTile256x128W8;
+        pl.shape = kTile256x128;
     else
         pl.shape = tiles128 * 4 > num_cus ? kTile128 : kTile64;
     if (g_forced_tile != 0) {
         pl.shape = g_forced_tile == 64 ? kTile64 : (g_forced_tile == 128 ? kTile128 : kTile256);
         if (g_forced_tile == 256 && g_forced_wg_per_cu == 2)
-            pl.shape = kTile256x128W8;
+            pl.shape = kTile256x128;
     }
     if (g_forced_waves != 0) {
         if (tile_shape_cols(pl.shape) != 256)

@@ -144,8 +144,8 @@ __device__ __forceinline__ int swizzle_of_row(int row) { return (row & 7) ^ ((ro
 // Wave layout: kWavesN x kWavesM wavefronts, each owning WTN x WTM times 32 x 32 outputs.  The
 // 256-tile runs as 2 x 4 wavefronts of 4 x 2 blocks (two wavefronts per SIMD: 128 accumulator
 // registers each, and eight wavefronts keep twice as many loads in flight on the L2 -> LDS path
-// as four) or as 2 x 2 wavefronts of 4 x 4 blocks; the 128- and 64-tiles as 2 x 2 wavefronts, two
-// workgroups per compute unit (second launch bound: two wavefronts per SIMD must fit).
+// as four) or as 2 x 2 wavefronts of 4 x 4 blocks; the 256 x 128 tile as 4 x 2 wavefronts of 2 x 2 blocks; the 128-
+// and 64-tiles as 2 x 2 wavefronts, two workgroups per compute unit (second launch bound: two wavefronts per SIMD must fit).
 //
 // STAGES: slabs the LDS has room for beside the parameters, two at 256 x 256 and where two workgroups share a unit,
 // three at 256 x 128 (one per unit): there two slabs travel while one is multiplied.
@@ -958,8 +958,7 @@ int max_blocks_per_cu()
 #define FF_TILE_DISPATCH(CALL)                                                         \
     if (bf16) {                                                                        \
         switch (shape) {                                                               \
-        case kTile256x128: FF_MODES(__bf16, 2, 2, 4, 2, 3, CALL)                       \
-        case kTile256x128W8: FF_MODES(__bf16, 4, 2, 2, 2, 3, CALL)                     \
+        case kTile256x128: FF_MODES(__bf16, 4, 2, 2, 2, 3, CALL)                       \
         case kTile256W8: FF_MODES(__bf16, 2, 4, 4, 2, 2, CALL)                         \
         case kTile256: FF_MODES(__bf16, 2, 2, 4, 4, 2, CALL)                           \
         case kTile128: FF_MODES(__bf16, 2, 2, 2, 2, 2, CALL)                           \
@@ -967,8 +966,7 @@ int max_blocks_per_cu()
         }                                                                              \
     }                                                                                  \
     switch (shape) {                                                                   \
-    case kTile256x128: FF_MODES(float, 2, 2, 4, 2, 3, CALL)                            \
-    case kTile256x128W8: FF_MODES(float, 4, 2, 2, 2, 3, CALL)                          \
+    case kTile256x128: FF_MODES(float, 4, 2, 2, 2, 3, CALL)                            \
     case kTile256W8: FF_MODES(float, 2, 4, 4, 2, 2, CALL)                              \
     case kTile256: FF_MODES(float, 2, 2, 4, 4, 2, CALL)                                \
     case kTile128: FF_MODES(float, 2, 2, 2, 2, 2, CALL)                                \

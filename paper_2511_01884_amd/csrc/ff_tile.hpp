@@ -154,16 +154,15 @@ enum TileShape {
     kTile128 = 1,      // 128 x 128, four wavefronts, two workgroups per compute unit
     kTile256 = 2,      // 256 x 256, four wavefronts of 4 x 4 MFMA blocks, one workgroup per compute unit
     kTile256W8 = 3,    // 256 x 256, eight wavefronts of 4 x 2 blocks, one workgroup per compute unit
-    kTile256x128 = 4,  // 256 columns x 128 rows, four wavefronts of 128 x 64 outputs, one workgroup per compute unit
-    kTile256x128W8 = 5,  // 256 columns x 128 rows, eight wavefronts of 64 x 64 outputs, one workgroup per compute unit
-    kNumTileShapes = 6
+    kTile256x128 = 4,  // 256 columns x 128 rows, eight wavefronts of 64 x 64 outputs, one workgroup per compute unit
+    kNumTileShapes = 5
 };
 inline int tile_shape_cols(int shape) { return shape == kTile64 ? 64 : (shape == kTile128 ? 128 : 256); }
 inline int tile_shape_rows(int shape)
 {
-    return shape == kTile64 ? 64 : ((shape == kTile128 || shape >= kTile256x128) ? 128 : 256);
+    return shape == kTile64 ? 64 : ((shape == kTile128 || shape == kTile256x128) ? 128 : 256);
 }
-inline int tile_shape_waves(int shape) { return shape == kTile256W8 || shape == kTile256x128W8 ? 8 : 4; }
+inline int tile_shape_waves(int shape) { return shape == kTile256W8 || shape == kTile256x128 ? 8 : 4; }
 hipError_t launch_tile_kernel(bool bf16, int shape, int mode, const TileParams &p, int grid, hipStream_t stream);
 int tile_kernel_blocks_per_cu(bool bf16, int shape, int mode);
 hipError_t launch_finalize_kernel(bool bf16, const FinalizeParams &p, hipStream_t stream);

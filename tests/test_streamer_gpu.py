@@ -87,7 +87,7 @@ def test_streamer_in_a_small_bound_workspace(M, K, N):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,K,N,waves", [(9, 840, 7248, 8), (2085, 264, 4088, 8), (1000, 320, 8136, 4)])
+@pytest.mark.parametrize("M,K,N,waves", [(9, 840, 7248, 8), (2085, 264, 4088, 8), (1000, 320, 8136, 8)])
 def test_expired_waits_are_reported(M, K, N, waves):
     """Streamer, 256 x 256 and 256 x 128 tiles: one arrival more than will come, a 3 ms limit, FF_ERR_DEVICE once."""
     plan = B.ff_plan_query(M, K, N, B.FF_BF16)

@@ -35,12 +35,12 @@ def test_slabs(shape, slabs, rest, dtype):
 
 
 @pytest.mark.parametrize("K", [64, 136, 200, 328])
-@pytest.mark.parametrize("M,N,waves", [(1000, 8136, 4), (1024, 8192, 8)])
-def test_tiles_of_half_the_height(M, K, N, waves):
-    """256 x 128 tiles as the plan takes them: cut rows of 32 tiles on every unit with four wavefronts, else eight."""
+@pytest.mark.parametrize("M,N", [(1000, 8136), (1024, 8192)])
+def test_tiles_of_half_the_height(M, K, N):
+    """256 x 128 tiles as the plan takes them: rows that end inside a tile, and whole ones."""
     print("[case] half height", M, K, N, flush=True)
     plan = B.ff_plan_query(M, K, N, B.FF_BF16)
-    assert (plan["tile_m"], plan["tile_n"], plan["waves"]) == (128, 256, waves)
+    assert (plan["tile_m"], plan["tile_n"], plan["waves"]) == (128, 256, 8)
     d = make_inputs(M, K, N, "bf16", seed=K)
     Y, used = gpu_run(d)
     assert used == B.FF_VARIANT_TILED_FUSED
