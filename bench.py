@@ -78,7 +78,7 @@ def sustained_ceiling(torch, B, bound: str):
         ev1.record()
         torch.cuda.synchronize()
         return {"value": flops / (ev0.elapsed_time(ev1) * 1e-3) / 1e12, "unit": "TFLOP/s",
-                "what": "register-resident loop of bf16 32x32x16 MFMAs, four wavefronts per compute unit"}
+                "what": "register-resident loop of bf16 16x16x32 MFMAs, operands unchanged, eight wavefronts per compute unit"}
     buf = torch.empty(1 << 30, dtype=torch.uint8, device="cuda").random_(0, 255)
     B.ff_debug_stream_read(buf)
     torch.cuda.synchronize()

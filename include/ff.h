@@ -272,7 +272,7 @@ int ff_debug_force_variant(int variant);
 int ff_debug_copy(const void *src, void *dst, size_t bytes, void *stream);
 
 /* Measured ceilings, on the default (null) stream: a register-resident loop of independent bf16
- * 32x32x16 MFMAs, `iters` rounds of 8 per wavefront, four wavefronts per compute unit, with no memory
+ * 16x16x32 MFMAs, `iters` rounds of 16 per wavefront, eight wavefronts per compute unit, with no memory
  * traffic (*flops, a host pointer, receives the flops the launch performs); and a streaming read of
  * `bytes` (a multiple of 16) from `src` (device, 16-byte aligned) with 16-byte loads, eight in flight
  * per thread.  Timed by the caller, they give what the chip sustains next to the published peaks. */

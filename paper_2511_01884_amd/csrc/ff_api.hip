@@ -1200,7 +1200,7 @@ int ff_debug_mfma_loop(int64_t iters, double *flops)
     if (!st)
         return FF_ERR_LAUNCH;
     // the kernel's per-thread results go to the workspace (they only keep the loop alive)
-    const int rc = prepare_workspace(*st, kCtrlBytes + (size_t)st->num_cus * 256 * sizeof(float), nullptr);
+    const int rc = prepare_workspace(*st, kCtrlBytes + (size_t)st->num_cus * 512 * sizeof(float), nullptr);
     if (rc != FF_OK)
         return rc;
     float *sink = reinterpret_cast<float *>(static_cast<char *>(st->ws) + kCtrlBytes);

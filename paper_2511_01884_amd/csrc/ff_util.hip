@@ -35,18 +35,20 @@ hipError_t launch_copy_kernel(const void *src, void *dst, size_t bytes, int num_
 // ---- measured ceilings --------------------------------------------------------
 // Two kernels that do nothing but the one thing a roofline is about, so that the fraction of the
 // published peak a kernel reaches can be read next to what the chip sustains at all:
-//   mfma_loop_kernel    a register-resident loop of independent bf16 32x32x16 MFMAs (no memory traffic)
+//   mfma_loop_kernel    a register-resident loop of independent bf16 16x16x32 MFMAs, the tile kernel's instruction
+//                       (no memory traffic, the same operands in every round)
 //   stream_read_kernel  16-byte streaming loads over a buffer, eight in flight per thread
 namespace ff {
 
 namespace {
 
-constexpr int kMfmaChains = 8;  // independent accumulators per wavefront: the matrix pipe never waits
+constexpr int kMfmaChains = 16;     // independent accumulators per wavefront
+constexpr int kMfmaThreads = 512;  // two wavefronts a SIMD: one alone does not issue these instructions at the pipe's rate
 
-__global__ __launch_bounds__(256) void mfma_loop_kernel(long long iters, float *sink)
+__global__ __launch_bounds__(kMfmaThreads) void mfma_loop_kernel(long long iters, float *sink)
 {
     // operands with varied bit patterns (the power an MFMA draws depends on its data)
-    const unsigned t = threadIdx.x + blockIdx.x * 256u;
+    const unsigned t = threadIdx.x + blockIdx.x * (unsigned)kMfmaThreads;
     uintx4 a, b;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -54,23 +56,23 @@ __global__ __launch_bounds__(256) void mfma_loop_kernel(long long iters, float *
         a[i] = ((h & 0x007f007fu) | 0x3f803f80u) ^ ((h >> 3) & 0x80008000u);          // bf16 pairs in +-[1, 2)
         b[i] = (((h >> 7) & 0x007f007fu) | 0x3f003f00u) ^ ((h >> 11) & 0x80008000u);  // bf16 pairs in +-[0.5, 1)
     }
-    floatx16 acc[kMfmaChains];
+    floatx4 acc[kMfmaChains];
 #pragma unroll
     for (int c = 0; c < kMfmaChains; ++c)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
+        for (int r = 0; r < 4; ++r)
             acc[c][r] = 0.0f;
     for (long long it = 0; it < iters; ++it) {
 #pragma unroll
         for (int c = 0; c < kMfmaChains; ++c)
-            acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+            acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                              __builtin_bit_cast(bf16x8, b), acc[c], 0, 0, 0);
     }
     float s = 0.0f;
 #pragma unroll
     for (int c = 0; c < kMfmaChains; ++c)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
+        for (int r = 0; r < 4; ++r)
             s += acc[c][r];
     sink[t] = s;
 }
@@ -96,11 +98,11 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const uintx4 *src, siz
 
 }  // namespace
 
-// one workgroup (four wavefronts) per compute unit; returns the flops the launch performs
+// one workgroup (eight wavefronts) per compute unit; sink: 512 floats a unit; returns the flops the launch performs
 hipError_t launch_mfma_loop(long long iters, float *sink, int num_cus, hipStream_t stream, double *flops)
 {
-    hipLaunchKernelGGL(mfma_loop_kernel, dim3(num_cus), dim3(256), 0, stream, iters, sink);
-    *flops = (double)num_cus * 4.0 * (double)iters * kMfmaChains * (2.0 * 32 * 32 * 16);
+    hipLaunchKernelGGL(mfma_loop_kernel, dim3(num_cus), dim3(kMfmaThreads), 0, stream, iters, sink);
+    *flops = (double)num_cus * (kMfmaThreads / 64) * (double)iters * kMfmaChains * (2.0 * 16 * 16 * 32);
     return hipGetLastError();
 }
 
