@@ -268,10 +268,9 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     //   more 256 x 256 tiles than half the compute units (in fp32, which is bound by the matrix units, only
     //     when 128 x 128 tiles two per unit would not do in one round: 2927 x 2952 x 2692 takes 395 us with
     //     those, 688 with 132 tiles of 256): 256 x 256 tiles, one workgroup of eight
-    //     wavefronts per unit.  Eight wavefronts run the epilogue faster than four (two wavefronts per
-    //     SIMD hide each other's latencies) and the K loop up to 4 % slower (half again as many LDS
-    //     fragment reads per MFMA); the sum favours eight (4096^3 115.7 against 116.7 us; 65536 x 1024
-    //     x 1024 159.5 against 170.7; 8192 x 4096 x 16384 950 against 966);
+    //     wavefronts per unit.  Two wavefronts per SIMD hide each other's latencies in the epilogue, and their
+    //     accumulators leave room for the blocks of 16 x 16, which draw less power than four wavefronts' of 32 x 32
+    //     (4096^3 112 against 127 us; 65536 x 1024 x 1024 149, 171; 8192 x 4096 x 16384 833, 967);
     //   else, in bf16, if the 128 x 128 tiles outnumber the units but the 256-column x 128-row tiles do not:
     //     256 x 128 tiles, one per unit, in one round, with three slabs of LDS and eight wavefronts (in fp32 128 x 128
     //     tiles win by a third): 1024 x 4096 x 8192 68 us, 15 such shapes 1.25 times as fast as with two slabs and four

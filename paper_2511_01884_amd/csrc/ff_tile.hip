@@ -2,8 +2,8 @@
 //
 // One workgroup (4 or 8 wavefronts) owns a BM x BN tile of the output and walks K in
 // 128-byte slabs (whole cache lines: one L2 request per line).  X and W slabs go
-// HBM -> LDS with 16-byte direct-to-LDS loads into two stages; the loads of the
-// slab after the next are issued in the shadow of the MFMAs, the single barrier per slab
+// HBM -> LDS with 16-byte direct-to-LDS loads into STAGES stages (two or three); the loads of the
+// slab STAGES further on are issued in the shadow of the MFMAs, the single barrier per slab
 // sits in its last k-step, and MFMA fragments are read one k-step ahead of
 // their use, so the matrix pipe does not wait on LDS latency after the barrier.  The MFMA is issued
 // "transposed" (A operand = W rows, B operand = X rows), so that a lane's
@@ -95,7 +95,8 @@ __device__ __forceinline__ void wave_lds_sync()
 // they live.  Where a wavefront's 256 registers hold everything, the accumulators are ordinary vector
 // registers, which the epilogue reads and writes as they are: as accumulation registers they cost two
 // copies an element in the GELU pass and one before the stores (v_accvgpr_read, _write: 640 of 2900 vector instructions
-// of an epilogue) and 46 registers more (1018 x 256 x 10944 bf16 25.9 -> 25.1 us, 6912 x 256 x 15208 196 -> 186).  Only
+// of an epilogue) and 46 registers more (before the loop had 16 x 16 x 32 instructions: 1018 x 256 x 10944 bf16
+// 25.9 -> 25.1 us, 6912 x 256 x 15208 196 -> 186).  Only
 // the four-wavefront 256 x 256 tile, whose accumulators alone are 256 registers, needs the other half of the register file.
 template <bool kAcc, typename Acc> __device__ __forceinline__ void pin_order(Acc &c)
 {
@@ -316,7 +317,9 @@ void tile_kernel(const TileParams p)
         // The last slab when K cuts it: a lane whose chunk lies at or beyond K reads outside the descriptor's range,
         // which puts zeros into its place in LDS.  (Through registers, with zeros
         // written for the missing chunks, it was a load latency in the open: 3001 x 2056 x 5000 spent 54.5 us up
-        // to the end of the product, against 46.2 for K = 2048.)
+        // to the end of the product, against 46.2 for K = 2048.)  In the loop's last steady step these loads stand one
+        // behind the other after the barrier, each in a loop of one round over the lanes (the compiler keeps the slab's
+        // offset in a vector register), not between the products as the uncut slabs' do.
         auto dma_cut = [&](int slab, int stage, int half) {
             // lane geometry re-derived through an opaque move: this rarely taken path
             // must not have its offsets precomputed (and spilled) at kernel entry

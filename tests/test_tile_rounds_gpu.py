@@ -1,5 +1,5 @@
 """The tile kernel where tile counts are no powers of two: rounds of whole row-blocks with a shorter last one, the
-column cut by N in every block row of a wavefront, every length of the slab that K cuts, both slab pipelines."""
+column cut by N in every block row of a wavefront, every length of the slab that K cuts, with two slabs of LDS and three."""
 import pytest
 import torch
 
@@ -53,8 +53,8 @@ def test_cut_slabs_f32(K, dtype):
 
 
 @pytest.mark.parametrize("K", [8, 72, 136, 200, 264])
-def test_cut_slabs_through_registers(K):
-    """256-column x 128-row tiles, whose X slabs go through registers."""
+def test_cut_slabs_of_half_height_tiles(K):
+    """256-column x 128-row tiles, which have three slabs of LDS."""
     print("[case] cut slab, half-height tiles", K, flush=True)
     plan = B.ff_plan_query(1000, K, 8136, B.FF_BF16)
     assert (plan["tile_m"], plan["tile_n"]) == (128, 256)
