@@ -136,7 +136,9 @@ __device__ __forceinline__ float from_lane(float v, int lane)
 
 // LDS placement of 16-byte chunk `c` (0..7) of tile row `row`: chunks are XORed
 // with row bits so that the consecutive rows a fragment read touches per pass
-// (stride 128 B) spread over all banks, for 8-lane and for 16-lane passes.
+// (stride 128 B) spread over all banks, for 8-lane and for 16-lane passes.  That is so for blocks of 32 rows: 2.8 % of the
+// LDS cycles of a bf16 4096^3 product were conflicts.  Blocks of 16, whose lane groups read neighbouring chunks of the
+// same 16 rows, have 49 %.
 __device__ __forceinline__ int swizzle_of_row(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
 // RAGGED_N: N is not a multiple of the tile width, so the last tile of each row
