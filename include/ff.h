@@ -211,7 +211,7 @@ size_t ff_workspace_bytes(int64_t M, int64_t K, int64_t N, int dtype);
  * The launch plan a call with this shape would take under the current variant selection, without
  * launching anything: out[0] the ff_variant, out[1] rows and out[2] columns of the output tile a
  * workgroup owns (small-M streamer: all M rows x one 32-column strip at a time), out[3] wavefronts
- * per workgroup (8 for the small-M streamer; of the kernel that cuts K, 8 for tiles of 128 columns and 64 or
+ * per workgroup (8 for the small-M streamer; of the kernel that cuts K, 8 for most tiles of 128 columns and 64 or
  * more rows, else 4), out[4]
  * workgroups in the launch (several per tile where K is cut), out[5] tiles per workgroup (rounds),
  * out[6] workgroups per compute unit, out[7] 1 if the tile order is the XCD-aware one by powers of

@@ -148,7 +148,7 @@ int resident_split_blocks(DeviceState *st, bool bf16, int shape)
 bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceState *st, Plan &pl)
 {
     // workgroups per compute unit that the LDS allows (what the runtime reports is asked as well)
-    constexpr int kPerCu[kNumSplitShapes] = {3, 2, 2, 1, 1};
+    constexpr int kPerCu[] = {3, 2, 2, 1, 1};
     struct Cost { double start, slab, mfma, hbm, fabric, unit_hbm, exch, exch_s, sums, epi, epi_large, epi128, tiles; };
     constexpr Cost kBf16 = {4.2, 0.0, 0.128, 5.1e6, 51.6e3, 32e3, 2.4, 0.25, 2.8e6, 2.3, 1.9, 0.9, 0.052};
     constexpr Cost kF32 = {4.5, 0.134, 0.48, 5.1e6, 1e9, 26e3, 2.5, 0.2, 2.5e6, 3.0, 3.0, 0.78, 0.056};
@@ -156,7 +156,7 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
     const int size = bf16 ? 2 : 4;
     const int64_t slabs = (K * size + 127) / 128;
     double best = 0.0;
-    for (int shape = 0; shape < kNumSplitShapes; ++shape) {
+    for (int shape = 0; shape <= kSplit128; ++shape) {
         const int bm = split_shape_rows(shape), bn = split_shape_cols(shape);
         // tiles of few rows pay only where they spare the padding of larger ones
         // (128 x 32 in bf16 up to 32 rows: two row blocks take W through four wavefronts' loads twice.  51 x 5080 x 15984
@@ -206,6 +206,13 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
     }
     if (pl.split_s == 0)
         return false;
+    // 128 x 128 tiles of long bf16 rows that do not begin on 64-byte boundaries keep four wavefronts.  There every line of
+    // a slab is requested twice, and eight wavefronts go to HBM for half of W's lines a second time (147 x 10568 x 6016
+    // 89 us, with four 76; K = 10560: 62, 66).  206 such shapes: up to 48 slabs a workgroup eight win (0.94 of the time),
+    // beyond them four do (0.95, at best 0.80: 1284 x 9832 x 2432 150 us, 119); with this line a call takes 0.5 % more than
+    // with the better of the two on average, 8.6 at most, 2.6 and 25 with eight throughout.
+    if (bf16 && pl.split_shape == kSplit128 && K % 32 != 0 && (slabs + pl.split_s - 1) / pl.split_s > 48)
+        pl.split_shape = kSplit128W4;
     pl.rounds = 1;
     pl.split_us = best;
     const size_t rows = (size_t)pl.tile_m / pl.split_s, tiles = (size_t)pl.RB * pl.NT;

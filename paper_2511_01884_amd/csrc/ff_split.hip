@@ -96,7 +96,8 @@ template <> struct RawCols<__bf16> {
 // 384 x 2048 x 6000 34.9, 31.4; 200 x 16384 x 3000 50.5, 47.2; 512 x 4096 x 4096 fp32 146, 139.  (A ring of five stages
 // is no faster, so it is not the time of a load; the fragments of the next slab read ahead of its barrier neither in
 // bf16, 4 % faster in long fp32 products and 0.3 us slower in short ones.  Both point at the rate at which a unit's
-// loads reach its LDS: 57 bytes a nanosecond.)
+// loads reach its LDS: 57 bytes a nanosecond.)  The plan keeps four in the 128 x 128 tile for long rows off the 64-byte
+// boundaries.
 template <typename T, int kWN, int kWM, int kWK, int WTN, int WTM>
 __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN == 1 ? 2 : 1) void split_kernel(const SplitParams p)
 {
@@ -562,6 +563,9 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     case kSplit128x32: FF_SPLIT_TYPES(kSplit128x32, 2, 1, 2, 2, 1, CALL)   \
     case kSplit64: FF_SPLIT_TYPES(kSplit64, 2, 2, 1, 1, 1, CALL)           \
     case kSplit128x64: FF_SPLIT_TYPES(kSplit128x64, 2, 2, 2, 2, 1, CALL)   \
+    case kSplit128W4:                                                      \
+        static_assert(split_shape_waves(kSplit128W4) == 4, "2 x 2 x 1");   \
+        return CALL(__bf16, 2, 2, 1, 2, 2);                                \
     default: FF_SPLIT_TYPES(kSplit128, 2, 2, 2, 2, 2, CALL)                \
     }
 
