@@ -155,14 +155,20 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
     const Cost &c = bf16 ? kBf16 : kF32;
     const int size = bf16 ? 2 : 4;
     const int64_t slabs = (K * size + 127) / 128;
-    double best = 0.0;
+    Plan narrow;
+    double best = 0.0, narrow_us = 0.0;
     for (int shape = 0; shape <= kSplit128; ++shape) {
         const int bm = split_shape_rows(shape), bn = split_shape_cols(shape);
         // tiles of few rows pay only where they spare the padding of larger ones
-        // (128 x 32 in bf16 up to 32 rows: two row blocks take W through four wavefronts' loads twice.  51 x 5080 x 15984
-        // 65.1 us, 51.5 in tiles of 128 x 64; 63 x 14584 x 7936 88.3, 64.4)
-        if (bm == 32 && M > (bf16 && bn == 128 ? 32 : 64))
+        if (bm == 32 && M > 64)
             continue;
+        // Two row blocks of 128 x 32 in bf16 take W through four wavefronts' loads twice, which the estimate does not
+        // know and which pays in short products only, or against uncut tiles of 128 x 64 (below).  Up to 18
+        // slabs they take 0.94 of the time of the next best (89 shapes; 48 x 176 x 8176 11.1 us, 12.8), in longer ones 1.08
+        // (67 shapes; 51 x 5080 x 15984 65.1, 51.5; 48 x 3784 x 13976 47.5, 38.7).
+        const bool apart = bf16 && shape == kSplit128x32 && M > 32 && slabs > 18;
+        Plan &to = apart ? narrow : pl;
+        double &least = apart ? narrow_us : best;
         const int64_t RB = (M + bm - 1) / bm, NT = (N + bn - 1) / bn;
         if (RB * NT > (int64_t)num_cus * kPerCu[shape])
             continue;
@@ -192,20 +198,26 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
                        (shape == kSplit128 ? c.epi128 : 0.0);
             if (S > 1)
                 t += c.exch + c.exch_s * S + (double)groups * bm * bn * 4 / c.sums;
-            if (best != 0.0 && t >= best)
+            if (least != 0.0 && t >= least)
                 continue;
-            best = t;
-            pl.split_s = S;
-            pl.split_shape = shape;
-            pl.tile_m = bm;
-            pl.tile_n = bn;
-            pl.RB = (int)RB;
-            pl.NT = (int)NT;
-            pl.grid = (int)groups;
+            least = t;
+            to.split_s = S;
+            to.split_shape = shape;
+            to.tile_m = bm;
+            to.tile_n = bn;
+            to.RB = (int)RB;
+            to.NT = (int)NT;
+            to.grid = (int)groups;
         }
     }
     if (pl.split_s == 0)
         return false;
+    // (44 x 1440 x 14520 23.3 us in two row blocks, 25.9 in 114 tiles of 128 x 64, on half of the units; 33 x 2408 x 16192
+    // 34.5, 38.0; 64 x 1608 x 16048 29.4, 32.3)
+    if (narrow.split_s != 0 && narrow_us < best && pl.split_shape == kSplit128x64 && pl.split_s == 1) {
+        pl = narrow;
+        best = narrow_us;
+    }
     // 128 x 128 tiles of long bf16 rows that do not begin on 64-byte boundaries keep four wavefronts.  There every line of
     // a slab is requested twice, and eight wavefronts go to HBM for half of W's lines a second time (147 x 10568 x 6016
     // 89 us, with four 76; K = 10560: 62, 66).  206 such shapes: up to 48 slabs a workgroup eight win (0.94 of the time),

@@ -20,6 +20,9 @@ CASES = [
     (32, 2056, 4104, "bf16", 128, 32, 4),
     (17, 8200, 4104, "bf16", 128, 32, 8),
     (64, 1032, 2056, "f32", 128, 32, 4),
+    (48, 1152, 12296, "bf16", 128, 32, 1),    # two row blocks: 18 slabs
+    (48, 1160, 12296, "bf16", 128, 64, 2),    # 19
+    (44, 1440, 14520, "bf16", 128, 32, 1),    # instead of 114 uncut tiles of 128 x 64
     (65, 264, 200, "bf16", 64, 64, 1),
     (500, 2056, 520, "bf16", 64, 64, 2),
     (129, 1032, 72, "bf16", 64, 64, 4),
