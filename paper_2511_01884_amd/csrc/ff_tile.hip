@@ -134,12 +134,14 @@ __device__ __forceinline__ float from_lane(float v, int lane)
     return __int_as_float(__builtin_amdgcn_ds_bpermute(lane << 2, __float_as_int(v)));
 }
 
-// LDS placement of 16-byte chunk `c` (0..7) of tile row `row`: chunks are XORed
-// with row bits so that the consecutive rows a fragment read touches per pass
-// (stride 128 B) spread over all banks, for 8-lane and for 16-lane passes.  That is so for blocks of 32 rows: 2.8 % of the
-// LDS cycles of a bf16 4096^3 product were conflicts.  Blocks of 16, whose lane groups read neighbouring chunks of the
-// same 16 rows, have 49 %.
-__device__ __forceinline__ int swizzle_of_row(int row) { return (row & 7) ^ ((row >> 3) & 1); }
+// LDS placement of 16-byte chunk `c` (0..7) of tile row `row`: slot c ^ swizzle, so that the rows a fragment read touches
+// spread over all 64 banks (two rows to 256 bytes).  The LDS serves such a read sixteen lanes at a time, 0-3 with 12-15,
+// 20-23 and 24-27 and so on: in blocks of 32 sixteen rows of one chunk, in blocks of 16 eight rows of one chunk and the
+// eight between them of its neighbour.  This swizzle has no conflict in either (255 bytes a clock of a unit read by eight
+// wavefronts; with row & 7 ^ row >> 3 & 1, free in blocks of 32 only, 128 in blocks of 16, and half of a bf16 product's LDS
+// cycles were conflicts).  The chip's power sets the rate of a long product, so that the time gains little: 4096^3 bf16 105.9 ->
+// 105.3 us, 8192 x 4096 x 16384 861 -> 856, 16384 x 512 x 4096 110.8 -> 109.6.
+__device__ __forceinline__ int swizzle_of_row(int row) { return (row >> 1) & 7; }
 
 // RAGGED_N: N is not a multiple of the tile width, so the last tile of each row
 // masks the columns at or beyond N in the statistics (chosen on the host).
