@@ -98,7 +98,17 @@ template <> struct RawCols<__bf16> {
 // bf16, 4 % faster in long fp32 products and 0.3 us slower in short ones.  Both point at the rate at which a unit's
 // loads reach its LDS: 57 bytes a nanosecond.)  The plan keeps four in the 128 x 128 tile for long rows off the 64-byte
 // boundaries.
-template <typename T, int kWN, int kWM, int kWK, int WTN, int WTM>
+//
+// LINES: what travels is not a tile row's 128 bytes of a slab but the 128-byte line of memory that holds its beginning.  Rows
+// that do not begin on line boundaries have two lines to every slab, and a unit's load path, which takes 27 bytes a
+// clock and a line at a time, is what bounds these shapes; each line is now requested once.  Rows begin on 16-byte
+// boundaries, that is on a chunk: chunk c of a row's slab i is chunk (c + lead) % 8 of its line i, or of line i + 1 where
+// c + lead >= 8, and lies in LDS at the slot that it would have without the shift, so that only the stage it is read from
+// differs between lanes.  Slab i needs lines i and i + 1: one line less is in flight and a share has one line more, which
+// short shares and W that lies in the L2 do not earn back (takes_lines).
+// 512 x 4104 x 4096 33.2 us, now 30.1; 237 x 6408 x 7648 62.1, 50.8; 2089 x 2952 x 1232 40.3, 31.4; 96 x 8200 x 8192 48.2,
+// 39.3; the same bits.
+template <typename T, int kWN, int kWM, int kWK, int WTN, int WTM, bool LINES>
 __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN == 1 ? 2 : 1) void split_kernel(const SplitParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)  // the body uses device-only types (buffer descriptors)
@@ -165,21 +175,32 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     const int full = total - (total > 0 && sl1 * kSlabElems > K ? 1 : 0);  // the rest: the slab that K cuts
 
     const size_t row_stride = (size_t)K * sizeof(T);
-    const char *w_tile = (const char *)p.W + (size_t)n0 * row_stride + (size_t)sl0 * kRowBytes;
-    const char *x_tile = (const char *)p.X + (size_t)m0 * row_stride + (size_t)sl0 * kRowBytes;
+    // LINES: a row's first chunk is chunk `lead` of its first line; a tile begins at a multiple of
+    // eight rows, so that the lead of its row r is (phase + r * row_chunks) % 8.
+    const int row_chunks = K / kChunkElems;
+    const int w_phase = LINES ? (int)(reinterpret_cast<uintptr_t>(p.W) >> 4) & 7 : 0;
+    const int x_phase = LINES ? (int)(reinterpret_cast<uintptr_t>(p.X) >> 4) & 7 : 0;
+    const char *w_tile = (const char *)p.W - w_phase * 16 + (size_t)n0 * row_stride + (size_t)sl0 * kRowBytes;
+    const char *x_tile = (const char *)p.X - x_phase * 16 + (size_t)m0 * row_stride + (size_t)sl0 * kRowBytes;
+    auto lead = [&](int phase, int r) { return LINES ? (phase + r * row_chunks) & 7 : 0; };
+    // where the line (LINES) or slab of row r begins, and the chunk of it that lies in `slot` of row `row` in LDS
+    auto line_offset = [&](int phase, int row, int r, int slot) {
+        const unsigned at = (unsigned)r * (unsigned)row_stride + phase * 16;
+        return (LINES ? at & ~127u : at) + ((((slot ^ swizzle_of_row(row)) + lead(phase, r)) & 7) << 4);
+    };
     unsigned offa[kDmaA], offb[kDmaB];
     // lane -> (row of an instruction's eight, stored chunk slot); rows beyond the matrix read its last row
 #pragma unroll
     for (int j = 0; j < kDmaA; ++j) {
         const int row = wave * (BN / kWaves) + j * 8 + (lane >> 3);
         const int rr = n0 + row < N ? row : N - 1 - n0;
-        offa[j] = (unsigned)rr * (unsigned)row_stride + (((lane & 7) ^ swizzle_of_row(row)) << 4);
+        offa[j] = line_offset(w_phase, row, rr, lane & 7);
     }
 #pragma unroll
     for (int j = 0; j < kDmaB; ++j) {
         const int row = wave * (BM / kWaves) + j * 8 + (lane >> 3);
         const int rr = m0 + row < M ? row : M - 1 - m0;
-        offb[j] = (unsigned)rr * (unsigned)row_stride + (((lane & 7) ^ swizzle_of_row(row)) << 4);
+        offb[j] = line_offset(x_phase, row, rr, lane & 7);
     }
     // Addresses are in bounds by construction: a tile's rows span at most 2^30 bytes.  An offset of kRangeBytes is
     // outside, and such a lane puts zeros into its place in LDS: the chunks of the last slab that lie beyond K.
@@ -210,7 +231,13 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
         for (int x = 0; x < kDma; ++x) {
             const int row = x < kDmaA ? wave * (BN / kWaves) + x * 8 : wave * (BM / kWaves) + (x - kDmaA) * 8;
             const int chunk = (lane & 7) ^ swizzle_of_row(row + (lane >> 3));
-            dma_one(i, x, (sl0 + i) * kSlabElems + chunk * kChunkElems < K);
+            int first = (sl0 + i) * 8;  // chunk of the matrix row that a slab or line begins with
+            if (LINES) {
+                const int r = row + (lane >> 3), last = x < kDmaA ? N - 1 - n0 : M - 1 - m0;
+                const int ld = lead(x < kDmaA ? w_phase : x_phase, r < last ? r : last);
+                first -= chunk + ld >= 8 ? 8 : 0;
+            }
+            dma_one(i, x, (unsigned)(first + chunk) < (unsigned)row_chunks);
         }
     };
 
@@ -225,19 +252,23 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     const int swz = swizzle_of_row(l32);
     const int a_base = (wn * WTN * 32 + l32) * kRowBytes;
     const int b_base = (BN + wm * WTM * 32 + l32) * kRowBytes;
+    const int a_lead = lead(w_phase, l32), b_lead = lead(x_phase, l32);
     auto multiply = [&](int stage) {
         const char *st = smem + stage * kStageBytes;
+        const int ahead = stage + 1 < kRing ? kStageBytes : -(kRing - 1) * kStageBytes;  // the next line's stage
         constexpr int kSteps = 4 / kWK;
         uintx4 a[kSteps][WTN], b[kSteps][WTM];
 #pragma unroll
         for (int ks = 0; ks < kSteps; ++ks) {
-            const int coff = ((2 * (wk * kSteps + ks) + h) ^ swz) << 4;
+            const int chunk = 2 * (wk * kSteps + ks) + h, coff = (chunk ^ swz) << 4;
+            const int a_off = a_base + coff + (LINES && chunk + a_lead >= 8 ? ahead : 0);
+            const int b_off = b_base + coff + (LINES && chunk + b_lead >= 8 ? ahead : 0);
 #pragma unroll
             for (int i = 0; i < WTN; ++i)
-                a[ks][i] = *reinterpret_cast<const uintx4 *>(st + a_base + i * 32 * kRowBytes + coff);
+                a[ks][i] = *reinterpret_cast<const uintx4 *>(st + a_off + i * 32 * kRowBytes);
 #pragma unroll
             for (int j = 0; j < WTM; ++j)
-                b[ks][j] = *reinterpret_cast<const uintx4 *>(st + b_base + j * 32 * kRowBytes + coff);
+                b[ks][j] = *reinterpret_cast<const uintx4 *>(st + b_off + j * 32 * kRowBytes);
         }
         __builtin_amdgcn_sched_barrier(0);  // all reads are under way before the first product waits for its own
 #pragma unroll
@@ -250,14 +281,21 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     };
 
     // ---- main loop ----
+    if constexpr (LINES) {
 #pragma unroll
-    for (int t = 0; t < kRing - 1; ++t)
-        if (t < full)
-            request(t);
-    if (__builtin_expect(total > full && total < kRing, 0))
-        request_cut(total - 1);
+        for (int t = 0; t < kRing - 1; ++t)
+            if (total > 0 && t <= total)
+                request_cut(t);
+    } else {
+#pragma unroll
+        for (int t = 0; t < kRing - 1; ++t)
+            if (t < full)
+                request(t);
+        if (__builtin_expect(total > full && total < kRing, 0))
+            request_cut(total - 1);
+    }
     if (p.timeline != nullptr) {  // the first slab has landed
-        if (total >= kRing - 1)
+        if (!LINES && total >= kRing - 1)
             wait_vm<(kRing - 2) * kDma>();
         else
             wait_vm<0>();
@@ -266,18 +304,36 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     stamp(1);
     stamp(kTimelineCycleSlot);
     int i = 0;
-    for (; i + kRing - 1 < full; ++i) {
-        wait_vm<(kRing - 2) * kDma>();  // this wave's rows of slab i have landed
-        lds_barrier();                  // everyone's have, and everyone has read slab i - 1
-        request(i + kRing - 1);  // into the stage slab i - 1 occupied
-        multiply(i % kRing);
-    }
-    if (__builtin_expect(i + kRing - 1 < total, 0)) {  // the last slab, cut by K
-        wait_vm<(kRing - 2) * kDma>();
-        lds_barrier();
-        request_cut(i + kRing - 1);
-        multiply(i % kRing);
-        ++i;
+    if constexpr (LINES) {
+        // Slab i needs lines i and i + 1; line i - 1 is done with.  Lines that a row's end cuts, or that lie behind it: the
+        // last two of the row.
+        const int whole = row_chunks / 8 - 1 - sl0 < total ? row_chunks / 8 - 1 - sl0 : total;
+        for (; i + kRing - 1 <= whole; ++i) {
+            wait_vm<(kRing - 3) * kDma>();
+            lds_barrier();
+            request(i + kRing - 1);
+            multiply(i % kRing);
+        }
+        for (; i + kRing - 1 <= total; ++i) {
+            wait_vm<(kRing - 3) * kDma>();
+            lds_barrier();
+            request_cut(i + kRing - 1);
+            multiply(i % kRing);
+        }
+    } else {
+        for (; i + kRing - 1 < full; ++i) {
+            wait_vm<(kRing - 2) * kDma>();  // this wave's rows of slab i have landed
+            lds_barrier();                  // everyone's have, and everyone has read slab i - 1
+            request(i + kRing - 1);  // into the stage slab i - 1 occupied
+            multiply(i % kRing);
+        }
+        if (__builtin_expect(i + kRing - 1 < total, 0)) {  // the last slab, cut by K
+            wait_vm<(kRing - 2) * kDma>();
+            lds_barrier();
+            request_cut(i + kRing - 1);
+            multiply(i % kRing);
+            ++i;
+        }
     }
     auto last = [&](auto left_c) {
         constexpr int left = decltype(left_c)::value;
@@ -289,7 +345,8 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
         }
     };
     static_assert(kRing == 4, "the last slabs");
-    last(std::integral_constant<int, 2>());
+    if constexpr (!LINES)
+        last(std::integral_constant<int, 2>());
     last(std::integral_constant<int, 1>());
     last(std::integral_constant<int, 0>());
     stamp(2);
@@ -569,22 +626,52 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     default: FF_SPLIT_TYPES(kSplit128, 2, 2, 2, 2, 2, CALL)                \
     }
 
+// The instances that exist by lines: bf16, tiles of 128 columns and 64 or 128 rows.  (In fp32, bound by the matrix units, lines
+// take 1 to 4 % more time, in the smaller tiles 0 to 8 %.)
+template <typename T, int WN, int WM, int WTN, int WTM> static constexpr bool has_lines()
+{
+    return sizeof(T) == 2 && WN * WTN == 4 && WM * WTM >= 2;
+}
+
+// Whether such a launch goes by lines: rows off the line boundaries, and enough slabs for each workgroup.  170 shapes, M
+// 33..2048: rows on every other 64-byte boundary, or K cut over four and more workgroups (narrow W mostly, which the L2
+// holds), gain from 24 slabs on (0.92 of the time; 10 to 23: 1.01), the rest from 9 (0.93; below 1.03).  The four wavefronts of the
+// long rows gain 0.84 where X and W together are beyond 72 MB; below, other row blocks find the second half of
+// a line in the L2, and they lose 1.01.
+static bool takes_lines(const SplitParams &p, int waves)
+{
+    const unsigned off = ((unsigned)p.K * 2u | (unsigned)(uintptr_t)p.W | (unsigned)(uintptr_t)p.X) & 127u;
+    if (off == 0)
+        return false;
+    if (waves == 4)
+        return ((double)p.M + (double)p.N) * (double)p.K * 2.0 > 72e6;
+    const int slabs = (p.K + 63) / 64, per = (slabs + p.S - 1) / p.S;
+    return per >= (off % 64 == 0 || p.S >= 4 ? 24 : 9);
+}
+
 template <typename T, int WN, int WM, int WK, int WTN, int WTM>
 static hipError_t launch_split(const SplitParams &p, int grid, hipStream_t stream)
 {
-    hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM>), dim3(grid), dim3(64 * WN * WM * WK), 0, stream, p);
+    if constexpr (has_lines<T, WN, WM, WTN, WTM>())
+        if (takes_lines(p, WN * WM * WK)) {
+            hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM, true>), dim3(grid), dim3(64 * WN * WM * WK), 0, stream, p);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM, false>), dim3(grid), dim3(64 * WN * WM * WK), 0, stream, p);
     return hipGetLastError();
 }
 
 template <typename T, int WN, int WM, int WK, int WTN, int WTM>
 static int split_blocks()
 {
-    int a = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, split_kernel<T, WN, WM, WK, WTN, WTM>, 64 * WN * WM * WK, 0) != hipSuccess) {
+    int a = 0, b = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, split_kernel<T, WN, WM, WK, WTN, WTM, false>, 64 * WN * WM * WK, 0) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, split_kernel<T, WN, WM, WK, WTN, WTM, has_lines<T, WN, WM, WTN, WTM>()>,
+                                                     64 * WN * WM * WK, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
-    return a;
+    return a < b ? a : b;
 }
 
 hipError_t launch_split_kernel(bool bf16, int shape, const SplitParams &p, int grid, hipStream_t stream)
