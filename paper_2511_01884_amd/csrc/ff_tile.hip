@@ -21,6 +21,8 @@
 // Modes: kFused (above), kTwoPass (writes fp32 G and the partials; a second
 // kernel normalises — used when a row has more tiles than co-resident
 // workgroups), kLinearOnly (test hook: fp32 Z = X W^T + b).
+#include <algorithm>
+
 #include "ff_tile.hpp"
 
 namespace ff {
@@ -155,11 +157,18 @@ __device__ __forceinline__ int swizzle_of_row(int row) { return (row >> 1) & 7; 
 // STAGES: slabs the LDS has room for beside the parameters, two at 256 x 256 and where two workgroups share a unit,
 // three at 256 x 128 (one per unit): there two slabs travel while one is multiplied.
 //
+// LINES: what travels is not a tile row's 128 bytes of a slab but the 128-byte line of memory that holds its beginning, so that
+// rows that do not begin on line boundaries still have one request a slab (a unit's load path takes 27 bytes a clock and a
+// line at a time).  Rows begin on 16-byte boundaries, that is on a chunk: chunk c of a row's slab i is chunk (c + lead) % 8 of its
+// line i, or of line i + 1 where c + lead >= 8, and lies in LDS at the slot that it would have without the shift, so that
+// only the stage it is read from differs between lanes.  Slab i needs lines i and i + 1: three stages, two slabs' time less
+// one.  4462 x 3848 x 952 67.9 us, now 61.8; 1024 x 4104 x 8192 72.6, 65.6; the same bits.
+//
 // Launch bound: 512 threads also where four wavefronts are launched, if 256 registers hold all of one's values.  Left with
 // 512, the compiler keeps the accumulators in the other half and copies them out and back at every pin_order.
 constexpr int launch_bound(int waves, int part) { return part >= 16 ? 64 * waves : 512; }
 
-template <typename T, int kWavesN, int kWavesM, int WTN, int WTM, int MODE, bool RAGGED_N, int STAGES>
+template <typename T, int kWavesN, int kWavesM, int WTN, int WTM, int MODE, bool RAGGED_N, int STAGES, bool LINES>
 __global__ __launch_bounds__(launch_bound(kWavesN * kWavesM, WTN * WTM), (kWavesN * kWavesM * WTN * WTM <= 32) ? 2 : 1)
 void tile_kernel(const TileParams p)
 {
@@ -271,24 +280,34 @@ void tile_kernel(const TileParams p)
         // DMA lane geometry: lane -> (row within a 16-row group, stored chunk slot)
         const int dma_r = lane / kChunksPerRow;
         const int dma_cs = lane % kChunksPerRow;
+        // LINES: a row's first chunk is chunk `lead` of its first line; a tile begins at a multiple of eight rows, so that the
+        // lead of its row r is (phase + r * row_chunks) % 8.
+        const int row_chunks = K / kChunkElems;
+        const int w_phase = LINES ? (int)(reinterpret_cast<uintptr_t>(p.W) >> 4) & 7 : 0;
+        const int x_phase = LINES ? (int)(reinterpret_cast<uintptr_t>(p.X) >> 4) & 7 : 0;
+        auto lead = [&](int phase, int r) { return LINES ? (phase + r * row_chunks) & 7 : 0; };
+        const int a_lead = lead(w_phase, block_row), b_lead = lead(x_phase, block_row);
+        // where the line (LINES) or slab of row r begins, and the chunk of it that lies in `slot` of row `row` in LDS
+        auto line_offset = [&](int phase, int row, int r, int slot) {
+            const unsigned at = (unsigned)r * (unsigned)row_stride + phase * 16;
+            return (LINES ? at & ~127u : at) + ((((slot ^ swizzle_of_row(row)) + lead(phase, r)) & 7) << 4);
+        };
 
         // ---- per-lane byte offsets of the DMA sources, relative to the tile's first row ----
-        const char *w_tile = (const char *)p.W + (size_t)n0 * row_stride;
-        const char *x_tile = (const char *)p.X + (size_t)m0 * row_stride;
+        const char *w_tile = (const char *)p.W - w_phase * 16 + (size_t)n0 * row_stride;
+        const char *x_tile = (const char *)p.X - x_phase * 16 + (size_t)m0 * row_stride;
         unsigned offa[kDmaA], offb[kDmaB];
 #pragma unroll
         for (int j = 0; j < kDmaA; ++j) {
             const int row = wave * (BN / kWaves) + j * kRowsPerDma + dma_r;
-            const int c = dma_cs ^ swizzle_of_row(row);
             const int rr = (n0 + row < N) ? row : (N - 1 - n0);  // clamp to the last valid row
-            offa[j] = (unsigned)rr * (unsigned)row_stride + c * 16;
+            offa[j] = line_offset(w_phase, row, rr, dma_cs);
         }
 #pragma unroll
         for (int j = 0; j < kDmaB; ++j) {
             const int row = wave * (BM / kWaves) + j * kRowsPerDma + dma_r;
-            const int c = dma_cs ^ swizzle_of_row(row);
             const int rr = (m0 + row < M) ? row : (M - 1 - m0);
-            offb[j] = (unsigned)rr * (unsigned)row_stride + c * 16;
+            offb[j] = line_offset(x_phase, row, rr, dma_cs);
         }
 
         // full slab: direct-to-LDS, nothing passes through registers.  dma_one issues
@@ -332,7 +351,12 @@ void tile_kernel(const TileParams p)
             for (int x = 0; x < (half == 0 ? kDmaA : kDmaB); ++x) {
                 const int row = wave * ((half == 0 ? BN : BM) / kWaves) + x * kRowsPerDma + lane_c / kChunksPerRow;
                 const int c = (lane_c % kChunksPerRow) ^ swizzle_of_row(row);
-                const bool in = slab * kSlabElems + c * kChunkElems < K;
+                int first = slab * kChunksPerRow;  // chunk of the matrix row that the slab or line begins with
+                if (LINES) {
+                    const int last = half == 0 ? N - 1 - n0 : M - 1 - m0;
+                    first -= c + lead(half == 0 ? w_phase : x_phase, row < last ? row : last) >= 8 ? 8 : 0;
+                }
+                const bool in = (unsigned)(first + c) < (unsigned)row_chunks;
                 char *dst = smem + stage * kStageBytes + (half == 0 ? 0 : kABytes) +
                             wave * ((half == 0 ? BN : BM) / kWaves) * kRowBytes + x * 1024;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -358,15 +382,18 @@ void tile_kernel(const TileParams p)
         // Fragments: W's in one buffer, each read again for the next k-step as soon as its products are issued; X's,
         // which every group of products reads, in two, by k-step.
         uintx4 fa[kBlocksN], fb[2][kBlocksM];
+        // byte offset of k-step s of the slab in `stage`; LINES: the line behind it where the shift carries the chunk there
+        auto step_offset = [&](int stage, int s, int ld) {
+            const int c = s * kLaneGroups + group;
+            const int ahead = stage + 1 < STAGES ? kStageBytes : -(STAGES - 1) * kStageBytes;
+            return stage * kStageBytes + ((c ^ frag_swz) << 4) + (LINES && c + ld >= 8 ? ahead : 0);
+        };
         auto read_a = [&](int stage, int s, int x) {
-            const int coff = ((s * kLaneGroups + group) ^ frag_swz) << 4;
-            fa[x] = *reinterpret_cast<const uintx4 *>(smem + stage * kStageBytes + a_frag_base +
-                                                      x * kBlock * kRowBytes + coff);
+            fa[x] = *reinterpret_cast<const uintx4 *>(smem + step_offset(stage, s, a_lead) + a_frag_base + x * kBlock * kRowBytes);
         };
         auto read_b = [&](int stage, int s, int x) {
-            const int coff = ((s * kLaneGroups + group) ^ frag_swz) << 4;
-            fb[s & 1][x] = *reinterpret_cast<const uintx4 *>(smem + stage * kStageBytes + b_frag_base +
-                                                             x * kBlock * kRowBytes + coff);
+            fb[s & 1][x] = *reinterpret_cast<const uintx4 *>(smem + step_offset(stage, s, b_lead) + b_frag_base +
+                                                             x * kBlock * kRowBytes);
         };
         // The products of a k-step are issued in groups, one per fragment of W.
         auto products = [&](int g, int s) {
@@ -410,7 +437,7 @@ void tile_kernel(const TileParams p)
         static_assert((STAGES == 2 || STAGES == 3) && kSync < kBlocksN, "the waits of the last slabs; reads behind the barrier");
         enum { kNoDma = 0, kDmaFull = 1, kDmaCut = 2 };
         auto request = [&](int slab, int stage) {
-            if (!k_ragged || slab + 1 < slabs) {
+            if (!LINES && (!k_ragged || slab + 1 < slabs)) {
 #pragma unroll
                 for (int x = 0; x < kDmaPerSlab; ++x)
                     dma_one(slab, stage, x);
@@ -438,18 +465,22 @@ void tile_kernel(const TileParams p)
         }
         lds_barrier();
         request(0, 0);
+        constexpr int kFirst = LINES ? 2 : 1;  // slabs or lines that the first slab's products need
+        const int requests = LINES ? slabs + 1 : slabs;
+        if (LINES)
+            request(1, 1);
         // (The slabs after the first are requested behind the first fragment reads: their instructions ahead of the wait
         // delayed the start of every tile by 1 us.  A workgroup's first tile has nothing to wait for but slab 0.)
-        const bool ahead = first_tile && p.timeline == nullptr && slabs >= STAGES;
+        const bool ahead = first_tile && p.timeline == nullptr && requests >= STAGES;
         auto request_early = [&]() {
 #pragma unroll
-            for (int t = 1; t < STAGES; ++t)
-                if (t < slabs)
+            for (int t = kFirst; t < STAGES; ++t)
+                if (t < requests)
                     request(t, t);
         };
         if (ahead) {
             request_early();
-            wait_vm<(STAGES - 1) * kDmaPerSlab>();  // slab 0 landed
+            wait_vm<(STAGES - kFirst) * kDmaPerSlab>();  // slab 0 landed
         } else {
             wait_vm<0>();  // also the previous tile's stores, whose completion order relative to loads is not relied on
         }
@@ -515,21 +546,39 @@ void tile_kernel(const TileParams p)
             stage = next;
         };
         using std::integral_constant;
-        while (i < slabs - STAGES - (k_ragged ? 1 : 0)) {
-            steps_inside(stage);
-            step_last(integral_constant<int, STAGES - 2>(), integral_constant<int, kDmaFull>());
-        }
-        if (k_ragged && slabs > STAGES) {
-            steps_inside(stage);
-            step_last(integral_constant<int, STAGES - 2>(), integral_constant<int, kDmaCut>());
-        }
-        if (STAGES == 3 && slabs > 2) {
-            steps_inside(stage);
-            step_last(integral_constant<int, 1>(), integral_constant<int, kNoDma>());
-        }
-        if (slabs > 1) {
-            steps_inside(stage);
-            step_last(integral_constant<int, 0>(), integral_constant<int, kNoDma>());
+        if constexpr (LINES) {
+            // Slab i + 1 needs lines i + 1 and i + 2; line i is done with.  A row's end cuts its last line or the one before.
+            static_assert(!LINES || STAGES == 3, "a line more than two slabs' in LDS");
+            const int whole = row_chunks / 8 - 1;
+            while (i + STAGES <= whole) {
+                steps_inside(stage);
+                step_last(integral_constant<int, 0>(), integral_constant<int, kDmaFull>());
+            }
+            while (i + STAGES <= slabs) {
+                steps_inside(stage);
+                step_last(integral_constant<int, 0>(), integral_constant<int, kDmaCut>());
+            }
+            while (i + 1 < slabs) {
+                steps_inside(stage);
+                step_last(integral_constant<int, 0>(), integral_constant<int, kNoDma>());
+            }
+        } else {
+            while (i < slabs - STAGES - (k_ragged ? 1 : 0)) {
+                steps_inside(stage);
+                step_last(integral_constant<int, STAGES - 2>(), integral_constant<int, kDmaFull>());
+            }
+            if (k_ragged && slabs > STAGES) {
+                steps_inside(stage);
+                step_last(integral_constant<int, STAGES - 2>(), integral_constant<int, kDmaCut>());
+            }
+            if (STAGES == 3 && slabs > 2) {
+                steps_inside(stage);
+                step_last(integral_constant<int, 1>(), integral_constant<int, kNoDma>());
+            }
+            if (slabs > 1) {
+                steps_inside(stage);
+                step_last(integral_constant<int, 0>(), integral_constant<int, kNoDma>());
+            }
         }
         steps_inside(stage);
         step_last(integral_constant<int, -1>(), integral_constant<int, kNoDma>());
@@ -930,16 +979,38 @@ __global__ __launch_bounds__(256) void finalize_kernel(const FinalizeParams p)
     }
 }
 
+// The instances that exist by lines: fused bf16 where LDS has a third stage.
+template <typename T, int MODE, int STAGES> constexpr bool has_lines() { return sizeof(T) == 2 && MODE == kFused && STAGES == 3; }
+// Whether such a launch goes by lines.  13 shapes with rows at every 16 bytes: 0.94 of the time (0.90 to 1.00).  At every 32 bytes
+// 0.96 of it with eight row-blocks and more, which find lines in the L2; with fewer every line comes from HBM, and one
+// line less in flight costs more (275 x 4240 x 13312 87.1 us, by lines 90.8).  At every 64 bytes it always does (3840 x 5408 x
+// 1280 73.5, 78.9).
+bool takes_lines(const TileParams &p)
+{
+    const unsigned off = ((unsigned)p.K * 2u | (unsigned)(uintptr_t)p.W | (unsigned)(uintptr_t)p.X) & 127u;
+    return off != 0 && (off % 32 != 0 || (off % 64 != 0 && p.RB >= 8));
+}
+
 template <typename T, int WN, int WM, int WTN, int WTM, int MODE, int STAGES>
 hipError_t launch_tile(const TileParams &p, int grid, hipStream_t stream)
 {
     constexpr int BN = WN * WTN * 32;
     constexpr int kThreads = 64 * WN * WM;
+    if constexpr (has_lines<T, MODE, STAGES>())
+        if (takes_lines(p)) {
+            if (p.N % BN != 0)
+                hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, true, STAGES, true>), dim3(grid), dim3(kThreads), 0,
+                                   stream, p);
+            else
+                hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, false, STAGES, true>), dim3(grid), dim3(kThreads), 0,
+                                   stream, p);
+            return hipGetLastError();
+        }
     if (p.N % BN != 0)
-        hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, true, STAGES>), dim3(grid), dim3(kThreads), 0,
+        hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, true, STAGES, false>), dim3(grid), dim3(kThreads), 0,
                            stream, p);
     else
-        hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, false, STAGES>), dim3(grid), dim3(kThreads), 0,
+        hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, false, STAGES, false>), dim3(grid), dim3(kThreads), 0,
                            stream, p);
     return hipGetLastError();
 }
@@ -947,16 +1018,23 @@ hipError_t launch_tile(const TileParams &p, int grid, hipStream_t stream)
 template <typename T, int WN, int WM, int WTN, int WTM, int MODE, int STAGES>
 int max_blocks_per_cu()
 {
-    int a = 0, b = 0;
-    constexpr int kThreads = 64 * WN * WM;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, tile_kernel<T, WN, WM, WTN, WTM, MODE, true, STAGES>,
-                                                     kThreads, 0) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, tile_kernel<T, WN, WM, WTN, WTM, MODE, false, STAGES>,
-                                                     kThreads, 0) != hipSuccess) {
-        (void)hipGetLastError();
-        return 0;
+    int least = 0;
+    auto ask = [&](auto kernel) {
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 64 * WN * WM, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            n = 0;
+        }
+        return n;
+    };
+    constexpr bool kLines = has_lines<T, MODE, STAGES>();
+    least = ask(tile_kernel<T, WN, WM, WTN, WTM, MODE, true, STAGES, false>);
+    least = std::min(least, ask(tile_kernel<T, WN, WM, WTN, WTM, MODE, false, STAGES, false>));
+    if (kLines) {
+        least = std::min(least, ask(tile_kernel<T, WN, WM, WTN, WTM, MODE, true, STAGES, kLines>));
+        least = std::min(least, ask(tile_kernel<T, WN, WM, WTN, WTM, MODE, false, STAGES, kLines>));
     }
-    return a < b ? a : b;
+    return least;
 }
 
 }  // namespace
