@@ -4,6 +4,7 @@
 #include <mutex>
 #include <vector>
 #include <algorithm>
+#include <cstring>
 
 #include "../../include/ff.h"
 #include "ff_tile.hpp"
@@ -54,6 +55,8 @@ struct DeviceState {
     void *no_alloc_ptr = nullptr;            // this device's copy of `scratch`, once asked for
     void *no_alloc_sums = nullptr;           // the same for `scratch_sums`
     bool no_alloc_used = false;
+    void *pinned = nullptr;                  // host memory that the selection's kernels write their results to
+    size_t pinned_bytes = 0;
     unsigned long long *timeline = nullptr;  // test hook: phase timestamps of the tiled kernels
     size_t timeline_bytes = 0;
     signed char blocks_per_cu[2][kNumTileShapes][3] = {};  // cached occupancy answers [bf16][shape][mode], 0 = not asked
@@ -517,6 +520,29 @@ int prepare_workspace(DeviceState &st, size_t bytes, hipStream_t stream)
     return FF_OK;
 }
 
+// Host memory of at least `bytes` that kernels can write to, or null: up to 4 MiB a device, held until the process ends.
+// Used under the lock from launch to synchronisation, so that nothing is in flight when it is replaced by a larger one.
+// (A copy into pageable memory behind the kernels: eight tasks of 10 x 300 take 15 us longer.)
+constexpr size_t kPinnedMost = 4u << 20;
+void *pinned_results(DeviceState &st, size_t bytes)
+{
+    if (bytes > kPinnedMost)
+        return nullptr;
+    if (st.pinned_bytes < bytes) {
+        void *mem = nullptr;
+        const size_t want = std::min(kPinnedMost, round_up(2 * bytes, 64u << 10));
+        if (hipHostMalloc(&mem, want, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        if (st.pinned != nullptr)
+            (void)hipHostFree(st.pinned);
+        st.pinned = mem;
+        st.pinned_bytes = want;
+    }
+    return st.pinned;
+}
+
 // The largest workspace a call on this stream can have: what a caller bound, or during a capture what the
 // library already owns (growing it would be illegal), is fixed.
 size_t workspace_limit(DeviceState &st, hipStream_t stream)
@@ -976,52 +1002,71 @@ int ff_metric_selection(const double *values, const double *runtime, int64_t n_t
         DeviceState *st = current_device_state();
         if (!st)
             return FF_ERR_LAUNCH;
-        // Workspace: r and the verdicts of all tasks; for a batch of tasks, the columns' means and scales and
-        // the pair bits.  A batch is what 64 MiB hold, or a bound workspace.  Where that has no room for all
-        // verdicts (very many tasks of very few metrics), a batch's are copied out before the next.
         const size_t words = ((size_t)J + 63) / 64;
-        const size_t per_task = filter ? (size_t)J * (2 * sizeof(double) + words * sizeof(unsigned long long) + 1) : 0;
         const bool bound = st->ws != nullptr && !st->ws_owned;
         const size_t have = bound ? (st->ws_bytes > kCtrlBytes ? st->ws_bytes - kCtrlBytes : 0) : SIZE_MAX;
-        size_t out_bytes = round_up(count * (sizeof(double) + (filter ? 1 : 0)), 256);
-        const bool together = have >= out_bytes + per_task;
-        if (!together)
-            out_bytes = round_up(count * sizeof(double), 256);
-        int batch = n;
-        if (filter) {
-            const size_t fit = (bound ? (have > out_bytes ? have - out_bytes : 0) : (size_t)64 << 20) / per_task;
-            batch = (int)std::min<size_t>({(size_t)n, fit < 1 ? 1 : fit, 32768});
-        }
-        const int rc = prepare_workspace(*st, kCtrlBytes + out_bytes + (size_t)batch * per_task, st_stream);
-        if (rc != FF_OK)
-            return rc;
-        char *ws = static_cast<char *>(st->ws);
-        double *r_dev = reinterpret_cast<double *>(ws + kCtrlBytes);
-        double *mean_dev = filter ? reinterpret_cast<double *>(ws + kCtrlBytes + out_bytes) : nullptr;
-        double *inv_dev = filter ? mean_dev + (size_t)batch * J : nullptr;
-        unsigned long long *mask_dev = filter ? reinterpret_cast<unsigned long long *>(inv_dev + (size_t)batch * J) : nullptr;
-        unsigned char *batch_keep = reinterpret_cast<unsigned char *>(mask_dev + (filter ? (size_t)batch * J * words : 0));
-        for (int i = 0; i < n; i += batch) {
-            const int m = n - i < batch ? n - i : batch;
-            const double *vals = values + (size_t)i * V * J;
-            if (launch_pearson(vals, runtime + (size_t)i * V, r_dev + (size_t)i * J, mean_dev, inv_dev, m, V, J, st_stream) !=
-                hipSuccess)
+        const size_t result_bytes = count * (sizeof(double) + (filter ? 1 : 0));
+        // One launch does it all where a task fits the LDS and there is room for all tasks' bits.
+        const size_t mask_bytes = (size_t)n * selection_mask_bytes(J);
+        const bool one_launch = filter && selection_fits(V, J) && n <= 4096 && mask_bytes <= std::min(have, (size_t)64 << 20);
+        double *const pinned = static_cast<double *>(one_launch || !bound ? pinned_results(*st, result_bytes) : nullptr);
+        if (one_launch && pinned != nullptr) {
+            const int rc = prepare_workspace(*st, kCtrlBytes + mask_bytes, st_stream);
+            if (rc != FF_OK)
+                return rc;
+            char *ws = static_cast<char *>(st->ws);
+            if (launch_selection(values, runtime, pinned, reinterpret_cast<unsigned char *>(pinned + count),
+                                 reinterpret_cast<unsigned long long *>(ws + kCtrlBytes),
+                                 reinterpret_cast<unsigned *>(ws + kCounterOffset), collinear_tau, n, V, J, st_stream) != hipSuccess)
                 return FF_ERR_LAUNCH;
+        } else {
+            // Workspace: r and the verdicts of all tasks, unless they go to host memory; for a batch of tasks, the columns'
+            // means and scales and the pair bits.  A batch is what 64 MiB hold, or a bound workspace.  Where that has no
+            // room for all verdicts (very many tasks of very few metrics), a batch's are copied out before the next.
+            const size_t per_task = filter ? (size_t)J * (2 * sizeof(double) + words * sizeof(unsigned long long) + 1) : 0;
+            size_t out_bytes = pinned != nullptr ? 0 : round_up(result_bytes, 256);
+            const bool together = have >= out_bytes + per_task;
+            if (!together)
+                out_bytes = round_up(count * sizeof(double), 256);
+            int batch = n;
             if (filter) {
-                const size_t done = (size_t)i * J;
-                unsigned char *keep_dev = together ? reinterpret_cast<unsigned char *>(r_dev + count) + done : batch_keep;
-                if (launch_duplicate_filter(vals, mean_dev, inv_dev, collinear_tau, mask_dev, keep_dev, m, V, J,
-                                            st_stream) != hipSuccess)
-                    return FF_ERR_LAUNCH;
-                if (!together && hipMemcpyAsync(keep + done, keep_dev, (size_t)m * J, hipMemcpyDeviceToHost, st_stream) !=
-                                     hipSuccess)
-                    return FF_ERR_LAUNCH;
+                const size_t fit = (bound ? (have > out_bytes ? have - out_bytes : 0) : (size_t)64 << 20) / per_task;
+                batch = (int)std::min<size_t>({(size_t)n, fit < 1 ? 1 : fit, 32768});
             }
+            const int rc = prepare_workspace(*st, kCtrlBytes + out_bytes + (size_t)batch * per_task, st_stream);
+            if (rc != FF_OK)
+                return rc;
+            char *ws = static_cast<char *>(st->ws);
+            double *r_dev = pinned != nullptr ? pinned : reinterpret_cast<double *>(ws + kCtrlBytes);
+            double *mean_dev = filter ? reinterpret_cast<double *>(ws + kCtrlBytes + out_bytes) : nullptr;
+            double *inv_dev = filter ? mean_dev + (size_t)batch * J : nullptr;
+            unsigned long long *mask_dev = filter ? reinterpret_cast<unsigned long long *>(inv_dev + (size_t)batch * J) : nullptr;
+            unsigned char *batch_keep = reinterpret_cast<unsigned char *>(mask_dev + (filter ? (size_t)batch * J * words : 0));
+            for (int i = 0; i < n; i += batch) {
+                const int m = n - i < batch ? n - i : batch;
+                const double *vals = values + (size_t)i * V * J;
+                if (launch_pearson(vals, runtime + (size_t)i * V, r_dev + (size_t)i * J, mean_dev, inv_dev, m, V, J, st_stream) !=
+                    hipSuccess)
+                    return FF_ERR_LAUNCH;
+                if (filter) {
+                    const size_t done = (size_t)i * J;
+                    unsigned char *keep_dev = together ? reinterpret_cast<unsigned char *>(r_dev + count) + done : batch_keep;
+                    if (launch_duplicate_filter(vals, mean_dev, inv_dev, collinear_tau, mask_dev, keep_dev, m, V, J,
+                                                st_stream) != hipSuccess)
+                        return FF_ERR_LAUNCH;
+                    if (!together && hipMemcpyAsync(keep + done, keep_dev, (size_t)m * J, hipMemcpyDeviceToHost, st_stream) !=
+                                         hipSuccess)
+                        return FF_ERR_LAUNCH;
+                }
+            }
+            if (pinned == nullptr && hipMemcpyAsync(r, r_dev, count * (sizeof(double) + (filter && together ? 1 : 0)),
+                                                    hipMemcpyDeviceToHost, st_stream) != hipSuccess)
+                return FF_ERR_LAUNCH;
         }
-        if (hipMemcpyAsync(r, r_dev, count * (sizeof(double) + (filter && together ? 1 : 0)), hipMemcpyDeviceToHost,
-                           st_stream) != hipSuccess ||
-            hipStreamSynchronize(st_stream) != hipSuccess)
+        if (hipStreamSynchronize(st_stream) != hipSuccess)
             return FF_ERR_LAUNCH;
+        if (pinned != nullptr)
+            std::memcpy(r, pinned, result_bytes);
     }
     metric_select_host(r, keep, n, J, top_k, percentile, min_tasks, top_host,
                        score_host, selected_host, threshold_host);

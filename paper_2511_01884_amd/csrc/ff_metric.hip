@@ -229,7 +229,228 @@ __global__ __launch_bounds__(64 * kGreedyWaves) void greedy_kernel(const unsigne
     }
 }
 
+// Correlations, pair bits and the greedy pass in one launch, for what fits the LDS (selection_fits): a workgroup takes 64 x 64
+// pairs on or above the diagonal of a task, brings their columns into LDS once, and finds their means and scales itself; those on
+// the diagonal write r.  The last workgroup of a task to arrive has all its bits and decides.  Every sum runs in the
+// order it has in the kernels above: the same bits.
+//
+// Bound by latency: a load of the columns, one store and one arrival, one load of the bits.  Three launches with a load or two
+// each were 22 us of eight tasks of 10 x 300; this one is 9.  Pair bits lie in memory as the greedy pass reads them: the rows
+// of block b, 64 of them, hold words b .. words - 1.
+constexpr int kFusedThreads = 256;
+__host__ __device__ constexpr size_t pair_words(int words) { return (size_t)32 * words * (words + 1); }
+__device__ __forceinline__ int pair_block(int words, int b) { return 64 * (b * words - b * (b - 1) / 2); }
+
+__global__ __launch_bounds__(kFusedThreads) void selection_kernel(const double *values, const double *runtime, double *r,
+                                                                  unsigned char *keep, unsigned long long *mask,
+                                                                  unsigned *arrived, double tau, int V, int J)
+{
+    extern __shared__ __align__(16) double z[];  // [V][128]: 64 columns of side a, 64 of side b; later the pair bits
+    __shared__ double s_mean[128], s_inv[128];
+    __shared__ unsigned long long bits[kPairTile];
+    __shared__ int s_last;
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const int words = (J + 63) / 64;
+    const size_t task = blockIdx.y;
+    int by = 0, bx = (int)blockIdx.x;  // the bx-th of row by, row by + 1, ... of the upper triangle
+    while (bx >= words - by) {
+        bx -= words - by;
+        ++by;
+    }
+    bx += by;
+    const int a0 = by * kPairTile, b0 = bx * kPairTile;
+    const bool diagonal = bx == by;
+    values += task * V * J;
+    runtime += task * V;
+    mask += task * pair_words(words);
+
+    {
+        const int col = tid & 127, first = (col < 64 ? a0 : b0) + (col & 63);
+        const double *src = values + (first < J ? first : J - 1);
+        for (int v0 = tid >> 7; v0 < V; v0 += 32) {
+            double x[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                x[u] = src[(size_t)(v0 + 2 * u < V ? v0 + 2 * u : V - 1) * J];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                if (v0 + 2 * u < V)
+                    z[(v0 + 2 * u) * 128 + col] = x[u];
+        }
+    }
+    if (tid < kPairTile)
+        bits[tid] = 0;
+    __syncthreads();
+    if (tid < 128) {
+        double mx = 0.0;
+        bool x_const = true;
+        const double x0 = z[tid];
+#pragma unroll 8
+        for (int v = 0; v < V; ++v) {
+            const double x = z[v * 128 + tid];
+            mx += x;
+            x_const = x_const && x == x0;
+        }
+        mx /= (double)V;
+        double sxx = 0.0;
+#pragma unroll 8
+        for (int v = 0; v < V; ++v) {
+            const double dx = z[v * 128 + tid] - mx;
+            sxx += dx * dx;
+        }
+        s_mean[tid] = mx;
+        s_inv[tid] = (!x_const && sxx > 0.0) ? 1.0 / sqrt(sxx) : __builtin_nan("");
+        if (diagonal && tid < 64 && a0 + tid < J) {
+            double my = 0.0;
+            bool y_const = true;
+            const double y0 = runtime[0];
+#pragma unroll 8
+            for (int v = 0; v < V; ++v) {
+                const double y = runtime[v];
+                my += y;
+                y_const = y_const && y == y0;
+            }
+            my /= (double)V;
+            double sxy = 0.0, syy = 0.0;
+#pragma unroll 8
+            for (int v = 0; v < V; ++v) {
+                const double dx = z[v * 128 + tid] - mx, dy = runtime[v] - my;
+                sxy += dx * dy;
+                syy += dy * dy;
+            }
+            r[task * J + a0 + tid] = (!x_const && !y_const && sxx > 0.0 && syy > 0.0) ? sxy / sqrt(sxx * syy) : __builtin_nan("");
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < V * 128; e += kFusedThreads)
+        z[e] = (z[e] - s_mean[e & 127]) * s_inv[e & 127];
+    __syncthreads();
+    double acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            acc[i][j] = 0.0;
+#pragma unroll 2
+    for (int v = 0; v < V; ++v) {
+        typedef double double2_t __attribute__((ext_vector_type(2)));
+        double x[4], y[4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const double2_t xv = *reinterpret_cast<const double2_t *>(&z[v * 128 + ty * 4 + 2 * i]);
+            const double2_t yv = *reinterpret_cast<const double2_t *>(&z[v * 128 + 64 + tx * 2 + 32 * i]);
+            x[2 * i] = xv[0];
+            x[2 * i + 1] = xv[1];
+            y[2 * i] = yv[0];
+            y[2 * i + 1] = yv[1];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[i][j] += x[i] * y[j];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned long long w = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int at = tx * 2 + (j & 1) + 32 * (j >> 1);  // column inside the tile
+            const int a = a0 + ty * 4 + i, b = b0 + at;
+            if (b < J && b > a && fabs(acc[i][j]) >= tau)
+                w |= 1ull << at;
+        }
+        if (w != 0)
+            atomicOr(&bits[ty * 4 + i], w);
+    }
+    __syncthreads();
+    if (tid < kPairTile)
+        __hip_atomic_store(mask + pair_block(words, by) + tid * (words - by) + bx - by, bits[tid], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    wait_published();
+    __syncthreads();
+    if (tid == 0)
+        s_last = atomic_add_device(arrived + task * 32, 1u) == gridDim.x - 1u;
+    __syncthreads();
+    if (!s_last)
+        return;
+
+    // ---- the greedy pass ----
+    unsigned long long *m = reinterpret_cast<unsigned long long *>(z);
+    const int total = (int)pair_words(words);
+    for (int e0 = tid; e0 < total; e0 += kFusedThreads * 8) {
+        unsigned long long w[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)  // other units' bits: past the L2 of this one
+            w[u] = __hip_atomic_load(mask + (e0 + u * kFusedThreads < total ? e0 + u * kFusedThreads : total - 1), __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (e0 + u * kFusedThreads < total)
+                m[e0 + u * kFusedThreads] = w[u];
+    }
+    if (tid == 0)
+        atomic_store_device(arrived + task * 32, 0u);
+    __syncthreads();
+    if (tid >= 64)
+        return;
+    // One wavefront: lane l has word l % 16 of what is struck out; it looks at every fourth row from l / 16 on.
+    const int word = tid & 15;
+    unsigned long long gone = 0;
+    for (int b = 0; b < words; ++b) {
+        const int pitch = words - b;
+        const unsigned long long *rows = m + pair_block(words, b);
+        const int count = J - b * 64 < 64 ? J - b * 64 : 64;
+        const unsigned long long diag = rows[tid * pitch];
+        unsigned long long g = (unsigned long long)__builtin_amdgcn_readlane((unsigned)(gone >> 32), b) << 32 |
+                               (unsigned)__builtin_amdgcn_readlane((unsigned)gone, b);
+        // only rows with a duplicate inside the block can decide anything in it
+        unsigned long long deciders = __ballot(tid < count && diag != 0);
+        while (deciders != 0) {
+            const int j = __builtin_ctzll(deciders);
+            deciders &= deciders - 1;
+            if (!((g >> j) & 1))
+                g |= (unsigned long long)(unsigned)__builtin_amdgcn_readlane((unsigned)(diag >> 32), j) << 32 |
+                     (unsigned)__builtin_amdgcn_readlane((unsigned)diag, j);
+        }
+        if (tid < count)
+            keep[task * J + b * 64 + tid] = ((g >> tid) & 1) ? 0 : 1;
+        const unsigned long long kept = ~g & (count == 64 ? ~0ull : (1ull << count) - 1);
+        const int at = word > b && word < words ? word - b : 0;
+        unsigned long long strike = 0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int row = u * 4 + (tid >> 4);
+            const unsigned long long w = rows[row * pitch + at];
+            strike |= ((kept >> row) & 1) ? w : 0;
+        }
+        strike |= __shfl_xor(strike, 16);
+        strike |= __shfl_xor(strike, 32);
+        gone |= at != 0 ? strike : 0;
+    }
+}
+
+// LDS of the kernel above: the columns, or the pair bits.
+size_t selection_lds(int V, int J)
+{
+    return std::max((size_t)V * 128 * sizeof(double), pair_words((J + 63) / 64) * sizeof(unsigned long long));
+}
+
 }  // namespace
+
+// Whether that kernel takes tasks of this size: two workgroups to a unit's LDS, and a lane for every word of a row of bits.
+bool selection_fits(int V, int J) { return J <= 1024 && selection_lds(V, J) <= 76u << 10; }
+size_t selection_mask_bytes(int J) { return pair_words((J + 63) / 64) * sizeof(unsigned long long); }
+
+// r and keep of n tasks; mask has room for selection_mask_bytes of each, arrived a zero word in every 128 bytes for each
+hipError_t launch_selection(const double *values, const double *runtime, double *r, unsigned char *keep, unsigned long long *mask,
+                            unsigned *arrived, double tau, int n, int V, int J, hipStream_t stream)
+{
+    const int words = (J + 63) / 64;
+    hipLaunchKernelGGL(selection_kernel, dim3(words * (words + 1) / 2, n), dim3(kFusedThreads), selection_lds(V, J), stream, values,
+                       runtime, r, keep, mask, arrived, tau, V, J);
+    return hipGetLastError();
+}
 
 hipError_t launch_pearson(const double *values, const double *runtime, double *r, double *mean, double *inv, int n,
                           int V, int J, hipStream_t stream)

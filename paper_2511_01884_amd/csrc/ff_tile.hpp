@@ -143,6 +143,10 @@ hipError_t launch_pearson(const double *values, const double *runtime, double *r
                           int V, int J, hipStream_t stream);
 hipError_t launch_duplicate_filter(const double *values, const double *mean, const double *inv, double tau,
                                    unsigned long long *mask, unsigned char *keep, int n, int V, int J, hipStream_t stream);
+bool selection_fits(int V, int J);
+size_t selection_mask_bytes(int J);
+hipError_t launch_selection(const double *values, const double *runtime, double *r, unsigned char *keep, unsigned long long *mask,
+                            unsigned *arrived, double tau, int n, int V, int J, hipStream_t stream);
 void metric_select_host(const double *r, const unsigned char *keep, int n, int J, int k, double q,
                         int min_tasks, int *top, double *score, unsigned char *selected, double *threshold);
 
