@@ -481,42 +481,65 @@ hipError_t launch_duplicate_filter(const double *values, const double *mean, con
 void metric_select_host(const double *r, const unsigned char *keep, int n, int J, int k, double q,
                         int min_tasks, int *top, double *score, unsigned char *selected, double *threshold)
 {
+    constexpr int kInsert = 64;  // up to this k a task's list is kept sorted as its metrics pass by
     std::vector<int> tops((size_t)n * k, -1);
-    std::vector<int> in_top((size_t)n * J, 0);
-    std::vector<int> cand;
+    std::vector<double> S(J, 0.0);
+    struct Seen { int tasks; unsigned char signs; };  // Top-k lists a metric is in, and its signs there: 1 +, 2 -, 4 zero
+    std::vector<Seen> seen(J, Seen{0, 0});
+    std::vector<std::pair<double, int>> cand;
+    auto before = [](const std::pair<double, int> &a, const std::pair<double, int> &b) {
+        return a.first > b.first || (a.first == b.first && a.second < b.second);
+    };
     for (int i = 0; i < n; ++i) {
         const double *ri = r + (size_t)i * J;
-        cand.clear();
-        for (int m = 0; m < J; ++m)
-            if ((!keep || keep[(size_t)i * J + m]) && !std::isnan(ri[m]))
-                cand.push_back(m);
-        const size_t top_n = cand.size() < (size_t)k ? cand.size() : (size_t)k;
-        std::partial_sort(cand.begin(), cand.begin() + top_n, cand.end(), [ri](int a, int b) {
-            const double fa = std::fabs(ri[a]), fb = std::fabs(ri[b]);
-            return fa > fb || (fa == fb && a < b);
-        });
-        for (int j = 0; j < k && j < (int)cand.size(); ++j) {
-            tops[(size_t)i * k + j] = cand[j];
-            in_top[(size_t)i * J + cand[j]] = 1;
+        const unsigned char *ki = keep ? keep + (size_t)i * J : nullptr;
+        int *list = tops.data() + (size_t)i * k;
+        int filled = 0;
+        if (k <= kInsert) {
+            double best[kInsert];
+            for (int m = 0; m < J; ++m) {
+                const double v = std::fabs(ri[m]);
+                if (!std::isnan(v))
+                    S[m] += v;
+                // (a NaN compares false; an equal |r| further on stays behind)
+                if ((ki && !ki[m]) || !(filled < k ? v >= 0.0 : v > best[k - 1]))
+                    continue;
+                int at = filled < k ? filled++ : k - 1;
+                for (; at > 0 && best[at - 1] < v; --at) {
+                    best[at] = best[at - 1];
+                    list[at] = list[at - 1];
+                }
+                best[at] = v;
+                list[at] = m;
+            }
+        } else {
+            cand.clear();
+            for (int m = 0; m < J; ++m) {
+                const double v = std::fabs(ri[m]);
+                if (std::isnan(v))
+                    continue;
+                S[m] += v;
+                if (!ki || ki[m])
+                    cand.emplace_back(v, m);
+            }
+            filled = cand.size() < (size_t)k ? (int)cand.size() : k;
+            std::partial_sort(cand.begin(), cand.begin() + filled, cand.end(), before);
+            for (int j = 0; j < filled; ++j)
+                list[j] = cand[j].second;
+        }
+        for (int j = 0; j < filled; ++j) {
+            const double v = ri[list[j]];
+            Seen &s = seen[list[j]];
+            ++s.tasks;
+            s.signs |= v > 0.0 ? 1 : (v < 0.0 ? 2 : 4);
         }
     }
-    std::vector<double> S(J, 0.0);
-    for (int m = 0; m < J; ++m) {
-        double acc = 0.0;
-        for (int i = 0; i < n; ++i) {
-            const double v = r[(size_t)i * J + m];
-            acc += std::isnan(v) ? 0.0 : std::fabs(v);
-        }
-        S[m] = acc / (double)n;
-    }
+    for (int m = 0; m < J; ++m)
+        S[m] /= (double)n;
     std::vector<double> cs;
-    for (int m = 0; m < J; ++m) {
-        bool c = false;
-        for (int i = 0; i < n && !c; ++i)
-            c = in_top[(size_t)i * J + m] != 0;
-        if (c)
+    for (int m = 0; m < J; ++m)
+        if (seen[m].tasks > 0)
             cs.push_back(S[m]);
-    }
     double cut = std::nan("");
     if (!cs.empty()) {
         std::sort(cs.begin(), cs.end());
@@ -525,26 +548,11 @@ void metric_select_host(const double *r, const unsigned char *keep, int n, int J
         const size_t hi = lo + 1 < cs.size() ? lo + 1 : cs.size() - 1;
         cut = cs[lo] + (pos - (double)lo) * (cs[hi] - cs[lo]);
     }
-    if (selected) {
+    if (selected)
         for (int m = 0; m < J; ++m) {
-            int count = 0;
-            bool pos_seen = false, neg_seen = false, zero_seen = false;
-            for (int i = 0; i < n; ++i) {
-                if (!in_top[(size_t)i * J + m])
-                    continue;
-                ++count;
-                const double v = r[(size_t)i * J + m];
-                if (v > 0.0)
-                    pos_seen = true;
-                else if (v < 0.0)
-                    neg_seen = true;
-                else
-                    zero_seen = true;
-            }
-            const int kinds = (pos_seen ? 1 : 0) + (neg_seen ? 1 : 0) + (zero_seen ? 1 : 0);
-            selected[m] = (count >= min_tasks && count > 0 && kinds == 1 && S[m] > cut) ? 1 : 0;
+            const unsigned char one = seen[m].signs;
+            selected[m] = seen[m].tasks >= min_tasks && (one == 1 || one == 2 || one == 4) && S[m] > cut ? 1 : 0;
         }
-    }
     if (top)
         std::copy(tops.begin(), tops.end(), top);
     if (score)
