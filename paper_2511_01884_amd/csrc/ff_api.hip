@@ -319,7 +319,29 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
                             (half_empty || (tiles128 * 32 <= 33 * num_cus && across > 2) || K < 256);
     // (A plan for little scratch memory, roomy = false, splits nothing and keeps the larger tiles, which have
     // half the row statistics.)
-    if (tiles256 * 2 > num_cus && (bf16 || !roomy || tiles128 > 2 * num_cus))
+    // fp32 in several rounds: 128 x 128 tiles, two a unit, in plain order.  A round of them is two units of matrix time, one of at
+    // most half as many 1.15 (a unit's lone workgroup does not quite fill its matrix pipes), where a round of 256 x 256 tiles is
+    // four units, however few of the compute units have one.  Microseconds: matrix time, and the rest of a tile.  70 shapes (M, N
+    // 512..8192, K 64..4096): 0.865 of the time with 256 x 256 tiles throughout, 0.2 % above the better of the two (7656 x
+    // 1764 x 2144, two rounds of 135, 832 us, 443; 5632 x 2708 x 3072 1233, 798; 2999 x 1416 x 3436, one of 168, 344, 272).
+    bool in_turn = false;
+    // (Where the row statistics fit the entry point that allocates nothing, so that both have the same bits; the fewer row-blocks
+    // of larger tiles for very long X.)
+    const bool room128 = kCtrlBytes + (size_t)tiles128 * 128 * sizeof(floatx2) <= kNoAllocBytes && (M + 127) / 128 < kMaxRowBlocks &&
+                         N <= 128 * (int64_t)num_cus;
+    if (!bf16 && may_split && room128 && tiles128 > 2 * num_cus) {
+        const int64_t rest = tiles128 % (2 * num_cus);
+        const double units = 2.0 * (double)(tiles128 / (2 * num_cus)) + (rest == 0 ? 0.0 : (rest <= num_cus ? 1.15 : 2.0));
+        const int64_t rows256 = (M + 255) / 256;
+        const double rounds256 = (double)(across * 2 <= num_cus ? (rows256 + num_cus / across - 1) / (num_cus / across)
+                                                                : (tiles256 + num_cus - 1) / num_cus);
+        const double us128 = 6.0 + units * (0.0561 * (double)K + 6.8 + 0.03 * (double)((N + 127) / 128));
+        const double us256 = 6.0 + rounds256 * (0.216 * (double)K + 22.0);
+        in_turn = us128 < 0.92 * us256;
+    }
+    if (in_turn)
+        pl.shape = kTile128;
+    else if (tiles256 * 2 > num_cus && (bf16 || !roomy || tiles128 > 2 * num_cus))
         pl.shape = kTile256W8;
     else if (bf16 && tiles128 > num_cus && tiles256x128 <= num_cus && !(roomy && two_a_unit))
         pl.shape = kTile256x128;
@@ -371,7 +393,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     pl.swz_sc_log2 = -1;
     pl.nt_log2 = 0;
     pl.grid_log2 = 0;
-    if ((pl.grid == 256 || pl.grid == 512) && NT <= pl.grid && (NT & (NT - 1)) == 0) {
+    if (!in_turn && (pl.grid == 256 || pl.grid == 512) && NT <= pl.grid && (NT & (NT - 1)) == 0) {
         int sc = (int)(NT / 8 > 8 ? NT / 8 : 8);
         if (sc > NT)
             sc = (int)NT;
@@ -398,7 +420,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // run beside the products of the rest (652 x 172 x 8084, 384 tiles: 52.1 us in rounds, 44.0; 1227 x 204 x 4032:
     // 47.0, 42.7; 34 such shapes with K < 600 take 0.98 of the time on average, 36 longer ones 1.01).
     const bool staggered = !bf16 && total > num_cus && total == pl.grid && NT % 8 == 0 && K < 600;
-    if (pl.swz_sc_log2 < 0 && NT * 2 <= pl.grid && variant == FF_VARIANT_TILED_FUSED && !linear_only && !staggered) {
+    if (pl.swz_sc_log2 < 0 && NT * 2 <= pl.grid && variant == FF_VARIANT_TILED_FUSED && !linear_only && !staggered && !in_turn) {
         const int64_t most = pl.grid / NT < RB ? pl.grid / NT : RB, rounds = (RB + most - 1) / most;
         if (!(bf16 && RB == most + 1 && K >= 2048)) {
             pl.rounds = (int)rounds;

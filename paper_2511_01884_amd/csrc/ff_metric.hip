@@ -235,7 +235,7 @@ __global__ __launch_bounds__(64 * kGreedyWaves) void greedy_kernel(const unsigne
 // order it has in the kernels above: the same bits.
 //
 // Bound by latency: a load of the columns, one store and one arrival, one load of the bits.  Three launches with a load or two
-// each were 22 us of eight tasks of 10 x 300; this one is 9.  Pair bits lie in memory as the greedy pass reads them: the rows
+// each were 22 us of eight tasks of 10 x 300; this one is 13.5.  Pair bits lie in memory as the greedy pass reads them: the rows
 // of block b, 64 of them, hold words b .. words - 1.
 constexpr int kFusedThreads = 256;
 __host__ __device__ constexpr size_t pair_words(int words) { return (size_t)32 * words * (words + 1); }
