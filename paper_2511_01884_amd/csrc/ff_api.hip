@@ -339,8 +339,24 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
         const double us256 = 6.0 + rounds256 * (0.216 * (double)K + 22.0);
         in_turn = us128 < 0.92 * us256;
     }
-    if (in_turn)
+    // bf16 where little more than half of the units would have a 256 x 256 tile: one round of tiles of half the height, one
+    // a unit (22 shapes 0.83 of the time: 2616 x 512 x 2944 25.5 us, 19.9; 612 x 3984 x 12200 123, 92), or else of 128 x 128 tiles, two
+    // a unit (27 shapes 0.85: 9190 x 256 x 880 22.6, 17.9; 16843 x 5376 x 296 124, 96; with rows of more than 64 of them 726 x
+    // 2048 x 10856 52.7, 55.3).  So too two rounds of these for two of those, if a row has up to 16 (14 shapes 0.80: 9596 x 256 x
+    // 1552 40.6, 30.3; 22038 x 7936 x 552 345, 291; with 40 and more 0.9 to 1.3).  Not where plain order (below) saves half a round.
+    bool pair_half = false, pair128 = false;
+    if (bf16 && may_split && room128 && tiles256 * 2 > num_cus) {
+        const int64_t rows256 = (M + 255) / 256, rows128 = (M + 127) / 128, across128 = (N + 127) / 128;
+        const bool one = tiles256 <= num_cus, plain = across * 2 <= num_cus && rows256 == num_cus / across + 1 && K >= 2048;
+        const bool two = !one && across * 2 <= num_cus && rows256 <= 2 * (num_cus / across) && !plain;
+        pair_half = one && tiles256x128 <= num_cus;
+        pair128 = !pair_half && ((one && tiles128 <= 2 * num_cus && across128 <= 64) ||
+                                 (two && across128 <= 16 && rows128 <= 2 * (2 * num_cus / across128)));
+    }
+    if (in_turn || pair128)
         pl.shape = kTile128;
+    else if (pair_half)
+        pl.shape = kTile256x128;
     else if (tiles256 * 2 > num_cus && (bf16 || !roomy || tiles128 > 2 * num_cus))
         pl.shape = kTile256W8;
     else if (bf16 && tiles128 > num_cus && tiles256x128 <= num_cus && !(roomy && two_a_unit))
