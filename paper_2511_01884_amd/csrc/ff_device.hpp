@@ -184,6 +184,34 @@ __device__ __forceinline__ bool wait_counter(const unsigned *counter, unsigned t
 constexpr int kSyncWays = 32;
 constexpr int kSyncStride = 1024;  // uint32 words between ways
 
+// Departure from such a meeting: the last workgroup of the last way re-arms every counter (only then has every workgroup
+// left its wait, so that no poller can see a counter go back to zero).  In three steps, one thread's, begun as soon as
+// the workgroup's own wait is over: the two round trips to memory pass behind the work that follows, and no
+// longer stand at the end of the kernel (16 x 8192 x 8192 36.6 us, now 36.2; second chain 300 x 4096 x 1024 12.5, 12.0).
+struct Departure {
+    unsigned seen = 0;
+    __device__ __forceinline__ void begin(unsigned *counters, unsigned way)
+    {
+        seen = atomic_add_device(counters + (size_t)way * kSyncStride + 1, 1u);
+    }
+    // behind the loads that the workgroup waits for next
+    __device__ __forceinline__ void middle(unsigned *counters, unsigned way, unsigned grid)
+    {
+        const bool last = seen == (grid + kSyncWays - 1 - way) / kSyncWays - 1u;
+        seen = last ? atomic_add_device(counters + 2, 1u) + 1u : 0u;
+    }
+    __device__ __forceinline__ void end(unsigned *counters, unsigned grid)
+    {
+        if (seen == (grid < (unsigned)kSyncWays ? grid : (unsigned)kSyncWays)) {
+            for (int w = 0; w < kSyncWays; ++w) {
+                atomic_store_device(counters + (size_t)w * kSyncStride, 0u);
+                atomic_store_device(counters + (size_t)w * kSyncStride + 1, 0u);
+            }
+            atomic_store_device(counters + 2, 0u);
+        }
+    }
+};
+
 // Called by every lane of one wavefront: the lanes with `polls` set wait for their own word `mine` to
 // reach their `target` (sticky: a word counts once seen).  False if the bound expired.
 __device__ __forceinline__ bool wait_ways(const unsigned *mine, bool polls, unsigned target, long long limit_ticks)

@@ -222,6 +222,9 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
             atomic_store_device(p.err, 1u);
     }
     __syncthreads();
+    Departure leave;
+    if (tid == 0)
+        leave.begin(p.counters, way);
 
     // ---- phase 2: wbar into LDS (chunk partials added in chunk order), c, then one wavefront per row ----
     const int quads = K / 4;
@@ -408,6 +411,8 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
             }
         }
     };
+    if (tid == 0)
+        leave.middle(p.counters, way, G);
     if constexpr (SETS == 1) {
         finish_rows(m_first, keep[0]);
     } else {
@@ -421,21 +426,8 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
         }
     }
 
-    // ---- departure: the last workgroup of the last way re-arms every counter ----
-    // (only then has every workgroup left its wait, so no poller can see a counter go back to zero)
-    if (tid == 0) {
-        const unsigned in_way = (unsigned)(G + kSyncWays - 1 - way) / kSyncWays;
-        const unsigned ways = G < kSyncWays ? (unsigned)G : (unsigned)kSyncWays;
-        if (atomic_add_device(p.counters + (size_t)way * kSyncStride + 1, 1u) == in_way - 1u) {
-            if (atomic_add_device(p.counters + 2, 1u) == ways - 1u) {
-                for (int w = 0; w < kSyncWays; ++w) {
-                    atomic_store_device(p.counters + (size_t)w * kSyncStride, 0u);
-                    atomic_store_device(p.counters + (size_t)w * kSyncStride + 1, 0u);
-                }
-                atomic_store_device(p.counters + 2, 0u);
-            }
-        }
-    }
+    if (tid == 0)
+        leave.end(p.counters, G);
 }
 
 template <typename T, int PL, int R, int WPR, int SETS = 2>

@@ -276,6 +276,9 @@ __global__ __launch_bounds__(kThreads) void smallm_kernel(const SmallMParams p)
             atomic_store_device(p.err, 1u);
     }
     __syncthreads();
+    Departure leave;
+    if (tid == 0)
+        leave.begin(p.counters, way);
     stamp(4);
     {
         // Every workgroup merges all strips' partials itself, in strip order: thread ->
@@ -344,6 +347,8 @@ __global__ __launch_bounds__(kThreads) void smallm_kernel(const SmallMParams p)
         }
         __syncthreads();
     }
+    if (tid == 0)
+        leave.middle(p.counters, way, gridDim.x);
     stamp(5);
     // ---- normalise and store ----
     owned = 0;
@@ -377,21 +382,8 @@ __global__ __launch_bounds__(kThreads) void smallm_kernel(const SmallMParams p)
     }
 
     stamp(6);
-    // ---- departure: the last workgroup of the last way re-arms every counter ----
-    // (only then has every workgroup left its wait, so no poller can see a counter go back to zero)
-    if (tid == 0) {
-        const unsigned in_way = (gridDim.x + kSyncWays - 1 - way) / kSyncWays;
-        const unsigned ways = gridDim.x < (unsigned)kSyncWays ? gridDim.x : (unsigned)kSyncWays;
-        if (atomic_add_device(p.counters + (size_t)way * kSyncStride + 1, 1u) == in_way - 1u) {
-            if (atomic_add_device(p.counters + 2, 1u) == ways - 1u) {
-                for (int w = 0; w < kSyncWays; ++w) {
-                    atomic_store_device(p.counters + (size_t)w * kSyncStride, 0u);
-                    atomic_store_device(p.counters + (size_t)w * kSyncStride + 1, 0u);
-                }
-                atomic_store_device(p.counters + 2, 0u);
-            }
-        }
-    }
+    if (tid == 0)
+        leave.end(p.counters, gridDim.x);
 }
 
 }  // namespace

@@ -382,6 +382,9 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     const bool mine = r_in_pass < rows; // fewer rows than a pass takes: the rest of the threads idle
 
     // ---- 1: sum over the tile's workgroups ----
+    // Departures: begun as soon as a wait is over, looked at when the rest is done.  (At the end of the kernel their round trips
+    // to memory stood one behind the other: 256 x 512 x 512 fp32 12.0 us, now 11.7.)
+    unsigned left_tile = 0, left_group = 0;
     floatx4 v[kMaxPass];
     const int tile = rb * p.NT + cb;
     if (S > 1) {
@@ -405,6 +408,8 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
                 atomic_store_device(p.err, 1u);
         }
         __syncthreads();
+        if (tid == 0)
+            left_tile = atomic_add_device(c + 1, 1u);
         const float *all = p.sums + (size_t)tile * S * (BM * BN);
         if constexpr (kWaves == 8) {
             // The parts of all of a thread's passes are requested together (S of each, kMaxPass or S in all) and added
@@ -518,6 +523,8 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
             atomic_store_device(p.err, 1u);
     }
     __syncthreads();
+    if (tid == 0)
+        left_group = atomic_add_device(group + 1, 1u);
     stamp(4);
 
     // ---- 3: merge, normalise, store ----
@@ -591,12 +598,12 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     if (tid == 0) {
         if (S > 1) {
             unsigned *c = p.counters + (size_t)tile * kSplitCounterStride;
-            if (atomic_add_device(c + 1, 1u) == (unsigned)S - 1u) {
+            if (left_tile == (unsigned)S - 1u) {
                 atomic_store_device(c, 0u);
                 atomic_store_device(c + 1, 0u);
             }
         }
-        if (atomic_add_device(group + 1, 1u) == (unsigned)p.NT - 1u) {
+        if (left_group == (unsigned)p.NT - 1u) {
             for (int w = 0; w < kSplitWays; ++w)
                 atomic_store_device(group + (size_t)w * kSplitCounterStride, 0u);
             atomic_store_device(group + 1, 0u);
