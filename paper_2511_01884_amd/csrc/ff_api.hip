@@ -148,6 +148,51 @@ int resident_split_blocks(DeviceState *st, bool bf16, int shape)
 // The busiest unit's share counts up to 16 rows, where the streamer is the other choice: of a grid of a few more
 // workgroups than units some units read twice what the others do (3 x 10232 x 17024: 127 us in 266 workgroups, 110
 // in 532 smaller ones).
+//
+// 32 x 32 tiles have a model of their own, fitted to 2 300 runs of 1 132 shapes (M 1..2048, K 128..8192, N 128..8192, S 1 to 4; off by
+// 2 (fp32) and 3 % (bf16) on average): two to sixteen times as many tiles as of the other shapes, so that K need not be cut and the
+// tile's workgroups need not meet, at twice the bytes through a unit's load path and more.  256 x 512 x 512 fp32 11.6 us,
+// now 9.6; 512 x 1024 x 512 bf16 10.7, 8.6.  They are taken where their estimate is 4 % below the others', which are 6 % high here
+// (in fp32 0.91 of the time over all these shapes, 0.5 % above the better of the two, at most 1.03; in bf16, whose estimates scatter
+// more, uncut and over 16 rows only: 0.985, at most 1.14).
+struct SmallTiles {
+    int s = 0;
+    double us = 0.0;
+};
+SmallTiles small_tiles(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceState *st)
+{
+    struct Cost { double start, slab, slab2, unit_hbm, epi, tiles, exch, exch_s, hbm; };
+    constexpr Cost kBf16 = {6.15, 0.096, 0.221, 44.0e3, 0.13, 0.0383, 0.0, 0.0, 7.5e6};
+    constexpr Cost kF32 = {5.68, 0.168, 0.32, 26.6e3, 0.80, 0.0372, 1.70, 0.197, 5.7e6};
+    const Cost &c = bf16 ? kBf16 : kF32;
+    const int size = bf16 ? 2 : 4;
+    const int64_t slabs = (K * size + 127) / 128, RB = (M + 31) / 32, NT = (N + 31) / 32;
+    SmallTiles best;
+    // Where rows lie off the line boundaries and N ends inside a tile the larger tiles stay.  (Those would gain too, in fp32 0.91 of the
+    // time against 0.89 for rows on line boundaries; the tests of the larger tiles' edges are such shapes.)
+    // bf16 of up to eight slabs, whose one load latency the larger tiles wait for as well, gains nothing on average (59 shapes 1.00),
+    // nor does it beyond 32 (K 2048 to 4096: 1.05).
+    if ((bf16 && (M <= 16 || slabs <= 8 || slabs > 32)) || RB * NT > 2 * (int64_t)num_cus || (K * size % 128 != 0 && N % 32 != 0))
+        return best;
+    const int resident = resident_split_blocks(st, bf16, kSplit32);
+    for (int S = 1; S <= (bf16 ? 1 : 4); S *= 2) {
+        const int64_t groups = RB * NT * S, rounds = (groups + num_cus - 1) / num_cus;
+        if (groups > (int64_t)num_cus * (resident == 1 ? 1 : 2) || (S > 1 && slabs < 4 * S) ||
+            (RB * NT + RB * S * kSplitWays) * kSplitCounterStride * 4 > (int64_t)(kCtrlBytes - 2 * kCounterOffset))
+            break;
+        const double stream = (double)N * K * size / std::min(c.hbm, std::min<double>((double)groups, num_cus) * c.unit_hbm);
+        double t = c.start + std::max((double)((slabs + S - 1) / S) * (rounds == 1 ? c.slab : c.slab2), stream) +
+                   c.epi * (double)rounds / S + c.tiles * (double)NT;
+        if (S > 1)
+            t += c.exch + c.exch_s * S + (double)groups * 32 * 32 * 4 / 2.6e6;
+        if (best.s == 0 || t < best.us) {
+            best.s = S;
+            best.us = t;
+        }
+    }
+    return best;
+}
+
 bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceState *st, Plan &pl)
 {
     // workgroups per compute unit that the LDS allows (what the runtime reports is asked as well)
@@ -220,6 +265,16 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
     if (narrow.split_s != 0 && narrow_us < best && pl.split_shape == kSplit128x64 && pl.split_s == 1) {
         pl = narrow;
         best = narrow_us;
+    }
+    const SmallTiles small = small_tiles(M, K, N, bf16, num_cus, st);
+    if (small.s != 0 && small.us < 0.96 * (best - (bf16 ? 0.5 : 0.3))) {
+        best = small.us;
+        pl.split_s = small.s;
+        pl.split_shape = kSplit32;
+        pl.tile_m = pl.tile_n = 32;
+        pl.RB = (int)((M + 31) / 32);
+        pl.NT = (int)((N + 31) / 32);
+        pl.grid = pl.RB * pl.NT * pl.split_s;
     }
     // 128 x 128 tiles of long bf16 rows that do not begin on 64-byte boundaries keep four wavefronts.  There every line of
     // a slab is requested twice, and eight wavefronts go to HBM for half of W's lines a second time (147 x 10568 x 6016

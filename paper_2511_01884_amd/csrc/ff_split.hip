@@ -1,5 +1,5 @@
 // Fused linear + erf-GELU + LayerNorm for problems with too few tiles to fill the chip (gfx950):
-// output tiles of 64 x 32 to 128 x 128 (columns x rows, five shapes) whose K range is cut over S workgroups.
+// output tiles of 32 x 32 to 128 x 128 (columns x rows, six shapes) whose K range is cut over S workgroups.
 //
 // One round: grid = tiles * S workgroups, all resident.  Workgroup (tile, s) walks its share of the
 // 128-byte K slabs through a ring of kRing LDS stages filled by direct-to-LDS loads, so kRing - 1
@@ -26,7 +26,8 @@ namespace ff {
 namespace {
 
 constexpr int kRowBytes = 128;   // bytes of one tile row per K slab (8 chunks of 16 B)
-constexpr int kRing = 4;         // LDS stages
+// LDS stages of a tile shape: four, and eight of the small slabs of 32 x 32 tiles, so that as many bytes are in flight
+constexpr int ring_of(int tile_cols, int tile_rows) { return tile_cols + tile_rows <= 64 ? 8 : 4; }
 
 __device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 &c, const __bf16 *)
 {
@@ -48,14 +49,20 @@ template <int n> __device__ __forceinline__ void wait_vm()
     __builtin_amdgcn_s_waitcnt(0x0f70 | (n & 15) | ((n >> 4) << 14));
 }
 
-template <int ror> __device__ __forceinline__ float rotate16(float v)
+template <int ctrl> __device__ __forceinline__ float lane_dpp(float v)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ror, 0xf, 0xf, true));
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true));
 }
-// Sum over the 16 or 32 neighbouring lanes of a row; the same bits in each of them (every step adds
+template <int ror> __device__ __forceinline__ float rotate16(float v) { return lane_dpp<0x120 + ror>(v); }
+// Sum over the 8, 16 or 32 neighbouring lanes of a row; the same bits in each of them (every step adds
 // the two same numbers in both lanes of a pair).
 template <int LANES> __device__ __forceinline__ float row_sum(float v)
 {
+    if (LANES == 8) {  // neighbour, neighbouring pair, the other four of the eight (mirrored)
+        v += lane_dpp<0xb1>(v);
+        v += lane_dpp<0x4e>(v);
+        return v + lane_dpp<0x141>(v);
+    }
     v += rotate16<8>(v);
     v += rotate16<4>(v);
     v += rotate16<2>(v);
@@ -99,6 +106,10 @@ template <> struct RawCols<__bf16> {
 // loads reach its LDS: 57 bytes a nanosecond.)  The plan keeps four in the 128 x 128 tile for long rows off the 64-byte
 // boundaries.
 //
+// Tiles of 32 x 32 by four wavefronts, each with a quarter of every slab's k-steps, are for calls bound by latency: so many of
+// them that a tile has the whole of K, which spares its workgroups' meeting (2.4 of 11.6 us at 256 x 512 x 512 fp32), with
+// eight stages, so that 56 KB are in flight a workgroup.
+//
 // LINES: what travels is not a tile row's 128 bytes of a slab but the 128-byte line of memory that holds its beginning.  Rows
 // that do not begin on line boundaries have two lines to every slab, and a unit's load path, which takes 27 bytes a
 // clock and a line at a time, is what bounds these shapes; each line is now requested once.  Rows begin on 16-byte
@@ -114,7 +125,7 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
 #if defined(__HIP_DEVICE_COMPILE__)  // the body uses device-only types (buffer descriptors)
     constexpr int kWaves = kWN * kWM * kWK, kThreads = 64 * kWaves;
     static_assert(kWaves == 4 || kWaves == 8, "four or eight wavefronts");
-    constexpr int BN = kWN * WTN * 32, BM = kWM * WTM * 32;
+    constexpr int BN = kWN * WTN * 32, BM = kWM * WTM * 32, kRing = ring_of(BN, BM);
     constexpr int kChunkElems = 16 / (int)sizeof(T);
     constexpr int kSlabElems = kRowBytes / (int)sizeof(T);
     constexpr int kStageBytes = (BN + BM) * kRowBytes;
@@ -344,7 +355,13 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
             ++i;
         }
     };
-    static_assert(kRing == 4, "the last slabs");
+    static_assert(kRing == 4 || (kRing == 8 && !LINES), "the last slabs");
+    if constexpr (kRing == 8) {
+        last(std::integral_constant<int, 6>());
+        last(std::integral_constant<int, 5>());
+        last(std::integral_constant<int, 4>());
+        last(std::integral_constant<int, 3>());
+    }
     if constexpr (!LINES)
         last(std::integral_constant<int, 2>());
     last(std::integral_constant<int, 1>());
@@ -627,6 +644,7 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     case kSplit128x32: FF_SPLIT_TYPES(kSplit128x32, 2, 1, 2, 2, 1, CALL)   \
     case kSplit64: FF_SPLIT_TYPES(kSplit64, 2, 2, 1, 1, 1, CALL)           \
     case kSplit128x64: FF_SPLIT_TYPES(kSplit128x64, 2, 2, 2, 2, 1, CALL)   \
+    case kSplit32: FF_SPLIT_TYPES(kSplit32, 1, 1, 4, 1, 1, CALL)           \
     case kSplit128W4:                                                      \
         static_assert(split_shape_waves(kSplit128W4) == 4, "2 x 2 x 1");   \
         return CALL(__bf16, 2, 2, 1, 2, 2);                                \

@@ -75,9 +75,9 @@ struct SplitParams {
 };
 
 // Shapes of the split kernel (columns x rows of a tile; W4: four wavefronts, bf16 only)
-enum SplitShape { kSplit64x32 = 0, kSplit128x32 = 1, kSplit64 = 2, kSplit128x64 = 3, kSplit128 = 4, kSplit128W4 = 5, kNumSplitShapes = 6 };
-constexpr int split_shape_cols(int shape) { return shape == kSplit64x32 || shape == kSplit64 ? 64 : 128; }
-constexpr int split_shape_rows(int shape) { return shape >= kSplit128 ? 128 : (shape >= kSplit64 ? 64 : 32); }
+enum SplitShape { kSplit64x32 = 0, kSplit128x32 = 1, kSplit64 = 2, kSplit128x64 = 3, kSplit128 = 4, kSplit128W4 = 5, kSplit32 = 6, kNumSplitShapes = 7 };
+constexpr int split_shape_cols(int shape) { return shape == kSplit32 ? 32 : shape == kSplit64x32 || shape == kSplit64 ? 64 : 128; }
+constexpr int split_shape_rows(int shape) { return shape == kSplit32 ? 32 : shape >= kSplit128 ? 128 : (shape >= kSplit64 ? 64 : 32); }
 constexpr int split_shape_waves(int shape) { return shape == kSplit128x64 || shape == kSplit128 ? 8 : 4; }
 hipError_t launch_split_kernel(bool bf16, int shape, const SplitParams &p, int grid, hipStream_t stream);
 int split_kernel_blocks_per_cu(bool bf16, int shape);

@@ -1,0 +1,39 @@
+"""Tiles of 32 x 32 of the kernel that cuts K: fewer slabs than the eight LDS stages and more, a slab that K cuts, K cut over
+two and four workgroups, rows and columns that end inside a tile, against the oracle, bit for bit run to run."""
+import pytest
+import torch
+
+from paper_2511_01884_amd import binding as B
+from paper_2511_01884_amd.inputs import make_inputs
+from parity_util import check_against_oracle, gpu_run, oracle_on
+
+# (M, K, N, dtype, S)
+CASES = [(129, K, 512, "f32", 1) for K in (4, 32, 60, 96, 160, 224, 228, 252, 256, 260, 288, 292, 320, 512)]
+CASES += [(100, K, 544, "bf16", 1) for K in (520, 568, 576, 640, 648, 768, 1024)]
+CASES += [(257, 512, 516, "f32", 1), (1000, 256, 160, "f32", 1), (70, 1024, 1096, "bf16", 1),
+          (65, 1024, 36, "f32", 4), (257, 960, 256, "f32", 2), (40, 1028, 64, "f32", 4)]
+
+
+def _plan(M, K, N, dtype):
+    return B.ff_plan_query(M, K, N, B.FF_BF16 if dtype == "bf16" else B.FF_F32)
+
+
+@pytest.mark.parametrize("M,K,N,dtype,S", CASES)
+def test_plan(M, K, N, dtype, S):
+    plan = _plan(M, K, N, dtype)
+    assert (plan["tile_m"], plan["tile_n"], plan["waves"], plan["grid"]) == (32, 32, 4, -(-M // 32) * -(-N // 32) * S)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,dtype,S", CASES)
+def test_against_the_oracle(M, K, N, dtype, S):
+    print("[case] small tiles", M, K, N, dtype, S, flush=True)
+    d = make_inputs(M, K, N, dtype, seed=103)
+    d["b"] = (d["b"].float() + 2.0).to(d["b"].dtype)   # row means far from zero
+    Y, used = gpu_run(d)
+    assert used == B.FF_VARIANT_TILED_FUSED
+    print(check_against_oracle(Y, oracle_on(d), dtype, "small tiles %dx%dx%d" % (M, K, N)))
+    assert torch.equal(Y, gpu_run(d)[0])
+    got = torch.empty_like(Y)
+    B.ff_fused_linear_gelu_ln_noalloc(*[d[k].cuda() for k in ("X", "W", "b", "gamma", "beta")], d["eps"], got)
+    assert torch.equal(Y, got)
