@@ -379,7 +379,13 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // four units, however few of the compute units have one.  Microseconds: matrix time, and the rest of a tile.  70 shapes (M, N
     // 512..8192, K 64..4096): 0.865 of the time with 256 x 256 tiles throughout, 0.2 % above the better of the two (7656 x
     // 1764 x 2144, two rounds of 135, 832 us, 443; 5632 x 2708 x 3072 1233, 798; 2999 x 1416 x 3436, one of 168, 344, 272).
-    bool in_turn = false;
+    //
+    // 64 x 64 tiles, four a unit, also in plain order, where even 128 x 128 tiles leave units half idle: a round of up to as many of these
+    // as units is a unit of matrix time, of up to twice as many two, where 64 x 64 tiles count in quarters.  They take more for
+    // each unit and for each tile of a row.  540 shapes of 129 to 520 tiles of 128 x 128: 0.89 of the time, 0.6 % above the
+    // better of the two, at most 1.05 (2906 x 4056 x 740 254 us, 189; 655 x 1216 x 3008 84, 66; 2637 x 156 x 868 22.7, 18.8; in rows of 70 and
+    // more tiles of 128 short products lose up to twofold: 982 x 172 x 7668 44, 99).
+    bool in_turn = false, in_turn64 = false;
     // (Where the row statistics fit the entry point that allocates nothing, so that both have the same bits; the fewer row-blocks
     // of larger tiles for very long X.)
     const bool room128 = kCtrlBytes + (size_t)tiles128 * 128 * sizeof(floatx2) <= kNoAllocBytes && (M + 127) / 128 < kMaxRowBlocks &&
@@ -393,6 +399,16 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
         const double us128 = 6.0 + units * (0.0561 * (double)K + 6.8 + 0.03 * (double)((N + 127) / 128));
         const double us256 = 6.0 + rounds256 * (0.216 * (double)K + 22.0);
         in_turn = us128 < 0.92 * us256;
+    }
+    const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
+    if (!bf16 && may_split && (in_turn || (tiles128 <= 2 * num_cus && tiles128 * 4 > num_cus)) && N <= 128 * (int64_t)num_cus &&
+        kCtrlBytes + (size_t)tiles64 * 64 * sizeof(floatx2) <= kNoAllocBytes && (M + 63) / 64 < kMaxRowBlocks) {
+        const int64_t rest = tiles128 % (2 * num_cus), rest64 = tiles64 % (4 * num_cus);
+        const double units128 = 2.0 * (double)(tiles128 / (2 * num_cus)) + (rest == 0 ? 0.0 : (rest <= num_cus ? 1.15 : 2.0));
+        const double units64 = (double)(tiles64 / (4 * num_cus)) + 0.25 * (double)((rest64 + num_cus - 1) / num_cus);
+        const double k = (double)K, nt128 = (double)((N + 127) / 128), nt64 = (double)((N + 63) / 64);
+        in_turn64 = 9.1 - 0.126 * nt64 + units64 * (0.0595 * k + 1.8 + 0.342 * nt64) <
+                    0.94 * (2.1 + units128 * (0.0541 * k + 9.1 + 0.034 * nt128));
     }
     // bf16 where little more than half of the units would have a 256 x 256 tile: one round of tiles of half the height, one
     // a unit (22 shapes 0.83 of the time: 2616 x 512 x 2944 25.5 us, 19.9; 612 x 3984 x 12200 123, 92), or else of 128 x 128 tiles, two
@@ -408,7 +424,9 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
         pair128 = !pair_half && ((one && tiles128 <= 2 * num_cus && across128 <= 64) ||
                                  (two && across128 <= 16 && rows128 <= 2 * (2 * num_cus / across128)));
     }
-    if (in_turn || pair128)
+    if (in_turn64)
+        pl.shape = kTile64;
+    else if (in_turn || pair128)
         pl.shape = kTile128;
     else if (pair_half)
         pl.shape = kTile256x128;
@@ -438,7 +456,8 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     pl.NT = (int)NT;
     const int64_t total = RB * NT;
     // workgroups per compute unit: a tile of 256 columns takes a whole unit's LDS, the other shapes half or less
-    int per_cu = tile_shape_cols(pl.shape) == 256 ? 1 : 2;
+    int per_cu = tile_shape_cols(pl.shape) == 256 ? 1 : (in_turn64 ? 4 : 2);
+    in_turn = in_turn || in_turn64;
     if (g_forced_wg_per_cu == 1)
         per_cu = 1;
     // The fused kernel's workgroups wait for one another inside the launch: never launch more of them

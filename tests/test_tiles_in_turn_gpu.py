@@ -1,5 +1,5 @@
-"""fp32 in 128 x 128 tiles, two a unit, in several rounds in plain order: a row-block's tiles lie in two rounds, the last round
-holds a few tiles, half as many as a full one and more, rows and columns end inside a tile."""
+"""fp32 in 128 x 128 tiles, two a unit, or in 64 x 64 tiles, four a unit, in plain order: a row-block's tiles lie in two rounds, the
+last round holds a few tiles, half as many as a full one and more, rows and columns end inside a tile."""
 import pytest
 import torch
 
@@ -19,8 +19,20 @@ def test_plan(M, K, N, rounds):
     assert B.ff_plan_query(16384, 2708, 8000, B.FF_F32)["tile_m"] == 256
 
 
+# 64 x 64 tiles: just over two a unit, one, 32 and 128 tiles in a second round
+SMALL = [(2637, 156, 868, 1), (1544, 260, 2580, 2), (2040, 200, 2052, 2), (4096, 200, 1100, 2)]
+
+
+@pytest.mark.parametrize("M,K,N,rounds", SMALL)
+def test_plan_of_small_tiles(M, K, N, rounds):
+    plan = B.ff_plan_query(M, K, N, B.FF_F32)
+    tiles = -(-M // 64) * -(-N // 64)
+    assert (plan["tile_m"], plan["tile_n"], plan["rounds"], plan["grid"]) == (64, 64, rounds, min(tiles, 1024))
+    assert B.ff_plan_query(982, 172, 7668, B.FF_F32)["tile_m"] == 128       # rows of many tiles
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,K,N,rounds", CASES)
+@pytest.mark.parametrize("M,K,N,rounds", CASES + SMALL)
 def test_against_the_oracle(M, K, N, rounds):
     print("[case] tiles in turn", M, K, N, flush=True)
     d = make_inputs(M, K, N, "f32", seed=97)
