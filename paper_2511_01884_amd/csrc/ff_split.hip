@@ -29,15 +29,17 @@ constexpr int kRowBytes = 128;   // bytes of one tile row per K slab (8 chunks o
 // LDS stages of a tile shape: four, and eight of the small slabs of 32 x 32 tiles, so that as many bytes are in flight
 constexpr int ring_of(int tile_cols, int tile_rows) { return tile_cols + tile_rows <= 64 ? 8 : 4; }
 
-__device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 &c, const __bf16 *)
+__device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 &c, floatx16 &, const __bf16 *)
 {
     c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
-__device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 &c, const float *)
+__device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 &c, floatx16 &odd, const float *)
 {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(b[e]), c, 0, 0, 0);
+    for (int e = 0; e < 4; ++e) {
+        floatx16 &to = e % 2 == 0 ? c : odd;
+        to = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(b[e]), to, 0, 0, 0);
+    }
 }
 
 // LDS placement of 16-byte chunk c of tile row `row`: slot c ^ swizzle, conflict-free for the fragment reads
@@ -252,6 +254,10 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
         }
     };
 
+    // fp32 tiles of one block a wavefront keep two sums, of the products at even and at odd places: the finer tiles cut K less often than
+    // the larger ones did, and this way no sum is longer than theirs.
+    constexpr bool kTwoSums = sizeof(T) == 4 && WTN * WTM == 1;
+    floatx16 odd = {};
     floatx16 acc[WTN][WTM];
 #pragma unroll
     for (int i = 0; i < WTN; ++i)
@@ -288,7 +294,7 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
             for (int i = 0; i < WTN; ++i)
 #pragma unroll
                 for (int j = 0; j < WTM; ++j)
-                    mma(a[ks][i], b[ks][j], acc[i][j], (const T *)nullptr);
+                    mma(a[ks][i], b[ks][j], acc[i][j], kTwoSums ? odd : acc[i][j], (const T *)nullptr);
     };
 
     // ---- main loop ----
@@ -369,6 +375,9 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     stamp(2);
     stamp(kTimelineCycleSlot + 1);
     lds_barrier();  // all fragment reads done: the stages become the product's place
+
+    if constexpr (kTwoSums)
+        acc[0][0] += odd;
 
     // ---- product to LDS, [kWK][row][column] ----
     float *prod = reinterpret_cast<float *>(smem);

@@ -1,4 +1,4 @@
-"""Tiles of 32 x 32 of the kernel that cuts K: fewer slabs than the eight LDS stages and more, a slab that K cuts, K cut over
+"""Tiles of 32 x 32, and in fp32 of 64 x 32 over 64 rows, of the kernel that cuts K: fewer slabs than the eight LDS stages and more, a slab that K cuts, K cut over
 two and four workgroups, rows and columns that end inside a tile, against the oracle, bit for bit run to run."""
 import pytest
 import torch
@@ -37,3 +37,20 @@ def test_against_the_oracle(M, K, N, dtype, S):
     got = torch.empty_like(Y)
     B.ff_fused_linear_gelu_ln_noalloc(*[d[k].cuda() for k in ("X", "W", "b", "gamma", "beta")], d["eps"], got)
     assert torch.equal(Y, got)
+
+
+# 64 x 32 tiles: one, two and three workgroups a unit, K cut in two
+FLAT = [(331, 1536, 1460, 1), (80, 544, 4608, 1), (1000, 320, 1056, 1), (400, 288, 2340, 1), (2033, 2560, 636, 1), (289, 2368, 1312, 2), (326, 992, 2156, 2)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,S", FLAT)
+def test_flat_tiles(M, K, N, S):
+    plan = _plan(M, K, N, "f32")
+    print("[case] flat tiles", M, K, N, plan, flush=True)
+    assert (plan["tile_m"], plan["tile_n"], plan["grid"]) == (32, 64, -(-M // 32) * -(-N // 64) * S)
+    d = make_inputs(M, K, N, "f32", seed=107)
+    Y, used = gpu_run(d)
+    assert used == B.FF_VARIANT_TILED_FUSED
+    print(check_against_oracle(Y, oracle_on(d), "f32", "flat tiles %dx%dx%d" % (M, K, N)))
+    assert torch.equal(Y, gpu_run(d)[0])
