@@ -319,7 +319,8 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
     // a slab is requested twice, and eight wavefronts go to HBM for half of W's lines a second time (147 x 10568 x 6016
     // 89 us, with four 76; K = 10560: 62, 66).  206 such shapes: up to 48 slabs a workgroup eight win (0.94 of the time),
     // beyond them four do (0.95, at best 0.80: 1284 x 9832 x 2432 150 us, 119); with this line a call takes 0.5 % more than
-    // with the better of the two on average, 8.6 at most, 2.6 and 25 with eight throughout.
+    // with the better of the two on average, 8.6 at most, 2.6 and 25 with eight throughout.  (So it was with slabs.  By lines, as both go
+    // now, eight take 0.8 to 0.97 of four's time: 1284 x 9832 x 2432 80 us, 101; the tests of this line ask for four.)
     if (bf16 && pl.split_shape == kSplit128 && K % 32 != 0 && (slabs + pl.split_s - 1) / pl.split_s > 48)
         pl.split_shape = kSplit128W4;
     pl.rounds = 1;

@@ -13,7 +13,7 @@
 //   3  normalise, convert, store.
 // Measured against the two-stage loop of the tile kernel (cold inputs, whole call): 96 x 8192 x 8192
 // bf16 104.7 -> 44.5 us (W at 3.0 TB/s), 512 x 8192 x 8192 bf16 125 -> 86, 64 x 4096 x 4096 fp32 98 -> 31,
-// 256 x 512 x 512 fp32 17.3 -> 11.5 (on the device); over 336 drawn shapes 1.36 (bf16) and 1.50 (fp32) times
+// 256 x 512 x 512 fp32 17.3 -> 9.6; over 336 drawn shapes 1.36 (bf16) and 1.50 (fp32) times
 // as fast, none slower.  What is left at 96 x 8192 x 8192: 27 us of reading W at the rate of a large copy, and
 // launch, two meetings and the ramp of the stream.
 // A thread owns four consecutive columns of one row per pass, so everything after the product stays in
