@@ -152,9 +152,9 @@ int resident_split_blocks(DeviceState *st, bool bf16, int shape)
 // 32 x 32 tiles have a model of their own, fitted to 2 300 runs of 1 132 shapes (M 1..2048, K 128..8192, N 128..8192, S 1 to 4; off by
 // 2 (fp32) and 3 % (bf16) on average): two to sixteen times as many tiles as of the other shapes, so that K need not be cut and the
 // tile's workgroups need not meet, at twice the bytes through a unit's load path and more.  256 x 512 x 512 fp32 11.6 us,
-// now 9.6; 512 x 1024 x 512 bf16 10.7, 8.6.  They are taken where their estimate is 4 % below the others', which are 6 % high here
-// (in fp32 0.91 of the time over all these shapes, 0.5 % above the better of the two, at most 1.03; in bf16, whose estimates scatter
-// more, uncut and over 16 rows only: 0.985, at most 1.14).
+// now 9.6; 512 x 1024 x 512 bf16 10.7, 8.6.  They are taken where their estimate is 4 (bf16, whose estimates scatter more: 10) % below the others', which
+// are 6 % high here, in bf16 uncut and over 16 rows only (fp32: 0.91 of the time over all these shapes, 0.5 % above the better of the two, at
+// most 1.03; bf16, where taken, 0.87, at most 0.93; between 0.90 and 0.99 of the others' estimate 0.90 to 1.07).
 // fp32 over 64 rows has 64 x 32 tiles beside them, up to three a unit, from eight slabs on: bound by the matrix units, it gains from
 // finer tiles where larger ones fill the last round badly.  Their model was fitted to 1 500 runs of 980 shapes (off by 2.6 %);
 // taken where it says 6 % less than the others, whose estimates are 5 % high here, 0.91 of the time, 1 % above the better of the
@@ -300,7 +300,7 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
     }
     SmallTiles small = small_tiles(M, K, N, bf16, num_cus, st);
     const SmallTiles flat = bf16 ? SmallTiles() : flat_tiles(M, K, N, num_cus, st);
-    bool takes = small.s != 0 && small.us < 0.96 * (best - (bf16 ? 0.5 : 0.3));
+    bool takes = small.s != 0 && small.us < (bf16 ? 0.90 * (best - 0.5) : 0.96 * (best - 0.3));
     if (flat.s != 0 && flat.us < 0.893 * best && !(takes && small.us <= flat.us)) {
         small = flat;
         takes = true;
