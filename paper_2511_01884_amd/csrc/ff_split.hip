@@ -29,17 +29,16 @@ constexpr int kRowBytes = 128;   // bytes of one tile row per K slab (8 chunks o
 // LDS stages of a tile shape: four, and eight of the small slabs of 32 x 32 tiles, so that as many bytes are in flight
 constexpr int ring_of(int tile_cols, int tile_rows) { return tile_cols + tile_rows <= 64 ? 8 : 4; }
 
-__device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 &c, floatx16 &, const __bf16 *)
+// c: a block's sum, or in fp32 the SUMS that it is kept in, its products dealt to them in turn
+template <int SUMS> __device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 (&c)[SUMS], const __bf16 *)
 {
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    c[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c[0], 0, 0, 0);
 }
-__device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 &c, floatx16 &odd, const float *)
+template <int SUMS> __device__ __forceinline__ void mma(const uintx4 &a, const uintx4 &b, floatx16 (&c)[SUMS], const float *)
 {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        floatx16 &to = e % 2 == 0 ? c : odd;
-        to = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(b[e]), to, 0, 0, 0);
-    }
+    for (int e = 0; e < 4; ++e)
+        c[e % SUMS] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(b[e]), c[e % SUMS], 0, 0, 0);
 }
 
 // LDS placement of 16-byte chunk c of tile row `row`: slot c ^ swizzle, conflict-free for the fragment reads
@@ -121,7 +120,7 @@ template <> struct RawCols<__bf16> {
 // short shares and W that lies in the L2 do not earn back (takes_lines).
 // 512 x 4104 x 4096 33.2 us, now 30.1; 237 x 6408 x 7648 62.1, 50.8; 2089 x 2952 x 1232 40.3, 31.4; 96 x 8200 x 8192 48.2,
 // 39.3; the same bits.
-template <typename T, int kWN, int kWM, int kWK, int WTN, int WTM, bool LINES>
+template <typename T, int kWN, int kWM, int kWK, int WTN, int WTM, bool LINES, int kSums>
 __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN == 1 ? 2 : 1) void split_kernel(const SplitParams p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)  // the body uses device-only types (buffer descriptors)
@@ -254,18 +253,16 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
         }
     };
 
-    // fp32 tiles of one block a wavefront keep two sums, of the products at even and at odd places: the finer tiles cut K less often than
-    // the larger ones did, and this way no sum is longer than theirs.
-    constexpr bool kTwoSums = sizeof(T) == 4 && WTN * WTM == 1;
-    floatx16 odd = {};
-    floatx16 acc[WTN][WTM];
+    floatx16 acc[WTN][WTM][kSums];
 #pragma unroll
     for (int i = 0; i < WTN; ++i)
 #pragma unroll
         for (int j = 0; j < WTM; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                acc[i][j][r] = 0.0f;
+            for (int k = 0; k < kSums; ++k)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    acc[i][j][k][r] = 0.0f;
     const int swz = swizzle_of_row(l32);
     const int a_base = (wn * WTN * 32 + l32) * kRowBytes;
     const int b_base = (BN + wm * WTM * 32 + l32) * kRowBytes;
@@ -294,7 +291,7 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
             for (int i = 0; i < WTN; ++i)
 #pragma unroll
                 for (int j = 0; j < WTM; ++j)
-                    mma(a[ks][i], b[ks][j], acc[i][j], kTwoSums ? odd : acc[i][j], (const T *)nullptr);
+                    mma(a[ks][i], b[ks][j], acc[i][j], (const T *)nullptr);
     };
 
     // ---- main loop ----
@@ -376,8 +373,11 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
     stamp(kTimelineCycleSlot + 1);
     lds_barrier();  // all fragment reads done: the stages become the product's place
 
-    if constexpr (kTwoSums)
-        acc[0][0] += odd;
+    static_assert(kSums == 1 || WTN * WTM == 1, "several sums of one block only");
+    if constexpr (kSums > 2)
+        acc[0][0][0] = (acc[0][0][0] + acc[0][0][1]) + (acc[0][0][2] + acc[0][0][3]);
+    else if constexpr (kSums > 1)
+        acc[0][0][0] += acc[0][0][1];
 
     // ---- product to LDS, [kWK][row][column] ----
     float *prod = reinterpret_cast<float *>(smem);
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(64 * kWN * kWM * kWK, kWN * kWM * kWK == 8 || WTN =
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     *reinterpret_cast<floatx4 *>(mine + ((wm * WTM + j) * 32 + l32) * kPitch + (wn * WTN + i) * 32 + q * 8 + h * 4) =
-                        floatx4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                        floatx4{acc[i][j][0][4 * q], acc[i][j][0][4 * q + 1], acc[i][j][0][4 * q + 2], acc[i][j][0][4 * q + 3]};
     }
     lds_barrier();
     const int r_in_pass = tid / kLanes;
@@ -667,6 +667,20 @@ template <typename T, int WN, int WM, int WTN, int WTM> static constexpr bool ha
     return sizeof(T) == 2 && WN * WTN == 4 && WM * WTM >= 2;
 }
 
+// Sums of a block in fp32 tiles of one block a wavefront.  Four, one for each of a chunk's elements, in those that take the place of larger ones
+// (32 x 32, and 64 x 32 over 64 rows): K is cut over fewer workgroups there, and this way no sum has more terms than in the larger tiles (316 x 3328 x
+// 512: 208 in 64 x 64 tiles cut in eight; in 32 x 32 with the whole of K 416 with two sums, which was up to 1.11 of the error,
+// 208 with four).  Two elsewhere: the others add 0.1 us.
+template <typename T, int WN, int WM, int WTN, int WTM> static constexpr int sums_of()
+{
+    return sizeof(T) == 2 || WTN * WTM > 1 ? 1 : (WM == 1 ? 4 : 2);
+}
+// the same up to 64 rows, where 64 x 32 tiles replace nothing
+template <typename T, int WN, int WM, int WTN, int WTM> static constexpr int few_rows_sums()
+{
+    return sums_of<T, WN, WM, WTN, WTM>() == 4 && WN == 2 ? 2 : sums_of<T, WN, WM, WTN, WTM>();
+}
+
 // Whether such a launch goes by lines: rows off the line boundaries, and enough slabs for each workgroup.  170 shapes, M
 // 33..2048: rows on every other 64-byte boundary, or K cut over four and more workgroups (narrow W mostly, which the L2
 // holds), gain from 24 slabs on (0.92 of the time; 10 to 23: 1.01), the rest from 9 (0.93; below 1.03).  The four wavefronts of the
@@ -686,21 +700,30 @@ static bool takes_lines(const SplitParams &p, int waves)
 template <typename T, int WN, int WM, int WK, int WTN, int WTM>
 static hipError_t launch_split(const SplitParams &p, int grid, hipStream_t stream)
 {
+    const dim3 threads(64 * WN * WM * WK);
+    constexpr int kSums = sums_of<T, WN, WM, WTN, WTM>();
     if constexpr (has_lines<T, WN, WM, WTN, WTM>())
         if (takes_lines(p, WN * WM * WK)) {
-            hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM, true>), dim3(grid), dim3(64 * WN * WM * WK), 0, stream, p);
+            hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM, true, 1>), dim3(grid), threads, 0, stream, p);
             return hipGetLastError();
         }
-    hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM, false>), dim3(grid), dim3(64 * WN * WM * WK), 0, stream, p);
+    constexpr int kFewRowsSums = few_rows_sums<T, WN, WM, WTN, WTM>();
+    if constexpr (kFewRowsSums != kSums)
+        if (p.M <= 64) {
+            hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM, false, kFewRowsSums>), dim3(grid), threads, 0, stream, p);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM, false, kSums>), dim3(grid), threads, 0, stream, p);
     return hipGetLastError();
 }
 
 template <typename T, int WN, int WM, int WK, int WTN, int WTM>
 static int split_blocks()
 {
+    constexpr int kSums = sums_of<T, WN, WM, WTN, WTM>();
     int a = 0, b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, split_kernel<T, WN, WM, WK, WTN, WTM, false>, 64 * WN * WM * WK, 0) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, split_kernel<T, WN, WM, WK, WTN, WTM, has_lines<T, WN, WM, WTN, WTM>()>,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, split_kernel<T, WN, WM, WK, WTN, WTM, false, kSums>, 64 * WN * WM * WK, 0) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, split_kernel<T, WN, WM, WK, WTN, WTM, has_lines<T, WN, WM, WTN, WTM>(), few_rows_sums<T, WN, WM, WTN, WTM>()>,
                                                      64 * WN * WM * WK, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 0;

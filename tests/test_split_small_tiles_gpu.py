@@ -1,5 +1,6 @@
 """Tiles of 32 x 32, and in fp32 of 64 x 32 over 64 rows, of the kernel that cuts K: fewer slabs than the eight LDS stages and more, a slab that K cuts, K cut over
-two and four workgroups, rows and columns that end inside a tile, against the oracle, bit for bit run to run."""
+two and four workgroups, rows and columns that end inside a tile, against the oracle, bit for bit run to run; fp32: how many terms a
+sum has."""
 import pytest
 import torch
 
@@ -54,3 +55,31 @@ def test_flat_tiles(M, K, N, S):
     assert used == B.FF_VARIANT_TILED_FUSED
     print(check_against_oracle(Y, oracle_on(d), "f32", "flat tiles %dx%dx%d" % (M, K, N)))
     assert torch.equal(Y, gpu_run(d)[0])
+
+
+# (M, K, N, rows and columns of a tile, terms of a sum in the larger tiles: K over the workgroups and wavefronts that shared it)
+SUMS = [(316, 3328, 512, 32, 32, 208), (256, 3072, 628, 32, 32, 192), (256, 1536, 2048, 32, 64, 192), (544, 1536, 768, 32, 64, 192),
+        (309, 1280, 1024, 32, 64, 160)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,rows,cols,terms", SUMS)
+def test_no_sum_is_longer_than_in_the_larger_tiles(M, K, N, rows, cols, terms):
+    """Every fourth column's row of W is 2^26, ones, and -2^26 at the same place of the last slab, so in the same sum: that sum
+    drops the ones between the two (half a unit in the last place of 2^26 is 4), every other sum keeps its own."""
+    plan = _plan(M, K, N, "f32")
+    print("[case] terms of a sum", M, K, N, plan, flush=True)
+    assert (plan["tile_m"], plan["tile_n"], plan["grid"]) == (rows, cols, -(-M // rows) * -(-N // cols))
+    X, W = torch.ones(M, K), torch.ones(N, K)
+    W[0::4, 0], W[0::4, K - 32] = 2.0 ** 26, -2.0 ** 26
+    W[1::4], W[2::4] = 0.25, 0.5
+    Y = B.ff_fused_linear_gelu_ln(X.cuda(), W.cuda(), None, None, None, 1e-5)
+    B.ff_check_device()
+    Y = Y.cpu().double()
+    # z is K / 4, K / 2 and K in the other columns, GELU leaves such values as they are, and the normalisation is affine
+    low, high = Y[:, 1:2], Y[:, 3:4]
+    z = K / 4 + (Y[:, 0::4] - low) / (high - low) * (K * 3 / 4)
+    dropped = K - 2 - z
+    print("dropped", float(dropped.min()), float(dropped.max()), "of", K, flush=True)
+    assert float((Y[:, 2:3] - low - (high - low) / 3).abs().max()) < 1e-5
+    assert 0 < float(dropped.min()) and float(dropped.max()) <= terms
