@@ -49,7 +49,7 @@
  *     it or a caller binds another: graphs recorded with it stay valid.
  *     A call whose automatic plan needs more than a bound workspace, or during a
  *     capture than the library's own, takes a plan that needs less where there is
- *     one (another kernel, or a smaller grid) before it returns FF_ERR_WORKSPACE:
+ *     one (larger tiles, another kernel, or a smaller grid) before it returns FF_ERR_WORKSPACE:
  *     slower, and not bit for bit the result with a workspace of the size that the
  *     *_workspace_bytes functions report.  With that size results are bitwise
  *     reproducible on a device.  Calls that share a workspace must

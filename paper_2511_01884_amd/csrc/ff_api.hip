@@ -89,6 +89,11 @@ struct Plan {
     size_t sums_off = 0;
 };
 
+// Which plans a call may take, by the scratch memory that there is: any; those without the finer tiles, which need up to twice the
+// row statistics of the tiles they replace, or partial products where those need none; those that need least, which cut no K and keep the
+// larger tiles.
+enum Scratch { kScratchAny, kScratchCoarse, kScratchLeast };
+
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 int validate_shape(int64_t M, int64_t K, int64_t N, int dtype)
@@ -225,7 +230,7 @@ SmallTiles flat_tiles(int64_t M, int64_t K, int64_t N, int num_cus, DeviceState 
     return best;
 }
 
-bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceState *st, Plan &pl)
+bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceState *st, bool finer, Plan &pl)
 {
     // workgroups per compute unit that the LDS allows (what the runtime reports is asked as well)
     constexpr int kPerCu[] = {3, 2, 2, 1, 1};
@@ -298,8 +303,8 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
         pl = narrow;
         best = narrow_us;
     }
-    SmallTiles small = small_tiles(M, K, N, bf16, num_cus, st);
-    const SmallTiles flat = bf16 ? SmallTiles() : flat_tiles(M, K, N, num_cus, st);
+    SmallTiles small = finer ? small_tiles(M, K, N, bf16, num_cus, st) : SmallTiles();
+    const SmallTiles flat = finer && !bf16 ? flat_tiles(M, K, N, num_cus, st) : SmallTiles();
     bool takes = small.s != 0 && small.us < (bf16 ? 0.90 * (best - 0.5) : 0.96 * (best - 0.3));
     if (flat.s != 0 && flat.us < 0.893 * best && !(takes && small.us <= flat.us)) {
         small = flat;
@@ -334,9 +339,9 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
 }
 
 int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceState *st, int forced,
-              bool linear_only, Plan &pl, bool roomy = true)
+              bool linear_only, Plan &pl, Scratch scratch = kScratchAny)
 {
-    const bool bf16 = dtype == FF_BF16;
+    const bool bf16 = dtype == FF_BF16, finer = scratch == kScratchAny, roomy = scratch != kScratchLeast;
     const int64_t strips = (N + kSmallMStripCols - 1) / kSmallMStripCols;
     const bool smallm_ok = bf16 && M <= 32 && strips <= (int64_t)num_cus * kSmallMMaxStripsPerGroup;
 
@@ -359,7 +364,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // Over 16 rows the streamer's registers no longer cover its loads (22 x 5888 x 6008: 34.6, 22; never faster).
     // (A forced variant, tile or wavefront count names the kernel it named before there was a split one.)
     const bool may_split = roomy && !linear_only && forced == FF_VARIANT_AUTO && g_forced_tile == 0 && g_forced_waves == 0;
-    if (may_split && plan_split(M, K, N, bf16, num_cus, st, pl)) {
+    if (may_split && plan_split(M, K, N, bf16, num_cus, st, finer, pl)) {
         // (short rows of W that end inside a line: 3 x 136 x 7720 stays with the streamer; from 512 on no such shape gains)
         const double split_us = pl.split_us + (K % 64 != 0 && K < 512 ? 0.7 : 0.0);
         const double rounds = (double)((strips + num_cus - 1) / num_cus);
@@ -412,8 +417,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     const bool half_empty = ((N + 127) / 128) % 2 != 0;
     const bool two_a_unit = tiles128 * 4 <= 5 * num_cus && pays &&
                             (half_empty || (tiles128 * 32 <= 33 * num_cus && across > 2) || K < 256);
-    // (A plan for little scratch memory, roomy = false, splits nothing and keeps the larger tiles, which have
-    // half the row statistics.)
+    // (A plan for the least scratch memory splits nothing and keeps the larger tiles, which have half the row statistics.)
     // fp32 in several rounds: 128 x 128 tiles, two a unit, in plain order.  A round of them is two units of matrix time, one of at
     // most half as many 1.15 (a unit's lone workgroup does not quite fill its matrix pipes), where a round of 256 x 256 tiles is
     // four units, however few of the compute units have one.  Microseconds: matrix time, and the rest of a tile.  70 shapes (M, N
@@ -430,7 +434,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // of larger tiles for very long X.)
     const bool room128 = kCtrlBytes + (size_t)tiles128 * 128 * sizeof(floatx2) <= kNoAllocBytes && (M + 127) / 128 < kMaxRowBlocks &&
                          N <= 128 * (int64_t)num_cus;
-    if (!bf16 && may_split && room128 && tiles128 > 2 * num_cus) {
+    if (!bf16 && may_split && finer && room128 && tiles128 > 2 * num_cus) {
         const int64_t rest = tiles128 % (2 * num_cus);
         const double units = 2.0 * (double)(tiles128 / (2 * num_cus)) + (rest == 0 ? 0.0 : (rest <= num_cus ? 1.15 : 2.0));
         const int64_t rows256 = (M + 255) / 256;
@@ -441,7 +445,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
         in_turn = us128 < 0.92 * us256;
     }
     const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
-    if (!bf16 && may_split && (in_turn || (tiles128 <= 2 * num_cus && tiles128 * 4 > num_cus)) && N <= 128 * (int64_t)num_cus &&
+    if (!bf16 && may_split && finer && (in_turn || (tiles128 <= 2 * num_cus && tiles128 * 4 > num_cus)) && N <= 128 * (int64_t)num_cus &&
         kCtrlBytes + (size_t)tiles64 * 64 * sizeof(floatx2) <= kNoAllocBytes && (M + 63) / 64 < kMaxRowBlocks) {
         const int64_t rest = tiles128 % (2 * num_cus), rest64 = tiles64 % (4 * num_cus);
         const double units128 = 2.0 * (double)(tiles128 / (2 * num_cus)) + (rest == 0 ? 0.0 : (rest <= num_cus ? 1.15 : 2.0));
@@ -456,7 +460,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // 2048 x 10856 52.7, 55.3).  So too two rounds of these for two of those, if a row has up to 16 (14 shapes 0.80: 9596 x 256 x
     // 1552 40.6, 30.3; 22038 x 7936 x 552 345, 291; with 40 and more 0.9 to 1.3).  Not where plain order (below) saves half a round.
     bool pair_half = false, pair128 = false;
-    if (bf16 && may_split && room128 && tiles256 * 2 > num_cus) {
+    if (bf16 && may_split && finer && room128 && tiles256 * 2 > num_cus) {
         const int64_t rows256 = (M + 255) / 256, rows128 = (M + 127) / 128, across128 = (N + 127) / 128;
         const bool one = tiles256 <= num_cus, plain = across * 2 <= num_cus && rows256 == num_cus / across + 1 && K >= 2048;
         const bool two = !one && across * 2 <= num_cus && rows256 <= 2 * (num_cus / across) && !plain;
@@ -746,20 +750,19 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
     DeviceState *st = current_device_state();
     if (!st)
         return FF_ERR_LAUNCH;
+    // the first plan that the scratch memory holds, or else the one that needs least
     Plan pl;
-    rc = make_plan(M, K, N, dtype, st->num_cus, st, g_forced_variant, linear_only, pl);
-    if (rc != FF_OK)
-        return rc;
-    char *ws = nullptr;
-    const size_t held = pl.split_s > 0 ? pl.sums_off : pl.total_bytes;  // without the partial products
-    if (no_alloc ? held > kNoAllocBytes || pl.total_bytes - held > kNoAllocSumBytes
-                 : pl.total_bytes > st->ws_bytes && pl.total_bytes > workspace_limit(*st, stream)) {
-        // not enough scratch memory for this plan: the one that needs least
+    for (const Scratch scratch : {kScratchAny, kScratchCoarse, kScratchLeast}) {
         pl = Plan();
-        rc = make_plan(M, K, N, dtype, st->num_cus, st, g_forced_variant, linear_only, pl, false);
+        rc = make_plan(M, K, N, dtype, st->num_cus, st, g_forced_variant, linear_only, pl, scratch);
         if (rc != FF_OK)
             return rc;
+        const size_t held = pl.split_s > 0 ? pl.sums_off : pl.total_bytes;  // without the partial products
+        if (no_alloc ? held <= kNoAllocBytes && pl.total_bytes - held <= kNoAllocSumBytes
+                     : pl.total_bytes <= st->ws_bytes || pl.total_bytes <= workspace_limit(*st, stream))
+            break;
     }
+    char *ws = nullptr;
     if (no_alloc) {
         // the static array is the workspace; what the kernels expect to find zero (error word, the
         // arrival counters this plan uses) is cleared by a kernel on the caller's stream first
