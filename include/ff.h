@@ -167,7 +167,9 @@ size_t ff_cross_entropy_workspace_bytes(int64_t B, int64_t C, int dtype);
  * Outputs are HOST pointers, each optional (NULL): r [n_tasks][n_metrics], score [n_metrics],
  * top int32 [n_tasks][top_k] (-1 padded), selected uint8 [n_metrics], threshold [1].
  * The correlations run on the device on `stream`; the call returns after the stream has been
- * synchronised and the host outputs are complete.  Uses the workspace.  Returns an ff_status.
+ * synchronised and the host outputs are complete.  Uses the workspace; beside the library's own it has up to
+ * 4 MiB of pinned host memory a device for the results, which is allocated and grown like it and freed when a caller
+ * binds or unbinds memory.  With a bound workspace nothing is allocated on the device or pinned.  Returns an ff_status.
  */
 int ff_metric_selection(const double *values, const double *runtime, int64_t n_tasks,
                         int64_t n_kernels, int64_t n_metrics, int top_k, double percentile,

@@ -55,7 +55,7 @@ struct DeviceState {
     void *no_alloc_ptr = nullptr;            // this device's copy of `scratch`, once asked for
     void *no_alloc_sums = nullptr;           // the same for `scratch_sums`
     bool no_alloc_used = false;
-    void *pinned = nullptr;                  // host memory that the selection's kernels write their results to
+    void *pinned = nullptr;                  // host memory that the selection's kernels write their results to, with the own workspace
     size_t pinned_bytes = 0;
     unsigned long long *timeline = nullptr;  // test hook: phase timestamps of the tiled kernels
     size_t timeline_bytes = 0;
@@ -676,23 +676,32 @@ int prepare_workspace(DeviceState &st, size_t bytes, hipStream_t stream)
     return FF_OK;
 }
 
-// Host memory of at least `bytes` that kernels can write to, or null: up to 4 MiB a device, held until the process ends.
-// Used under the lock from launch to synchronisation, so that nothing is in flight when it is replaced by a larger one.
-// (A copy into pageable memory behind the kernels: eight tasks of 10 x 300 take 15 us longer.)
+// Host memory of at least `bytes` that kernels can write to, or null: up to 4 MiB a device.  It belongs to the library's own workspace: a
+// caller who binds memory gets no allocation from a call, and binding or unbinding frees it.  Used under the lock from launch to
+// synchronisation, so that nothing is in flight when it is freed or replaced by a larger one.
+// (A copy into pageable memory behind the kernel: eight tasks of 10 x 300 take 15 us longer.)
 constexpr size_t kPinnedMost = 4u << 20;
-void *pinned_results(DeviceState &st, size_t bytes)
+void release_pinned(DeviceState &st)
+{
+    if (st.pinned != nullptr && hipHostFree(st.pinned) != hipSuccess)
+        (void)hipGetLastError();
+    st.pinned = nullptr;
+    st.pinned_bytes = 0;
+}
+void *pinned_results(DeviceState &st, size_t bytes, hipStream_t stream)
 {
     if (bytes > kPinnedMost)
         return nullptr;
     if (st.pinned_bytes < bytes) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         void *mem = nullptr;
         const size_t want = std::min(kPinnedMost, round_up(2 * bytes, 64u << 10));
-        if (hipHostMalloc(&mem, want, hipHostMallocDefault) != hipSuccess) {
+        if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone ||
+            hipHostMalloc(&mem, want, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
         }
-        if (st.pinned != nullptr)
-            (void)hipHostFree(st.pinned);
+        release_pinned(st);
         st.pinned = mem;
         st.pinned_bytes = want;
     }
@@ -1161,18 +1170,21 @@ int ff_metric_selection(const double *values, const double *runtime, int64_t n_t
         const bool bound = st->ws != nullptr && !st->ws_owned;
         const size_t have = bound ? (st->ws_bytes > kCtrlBytes ? st->ws_bytes - kCtrlBytes : 0) : SIZE_MAX;
         const size_t result_bytes = count * (sizeof(double) + (filter ? 1 : 0));
+        double *const pinned = bound ? nullptr : static_cast<double *>(pinned_results(*st, result_bytes, st_stream));
         // One launch does it all where a task fits the LDS and there is room for all tasks' bits.
         const size_t mask_bytes = (size_t)n * selection_mask_bytes(J);
-        const bool one_launch = filter && selection_fits(V, J) && n <= 4096 && mask_bytes <= std::min(have, (size_t)64 << 20);
-        double *const pinned = static_cast<double *>(one_launch || !bound ? pinned_results(*st, result_bytes) : nullptr);
-        if (one_launch && pinned != nullptr) {
-            const int rc = prepare_workspace(*st, kCtrlBytes + mask_bytes, st_stream);
+        const size_t one_out = pinned != nullptr ? 0 : round_up(result_bytes, 256);
+        if (filter && selection_fits(V, J) && n <= 4096 && mask_bytes <= (size_t)64 << 20 && one_out + mask_bytes <= have) {
+            const int rc = prepare_workspace(*st, kCtrlBytes + one_out + mask_bytes, st_stream);
             if (rc != FF_OK)
                 return rc;
             char *ws = static_cast<char *>(st->ws);
-            if (launch_selection(values, runtime, pinned, reinterpret_cast<unsigned char *>(pinned + count),
-                                 reinterpret_cast<unsigned long long *>(ws + kCtrlBytes),
+            double *const r_out = pinned != nullptr ? pinned : reinterpret_cast<double *>(ws + kCtrlBytes);
+            if (launch_selection(values, runtime, r_out, reinterpret_cast<unsigned char *>(r_out + count),
+                                 reinterpret_cast<unsigned long long *>(ws + kCtrlBytes + one_out),
                                  reinterpret_cast<unsigned *>(ws + kCounterOffset), collinear_tau, n, V, J, st_stream) != hipSuccess)
+                return FF_ERR_LAUNCH;
+            if (pinned == nullptr && hipMemcpyAsync(r, r_out, result_bytes, hipMemcpyDeviceToHost, st_stream) != hipSuccess)
                 return FF_ERR_LAUNCH;
         } else {
             // Workspace: r and the verdicts of all tasks, unless they go to host memory; for a batch of tasks, the columns'
@@ -1286,6 +1298,7 @@ int ff_set_workspace(void *dev_ptr, size_t bytes)
         (void)hipGetLastError();
         return FF_ERR_LAUNCH;  // the old binding stays
     }
+    release_pinned(*st);
     if (st->ws != nullptr && st->ws_owned && !release_own(*st)) {
         (void)hipGetLastError();
         return FF_ERR_LAUNCH;
