@@ -187,7 +187,8 @@ constexpr int kSyncStride = 1024;  // uint32 words between ways
 // Departure from such a meeting: the last workgroup of the last way re-arms every counter (only then has every workgroup
 // left its wait, so that no poller can see a counter go back to zero).  In three steps, one thread's, begun as soon as
 // the workgroup's own wait is over: the two round trips to memory pass behind the work that follows, and no
-// longer stand at the end of the kernel (16 x 8192 x 8192 36.6 us, now 36.2; second chain 300 x 4096 x 1024 12.5, 12.0).
+// longer stand at the end of the kernel (16 x 8192 x 8192 36.6 us, now 36.2; second chain 300 x 4096 x 1024 12.5, 12.0;
+// of much X it begins behind the rows).
 struct Departure {
     unsigned seen = 0;
     __device__ __forceinline__ void begin(unsigned *counters, unsigned way)

@@ -223,7 +223,8 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
     }
     __syncthreads();
     Departure leave;
-    if (tid == 0)
+    const bool leaves_early = p.leaves_early != 0;
+    if (leaves_early && tid == 0)
         leave.begin(p.counters, way);
 
     // ---- phase 2: wbar into LDS (chunk partials added in chunk order), c, then one wavefront per row ----
@@ -411,7 +412,7 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
             }
         }
     };
-    if (tid == 0)
+    if (leaves_early && tid == 0)
         leave.middle(p.counters, way, G);
     if constexpr (SETS == 1) {
         finish_rows(m_first, keep[0]);
@@ -426,8 +427,13 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
         }
     }
 
-    if (tid == 0)
+    if (tid == 0) {
+        if (!leaves_early) {
+            leave.begin(p.counters, way);
+            leave.middle(p.counters, way, G);
+        }
         leave.end(p.counters, G);
+    }
 }
 
 template <typename T, int PL, int R, int WPR, int SETS = 2>
