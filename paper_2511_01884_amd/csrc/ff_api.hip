@@ -163,7 +163,9 @@ int resident_split_blocks(DeviceState *st, bool bf16, int shape)
 // fp32 over 64 rows has 64 x 32 tiles beside them, up to three a unit, from eight slabs on: bound by the matrix units, it gains from
 // finer tiles where larger ones fill the last round badly.  Their model was fitted to 1 500 runs of 980 shapes (off by 2.6 %);
 // taken where it says 6 % less than the others, whose estimates are 5 % high here, 0.91 of the time, 1 % above the better of the
-// two, at most 1.02 (2033 x 2560 x 632 89 us, 71; 855 x 2272 x 1024 49, 46).
+// two, at most 1.02 (2033 x 2560 x 632 89 us, 71; 855 x 2272 x 1024 49, 46).  Two whole ones a unit do not replace tiles up to 128 x 64 with K cut in
+// two (67 shapes 1.03 to 1.07: 256 x 2560 x 3840 50.6 us, 53.7; but 206 x 3840 x 4372, 128 x 128 cut in two, 0.62), nor more than 2.3 a unit under
+// ten slabs where a row has 80 and more (60 shapes 1.03, at most 1.05: 256 x 256 x 5888 18.4 us, 19.2; up to 2.3 0.96 to 1.00, with 60 to 79 tiles 0.96).
 struct SmallTiles {
     int shape = kSplit32, s = 0;
     double us = 0.0;
@@ -180,8 +182,12 @@ SmallTiles small_tiles(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, 
     // Where rows lie off the line boundaries and N ends inside a tile the larger tiles stay.  (Those would gain too, in fp32 0.91 of the
     // time against 0.89 for rows on line boundaries; the tests of the larger tiles' edges are such shapes.)
     // bf16 of up to eight slabs, whose one load latency the larger tiles wait for as well, gains nothing on average (59 shapes 1.00),
-    // nor does it beyond 32 (K 2048 to 4096: 1.05).
-    if ((bf16 && (M <= 16 || slabs <= 8 || slabs > 32)) || RB * NT > 2 * (int64_t)num_cus || (K * size % 128 != 0 && N % 32 != 0))
+    // nor does it beyond 32 (K 2048 to 4096: 1.05), nor with two workgroups a unit and rows on 64-byte boundaries (0.98 to 1.14 of the larger
+    // tiles' time: 1995 x 1280 x 256 11.0 us, 12.6 in 504 of these; rows off them 0.90 to 1.05: 671 x 1992 x 768 16.8, 15.4).
+    // fp32 of few rows in 80 and more tiles each has too many to merge (70 shapes 1.07, at most 1.12: 29 x 416 x 2560 10.4, 11.5).
+    const bool two_a_unit = !bf16 || K % 32 != 0;
+    if ((bf16 && (M <= 16 || slabs <= 8 || slabs > 32)) || RB * NT > (two_a_unit ? 2 : 1) * (int64_t)num_cus ||
+        (K * size % 128 != 0 && N % 32 != 0) || (!bf16 && M <= 64 && NT >= 80))
         return best;
     const int resident = resident_split_blocks(st, bf16, kSplit32);
     for (int S = 1; S <= (bf16 ? 1 : 4); S *= 2) {
@@ -202,7 +208,7 @@ SmallTiles small_tiles(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, 
     return best;
 }
 
-SmallTiles flat_tiles(int64_t M, int64_t K, int64_t N, int num_cus, DeviceState *st)
+SmallTiles flat_tiles(int64_t M, int64_t K, int64_t N, int num_cus, DeviceState *st, const Plan &other)
 {
     constexpr double kSlab[] = {0.313, 0.530, 0.784};  // of one, two and three workgroups a unit
     const int64_t slabs = (K + 31) / 32, RB = (M + 31) / 32, NT = (N + 63) / 64;
@@ -218,6 +224,8 @@ SmallTiles flat_tiles(int64_t M, int64_t K, int64_t N, int num_cus, DeviceState 
             (RB * NT + RB * S * kSplitWays) * kSplitCounterStride * 4 > (int64_t)(kCtrlBytes - 2 * kCounterOffset))
             break;
         const int64_t rounds = (groups + num_cus - 1) / num_cus;
+        if ((S == 1 && rounds == 2 && other.split_s == 2 && other.split_shape != kSplit128) || (groups * 10 > 23 * num_cus && NT >= 80 && slabs < 10))
+            continue;
         double t = 6.29 + (double)((slabs + S - 1) / S) * kSlab[rounds - 1] + 0.766 * (double)rounds / S + 0.0344 * (double)NT;
         if (S > 1)
             t += 1.02 + (double)groups * 64 * 32 * 4 / 2.5e6;
@@ -304,7 +312,7 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
         best = narrow_us;
     }
     SmallTiles small = finer ? small_tiles(M, K, N, bf16, num_cus, st) : SmallTiles();
-    const SmallTiles flat = finer && !bf16 ? flat_tiles(M, K, N, num_cus, st) : SmallTiles();
+    const SmallTiles flat = finer && !bf16 ? flat_tiles(M, K, N, num_cus, st, pl) : SmallTiles();
     bool takes = small.s != 0 && small.us < (bf16 ? 0.90 * (best - 0.5) : 0.96 * (best - 0.3));
     if (flat.s != 0 && flat.us < 0.893 * best && !(takes && small.us <= flat.us)) {
         small = flat;

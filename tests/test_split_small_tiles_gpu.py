@@ -57,6 +57,29 @@ def test_flat_tiles(M, K, N, S):
     assert torch.equal(Y, gpu_run(d)[0])
 
 
+# Both sides of the lines between these tiles and larger ones: (M, K, N, dtype, rows and columns of a tile)
+SIDES = [(1995, 1280, 256, "bf16", 64, 64), (671, 1992, 768, "bf16", 32, 32), (29, 416, 2560, "f32", 32, 64), (50, 512, 2396, "f32", 32, 32),
+         (256, 2560, 3840, "f32", 64, 128), (206, 3840, 4372, "f32", 32, 64), (256, 256, 5888, "f32", 64, 128), (188, 256, 5632, "f32", 32, 64)]
+
+
+@pytest.mark.parametrize("M,K,N,dtype,rows,cols", SIDES)
+def test_plan_draws_the_lines(M, K, N, dtype, rows, cols):
+    plan = _plan(M, K, N, dtype)
+    assert (plan["tile_m"], plan["tile_n"]) == (rows, cols)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,dtype,rows,cols", SIDES)
+def test_both_sides_of_the_lines(M, K, N, dtype, rows, cols):
+    plan = _plan(M, K, N, dtype)
+    print("[case] small tiles, lines", M, K, N, dtype, plan, flush=True)
+    assert (plan["tile_m"], plan["tile_n"]) == (rows, cols)
+    d = make_inputs(M, K, N, dtype, seed=109)
+    Y, _ = gpu_run(d)
+    check_against_oracle(Y, oracle_on(d), dtype, "small tiles, lines %dx%dx%d" % (M, K, N))
+    assert torch.equal(Y, gpu_run(d)[0])
+
+
 # (M, K, N, rows and columns of a tile, terms of a sum in the larger tiles: K over the workgroups and wavefronts that shared it)
 SUMS = [(316, 3328, 512, 32, 32, 208), (256, 3072, 628, 32, 32, 192), (256, 1536, 2048, 32, 64, 192), (544, 1536, 768, 32, 64, 192),
         (309, 1280, 1024, 32, 64, 160)]
