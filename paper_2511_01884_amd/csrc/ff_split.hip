@@ -684,15 +684,16 @@ template <typename T, int WN, int WM, int WTN, int WTM> static constexpr int few
 // Whether such a launch goes by lines: rows off the line boundaries, and enough slabs for each workgroup.  170 shapes, M
 // 33..2048: rows on every other 64-byte boundary, or K cut over four and more workgroups (narrow W mostly, which the L2
 // holds), gain from 24 slabs on (0.92 of the time; 10 to 23: 1.01), the rest from 9 (0.93; below 1.03).  The four wavefronts of the
-// long rows gain 0.84 where X and W together are beyond 72 MB; below, other row blocks find the second half of
-// a line in the L2, and they lose 1.01.
+// long rows gain 0.84 where rows come from HBM; from the caches, where other row blocks find the second half of a line, they lose 1.02.
+// Timed on three sets of inputs in turn, X and W together stay in the 256 MB of the Infinity Cache up to 72 MB, with the whole of K in
+// a tile and W the larger of them up to 81 MB (72 to 81 MB: 19 such shapes 1.02 by lines, 19 with K cut 0.96).
 static bool takes_lines(const SplitParams &p, int waves)
 {
     const unsigned off = ((unsigned)p.K * 2u | (unsigned)(uintptr_t)p.W | (unsigned)(uintptr_t)p.X) & 127u;
     if (off == 0)
         return false;
     if (waves == 4)
-        return ((double)p.M + (double)p.N) * (double)p.K * 2.0 > 72e6;
+        return ((double)p.M + (double)p.N) * (double)p.K * 2.0 > (p.S == 1 && p.M < p.N ? 81e6 : 72e6);
     const int slabs = (p.K + 63) / 64, per = (slabs + p.S - 1) / p.S;
     return per >= (off % 64 == 0 || p.S >= 4 ? 24 : 9);
 }
