@@ -1003,10 +1003,7 @@ int ff_fused_linear_sub_rowmean_gelu_residual(const void *X, const void *W, cons
     p.M = (int)M; p.K = (int)K; p.N = (int)N;
     p.strips = pl.strips; p.k_pad = pl.k_pad; p.chunks = pl.chunks; p.rows_per_chunk = pl.rows_per_chunk;
     p.grid = st->num_cus;  // one workgroup per compute unit, all resident: the phases meet inside the launch
-    // A departure begun before the rows spares two round trips at the end, but wavefront 0's loads stand behind it, and where the memory
-    // is busy with X for long it takes longer itself.  Up to 40 KiB of X a unit 453 drawn shapes take 0.957 of the time with departures at the
-    // end, at most 1.00; of 50 KiB and more 146 take 1.008, up to 1.09 (4222 x 2048 x 868 fp32 16.7 us, begun early 18.3).
-    p.leaves_early = M * K * (dtype == FF_BF16 ? 2 : 4) <= (int64_t)40960 * p.grid;
+    p.leaves_early = M * K * (dtype == FF_BF16 ? 2 : 4) <= (int64_t)40960 * p.grid;  // (of what the kernel leaves open)
     p.extra_arrivals = g_extra_arrivals;
     p.wait_ticks = g_wait_limit_us * st->ticks_per_us;
     if (launch_rowmean_chain(dtype == FF_BF16, p, static_cast<hipStream_t>(stream)) != hipSuccess)
