@@ -268,6 +268,10 @@ int ff_debug_linear(const void *X, const void *W, const void *b,
  * FF_ERR_UNSUPPORTED; it never silently runs something else. */
 int ff_debug_force_variant(int variant);
 
+/* 1 if the kernel of the most recent successful ff_fused_linear_gelu_ln call on this host thread took X and W line by
+ * line of memory (bf16 rows off the 128-byte lines, the larger tiles of the kernel that cuts K and the 256 x 128 tiles), else 0. */
+int ff_debug_last_by_lines(void);
+
 /* Plain device-to-device copy of `bytes` (a multiple of 16; both pointers 16-byte aligned, device,
  * not overlapping) on `stream`.  A kernel of exactly known HBM traffic, used to scale hardware byte
  * counters when the traffic of the other kernels is measured. */

@@ -22,7 +22,7 @@ EXPORTS = [
     "ff_cross_entropy_mean", "ff_cross_entropy_workspace_bytes",
     "ff_metric_selection", "ff_metric_select_host",
     "ff_workspace_bytes", "ff_plan_query", "ff_set_workspace", "ff_check_device",
-    "ff_status_string", "ff_version", "ff_last_variant", "ff_debug_linear",
+    "ff_status_string", "ff_version", "ff_last_variant", "ff_debug_linear", "ff_debug_last_by_lines",
     "ff_debug_force_variant", "ff_debug_force_tile", "ff_debug_force_waves", "ff_debug_set_stagger_us", "ff_debug_set_timeline", "ff_debug_copy", "ff_debug_mfma_loop", "ff_debug_stream_read", "ff_debug_set_wait_limit_us", "ff_debug_expect_extra_arrivals",
 ]
 
@@ -74,6 +74,7 @@ def load() -> ctypes.CDLL:
         lib.ff_status_string.argtypes = [ci]
         lib.ff_version.restype = ci
         lib.ff_last_variant.restype = ci
+        lib.ff_debug_last_by_lines.restype = ci
         lib.ff_debug_linear.restype = ci
         lib.ff_debug_linear.argtypes = [vp, vp, vp, i64, i64, i64, ci, vp, vp]
         lib.ff_debug_force_variant.restype = ci
@@ -178,6 +179,10 @@ def ff_version() -> int:
 
 def ff_last_variant() -> int:
     return int(load().ff_last_variant())
+
+
+def ff_debug_last_by_lines() -> int:
+    return int(load().ff_debug_last_by_lines())
 
 
 def ff_plan_query(M: int, K: int, N: int, dtype: int) -> dict:

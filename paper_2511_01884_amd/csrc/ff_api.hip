@@ -72,6 +72,7 @@ int g_forced_tile = 0;        // 0 = automatic, else 64, 128 or 256
 int g_forced_wg_per_cu = 0;   // 0 = automatic (one workgroup per compute unit), else 1 or 2
 int g_forced_waves = 0;       // 0 = automatic, else 4 or 8 wavefronts per workgroup of the 256 x 256 tile
 thread_local int t_last_variant = 0;
+thread_local int t_last_by_lines = 0;
 
 struct Plan {
     int variant = 0;
@@ -830,6 +831,7 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
                          : nullptr;
         if (launch_smallm_kernel(pl.mt, p, pl.grid, stream) != hipSuccess)
             return FF_ERR_LAUNCH;
+        t_last_by_lines = 0;
         t_last_variant = pl.variant;
         return FF_OK;
     }
@@ -852,6 +854,7 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
                          : nullptr;
         if (launch_split_kernel(bf16, pl.split_shape, p, pl.grid, stream) != hipSuccess)
             return FF_ERR_LAUNCH;
+        t_last_by_lines = split_kernel_by_lines(bf16, pl.split_shape, p);
         t_last_variant = pl.variant;
         return FF_OK;
     }
@@ -887,8 +890,10 @@ int run(const void *X, const void *W, const void *b, const void *gamma, const vo
         if (launch_finalize_kernel(bf16, f, stream) != hipSuccess)
             return FF_ERR_LAUNCH;
     }
-    if (!linear_only)
+    if (!linear_only) {
         t_last_variant = pl.variant;
+        t_last_by_lines = tile_kernel_by_lines(bf16, pl.shape, mode, p);
+    }
     return FF_OK;
 }
 
@@ -1366,6 +1371,8 @@ const char *ff_status_string(int status)
 int ff_version(void) { return 100; }
 
 int ff_last_variant(void) { return t_last_variant; }
+
+int ff_debug_last_by_lines(void) { return t_last_by_lines; }
 
 int ff_debug_force_variant(int variant)
 {

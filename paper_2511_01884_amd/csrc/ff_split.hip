@@ -698,13 +698,18 @@ static bool takes_lines(const SplitParams &p, int waves)
     return per >= (off % 64 == 0 || p.S >= 4 ? 24 : 9);
 }
 
+template <typename T, int WN, int WM, int WK, int WTN, int WTM> static bool by_lines(const SplitParams &p)
+{
+    return has_lines<T, WN, WM, WTN, WTM>() && takes_lines(p, WN * WM * WK);
+}
+
 template <typename T, int WN, int WM, int WK, int WTN, int WTM>
 static hipError_t launch_split(const SplitParams &p, int grid, hipStream_t stream)
 {
     const dim3 threads(64 * WN * WM * WK);
     constexpr int kSums = sums_of<T, WN, WM, WTN, WTM>();
     if constexpr (has_lines<T, WN, WM, WTN, WTM>())
-        if (takes_lines(p, WN * WM * WK)) {
+        if (by_lines<T, WN, WM, WK, WTN, WTM>(p)) {
             hipLaunchKernelGGL((split_kernel<T, WN, WM, WK, WTN, WTM, true, 1>), dim3(grid), threads, 0, stream, p);
             return hipGetLastError();
         }
@@ -735,6 +740,14 @@ static int split_blocks()
 hipError_t launch_split_kernel(bool bf16, int shape, const SplitParams &p, int grid, hipStream_t stream)
 {
 #define FF_CALL(T, WN, WM, WK, WTN, WTM) launch_split<T, WN, WM, WK, WTN, WTM>(p, grid, stream)
+    FF_SPLIT_DISPATCH(FF_CALL)
+#undef FF_CALL
+}
+
+// Whether such a launch goes by lines.
+bool split_kernel_by_lines(bool bf16, int shape, const SplitParams &p)
+{
+#define FF_CALL(T, WN, WM, WK, WTN, WTM) by_lines<T, WN, WM, WK, WTN, WTM>(p)
     FF_SPLIT_DISPATCH(FF_CALL)
 #undef FF_CALL
 }

@@ -991,13 +991,15 @@ bool takes_lines(const TileParams &p)
     return off != 0 && (off % 32 != 0 || (off % 64 != 0 && p.RB >= 8));
 }
 
+template <typename T, int MODE, int STAGES> bool by_lines(const TileParams &p) { return has_lines<T, MODE, STAGES>() && takes_lines(p); }
+
 template <typename T, int WN, int WM, int WTN, int WTM, int MODE, int STAGES>
 hipError_t launch_tile(const TileParams &p, int grid, hipStream_t stream)
 {
     constexpr int BN = WN * WTN * 32;
     constexpr int kThreads = 64 * WN * WM;
     if constexpr (has_lines<T, MODE, STAGES>())
-        if (takes_lines(p)) {
+        if (by_lines<T, MODE, STAGES>(p)) {
             if (p.N % BN != 0)
                 hipLaunchKernelGGL((tile_kernel<T, WN, WM, WTN, WTM, MODE, true, STAGES, true>), dim3(grid), dim3(kThreads), 0,
                                    stream, p);
@@ -1067,6 +1069,14 @@ int max_blocks_per_cu()
 hipError_t launch_tile_kernel(bool bf16, int shape, int mode, const TileParams &p, int grid, hipStream_t stream)
 {
 #define FF_CALL(T, WN, WM, WTN, WTM, MODE, STAGES) launch_tile<T, WN, WM, WTN, WTM, MODE, STAGES>(p, grid, stream)
+    FF_TILE_DISPATCH(FF_CALL)
+#undef FF_CALL
+}
+
+// Whether such a launch goes by lines.
+bool tile_kernel_by_lines(bool bf16, int shape, int mode, const TileParams &p)
+{
+#define FF_CALL(T, WN, WM, WTN, WTM, MODE, STAGES) by_lines<T, MODE, STAGES>(p)
     FF_TILE_DISPATCH(FF_CALL)
 #undef FF_CALL
 }

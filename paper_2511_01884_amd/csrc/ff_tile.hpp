@@ -81,6 +81,7 @@ constexpr int split_shape_rows(int shape) { return shape == kSplit32 ? 32 : shap
 constexpr int split_shape_waves(int shape) { return shape == kSplit128x64 || shape == kSplit128 ? 8 : 4; }
 hipError_t launch_split_kernel(bool bf16, int shape, const SplitParams &p, int grid, hipStream_t stream);
 int split_kernel_blocks_per_cu(bool bf16, int shape);
+bool split_kernel_by_lines(bool bf16, int shape, const SplitParams &p);
 
 struct SmallMParams {
     const void *X, *W, *b, *gamma, *beta;
@@ -170,6 +171,7 @@ inline int tile_shape_rows(int shape)
 inline int tile_shape_waves(int shape) { return shape == kTile256W8 || shape == kTile256x128 ? 8 : 4; }
 hipError_t launch_tile_kernel(bool bf16, int shape, int mode, const TileParams &p, int grid, hipStream_t stream);
 int tile_kernel_blocks_per_cu(bool bf16, int shape, int mode);
+bool tile_kernel_by_lines(bool bf16, int shape, int mode, const TileParams &p);
 hipError_t launch_finalize_kernel(bool bf16, const FinalizeParams &p, hipStream_t stream);
 hipError_t launch_smallm_kernel(int mt, const SmallMParams &p, int grid, hipStream_t stream);
 

@@ -12,6 +12,8 @@ SHAPES = [(200, K, 4104) for K in (520, 528, 536, 568, 576 - 8, 584, 640 - 8)]  
 SHAPES += [(500, K, 4104) for K in (1096, 1112, 1160)]                                       # 128 x 128
 SHAPES += [(65, 6184, 2056), (200, 1568, 4104), (129, 8200, 1032)]                            # K cut; rows on 64-byte boundaries
 SHAPES += [(200, 4104, 9000), (300, 12296, 4104)]                                            # long rows, four wavefronts
+SHAPES += [(65, 3080, 8200), (129, 6184, 2056), (200, 6184, 2056), (65, 12320, 2056)]         # K cut in 2, 4 and 8, long enough for lines
+BY_SLABS = [(65, 6184, 2056), (129, 8200, 1032), (200, 4104, 9000)]                          # too short shares; too few bytes
 
 
 def moved(t, off):  # the same rows, `off` elements behind a line boundary, with NaN before and behind them
@@ -29,6 +31,7 @@ def test_lines(M, K, N):
     assert plan["tile_n"] == 128 and plan["tile_m"] in (64, 128) and plan["rounds"] == 1
     d = make_inputs(M, K, N, "bf16", seed=79)
     Y, _ = gpu_run(d)
+    assert B.ff_debug_last_by_lines() == ((M, K, N) not in BY_SLABS)
     print(check_against_oracle(Y, oracle_on(d), "bf16", "lines %dx%dx%d" % (M, K, N)))
     assert torch.equal(Y, gpu_run(d)[0])
     padded = -(-K // 64) * 64
@@ -40,15 +43,17 @@ def test_lines(M, K, N):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("x_off,w_off", [(8, 0), (0, 24), (40, 56), (32, 32)])
-@pytest.mark.parametrize("M,K,N", [(200, 2048, 4104), (500, 1096, 4104), (200, 4104, 9000)])
+@pytest.mark.parametrize("M,K,N", [(200, 2048, 4104), (500, 1096, 4104), (200, 4104, 9000), (200, 4104, 10008), (129, 6184, 2056)])
 def test_tensors_off_the_lines(M, K, N, x_off, w_off):
     print("[case] lines, tensors at", x_off, w_off, M, K, N, flush=True)
     d = make_inputs(M, K, N, "bf16", seed=83)
     Y, _ = gpu_run(d)
+    assert B.ff_debug_last_by_lines() == (K % 64 != 0 and (M, K, N) not in BY_SLABS)
 
     X, W = moved(d["X"], x_off), moved(d["W"], w_off)
     assert X.data_ptr() % 128 == 2 * x_off and W.data_ptr() % 128 == 2 * w_off
     got = B.ff_fused_linear_gelu_ln(X, W, d["b"].cuda(), d["gamma"].cuda(), d["beta"].cuda(), d["eps"])
+    assert B.ff_debug_last_by_lines() == ((M, K, N) not in BY_SLABS)
     assert torch.equal(Y.cpu(), got.cpu())
 
 
@@ -63,8 +68,10 @@ def test_tiles_of_half_the_height(K, x_off, w_off):
     B.ff_debug_force_tile(256, 2)
     try:
         Y, _ = gpu_run(d)
+        assert B.ff_debug_last_by_lines() == (K % 64 != 0)
         got = B.ff_fused_linear_gelu_ln(moved(d["X"], x_off), moved(d["W"], w_off), d["b"].cuda(), d["gamma"].cuda(),
                                         d["beta"].cuda(), d["eps"])
+        assert B.ff_debug_last_by_lines() == (K % 64 != 0 or x_off != 0)
         padded = -(-K // 64) * 64 - K
         whole = dict(d, X=torch.nn.functional.pad(d["X"], (0, padded)), W=torch.nn.functional.pad(d["W"], (0, padded)))
         want, _ = gpu_run(whole)

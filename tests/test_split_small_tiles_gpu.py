@@ -28,7 +28,9 @@ def test_plan(M, K, N, dtype, S):
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N,dtype,S", CASES)
 def test_against_the_oracle(M, K, N, dtype, S):
-    print("[case] small tiles", M, K, N, dtype, S, flush=True)
+    plan = _plan(M, K, N, dtype)
+    print("[case] small tiles", M, K, N, dtype, plan, flush=True)
+    assert (plan["tile_m"], plan["tile_n"], plan["grid"]) == (32, 32, -(-M // 32) * -(-N // 32) * S)
     d = make_inputs(M, K, N, dtype, seed=103)
     d["b"] = (d["b"].float() + 2.0).to(d["b"].dtype)   # row means far from zero
     Y, used = gpu_run(d)

@@ -25,9 +25,11 @@ def test_larger_tiles_stay(M, K, N):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,K,N", [c[:3] for c in CASES])
-def test_against_the_oracle(M, K, N):
-    print("[case] half full", M, K, N, flush=True)
+@pytest.mark.parametrize("M,K,N,rows,cols,rounds", CASES)
+def test_against_the_oracle(M, K, N, rows, cols, rounds):
+    plan = B.ff_plan_query(M, K, N, B.FF_BF16)
+    print("[case] half full", M, K, N, plan, flush=True)
+    assert (plan["tile_m"], plan["tile_n"], plan["rounds"]) == (rows, cols, rounds)
     d = make_inputs(M, K, N, "bf16", seed=101)
     Y, used = gpu_run(d)
     assert used == B.FF_VARIANT_TILED_FUSED

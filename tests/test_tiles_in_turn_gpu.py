@@ -34,7 +34,11 @@ def test_plan_of_small_tiles(M, K, N, rounds):
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N,rounds", CASES + SMALL)
 def test_against_the_oracle(M, K, N, rounds):
-    print("[case] tiles in turn", M, K, N, flush=True)
+    plan = B.ff_plan_query(M, K, N, B.FF_F32)   # with this device's units and the workgroups that one holds
+    print("[case] tiles in turn", M, K, N, plan, flush=True)
+    size, most = (128, 512) if (M, K, N, rounds) in CASES else (64, 1024)
+    assert (plan["tile_m"], plan["tile_n"], plan["rounds"]) == (size, size, rounds)
+    assert plan["grid"] == min(-(-M // size) * -(-N // size), most)
     d = make_inputs(M, K, N, "f32", seed=97)
     Y, used = gpu_run(d)
     assert used == B.FF_VARIANT_TILED_FUSED
