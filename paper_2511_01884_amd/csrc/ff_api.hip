@@ -180,8 +180,8 @@ SmallTiles small_tiles(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, 
     const int size = bf16 ? 2 : 4;
     const int64_t slabs = (K * size + 127) / 128, RB = (M + 31) / 32, NT = (N + 31) / 32;
     SmallTiles best;
-    // Where rows lie off the line boundaries and N ends inside a tile the larger tiles stay.  (Those would gain too, in fp32 0.91 of the
-    // time against 0.89 for rows on line boundaries; the tests of the larger tiles' edges are such shapes.)
+    // Where rows lie off the line boundaries and N ends inside a tile the larger tiles stay.  (They need not: in fp32 these would take 0.91 of
+    // their time there, against 0.89 for rows on line boundaries.)
     // bf16 of up to eight slabs, whose one load latency the larger tiles wait for as well, gains nothing on average (59 shapes 1.00),
     // nor does it beyond 32 (K 2048 to 4096: 1.05), nor with two workgroups a unit and rows on 64-byte boundaries (0.98 to 1.14 of the larger
     // tiles' time: 1995 x 1280 x 256 11.0 us, 12.6 in 504 of these; rows off them 0.90 to 1.05: 671 x 1992 x 768 16.8, 15.4).
@@ -329,12 +329,11 @@ bool plan_split(int64_t M, int64_t K, int64_t N, bool bf16, int num_cus, DeviceS
         pl.NT = (int)((N + pl.tile_n - 1) / pl.tile_n);
         pl.grid = pl.RB * pl.NT * pl.split_s;
     }
-    // 128 x 128 tiles of long bf16 rows that do not begin on 64-byte boundaries keep four wavefronts.  There every line of
+    // 128 x 128 tiles of long bf16 rows that do not begin on 64-byte boundaries keep four wavefronts.  By slabs every line of
     // a slab is requested twice, and eight wavefronts go to HBM for half of W's lines a second time (147 x 10568 x 6016
-    // 89 us, with four 76; K = 10560: 62, 66).  206 such shapes: up to 48 slabs a workgroup eight win (0.94 of the time),
-    // beyond them four do (0.95, at best 0.80: 1284 x 9832 x 2432 150 us, 119); with this line a call takes 0.5 % more than
-    // with the better of the two on average, 8.6 at most, 2.6 and 25 with eight throughout.  (So it was with slabs.  By lines, as both go
-    // now, eight take 0.8 to 0.97 of four's time: 1284 x 9832 x 2432 80 us, 101; the tests of this line ask for four.)
+    // 89 us, with four 76; K = 10560: 62, 66).  206 such shapes, all by slabs: up to 48 slabs a workgroup eight win (0.94 of the time),
+    // beyond them four do (0.95, at best 0.80: 1284 x 9832 x 2432 150 us, 119).  By lines, as four go where rows come from HBM, they take 0.84 of
+    // that, and eight by lines would take 0.80 to 0.97 of four's time (1284 x 9832 x 2432 101 us, 80): this line was drawn before there were any.
     if (bf16 && pl.split_shape == kSplit128 && K % 32 != 0 && (slabs + pl.split_s - 1) / pl.split_s > 48)
         pl.split_shape = kSplit128W4;
     pl.rounds = 1;

@@ -105,7 +105,7 @@ template <> struct RawCols<__bf16> {
 // is no faster, so it is not the time of a load; the fragments of the next slab read ahead of its barrier neither in
 // bf16, 4 % faster in long fp32 products and 0.3 us slower in short ones.  Both point at the rate at which a unit's
 // loads reach its LDS: 57 bytes a nanosecond.)  The plan keeps four in the 128 x 128 tile for long rows off the 64-byte
-// boundaries.
+// boundaries, which by slabs are faster so (plan_split has both sides).
 //
 // Tiles of 32 x 32 by four wavefronts, each with a quarter of every slab's k-steps, are for calls bound by latency: so many of
 // them that a tile has the whole of K, which spares its workgroups' meeting (2.4 of 11.6 us at 256 x 512 x 512 fp32), with
