@@ -164,7 +164,7 @@ int resident_split_blocks(DeviceState *st, bool bf16, int shape)
 // fp32 over 64 rows has 64 x 32 tiles beside them, up to three a unit, from eight slabs on: bound by the matrix units, it gains from
 // finer tiles where larger ones fill the last round badly.  Their model was fitted to 1 500 runs of 980 shapes (off by 2.6 %);
 // taken where it says 6 % less than the others, whose estimates are 5 % high here, 0.91 of the time, 1 % above the better of the
-// two, at most 1.02 (2033 x 2560 x 632 89 us, 71; 855 x 2272 x 1024 49, 46).  Two whole ones a unit do not replace tiles up to 128 x 64 with K cut in
+// two, at most 1.02 (2033 x 2560 x 632 88 us, 69; 855 x 2272 x 1024 49, 47).  Two whole ones a unit do not replace tiles up to 128 x 64 with K cut in
 // two (67 shapes 1.03 to 1.07: 256 x 2560 x 3840 50.6 us, 53.7; but 206 x 3840 x 4372, 128 x 128 cut in two, 0.62), nor more than 2.3 a unit under
 // ten slabs where a row has 80 and more (60 shapes 1.03, at most 1.05: 256 x 256 x 5888 18.4 us, 19.2; up to 2.3 0.96 to 1.00, with 60 to 79 tiles 0.96).
 struct SmallTiles {
