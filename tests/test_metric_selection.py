@@ -45,6 +45,22 @@ def test_host_selection_matches_oracle(n, V, J, k, q, min_tasks):
     _compare(got, ref, k)
 
 
+@pytest.mark.parametrize("k", [1, 2, 20, 64, 65])
+@pytest.mark.parametrize("order", ["rising", "falling", "steps", "level"])
+def test_host_selection_of_ordered_metrics(order, k):
+    """|r| that rises or falls with the metric, each a new first or a new last one of the list, in steps of equal ones, and level."""
+    J = 150
+    size = {"rising": np.arange(J) / J, "falling": 1 - np.arange(J) / J, "steps": np.arange(J) // 7 / J, "level": np.full(J, 0.5)}[order]
+    r = np.stack([size * np.where(np.arange(J) % 3 == i, -1.0, 1.0) for i in range(3)])
+    r[1, ::11] = np.nan
+    keep = np.ones((3, J), dtype=np.uint8)
+    keep[2, 1::5] = 0
+    got = B.ff_metric_select_host(r, keep, top_k=k)
+    want = oracle_ms.select_from_r(r, keep.astype(bool), k=k)
+    assert got["top"] == want["top"] and got["selected"] == want["selected"]
+    assert np.allclose(got["score"], want["score"], rtol=1e-15, atol=0)
+
+
 def test_host_selection_with_keep_mask_and_edge_cases():
     values, runtime = make_metric_inputs(4, 10, 60, seed=22)
     v = values.numpy()
