@@ -438,6 +438,11 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
     // better of the two, at most 1.05 (2906 x 4056 x 740 254 us, 189; 655 x 1216 x 3008 84, 66; 2637 x 156 x 868 22.7, 18.8; in rows of 70 and
     // more tiles of 128 short products lose up to twofold: 982 x 172 x 7668 44, 99).
     bool in_turn = false, in_turn64 = false;
+    // (the estimates below are of two and four workgroups a unit: not where the runtime says that a unit holds fewer)
+    auto holds = [&](int shape, int workgroups) {
+        const int fit = resident_blocks_per_cu(st, bf16, shape, kFused);
+        return fit == 0 || fit >= workgroups;
+    };
     // (Where the row statistics fit the entry point that allocates nothing, so that both have the same bits; the fewer row-blocks
     // of larger tiles for very long X.)
     const bool room128 = kCtrlBytes + (size_t)tiles128 * 128 * sizeof(floatx2) <= kNoAllocBytes && (M + 127) / 128 < kMaxRowBlocks &&
@@ -450,7 +455,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
                                                                 : (tiles256 + num_cus - 1) / num_cus);
         const double us128 = 6.0 + units * (0.0561 * (double)K + 6.8 + 0.03 * (double)((N + 127) / 128));
         const double us256 = 6.0 + rounds256 * (0.216 * (double)K + 22.0);
-        in_turn = us128 < 0.92 * us256;
+        in_turn = us128 < 0.92 * us256 && holds(kTile128, 2);
     }
     const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
     if (!bf16 && may_split && finer && (in_turn || (tiles128 <= 2 * num_cus && tiles128 * 4 > num_cus)) && N <= 128 * (int64_t)num_cus &&
@@ -460,7 +465,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
         const double units64 = (double)(tiles64 / (4 * num_cus)) + 0.25 * (double)((rest64 + num_cus - 1) / num_cus);
         const double k = (double)K, nt128 = (double)((N + 127) / 128), nt64 = (double)((N + 63) / 64);
         in_turn64 = 9.1 - 0.126 * nt64 + units64 * (0.0595 * k + 1.8 + 0.342 * nt64) <
-                    0.94 * (2.1 + units128 * (0.0541 * k + 9.1 + 0.034 * nt128));
+                    0.94 * (2.1 + units128 * (0.0541 * k + 9.1 + 0.034 * nt128)) && holds(kTile64, 4);
     }
     // bf16 where little more than half of the units would have a 256 x 256 tile: one round of tiles of half the height, one
     // a unit (22 shapes 0.83 of the time: 2616 x 512 x 2944 25.5 us, 19.9; 612 x 3984 x 12200 123, 92), or else of 128 x 128 tiles, two
@@ -474,7 +479,7 @@ int make_plan(int64_t M, int64_t K, int64_t N, int dtype, int num_cus, DeviceSta
         const bool two = !one && across * 2 <= num_cus && rows256 <= 2 * (num_cus / across) && !plain;
         pair_half = one && tiles256x128 <= num_cus;
         pair128 = !pair_half && ((one && tiles128 <= 2 * num_cus && across128 <= 64) ||
-                                 (two && across128 <= 16 && rows128 <= 2 * (2 * num_cus / across128)));
+                                 (two && across128 <= 16 && rows128 <= 2 * (2 * num_cus / across128))) && holds(kTile128, 2);
     }
     if (in_turn64)
         pl.shape = kTile64;
