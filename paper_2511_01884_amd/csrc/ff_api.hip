@@ -1012,7 +1012,6 @@ int ff_fused_linear_sub_rowmean_gelu_residual(const void *X, const void *W, cons
     p.M = (int)M; p.K = (int)K; p.N = (int)N;
     p.strips = pl.strips; p.k_pad = pl.k_pad; p.chunks = pl.chunks; p.rows_per_chunk = pl.rows_per_chunk;
     p.grid = st->num_cus;  // one workgroup per compute unit, all resident: the phases meet inside the launch
-    p.leaves_early = M * K * (dtype == FF_BF16 ? 2 : 4) <= (int64_t)40960 * p.grid;  // (of what the kernel leaves open)
     p.extra_arrivals = g_extra_arrivals;
     p.wait_ticks = g_wait_limit_us * st->ticks_per_us;
     if (launch_rowmean_chain(dtype == FF_BF16, p, static_cast<hipStream_t>(stream)) != hipSuccess)

@@ -186,29 +186,34 @@ constexpr int kSyncStride = 1024;  // uint32 words between ways
 
 // Departure from such a meeting: the last workgroup of the last way re-arms every counter (only then has every workgroup
 // left its wait, so that no poller can see a counter go back to zero).  In three steps, one thread's, begun as soon as
-// the workgroup's own wait is over: the two round trips to memory pass behind the work that follows, and no
-// longer stand at the end of the kernel (16 x 8192 x 8192 36.6 us, now 36.2; second chain 300 x 4096 x 1024 12.5, 12.0;
-// of much X it begins behind the rows).
+// the workgroup's own wait is over: the two round trips to memory pass behind the work that follows, and do not
+// stand at the end of the kernel (16 x 8192 x 8192 36.6 us, now 36.2; second chain 300 x 4096 x 1024 12.4, 11.9).
+// Departures are counted in lines that nobody polls.  Beside a way's arrivals they hold up whoever still waits: the second
+// chain with more than 40 KiB of X a unit took 1.01 (90 drawn shapes; at most 1.08) of its time with departures at the end of the kernel,
+// in lines of their own 0.98 (at most 1.01; 4222 x 2048 x 868 fp32 16.7 us, 18.1, now 16.4).
+constexpr int kSyncDeparted = 32;            // uint32 words from a way's arrivals to its departures
+constexpr int kSyncWaysDeparted = 64;        // and, from the first way's arrivals, to the ways that all have left
+static_assert(kSyncWaysDeparted < kSyncStride, "inside the first way's own words");
 struct Departure {
     unsigned seen = 0;
     __device__ __forceinline__ void begin(unsigned *counters, unsigned way)
     {
-        seen = atomic_add_device(counters + (size_t)way * kSyncStride + 1, 1u);
+        seen = atomic_add_device(counters + (size_t)way * kSyncStride + kSyncDeparted, 1u);
     }
     // behind the loads that the workgroup waits for next
     __device__ __forceinline__ void middle(unsigned *counters, unsigned way, unsigned grid)
     {
         const bool last = seen == (grid + kSyncWays - 1 - way) / kSyncWays - 1u;
-        seen = last ? atomic_add_device(counters + 2, 1u) + 1u : 0u;
+        seen = last ? atomic_add_device(counters + kSyncWaysDeparted, 1u) + 1u : 0u;
     }
     __device__ __forceinline__ void end(unsigned *counters, unsigned grid)
     {
         if (seen == (grid < (unsigned)kSyncWays ? grid : (unsigned)kSyncWays)) {
             for (int w = 0; w < kSyncWays; ++w) {
                 atomic_store_device(counters + (size_t)w * kSyncStride, 0u);
-                atomic_store_device(counters + (size_t)w * kSyncStride + 1, 0u);
+                atomic_store_device(counters + (size_t)w * kSyncStride + kSyncDeparted, 0u);
             }
-            atomic_store_device(counters + 2, 0u);
+            atomic_store_device(counters + kSyncWaysDeparted, 0u);
         }
     }
 };

@@ -71,13 +71,6 @@ __device__ __forceinline__ floatx4 masked(const floatx4 &v, bool ok)
     return __builtin_bit_cast(floatx4, __builtin_bit_cast(uintx4, v) & (ok ? 0xffffffffu : 0u));
 }
 
-// Whether the departure from the meeting begins before the rows whatever their size: where a wavefront's rows are few or short.  Elsewhere where
-// one set of shared rows is all, or up to 40 KiB of X a unit (leaves_early of the parameters).  It spares two round trips at the end,
-// but wavefront 0's loads stand behind it, and it takes longer itself where the memory is busy with X.  Of the time with departures at
-// the end, drawn shapes: always 0.96 (400 shapes, at most 1.00), one set of shared rows 0.96 (100, at most 1.00), up to 40 KiB 0.96 (40); the rest,
-// which begin it behind the rows, would take 1.01 (200, at most 1.10: 4222 x 2048 x 868 fp32 16.7 us, 18.3).
-template <int PL, int R, int WPR, int SETS> constexpr bool leaves_early_always() { return SETS == 1 || (WPR == 1 && (PL * R < 4 || PL == 1)); }
-
 // A row is shared by WPR wavefronts; PL = 16-byte chunks of it a lane keeps in registers; R = rows of a set: in
 // phase 2 one of SETS = 2 is finished while the other travels, or (SETS = 1) a wavefront has no row after its first.
 template <typename T, int PL, int R, int WPR, int SETS>
@@ -230,8 +223,7 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
     }
     __syncthreads();
     Departure leave;
-    const bool leaves_early = leaves_early_always<PL, R, WPR, SETS>() || p.leaves_early != 0 || (WPR > 1 && M <= R * row_step);
-    if (leaves_early && tid == 0)
+    if (tid == 0)
         leave.begin(p.counters, way);
 
     // ---- phase 2: wbar into LDS (chunk partials added in chunk order), c, then one wavefront per row ----
@@ -419,7 +411,7 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
             }
         }
     };
-    if (leaves_early && tid == 0)
+    if (tid == 0)
         leave.middle(p.counters, way, G);
     if constexpr (SETS == 1) {
         finish_rows(m_first, keep[0]);
@@ -434,13 +426,8 @@ __global__ __launch_bounds__(kThreads) void rowmean_kernel(const RowMeanParams p
         }
     }
 
-    if (tid == 0) {
-        if (!leaves_early) {
-            leave.begin(p.counters, way);
-            leave.middle(p.counters, way, G);
-        }
+    if (tid == 0)
         leave.end(p.counters, G);
-    }
 }
 
 template <typename T, int PL, int R, int WPR, int SETS = 2>

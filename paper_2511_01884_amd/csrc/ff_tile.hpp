@@ -114,7 +114,6 @@ struct RowMeanParams {
     int k_pad;
     int chunks, rows_per_chunk;  // row chunks of W; rows_per_chunk is a multiple of kRowMeanRowsPerStep
     int grid;            // one workgroup per compute unit: all co-resident
-    int leaves_early;    // the departure from the meeting begins before the rows, not behind them
     int extra_arrivals;  // test hook
     long long wait_ticks;
 };

@@ -59,9 +59,9 @@ def test_one_row_a_wavefront_and_one_more(M, K, N, dtype):
 
 @pytest.mark.parametrize("M,K,N,dtype", [(2560, 2048, 72, "bf16"), (2561, 2048, 72, "bf16"), (1280, 2048, 68, "f32"), (1281, 2048, 68, "f32"),
                                          (637, 8232, 16, "bf16"), (638, 8232, 16, "bf16"), (1024, 5376, 16, "bf16"), (1025, 5376, 16, "bf16")])
-def test_departure_before_and_behind_the_rows(M, K, N, dtype):
-    """40 KiB of X a unit (of 256) and, of more, one set of shared rows, where the departure from the meeting begins before the rows, and the
-    next shape; the second call finds the counters that the first one re-armed."""
+def test_departures_beside_little_and_much_x(M, K, N, dtype):
+    """Kernels of one and two sets of rows, own and shared, with less and more of X to come; the second call finds the counters that
+    the first one re-armed."""
     _check(M, K, N, dtype, 101)
 
 
